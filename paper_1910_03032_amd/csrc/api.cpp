@@ -14,6 +14,7 @@
 #include <string>
 #include <vector>
 
+#include "geom.h"
 #include "internal.h"
 #include "flow.h"
 #include "lor.h"
@@ -75,8 +76,8 @@ struct sfem_ctx {
   Rules1D rules;
   int32_t *d_map = nullptr;        // [nelem][n^3] flagged (sole / essential bits)
   double *d_xyz = nullptr;         // [nelem][8][3]
+  double *d_geo = nullptr;         // [nelem][kGeoStride] trilinear coefficients (geom.h)
   double *d_qd = nullptr;          // [nelem][7][q^3]
-  float *d_qd32 = nullptr;
   // assembly of the shared and essential DoFs
   int compact = 0;                 // E-vector over surface nodes only
   int64_t epe = 0;                 // E-vector entries per element (surface nodes or n^3)
@@ -107,10 +108,8 @@ struct sfem_ctx {
   double alpha = 1.0, beta = 1.0;
   int nfield = 1;
   bool has_nu = false;
-  double *d_fold64 = nullptr;  // [nfield][nelem][7 q^3], slice-pair order (k_setup.hip: fold_kernel)
-  float *d_fold32 = nullptr;
-  double *d_nu64 = nullptr;    // [nfield][nelem][q^3]
-  float *d_nu32 = nullptr;
+  double *d_cw = nullptr;      // with a nu field (has_nu): w nu / |J| at the points, [nfield][nelem][q^3]
+  double *d_nu64 = nullptr;    // with a nu field: nu
 
   // ---- diagonals per operator kind: [nf][ndof]
   bool diag_ok[3] = {false, false, false};
@@ -216,14 +215,10 @@ void free_lor(sfem_ctx *c) {
 
 void free_coeffs(sfem_ctx *c) {
   free_lor(c);
-  dfree(c, c->d_fold64);
-  dfree(c, c->d_fold32);
+  dfree(c, c->d_cw);
   dfree(c, c->d_nu64);
-  dfree(c, c->d_nu32);
-  c->d_fold64 = nullptr;
-  c->d_fold32 = nullptr;
+  c->d_cw = nullptr;
   c->d_nu64 = nullptr;
-  c->d_nu32 = nullptr;
   for (int o = 0; o < 3; ++o) {
     dfree(c, c->d_diag[o]);
     dfree(c, c->d_dinv[o]);
@@ -245,8 +240,8 @@ void free_all(sfem_ctx *c) {
   c->bytes = 0;
   c->d_map = nullptr;
   c->d_xyz = nullptr;
+  c->d_geo = nullptr;
   c->d_qd = nullptr;
-  c->d_qd32 = nullptr;
   c->d_alist = nullptr;
   c->d_aoff = nullptr;
   c->d_pos = nullptr;
@@ -265,10 +260,8 @@ void free_all(sfem_ctx *c) {
   c->pnentries = 0;
   c->pplan = AsmPlan{};
   c->d_cq = nullptr;
-  c->d_fold64 = nullptr;
-  c->d_fold32 = nullptr;
+  c->d_cw = nullptr;
   c->d_nu64 = nullptr;
-  c->d_nu32 = nullptr;
   for (int o = 0; o < 3; ++o) {
     c->d_diag[o] = c->d_dinv[o] = nullptr;
     c->d_diag32[o] = c->d_dinv32[o] = nullptr;
@@ -293,14 +286,13 @@ sfem_status fold_coeffs(sfem_ctx *c, const double *nu_user, int nfield, double a
   c->beta = beta;
   c->nfield = nfield;
   c->has_nu = nu_user != nullptr;
+  if (!nu_user) return SFEM_OK;  // nu = 1: the kernels form 1 / |J| themselves
   const int64_t nq = c->nelem * q3_of(c);
   sfem_status st;
-  if ((st = dalloc(c, &c->d_fold64, nq * kQdSlots * nfield)) != SFEM_OK) return st;
-  if ((st = dalloc(c, &c->d_fold32, nq * kQdSlots * nfield)) != SFEM_OK) return st;
+  if ((st = dalloc(c, &c->d_cw, nq * nfield)) != SFEM_OK) return st;
   if ((st = dalloc(c, &c->d_nu64, nq * nfield)) != SFEM_OK) return st;
-  if ((st = dalloc(c, &c->d_nu32, nq * nfield)) != SFEM_OK) return st;
-  HIPCHK(c, launch_fold(c->q, c->d_qd, nu_user, c->nelem, nfield, alpha, beta, c->d_fold64,
-                        c->d_fold32, c->d_nu64, c->d_nu32, c->stream));
+  HIPCHK(c, launch_fold(c->q, c->rules.gauss_x.data(), c->rules.gauss_w.data(), c->d_geo, nu_user,
+                        c->nelem, nfield, c->d_cw, c->d_nu64, c->stream));
   return SFEM_OK;
 }
 
@@ -471,21 +463,11 @@ sfem_status do_apply(sfem_ctx *c, int op, bool f32, int nbatch, const void *x, v
   a.compact = c->compact;
   a.part = part;
   a.part_mstride = nparts;
-  a.nu = nullptr;
-  a.qd_mstride = 0;
-  a.nu_mstride = 0;
-  const int64_t nq = c->nelem * q3_of(c);
-  const bool per_member = c->nfield > 1;
-  if (op == SFEM_HELMHOLTZ) {
-    a.qd = f32 ? (const void *)c->d_fold32 : (const void *)c->d_fold64;
-    a.qd_mstride = per_member ? nq * kQdSlots : 0;
-  } else {
-    a.qd = f32 ? (const void *)c->d_qd32 : (const void *)c->d_qd;
-    if (op == SFEM_DIFFUSION) {  // nu = 1 is stored when no field was given
-      a.nu = f32 ? (const void *)c->d_nu32 : (const void *)c->d_nu64;
-      a.nu_mstride = per_member ? nq : 0;
-    }
-  }
+  a.geo = c->d_geo;
+  a.cw = op != SFEM_MASS ? c->d_cw : nullptr;
+  a.cw_mstride = c->nfield > 1 ? c->nelem * q3_of(c) : 0;
+  a.alpha = op == SFEM_HELMHOLTZ ? c->alpha : (op == SFEM_MASS ? 1.0 : 0.0);
+  a.beta = op == SFEM_HELMHOLTZ ? c->beta : (op == SFEM_MASS ? 0.0 : 1.0);
   hipError_t e = f32 ? launch_apply_f32(a, c->stream) : launch_apply_f64(a, c->stream);
   if (e != hipSuccess) return fail(c, SFEM_E_HIP, std::string("apply launch: ") + hipGetErrorString(e));
   if (!assemble) return SFEM_OK;
@@ -942,7 +924,7 @@ static sfem_status sfem_setup_body(sfem_ctx *c, int p, int q, int64_t nelem, con
   if ((st = dalloc(c, &c->d_map, nelem * n3)) != SFEM_OK) return st;
   if ((st = dalloc(c, &c->d_xyz, nelem * 24)) != SFEM_OK) return st;
   if ((st = dalloc(c, &c->d_qd, nelem * q3 * kQdSlots)) != SFEM_OK) return st;
-  if ((st = dalloc(c, &c->d_qd32, nelem * q3 * kQdSlots)) != SFEM_OK) return st;
+  if ((st = dalloc(c, &c->d_geo, nelem * kGeoStride)) != SFEM_OK) return st;
   if ((st = dalloc(c, &c->d_alist, na)) != SFEM_OK) return st;
   if ((st = dalloc(c, &c->d_aoff, na + 1)) != SFEM_OK) return st;
   if ((st = dalloc(c, &c->d_pos, (int64_t)pos.size())) != SFEM_OK) return st;
@@ -973,7 +955,7 @@ static sfem_status sfem_setup_body(sfem_ctx *c, int p, int q, int64_t nelem, con
     HIPCHK(c, VecOps<float>::fill((float *)d_bad, 0.0f, 1, c->stream));
     HIPCHK(c, launch_qdata_setup(q, c->rules.gauss_x.data(), c->rules.gauss_w.data(), c->d_xyz,
                                  nelem, c->d_qd, d_bad, c->stream));
-    HIPCHK(c, launch_cast_f32(c->d_qd, c->d_qd32, nelem * q3 * kQdSlots, c->stream));
+    HIPCHK(c, launch_geo_setup(c->d_xyz, nelem, c->d_geo, c->stream));
     HIPCHK(c, hipMemcpyAsync(&h_bad, d_bad, sizeof(int), hipMemcpyDeviceToHost, c->stream));
   }
   HIPCHK(c, hipStreamSynchronize(c->stream));

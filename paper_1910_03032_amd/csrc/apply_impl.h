@@ -2,8 +2,8 @@
 //
 // Per element (Section 3.1, eq. sumFactorized and L^K = G^T W G):
 //   gather x_e -> contract xi_1 with B, G -> contract xi_2 -> contract xi_3
-//   -> pointwise quadrature function with the stored factors
-//      (v = m u,  g = Gq grad_ref u)
+//   -> pointwise quadrature function (v = alpha w|J| u, g = beta nu w|J| J^-1 J^-T grad_ref u)
+//      with the geometric factors formed from the element's trilinear map (geom.h)
 //   -> transposed contractions xi_3 -> xi_2 -> xi_1 -> scatter into y.
 //
 // Work decomposition: one element is owned by q^2 threads; in every stage a thread
@@ -39,7 +39,10 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "eo.h"
+#include "geom.h"
 #include "internal.h"
 #include "rules.h"
 
@@ -110,86 +113,123 @@ constexpr RankTable<P> make_rank_table() {
 template <int P>
 __constant__ RankTable<P> kRankTable = make_rank_table<P>();
 template <int P>
-__device__ __forceinline__ int surf_rank(int l) {
-  return kRankTable<P>.r[l];
+constexpr RankTable<P> make_node_table() {
+  RankTable<P> t{};
+  for (int l = 0; l < (P + 1) * (P + 1) * (P + 1); ++l) t.r[l] = (int16_t)l;
+  return t;
 }
+// The general layout's entry order: the node itself.
+template <int P>
+__constant__ RankTable<P> kNodeTable = make_node_table<P>();
 template <int P>
 __host__ __device__ constexpr int surf_count() {
   return 2 * (P + 1) * (P + 1) + (P - 1) * 4 * P;
 }
 
-// Gather the element's nodal values (essential DoFs as 0) into buf[k][j][i].  All map
-// loads of the thread are issued together, then all value loads.  Loads are
-// unconditional (an inactive slot reads a valid element's entries and discards them)
-// so that the compiler can batch them.  If smap is given (LDS), it receives each
-// node's map entry -- except, with POS (DoF-ordered E-vector), that a shared node gets
-// its E-vector entry from the element's row epos of the position table, read together
-// with the map.
-template <int P, typename T, bool POS = false>
-__device__ __forceinline__ void gather_e(T *buf, int t, bool active, const int32_t *emap,
-                                         const T *__restrict__ xm, int32_t *smap = nullptr,
-                                         const int32_t *epos = nullptr, bool compact = true) {
-  using D = Dims<P>;
-  constexpr int NL = Per<P>::NL;
-  int32_t c[NL], q[NL];
-#pragma unroll
-  for (int k = 0; k < NL; ++k) {
-    const int l0 = t + k * D::TPE;
-    const int l = l0 < D::N3 ? l0 : D::N3 - 1;
-    c[k] = emap[l];
-    if constexpr (POS) {
-      const int r = compact ? surf_rank<P>(l) : l;
-      q[k] = epos[r >= 0 ? r : 0];
-    }
+// One value at a byte offset from a pointer that is the same in all lanes (scalar base and
+// 32-bit lane offset, no 64-bit address arithmetic per lane).
+template <typename T>
+__device__ __forceinline__ T ld(const void *base, uint32_t byte) {
+  return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) + byte);
+}
+
+// Index tables of the elements of one workgroup, advanced to its first element (e0).
+struct ElemTab {
+  const int32_t *map;   // [..][n^3] flagged map
+  const int32_t *pos;   // [..][epe] E-vector entries (DoF-ordered E-vector), or unused
+  const int16_t *rank;  // node -> entry within the element's E-vector row (-1: none)
+  uint32_t ebase;       // element-ordered E-vector: entry of e0's row
+  uint32_t epe;         // entries per element
+};
+template <int P>
+__device__ __forceinline__ ElemTab elem_tab(const int32_t *map, const int32_t *pos, int compact,
+                                            int64_t e0) {
+  ElemTab z;
+  z.epe = compact ? surf_count<P>() : Dims<P>::N3;
+  z.map = map + e0 * Dims<P>::N3;
+  z.pos = pos ? pos + e0 * z.epe : nullptr;
+  z.rank = compact ? kRankTable<P>.r : kNodeTable<P>.r;
+  z.ebase = (uint32_t)(e0 * z.epe);
+  return z;
+}
+
+// What one thread needs of its nodes l = t + k TPE: the map entry c and the destination d
+// of the node's value (the map entry of a sole or essential DoF, the E-vector entry of a
+// shared one).  A thread without a k-th node takes the last node, with the same values as
+// that node's owner, so that no load or LDS store is predicated: all loads of a group are in
+// flight together.
+template <int P>
+struct Nodes {
+  static constexpr int NL = Per<P>::NL;
+  int32_t c[NL], r[NL], d[NL];
+  static __device__ __forceinline__ int node(int t, int k) {
+    const int l = t + k * Dims<P>::TPE;
+    return l < Dims<P>::N3 ? l : Dims<P>::N3 - 1;
   }
-  T v[NL];
+  // rel: the thread's element, relative to the workgroup's first
+  __device__ __forceinline__ void load_map(const ElemTab &z, int t, uint32_t rel) {
 #pragma unroll
-  for (int k = 0; k < NL; ++k) v[k] = xm[c[k] & kDofMask];
-#pragma unroll
-  for (int k = 0; k < NL; ++k) {
-    const int l = t + k * D::TPE;
-    if (l < D::N3) {
-      buf[l] = (active && c[k] >= 0) ? v[k] : T(0);
-      if (smap) {
-        if constexpr (POS)
-          smap[l] = (c[k] >= 0 && !(c[k] & kSoleBit)) ? q[k] : c[k];
-        else
-          smap[l] = c[k];
-      }
-    }
+    for (int k = 0; k < NL; ++k) c[k] = ld<int32_t>(z.map, (rel * Dims<P>::N3 + node(t, k)) * 4u);
   }
+  __device__ __forceinline__ void load_rank(const ElemTab &z, int t) {
+#pragma unroll
+    for (int k = 0; k < NL; ++k) r[k] = ld<int16_t>(z.rank, node(t, k) * 2u);
+  }
+  // (after load_map and load_rank)
+  template <bool POS>
+  __device__ __forceinline__ void load_dest(const ElemTab &z, uint32_t rel) {
+#pragma unroll
+    for (int k = 0; k < NL; ++k) {
+      const uint32_t w = rel * z.epe + (uint32_t)(r[k] > 0 ? r[k] : 0);
+      d[k] = POS ? ld<int32_t>(z.pos, w * 4u) : (int32_t)(z.ebase + w);
+    }
+#pragma unroll
+    for (int k = 0; k < NL; ++k) d[k] = (c[k] >= 0 && !(c[k] & kSoleBit)) ? d[k] : c[k];
+  }
+  template <typename T>
+  __device__ __forceinline__ void load_values(const T *xm, T (&v)[NL]) const {
+#pragma unroll
+    for (int k = 0; k < NL; ++k) v[k] = xm[c[k] & kDofMask];
+  }
+  __device__ __forceinline__ void keep(int32_t *smap, int t) const {
+#pragma unroll
+    for (int k = 0; k < NL; ++k) smap[node(t, k)] = d[k];
+  }
+};
+
+// Gather the element's nodal values (essential DoFs as 0, unless ESS) into buf[k][j][i].
+// Ends with a barrier.
+template <int P, typename T, bool ESS = false>
+__device__ __forceinline__ void gather_e(T *buf, int t, bool active, const Nodes<P> &nd,
+                                         const T *__restrict__ xm) {
+  T v[Nodes<P>::NL];
+  nd.load_values(xm, v);
+#pragma unroll
+  for (int k = 0; k < Nodes<P>::NL; ++k)
+    buf[Nodes<P>::node(t, k)] = (active && (ESS || nd.c[k] >= 0)) ? v[k] : T(0);
   __syncthreads();
 }
 
-// Output of the element vector buf[l] of element e: sole DoFs -> y, shared nodes ->
-// their E-vector entry (POS: the entry kept in smap by the gather; otherwise e * S + the
-// node's surface rank, or e * n^3 + l for the general layout), essential -> nothing.
-// The map entries come from LDS, kept by the gather.  With DOT, returns this thread's
-// part of sum x_g y_g over the sole DoFs (x read again from xm).
-template <int P, typename T, bool DOT, bool POS>
+// Output of the element vector buf[l]: sole DoFs -> y, shared nodes -> their E-vector
+// entry, essential -> nothing.  The destinations come from LDS, kept by the gather.  With
+// DOT, returns this thread's part of sum x_g y_g over the sole DoFs (x read again from xm).
+template <int P, typename T, bool DOT>
 __device__ __forceinline__ double emit_e(const T *buf, int t, bool active, const int32_t *smap,
-                                         const T *__restrict__ xm, int64_t e, bool compact,
-                                         T *__restrict__ Y, T *__restrict__ y) {
+                                         const T *__restrict__ xm, T *__restrict__ Y,
+                                         T *__restrict__ y) {
   using D = Dims<P>;
   constexpr int NL = Per<P>::NL;
   double dot = 0.0;
 #pragma unroll
   for (int k = 0; k < NL; ++k) {
-    const int l0 = t + k * D::TPE;
-    const int l = l0 < D::N3 ? l0 : D::N3 - 1;
+    const int l = Nodes<P>::node(t, k);
     const int32_t c = smap[l];
     const T v = buf[l];
     // one predicated store per node: the destination is selected, not branched to
-    const bool ok = active && l0 < D::N3 && c >= 0;
+    const bool ok = active && t + k * D::TPE < D::N3 && c >= 0;
     const bool sole = (c & kSoleBit) != 0;
     const int32_t g = c & kDofMask;
-    int64_t ye;
-    if constexpr (POS)
-      ye = c;
-    else
-      ye = compact ? e * surf_count<P>() + surf_rank<P>(l) : e * D::N3 + l;
-    T *dst = sole ? y + g : Y + ye;
-    if (ok) *dst = v;
+    if (ok) (sole ? y : Y)[g] = v;
     if constexpr (DOT) {
       const T xv = xm[sole ? g : 0];  // in range for every entry
       if (ok && sole) dot += (double)xv * (double)v;
@@ -394,28 +434,18 @@ __device__ __forceinline__ int xcd_block() {
   return (int)(xcd * q8 + (xcd < r8 ? xcd : r8) + k);
 }
 
-// How the element kernel of order P and precision T feeds its xi_3 stage (chosen by
-// measurement on MI355X, see the design notes):
-//   ZLDS   the stage's input lines are read from LDS again for every slice pair instead
-//          of being held in registers for the whole stage (fewer registers);
-//   PRE_X, PRE_Y  slice pairs [0, PRE_X) of quadrature data are requested before the
-//          xi_1 contraction and [PRE_X, PRE_Y) before the xi_2 contraction;
-//   LA     in the xi_3 loop, pair c + LA is requested when pair c starts;
+// How the element kernel of order P and precision T is built (chosen by measurement on
+// MI355X):
+//   ZLDS   the xi_3 stage's input lines are read from LDS again for every slice pair
+//          instead of being held in registers for the whole stage (fewer registers);
 //   OCC    minimum waves per SIMD the kernel is compiled for (launch bound);
 //   E      elements per workgroup (q^2 threads each).
 template <int P, typename T>
 struct ApplyCfg {
   static constexpr bool F64 = sizeof(T) == 8;
-  // (p = 8 with 5 elements per workgroup, 500 of 512 lanes busy instead of 200 of 256,
-  // measured 4 % slower in FP64: one workgroup per CU at its register count)
   static constexpr int E = Dims<P>::E;
   static constexpr int THREADS = E * Dims<P>::TPE;
   static constexpr bool ZLDS = F64 ? (P >= 5) : (P == 6 || P == 8);
-  // (p = 4, FP64: slice pair 0 requested before the xi_1 stage, pair 1 before xi_2, pair 2
-  // when the xi_3 loop starts; 2 % faster than one pair ahead with the factors stored by
-  // slice pair)
-  static constexpr bool AHEAD = F64 ? (P == 8 || P == 4) : (P == 6 || P == 8);
-  static constexpr int PRE_X = AHEAD ? 1 : 0, PRE_Y = (P == 4) ? 2 : 1, LA = AHEAD ? 1 : 0;
   static constexpr int OCC = Dims<P>::OCC;
 };
 
@@ -424,15 +454,27 @@ struct ApplyCfg {
 // of x_g y_g over the sole DoFs (part[m * part_mstride + block], 0 for a member with no
 // element in the block).
 //
+// The geometric factors are formed from the element's trilinear coefficients (geom.h) along
+// each thread's xi_3 line; with NU the kernel reads one value per point, cw = w nu / |J|
+// ([nelem][q^3] per field, float64 for both precisions), and without (nu = 1) none.  The
+// float64 operators multiply by adj(J) twice.  The float32 ones form the six factors in
+// float64 and round each once, so that they are those a stored float32 copy would hold
+// (forming them in float32 rounds adj(J) twice each: 5-15 % more error of the apply).
+//
+// Reading the factors (7 values per point) bound the kernel by HBM: of the 553 MB of an apply
+// at 32^3 p = 4 in float64, 396 MB were factors.  Formed, they cost 35 to 40 operations a
+// point, and the kernel is bound by VALU issue, LDS and the latency between its barriers:
+// 120.3 -> 77.3 us there, 212 -> 126 us for nu = 1 at 63 x 61 x 59 p = 2, float32 32^3 p = 8
+// 341 -> 290 us.
+//
 // Work items are (element, member) pairs, pair v = e * nbatch + m, E per workgroup: the
 // members of one element run side by side (in the same workgroup or in neighbouring
-// ones, on one XCD) and read the element's quadrature data, which all members share
-// unless qd_mstride != 0, from the same cache lines, so that it comes from HBM once for
-// all members.
-template <int P, typename T, int OP>
+// ones, on one XCD) and read the element's coefficients, which all members share unless
+// cw_mstride != 0, from the same cache lines.
+template <int P, typename T, int OP, bool NU>
 __global__ void __launch_bounds__((ApplyCfg<P, T>::THREADS), (ApplyCfg<P, T>::OCC))
-apply_kernel(const int32_t *__restrict__ map, const T *__restrict__ qd,
-             int64_t qd_mstride, const T *__restrict__ nu, int64_t nu_mstride, int64_t nelem,
+apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
+             const double *__restrict__ cw, int64_t cw_mstride, double alpha, double beta, int64_t nelem,
              int nbatch, int64_t ndof, const T *__restrict__ x, T *__restrict__ Y,
              int64_t estride, const int32_t *__restrict__ pos, int compact, T *__restrict__ y,
              double *__restrict__ part,
@@ -448,65 +490,57 @@ apply_kernel(const int32_t *__restrict__ map, const T *__restrict__ qd,
   // (E * BUF * sizeof(T) >= THREADS * 8 bytes)
   static_assert(E * D::BUF * sizeof(T) >= THREADS * sizeof(double), "block sum space");
   __shared__ __align__(16) T smem[E * D::BUF];
+  __shared__ __align__(16) double sgeo[E * kGeoStride];  // the elements' trilinear coefficients
   __shared__ int32_t smap_all[E * N3];  // the elements' map entries, kept for the output
   const int le = threadIdx.x / TPE;
   const int t = threadIdx.x - le * TPE;
-  // the grid has one workgroup per E (element, member) pairs (nelem * nbatch pairs)
+  // the grid has one workgroup per E (element, member) pairs (nelem * nbatch pairs); the
+  // workgroup's first pair is (e0, r0), the thread's is (e0 + rel, m)
   const int64_t npair = nelem * (int64_t)nbatch;
-  const int64_t v = (int64_t)xcd_block() * E + le;
-  const bool active = v < npair;
-  const int64_t vs = active ? v : 0;
-  const int es = (int)(vs / nbatch);
-  const int m = (int)(vs - (int64_t)es * nbatch);
+  const int64_t v_lo = (int64_t)xcd_block() * E;
+  const int count = (int)((npair - v_lo) < E ? (npair - v_lo) : E);
+  const bool active = le < count;
+  int64_t e0 = v_lo;
+  uint32_t r0 = 0, rel = active ? le : 0, m = 0;  // (inactive slots redo e0's data)
+  if (nbatch != 1) {
+    e0 = v_lo / nbatch;
+    r0 = (uint32_t)(v_lo - e0 * nbatch);
+    const uint32_t rr = r0 + rel;
+    rel = rr / (uint32_t)nbatch;
+    m = rr - rel * (uint32_t)nbatch;
+  }
   T *buf = smem + le * D::BUF;
 
-  // Quadrature values one thread needs per slice c: w|J| (mass), the 6 entries of
-  // w|J| J^-1 J^-T (diffusion), and nu for the diffusion operator.
-  constexpr int NS = (OP == 0) ? 1 : (OP == 2 ? 7 : 7);
   {
     const T *xm = x + (int64_t)m * ndof;
-    const T *qe = qd + (int64_t)m * qd_mstride + es * (int64_t)(kQdSlots * Q3);
-    const T *ne = nullptr;
-    if constexpr (OP == 1) ne = nu + (int64_t)m * nu_mstride + es * (int64_t)Q3;
-    // (inactive slots read element 0's data, which is discarded)
-    auto load_slice = [&](T (&dst)[NS], int c) {
-      const int qi = c * Q2 + t;
-      if constexpr (OP == 0) {
-        dst[0] = qe[qi];
-      } else if constexpr (OP == 2) {
-        // the folded factors are stored by slice pair, then slice, then slot
-        const int pc = c <= Q - 1 - c ? c : Q - 1 - c;
-        const int base = (2 * pc + (c > Q - 1 - c ? 1 : 0)) * 7 * Q2 + t;
+    // first group of loads: the map, the entry order, the coefficients of the element and
+    // of the thread's points; then what the map leads to
+    const ElemTab z = elem_tab<P>(map, pos, compact, e0);
+    Nodes<P> nd;
+    nd.load_map(z, t, rel);
+    nd.load_rank(z, t);
+    constexpr int NG = (kGeoStride + TPE - 1) / TPE;
+    double gv[NG];
 #pragma unroll
-        for (int s = 0; s < 7; ++s) dst[s] = qe[base + s * Q2];
-      } else {
+    for (int k = 0; k < NG; ++k) {
+      const int i = t + k * TPE < kGeoStride ? t + k * TPE : kGeoStride - 1;
+      gv[k] = ld<double>(geo + e0 * kGeoStride, (rel * kGeoStride + i) * 8u);
+    }
+    double cv[Q];  // w nu / |J| at the points of the thread's line
+    if constexpr (NU) {
+      const double *ce = cw + (int64_t)m * cw_mstride + e0 * (int64_t)Q3 + (rel * Q3 + t);
 #pragma unroll
-        for (int s = 0; s < 6; ++s) dst[s] = qe[(s + 1) * Q3 + qi];
-        dst[6] = ne[qi];
-      }
-    };
-
+      for (int c = 0; c < Q; ++c) cv[c] = ce[c * Q2];
+    }
+    nd.template load_dest<POS>(z, rel);
     int32_t *smap = smap_all + le * N3;
-    const int64_t moff = (int64_t)es * N3;
-    const int64_t epe = compact ? surf_count<P>() : N3;
-    gather_e<P, T, POS>(buf, t, active, map + moff, xm, smap,
-                        POS ? pos + (int64_t)es * epe : nullptr, compact != 0);
-    // quadrature data of slice pair c (slices c and q-1-c; the middle slice of an odd q
-    // alone), requested ahead of use as ApplyCfg sets
+#pragma unroll
+    for (int k = 0; k < NG; ++k)
+      sgeo[le * kGeoStride + (t + k * TPE < kGeoStride ? t + k * TPE : kGeoStride - 1)] = gv[k];
+    nd.keep(smap, t);
+    gather_e<P, T>(buf, t, active, nd, xm);
     using C = ApplyCfg<P, T>;
-    constexpr int NPR = (Q + 1) / 2;
-    constexpr int PRE_X = C::PRE_X < NPR ? C::PRE_X : NPR;
-    constexpr int PRE_Y = C::PRE_Y < NPR ? C::PRE_Y : NPR;
-    T qlo[NPR][NS], qhi[NPR][NS];
-    auto load_pair = [&](int c) {
-      load_slice(qlo[c], c);
-      if (c != Q - 1 - c) load_slice(qhi[c], Q - 1 - c);
-    };
-#pragma unroll
-    for (int c = 0; c < PRE_X; ++c) load_pair(c);
     fwd_x<P, T, DIFF>(buf, t);
-#pragma unroll
-    for (int c = PRE_X; c < PRE_Y; ++c) load_pair(c);
     fwd_y<P, T, DIFF>(buf, t);
 
     // xi_3 contraction, quadrature function, transposed xi_3: thread = line (a, b),
@@ -514,6 +548,13 @@ apply_kernel(const int32_t *__restrict__ map, const T *__restrict__ qd,
     {
       using BT = eo::Tab1<P, 0>;
       using GT = eo::Tab1<P, 1>;
+      constexpr rules::GaussRule<Q> gr = rules::gauss<Q>();
+      std::conditional_t<sizeof(T) == 8, LineGeom, LineMetric> L;
+      const int la = t % Q, lb = t / Q;
+      L.init(sgeo + le * kGeoStride, kGaussRule<Q>.x[la], kGaussRule<Q>.x[lb]);
+      const double wab = kGaussRule<Q>.w[la] * kGaussRule<Q>.w[lb];
+      const double wm = alpha * wab;             // mass weight of the line
+      const double ws = NU ? beta : beta * wab;  // diffusion weight (cw holds w)
       // the stage's input lines (split into even and odd parts), held in registers or,
       // with ZLDS, read from LDS again for every slice pair
       eo::Split<N, T> rbb{}, rgb{}, rbg{};
@@ -561,34 +602,34 @@ apply_kernel(const int32_t *__restrict__ map, const T *__restrict__ qd,
         if constexpr (N % 2 == 1 && TT::S > 0) M += (T)TT::t(Q / 2, N / 2) * x.e[N / 2];
         return M;
       };
+      // v = alpha w |J| u and g = beta nu w |J| J^-1 J^-T grad_ref u at slice c
       auto qfun = [&](int c, T u, T dx, T dy, T dz, T &v, T &g1, T &g2, T &g3) {
-        T cur[NS];
-        const int pc = c <= Q - 1 - c ? c : Q - 1 - c;  // the slice's pair
-        if (C::LA == 0 && pc >= PRE_Y) {
-          load_slice(cur, c);  // not requested ahead: load at its use
-        } else {
-#pragma unroll
-          for (int z = 0; z < NS; ++z) cur[z] = (c == pc) ? qlo[pc][z] : qhi[pc][z];
-        }
+        const double xc = gr.x[c], wc = gr.w[c];
         v = g1 = g2 = g3 = T(0);
-        if constexpr (MASS) v = cur[0] * u;
+        double det = 0.0;
+        if constexpr (MASS || !NU) det = L.det(xc);
+        if constexpr (MASS) v = (T)((wm * wc) * det) * u;
         if constexpr (DIFF) {
-          constexpr int o = MASS ? 1 : 0;
-          const T G11 = cur[o + 0], G22 = cur[o + 1], G33 = cur[o + 2];
-          const T G12 = cur[o + 3], G13 = cur[o + 4], G23 = cur[o + 5];
-          g1 = G11 * dx + G12 * dy + G13 * dz;
-          g2 = G12 * dx + G22 * dy + G23 * dz;
-          g3 = G13 * dx + G23 * dy + G33 * dz;
-          if constexpr (OP == 1) {
-            g1 *= cur[NS - 1];
-            g2 *= cur[NS - 1];
-            g3 *= cur[NS - 1];
+          const double s = NU ? cv[c] * ws : (ws * wc) * recip(det);
+          if constexpr (sizeof(T) == 8) {
+            double r1[3], r2[3], r3[3], f[3];
+            L.adj(xc, r1, r2, r3);
+#pragma unroll
+            for (int r = 0; r < 3; ++r) f[r] = s * (r1[r] * dx + r2[r] * dy + r3[r] * dz);
+            g1 = r1[0] * f[0] + r1[1] * f[1] + r1[2] * f[2];
+            g2 = r2[0] * f[0] + r2[1] * f[1] + r2[2] * f[2];
+            g3 = r3[0] * f[0] + r3[1] * f[1] + r3[2] * f[2];
+          } else {
+            float G[6];
+            L.factors(xc, s, G);
+            g1 = G[0] * dx + G[3] * dy + G[4] * dz;
+            g2 = G[3] * dx + G[1] * dy + G[5] * dz;
+            g3 = G[4] * dx + G[5] * dy + G[2] * dz;
           }
         }
       };
 #pragma unroll
       for (int c = 0; c < Q / 2; ++c) {
-        if (C::LA > 0 && c + C::LA >= PRE_Y && c + C::LA < NPR) load_pair(c + C::LA);
         T u0 = 0, u1 = 0, dx0 = 0, dx1 = 0, dy0 = 0, dy1 = 0, dz0 = 0, dz1 = 0;
         eo::Split<N, T> sbb, sgb, sbg;
         zlines(sbb, sgb, sbg);
@@ -648,22 +689,19 @@ apply_kernel(const int32_t *__restrict__ map, const T *__restrict__ qd,
     bwd_y<P, T, DIFF>(buf, t);
     bwd_x<P, T, DIFF>(buf, t);
     if (part) {
-      const double dot = emit_e<P, T, true, POS>(buf, t, active, smap, xm, es, compact != 0,
-                                                 Y + (int64_t)m * estride, y + (int64_t)m * ndof);
+      const double dot =
+          emit_e<P, T, true>(buf, t, active, smap, xm, Y + (int64_t)m * estride, y + (int64_t)m * ndof);
       // one sum per member; the block's pairs v_lo.. hold members (v_lo + k) mod nbatch,
       // k < count (a uniform test: members without a pair here get 0 without a sum)
-      const int64_t v_lo = (int64_t)xcd_block() * E;
-      const int64_t count = (npair - v_lo) < E ? (npair - v_lo) : E;
-      const int r_lo = (int)(v_lo % nbatch);
       for (int mm = 0; mm < nbatch; ++mm) {
-        const bool here = ((mm - r_lo + nbatch) % nbatch) < count;
+        const bool here = ((mm - (int)r0 + nbatch) % nbatch) < count;
         double sum = 0.0;
-        if (here) sum = block_sum_d((active && m == mm) ? dot : 0.0, reinterpret_cast<double *>(smem));
+        if (here)
+          sum = block_sum_d((active && (int)m == mm) ? dot : 0.0, reinterpret_cast<double *>(smem));
         if (threadIdx.x == 0) part[(int64_t)mm * part_mstride + blockIdx.x] = sum;
       }
     } else {
-      emit_e<P, T, false, POS>(buf, t, active, smap, xm, es, compact != 0,
-                               Y + (int64_t)m * estride, y + (int64_t)m * ndof);
+      emit_e<P, T, false>(buf, t, active, smap, xm, Y + (int64_t)m * estride, y + (int64_t)m * ndof);
     }
   }
 }
@@ -676,25 +714,20 @@ hipError_t launch_apply_pt(const ApplyArgs &a, hipStream_t s) {
   using C = ApplyCfg<P, T>;
   dim3 grid((unsigned)((a.nelem * a.nbatch + C::E - 1) / C::E));
   dim3 block(C::THREADS);
-  const T *qd = (const T *)a.qd;
-  const T *nu = (const T *)a.nu;
   const T *x = (const T *)a.x;
   T *Y = (T *)a.evec;
   T *y = (T *)a.y;
 #define SFEM_APPLY_ARGS                                                                    \
-  a.map, qd, a.qd_mstride, nu, a.nu_mstride, a.nelem, a.nbatch, a.ndof, x, Y, a.estride, \
+  a.map, a.geo, a.cw, a.cw_mstride, a.alpha, a.beta, a.nelem, a.nbatch, a.ndof, x, Y, a.estride, \
       a.pos, a.compact, y, a.part, a.part_mstride
-  switch (a.op) {
-    case SFEM_MASS:
-      hipLaunchKernelGGL((apply_kernel<P, T, 0>), grid, block, 0, s, SFEM_APPLY_ARGS);
-      break;
-    case SFEM_DIFFUSION:
-      hipLaunchKernelGGL((apply_kernel<P, T, 1>), grid, block, 0, s, SFEM_APPLY_ARGS);
-      break;
-    default:
-      hipLaunchKernelGGL((apply_kernel<P, T, 2>), grid, block, 0, s, SFEM_APPLY_ARGS);
-      break;
-  }
+#define SFEM_APPLY(OP, NU) \
+  hipLaunchKernelGGL((apply_kernel<P, T, OP, NU>), grid, block, 0, s, SFEM_APPLY_ARGS)
+  if (a.op == SFEM_MASS) SFEM_APPLY(0, false);
+  else if (a.op == SFEM_DIFFUSION && a.cw) SFEM_APPLY(1, true);
+  else if (a.op == SFEM_DIFFUSION) SFEM_APPLY(1, false);
+  else if (a.cw) SFEM_APPLY(2, true);
+  else SFEM_APPLY(2, false);
+#undef SFEM_APPLY
 #undef SFEM_APPLY_ARGS
   return hipGetLastError();
 }

@@ -56,10 +56,10 @@ struct ApplyArgs {
   int p;
   int op;                   // SFEM_MASS / SFEM_DIFFUSION / SFEM_HELMHOLTZ
   const int32_t *map;       // [nei][n^3] flagged map, internal element order
-  const void *qd;           // quadrature data, [nei][7][q^3] (slot layout above)
-  int64_t qd_mstride;       // elements of qd between batch members (0 = shared)
-  const void *nu;           // DIFFUSION only: [nei][q^3] or null
-  int64_t nu_mstride;
+  const double *geo;        // trilinear coefficients of the elements, [nei][kGeoStride] (geom.h)
+  const double *cw;         // w nu / |J| at the points, [nei][q^3], or null (nu = 1)
+  int64_t cw_mstride;       // entries of cw between batch members (0 = shared)
+  double alpha, beta;       // coefficients of the mass and diffusion terms
   int64_t ndof;
   int nbatch;
   int64_t nelem;
@@ -124,9 +124,11 @@ hipError_t launch_colloc_mass(int p, const double *gll_x, const double *gll_w, c
                               double *diag, double *evec, hipStream_t s);
 hipError_t launch_qpoint_coords(int q, const double *gx, const double *gw, const double *xyz,
                                 int64_t nei, double *xq, hipStream_t s);
-hipError_t launch_fold(int q, const double *qd, const double *nu_user, int64_t nei, int nfield,
-                       double alpha, double beta, double *fold64, float *fold32, double *nu64,
-                       float *nu32, hipStream_t s);
+// Trilinear coefficients of the elements (geom.h), [nei][kGeoStride].
+hipError_t launch_geo_setup(const double *xyz, int64_t nei, double *geo, hipStream_t s);
+// cw = w nu / |J| at the points of nfield coefficient fields, and the library's copy of nu.
+hipError_t launch_fold(int q, const double *gx, const double *gw, const double *geo, const double *nu_user,
+                       int64_t nei, int nfield, double *cw, double *nu64, hipStream_t s);
 hipError_t launch_cast_f32(const double *src, float *dst, int64_t n, hipStream_t s);
 
 struct GradArgs {

@@ -119,7 +119,7 @@ diag_kernel(const int32_t *__restrict__ map, const double *__restrict__ qd,
     if (c & kSoleBit)
       diag[c & kDofMask] = s0[l];
     else {
-      const int64_t q = compact ? e * surf_count<P>() + surf_rank<P>(l) : e * N3 + l;
+      const int64_t q = compact ? e * surf_count<P>() + kRankTable<P>.r[l] : e * N3 + l;
       Y[pos ? pos[q] : q] = s0[l];
     }
   }

@@ -19,12 +19,12 @@ namespace {
 // Reference gradient (d/dxi_1, d/dxi_2, d/dxi_3) of a nodal field at the q points of
 // this thread's xi_3 line.
 template <int P, typename T>
-__device__ __forceinline__ void ref_grad_line(T *buf, int t, bool active, const int32_t *emap,
+__device__ __forceinline__ void ref_grad_line(T *buf, int t, bool active, const Nodes<P> &nd,
                                               const T *__restrict__ v,
                                               T (&gx)[P + 2], T (&gy)[P + 2], T (&gz)[P + 2]) {
   constexpr int N = P + 1, Q = P + 2;
   using TB = Tab<P, T>;
-  gather_e<P, T>(buf, t, active, emap, v);
+  gather_e<P, T>(buf, t, active, nd, v);
   fwd_x<P, T, true>(buf, t);
   fwd_y<P, T, true>(buf, t);
   T zbb[N], zgb[N], zbg[N];
@@ -55,16 +55,18 @@ grad_kernel(const int32_t *__restrict__ map, const double *__restrict__ qd, doub
   __shared__ double smem[E * D::BUF];
   const int le = threadIdx.x / TPE;
   const int t = threadIdx.x - le * TPE;
-  const int64_t e = (int64_t)blockIdx.x * E + le;
+  const int64_t e0 = (int64_t)blockIdx.x * E;
+  const int64_t e = e0 + le;
   const bool active = e < nei;
-  const int64_t es = active ? e : 0;
+  const int64_t es = active ? e : e0;
   double *buf = smem + le * D::BUF;
-  const int32_t *emap = map + es * (int64_t)D::N3;
+  Nodes<P> nd;
+  nd.load_map(elem_tab<P>(map, nullptr, 1, e0), t, (uint32_t)(es - e0));
   const double *qe = qd + es * (int64_t)(kQdSlots * Q3);
   for (int m = 0; m < nbatch; ++m) {
     double lx[Q], ly[Q], lz[Q], ux[Q], uy[Q], uz[Q];
-    ref_grad_line<P, double>(buf, t, active, emap, lam + (int64_t)m * ndof, lx, ly, lz);
-    ref_grad_line<P, double>(buf, t, active, emap, u + (int64_t)m * ndof, ux, uy, uz);
+    ref_grad_line<P, double>(buf, t, active, nd, lam + (int64_t)m * ndof, lx, ly, lz);
+    ref_grad_line<P, double>(buf, t, active, nd, u + (int64_t)m * ndof, ux, uy, uz);
     if (active) {
       double *go = g + ((int64_t)m * nei + e) * Q3;
 #pragma unroll
@@ -126,7 +128,7 @@ load_kernel(const int32_t *__restrict__ map, const double *__restrict__ qd, int6
         if (c & kSoleBit) {
           bm[c & kDofMask] = buf[l];
         } else {
-          const int64_t q = compact ? e * surf_count<P>() + surf_rank<P>(l) : e * D::N3 + l;
+          const int64_t q = compact ? e * surf_count<P>() + kRankTable<P>.r[l] : e * D::N3 + l;
           Ym[pos ? pos[q] : q] = buf[l];
         }
       }

@@ -1,8 +1,9 @@
-// Setup kernels: quadrature data (Section 3.1: w|J| and w|J| J^-1 J^-T stored at the
-// quadrature points), physical quadrature-point coordinates, folding of the
-// Helmholtz coefficients into the stored factors, precision casts.
+// Setup kernels: the elements' trilinear coefficients, quadrature data (Section 3.1: w|J|
+// and w|J| J^-1 J^-T at the quadrature points), physical quadrature-point coordinates, the
+// coefficient w nu / |J| of the applies, precision casts.
 #include <hip/hip_runtime.h>
 
+#include "geom.h"
 #include "internal.h"
 #include "flow.h"
 
@@ -181,36 +182,45 @@ __global__ void qpoint_coords_kernel(GaussArg g, int q, const double *__restrict
   xq[2 * plane + o] = pos[2];
 }
 
-// Folded Helmholtz factors, slot s = 0: alpha w|J|; s = 1..6: beta nu_f w|J| J^-1 J^-T, stored
-// per element in the order the element kernel reads them: slice pairs (c, q-1-c) in turn,
-// within a pair slice c then slice q-1-c (the middle slice of an odd q alone), within a
-// slice the 7 slots, each the q^2 points of the slice:
-//   fold[f][e][(2 min(c, q-1-c) + [c > q-1-c]) 7 q^2 + s q^2 + a + q b]   (point (a, b, c))
-__global__ void fold_kernel(int q, int q3, const double *__restrict__ qd,
-                            const double *__restrict__ nu_user, int64_t nei, int nfield,
-                            double alpha, double beta,
-                            double *__restrict__ fold64, float *__restrict__ fold32,
-                            double *__restrict__ nu64, float *__restrict__ nu32) {
+// Trilinear coefficients of the elements: sums of vertex differences, so that no digits are
+// lost to the element's distance from the origin.
+__global__ void geo_setup_kernel(const double *__restrict__ xyz, int64_t nei, double *__restrict__ geo) {
   const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t per_field = nei * q3;
+  if (gid >= nei * 3) return;
+  const int64_t e = gid / 3;
+  const int r = (int)(gid - e * 3);
+  const double *X = xyz + e * 24 + r;
+  // differences along xi_1 of the edges (j, k), and along xi_2, xi_3 of the xi_1 = -1 face
+  const double d00 = X[3] - X[0], d10 = X[9] - X[6], d01 = X[15] - X[12], d11 = X[21] - X[18];
+  const double f0 = X[6] - X[0], f1 = X[9] - X[3], f2 = X[18] - X[12], f3 = X[21] - X[15];
+  const double h0 = X[12] - X[0], h1 = X[15] - X[3], h2 = X[18] - X[6], h3 = X[21] - X[9];
+  double *o = geo + e * kGeoStride + r;
+  o[0] = 0.125 * ((d00 + d10) + (d01 + d11));
+  o[3] = 0.125 * ((f0 + f1) + (f2 + f3));
+  o[6] = 0.125 * ((h0 + h1) + (h2 + h3));
+  o[9] = 0.125 * ((d10 - d00) + (d11 - d01));
+  o[12] = 0.125 * ((d01 - d00) + (d11 - d10));
+  o[15] = 0.125 * ((f2 - f0) + (f3 - f1));
+  o[18] = 0.125 * ((d11 - d10) - (d01 - d00));
+  o[21] = 0.0;
+}
+
+// cw[f][e][point] = w nu_f / |J|, the one coefficient the element kernel reads per point, and
+// a copy of nu.
+__global__ void fold_kernel(GaussArg g, int q, const double *__restrict__ geo,
+                            const double *__restrict__ nu_user, int64_t nei, int nfield,
+                            double *__restrict__ cw, double *__restrict__ nu64) {
+  const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t q3 = (int64_t)q * q * q, per_field = nei * q3;
   if (gid >= per_field * nfield) return;
-  const int64_t f = gid / per_field;
-  const int64_t r = gid - f * per_field;
-  const int64_t e = r / q3;
+  const int64_t f = gid / per_field, r = gid - f * per_field, e = r / q3;
   const int qi = (int)(r - e * q3);
-  const double nv = nu_user ? nu_user[f * per_field + r] : 1.0;
-  const double *src = qd + e * (int64_t)(kQdSlots * q3) + qi;
-  const int q2 = q * q, c = qi / q2, t = qi - c * q2;
-  const int pc = c <= q - 1 - c ? c : q - 1 - c;
-  const int64_t o = (f * nei + e) * (int64_t)(kQdSlots * q3) +
-                    (int64_t)(2 * pc + (c > q - 1 - c ? 1 : 0)) * kQdSlots * q2 + t;
-  for (int s = 0; s < kQdSlots; ++s) {
-    const double v = (s == 0) ? alpha * src[0] : beta * nv * src[(int64_t)s * q3];
-    fold64[o + (int64_t)s * q2] = v;
-    fold32[o + (int64_t)s * q2] = (float)v;
-  }
-  nu64[f * per_field + r] = nv;
-  nu32[f * per_field + r] = (float)nv;
+  const int a = qi % q, b = (qi / q) % q, c = qi / (q * q);
+  LineGeom L;
+  L.init(geo + e * kGeoStride, g.x[a], g.x[b]);
+  const double nv = nu_user[gid];
+  cw[gid] = g.w[a] * g.w[b] * g.w[c] * nv / L.det(g.x[c]);
+  nu64[gid] = nv;
 }
 
 __global__ void cast_kernel(const double *__restrict__ src, float *__restrict__ dst, int64_t n) {
@@ -259,14 +269,18 @@ hipError_t launch_qpoint_coords(int q, const double *gx, const double *gw, const
   return hipGetLastError();
 }
 
-hipError_t launch_fold(int q, const double *qd, const double *nu_user, int64_t nei, int nfield,
-                       double alpha, double beta, double *fold64, float *fold32, double *nu64,
-                       float *nu32, hipStream_t s) {
-  const int q3 = q * q * q;
-  const int64_t n = nei * (int64_t)q3 * nfield;
+hipError_t launch_geo_setup(const double *xyz, int64_t nei, double *geo, hipStream_t s) {
+  if (nei == 0) return hipSuccess;
+  hipLaunchKernelGGL(geo_setup_kernel, dim3(nblocks(nei * 3, 256)), dim3(256), 0, s, xyz, nei, geo);
+  return hipGetLastError();
+}
+
+hipError_t launch_fold(int q, const double *gx, const double *gw, const double *geo, const double *nu_user,
+                       int64_t nei, int nfield, double *cw, double *nu64, hipStream_t s) {
+  const int64_t n = nei * (int64_t)q * q * q * nfield;
   if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(fold_kernel, dim3(nblocks(n, 256)), dim3(256), 0, s, q, q3, qd, nu_user,
-                     nei, nfield, alpha, beta, fold64, fold32, nu64, nu32);
+  hipLaunchKernelGGL(fold_kernel, dim3(nblocks(n, 256)), dim3(256), 0, s, gauss_arg(gx, gw, q), q, geo,
+                     nu_user, nei, nfield, cw, nu64);
   return hipGetLastError();
 }
 

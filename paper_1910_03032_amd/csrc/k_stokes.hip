@@ -241,33 +241,10 @@ __device__ __forceinline__ void emit_pres(const double *buf, int t, bool active,
     const double v = buf[l];
     const bool ok = active && l0 < NP3;
     const bool sole = (c & kSoleBit) != 0;
-    const int64_t ye = compact ? e * surf_count<P - 1>() + surf_rank<P - 1>(l) : e * NP3 + l;
+    const int64_t ye = compact ? e * surf_count<P - 1>() + kRankTable<P - 1>.r[l] : e * NP3 + l;
     double *dst = sole ? y + (c & kDofMask) : Y + ye;
     if (ok) *dst = v;
   }
-}
-
-// The velocity element's map entries into smap (as the apply's gather keeps them: with
-// POS the E-vector entry of each shared node, from the position table row epos).
-template <int P, bool POS>
-__device__ __forceinline__ void vel_entries(int t, const int32_t *emap, int32_t *smap,
-                                            const int32_t *epos, bool compact) {
-  using D = Dims<P>;
-  constexpr int NL = Per<P>::NL;
-#pragma unroll
-  for (int k = 0; k < NL; ++k) {
-    const int l0 = t + k * D::TPE;
-    const int l = l0 < D::N3 ? l0 : D::N3 - 1;
-    const int32_t c = emap[l];
-    int32_t v = c;
-    if constexpr (POS) {
-      const int r = compact ? surf_rank<P>(l) : l;
-      const int32_t q = epos[r >= 0 ? r : 0];
-      v = (c >= 0 && !(c & kSoleBit)) ? q : c;
-    }
-    if (l0 < D::N3) smap[l] = v;
-  }
-  __syncthreads();
 }
 
 // Offset of slot z at slice c (points a + q b follow) within an element's coupling
@@ -301,23 +278,22 @@ struct SDims {
 // assembly).
 template <int P, bool POS>
 __device__ __forceinline__ void emit_add_vel(const double *buf, int t, bool active,
-                                             const int32_t *smap, int64_t e, bool compact,
-                                             double *__restrict__ Y, double *__restrict__ y) {
+                                             const int32_t *smap, double *__restrict__ Y,
+                                             double *__restrict__ y) {
   using D = Dims<P>;
   constexpr int NL = Per<P>::NL;
 #pragma unroll
   for (int k = 0; k < NL; ++k) {
-    const int l0 = t + k * D::TPE;
-    const int l = l0 < D::N3 ? l0 : D::N3 - 1;
+    const int l = Nodes<P>::node(t, k);
     const int32_t c = smap[l];
     const double v = buf[l];
-    if (!(active && l0 < D::N3 && c >= 0)) continue;
+    if (!(active && t + k * D::TPE < D::N3 && c >= 0)) continue;
     if (c & kSoleBit) {
       y[c & kDofMask] += v;
     } else if constexpr (POS) {
       Y[c] += v;
     } else {
-      Y[compact ? e * surf_count<P>() + surf_rank<P>(l) : e * D::N3 + l] = v;
+      Y[c] = v;
     }
   }
 }
@@ -344,9 +320,10 @@ coupling_kernel(const int32_t *__restrict__ vmap, const int32_t *__restrict__ vp
   const int le = threadIdx.x / TPE;
   const int t0 = threadIdx.x - le * TPE;
   const int t = t0;
-  const int e = xcd_block() * E + le;
+  const int64_t e0 = (int64_t)xcd_block() * E;
+  const int64_t e = e0 + le;
   const bool active = e < nelem;
-  const int es = active ? e : 0;
+  const int64_t es = active ? e : e0;
   double *buf = smem + le * D::BUF;
   int32_t *smap = smap_all + le * N3;
   // pressure element: the xi_3 lines of its reference gradient
@@ -365,10 +342,16 @@ coupling_kernel(const int32_t *__restrict__ vmap, const int32_t *__restrict__ vp
     pgb = eo::split(zg);
     pbg = eo::split(zx);
   }
-  // the velocity element's map entries for the output
-  const int64_t vepe = vcompact ? surf_count<P>() : N3;
-  vel_entries<P, POS>(t, vmap + (int64_t)es * N3, smap, POS ? vpos + (int64_t)es * vepe : nullptr,
-                      vcompact != 0);
+  // the velocity element's destinations for the output
+  const ElemTab z = elem_tab<P>(vmap, vpos, vcompact, e0);
+  {
+    Nodes<P> nd;
+    nd.load_map(z, t, (uint32_t)(es - e0));
+    nd.load_rank(z, t);
+    nd.template load_dest<POS>(z, (uint32_t)(es - e0));
+    nd.keep(smap, t);
+    __syncthreads();
+  }
   const double *ce = cq + (int64_t)es * (9 * Q3) + t;
   double s[1][Q];
 #pragma unroll
@@ -380,7 +363,11 @@ coupling_kernel(const int32_t *__restrict__ vmap, const int32_t *__restrict__ vp
     int t = t0;
     asm volatile("" : "+v"(t));
     // velocity component r (essential DoFs read as 0)
-    gather_e<P, double, false>(buf, t, active, vmap + (int64_t)es * N3, u + r * nv);
+    {
+      Nodes<P> nd;
+      nd.load_map(z, t, (uint32_t)(es - e0));
+      gather_e<P, double>(buf, t, active, nd, u + r * nv);
+    }
     fwd_grad_xy<P, Q>(buf, t);
     eo::Split<N, double> ubb, ugb, ubg;
     {
@@ -424,7 +411,7 @@ coupling_kernel(const int32_t *__restrict__ vmap, const int32_t *__restrict__ vp
             row_mid<PB>(pgb), row_mid<PG>(pbb));
     // G p, component r: added into yv / the velocity E-vector
     bwd_mass<P, Q, 1>(buf, t, v);
-    emit_add_vel<P, POS>(buf, t, active, smap, es, vcompact != 0, Yv + r * vestride, yv + r * nv);
+    emit_add_vel<P, POS>(buf, t, active, smap, Yv + r * vestride, yv + r * nv);
     __syncthreads();  // buf is reused by the next gather
   }
   // -D P u: one pressure field
@@ -440,30 +427,6 @@ coupling_kernel(const int32_t *__restrict__ vmap, const int32_t *__restrict__ vp
     __syncthreads();
   }
   emit_pres<P>(buf, t, active, smap, es, pcompact != 0, Yp, yp);
-}
-
-// Gather of a velocity component with the values of every DoF, essential ones included
-// (the convection term takes u as it is).
-template <int P>
-__device__ __forceinline__ void gather_all(double *buf, int t, bool active, const int32_t *emap,
-                                           const double *__restrict__ x) {
-  using D = Dims<P>;
-  constexpr int NL = Per<P>::NL;
-  int32_t c[NL];
-#pragma unroll
-  for (int k = 0; k < NL; ++k) {
-    const int l0 = t + k * D::TPE;
-    c[k] = emap[l0 < D::N3 ? l0 : D::N3 - 1];
-  }
-  double v[NL];
-#pragma unroll
-  for (int k = 0; k < NL; ++k) v[k] = x[c[k] & kDofMask];
-#pragma unroll
-  for (int k = 0; k < NL; ++k) {
-    const int l = t + k * D::TPE;
-    if (l < D::N3) buf[l] = active ? v[k] : 0.0;
-  }
-  __syncthreads();
 }
 
 // Interpolation of a nodal field of order P to the points, stages xi_1 and xi_2 (B only):
@@ -542,18 +505,28 @@ __device__ __forceinline__ void phi_test_body(const int32_t *__restrict__ vmap,
   __shared__ int32_t smap_all[E * N3];
   const int le = threadIdx.x / TPE;
   const int t0 = threadIdx.x - le * TPE;
-  const int e = xcd_block() * E + le;
+  const int64_t e0 = (int64_t)xcd_block() * E;
+  const int64_t e = e0 + le;
   const bool active = e < nelem;
-  const int es = active ? e : 0;
+  const int64_t es = active ? e : e0;
   double *buf = smem + le * D::BUF;
   int32_t *smap = smap_all + le * N3;
-  const int32_t *emap = vmap + (int64_t)es * N3;
+  // the nodes' map entries and destinations (the terms take u as it is, essential DoFs
+  // included)
+  Nodes<P> nd;
+  {
+    const ElemTab z = elem_tab<P>(vmap, vpos, vcompact, e0);
+    nd.load_map(z, t0, (uint32_t)(es - e0));
+    nd.load_rank(z, t0);
+    nd.template load_dest<POS>(z, (uint32_t)(es - e0));
+    nd.keep(smap, t0);
+  }
   // the input components' xi_3 lines (value and reference-gradient fields, even-odd
   // split), one gather and one forward pass each
   eo::Split<N, double> sbb[NIN], sgb[NIN], sbg[NIN];
 #pragma unroll
   for (int r = 0; r < NIN; ++r) {
-    gather_all<P>(buf, t0, active, emap, u + r * nv);
+    gather_e<P, double, true>(buf, t0, active, nd, u + r * nv);
     fwd_grad_xy<P, Q>(buf, t0);
     double zb[N], zg[N], zx[N];
 #pragma unroll
@@ -567,8 +540,6 @@ __device__ __forceinline__ void phi_test_body(const int32_t *__restrict__ vmap,
     sbg[r] = eo::split(zx);
     __syncthreads();  // buf is reused by the next gather
   }
-  const int64_t vepe = vcompact ? surf_count<P>() : N3;
-  vel_entries<P, POS>(t0, emap, smap, POS ? vpos + (int64_t)es * vepe : nullptr, vcompact != 0);
   const double *ce = cq + (int64_t)es * (9 * Q3) + t0;
   // the three outputs at the points of the line
   double n[3][Q];
@@ -626,8 +597,7 @@ __device__ __forceinline__ void phi_test_body(const int32_t *__restrict__ vmap,
   bwd_mass<P, Q, 3>(buf, t0, n);
 #pragma unroll
   for (int r = 0; r < 3; ++r)
-    emit_e<P, double, false, POS>(buf + r * N3, t0, active, smap, u, es, vcompact != 0,
-                                  Yv + r * vestride, yv + r * nv);
+    emit_e<P, double, false>(buf + r * N3, t0, active, smap, u, Yv + r * vestride, yv + r * nv);
 }
 
 template <int P, bool POS>
@@ -759,16 +729,26 @@ weak_div_kernel(const int32_t *__restrict__ vmap, const int32_t *__restrict__ vp
   __shared__ int32_t smap_all[E * N3];
   const int le = threadIdx.x / TPE;
   const int t0 = threadIdx.x - le * TPE;
-  const int e = xcd_block() * E + le;
+  const int64_t e0 = (int64_t)xcd_block() * E;
+  const int64_t e = e0 + le;
   const bool active = e < nelem;
-  const int es = active ? e : 0;
+  const int64_t es = active ? e : e0;
   double *buf = smem + le * D::BUF;
   int32_t *smap = smap_all + le * N3;
-  const int32_t *emap = vmap + (int64_t)es * N3;
+  // the nodes' map entries and destinations (the terms take u as it is, essential DoFs
+  // included)
+  Nodes<P> nd;
+  {
+    const ElemTab z = elem_tab<P>(vmap, vpos, vcompact, e0);
+    nd.load_map(z, t0, (uint32_t)(es - e0));
+    nd.load_rank(z, t0);
+    nd.template load_dest<POS>(z, (uint32_t)(es - e0));
+    nd.keep(smap, t0);
+  }
   eo::Split<N, double> sv[3];
 #pragma unroll
   for (int r = 0; r < 3; ++r) {
-    gather_all<P>(buf, t0, active, emap, u + r * nv);
+    gather_e<P, double, true>(buf, t0, active, nd, u + r * nv);
     fwd_val_xy<P, Q>(buf, t0);
     double z[N];
 #pragma unroll
@@ -776,8 +756,6 @@ weak_div_kernel(const int32_t *__restrict__ vmap, const int32_t *__restrict__ vp
     sv[r] = eo::split(z);
     __syncthreads();
   }
-  const int64_t vepe = vcompact ? surf_count<P>() : N3;
-  vel_entries<P, POS>(t0, emap, smap, POS ? vpos + (int64_t)es * vepe : nullptr, vcompact != 0);
   const double *ce = cq + (int64_t)es * (9 * Q3) + t0;
   double h[3][Q];  // (C^T V)_k at the points of the line
   auto point = [&](int c, const double (&vv)[3]) {
@@ -803,7 +781,7 @@ weak_div_kernel(const int32_t *__restrict__ vmap, const int32_t *__restrict__ vp
     point(Q / 2, vm);
   }
   bwd_grad<P, Q>(buf, t0, h);
-  emit_e<P, double, false, POS>(buf, t0, active, smap, u, es, vcompact != 0, Yv, yv);
+  emit_e<P, double, false>(buf, t0, active, smap, u, Yv, yv);
 }
 
 template <int P>
