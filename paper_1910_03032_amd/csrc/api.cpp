@@ -95,14 +95,13 @@ struct sfem_ctx {
   double *d_m1 = nullptr;          // M 1 (the integral of a DoF vector is m1^T x)
   double m1sum = 0.0;              // 1^T M 1 = |Omega| (no essential DoFs)
   AsmPlan plan{};                  // the three arrays above, for the assembly kernel
-  // Taylor-Hood pressure space (order p - 1) and the Stokes coupling factors
+  // Taylor-Hood pressure space (order p - 1)
   bool pres_ready = false;
   int64_t npres = 0;
   int32_t *d_pmap = nullptr;       // [nelem][p^3] flagged pressure map
   int pcompact = 0;
   int64_t pnentries = 0;           // pressure E-vector entries (element-ordered)
   AsmPlan pplan{};
-  double *d_cq = nullptr;          // [nelem][9 q^3] coupling factors w |J| J^{-T}, slice-pair order
 
   // ---- coefficients
   double alpha = 1.0, beta = 1.0;
@@ -259,7 +258,6 @@ void free_all(sfem_ctx *c) {
   c->pcompact = 0;
   c->pnentries = 0;
   c->pplan = AsmPlan{};
-  c->d_cq = nullptr;
   c->d_cw = nullptr;
   c->d_nu64 = nullptr;
   for (int o = 0; o < 3; ++o) {
@@ -1395,18 +1393,6 @@ sfem_status sfem_pcg(sfem_ctx *c, int op, int nbatch, const double *b, double *x
   return guarded(c, [&] { return sfem_pcg_body(c, op, nbatch, b, x, opts, info); });
 }
 
-// Coupling factors w |J| J^{-T} at the quadrature points (Stokes blocks, convection),
-// computed on first use.
-sfem_status ensure_cq(sfem_ctx *c) {
-  if (c->d_cq || c->nelem == 0) return SFEM_OK;
-  sfem_status st;
-  const int64_t q3 = (int64_t)c->q * c->q * c->q;
-  if ((st = dalloc(c, &c->d_cq, c->nelem * 9 * q3)) != SFEM_OK) return st;
-  HIPCHK(c, launch_coupling_setup(c->q, c->rules.gauss_x.data(), c->rules.gauss_w.data(), c->d_xyz,
-                                  c->nelem, c->d_cq, c->stream));
-  return SFEM_OK;
-}
-
 static sfem_status sfem_setup_pressure_body(sfem_ctx *c, const int32_t *pres_dofs, int64_t npres) {
   sfem_status st;
   if ((st = require_ready(c)) != SFEM_OK) return st;
@@ -1434,7 +1420,6 @@ static sfem_status sfem_setup_pressure_body(sfem_ctx *c, const int32_t *pres_dof
     if (rc != 0) return fail(c, (sfem_status)rc, "pressure map: " + err);
   }
   if (hp.nentries >= (int64_t)kDofMask) return fail(c, SFEM_E_ARG, "mesh too large");
-  const int64_t q3 = (int64_t)c->q * c->q * c->q;
   if ((st = dalloc(c, &c->d_pmap, c->nelem * n3p)) != SFEM_OK) return st;
   int32_t *d_alist = nullptr, *d_aoff = nullptr, *d_slot = nullptr;
   if ((st = dalloc(c, &d_alist, hp.na)) != SFEM_OK) return st;
@@ -1452,7 +1437,6 @@ static sfem_status sfem_setup_pressure_body(sfem_ctx *c, const int32_t *pres_dof
   if (!hp.slots.empty())
     HIPCHK(c, hipMemcpyAsync(d_slot, hp.slots.data(), hp.slots.size() * sizeof(int32_t),
                              hipMemcpyHostToDevice, c->stream));
-  if ((st = ensure_cq(c)) != SFEM_OK) return st;
   HIPCHK(c, hipStreamSynchronize(c->stream));
   c->pplan.alist = d_alist;
   c->pplan.aoff = d_aoff;
@@ -1503,7 +1487,7 @@ sfem_status sfem_stokes_apply(sfem_ctx *c, const double *u, const double *pres, 
   a.vcompact = c->compact;
   a.pmap = c->d_pmap;
   a.pcompact = c->pcompact;
-  a.cq = c->d_cq;
+  a.geo = c->d_geo;
   a.u = u;
   a.pres = pres;
   a.nv = nv;
@@ -1528,7 +1512,6 @@ sfem_status sfem_convection(sfem_ctx *c, const double *u, double *y) {
   if (!u || !y) return fail(c, SFEM_E_ARG, "u and y must not be NULL");
   if ((const void *)u == (const void *)y) return fail(c, SFEM_E_ARG, "y must not alias u");
   DeviceGuard g(c->device);
-  if ((st = ensure_cq(c)) != SFEM_OK) return st;
   if ((st = ensure_evec(c, (size_t)c->nentries * 3 * sizeof(double))) != SFEM_OK) return st;
   ConvArgs a{};
   a.p = c->p;
@@ -1536,7 +1519,7 @@ sfem_status sfem_convection(sfem_ctx *c, const double *u, double *y) {
   a.vmap = c->d_map;
   a.vpos = c->d_pos;
   a.vcompact = c->compact;
-  a.cq = c->d_cq;
+  a.geo = c->d_geo;
   a.u = u;
   a.nv = nv;
   a.Yv = (double *)c->evec.p;
@@ -1558,7 +1541,6 @@ sfem_status sfem_weak_op(sfem_ctx *c, int kind, const double *x, double *y) {
   if (!x || !y) return fail(c, SFEM_E_ARG, "x and y must not be NULL");
   if ((const void *)x == (const void *)y) return fail(c, SFEM_E_ARG, "y must not alias x");
   DeviceGuard g(c->device);
-  if ((st = ensure_cq(c)) != SFEM_OK) return st;
   if ((st = ensure_evec(c, (size_t)c->nentries * 3 * sizeof(double))) != SFEM_OK) return st;
   ConvArgs a{};
   a.kind = kind == SFEM_WEAK_GRADIENT ? kWeakGradient
@@ -1568,7 +1550,7 @@ sfem_status sfem_weak_op(sfem_ctx *c, int kind, const double *x, double *y) {
   a.vmap = c->d_map;
   a.vpos = c->d_pos;
   a.vcompact = c->compact;
-  a.cq = c->d_cq;
+  a.geo = c->d_geo;
   a.u = x;
   a.nv = nv;
   a.Yv = (double *)c->evec.p;

@@ -1,6 +1,5 @@
 // Internal interfaces of the flow-solver operators (not part of the C ABI): the
-// Taylor-Hood coupling blocks of the Stokes operator and the convection term, with the
-// coupling factors they read.
+// Taylor-Hood coupling blocks of the Stokes operator and the convection term.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -23,7 +22,7 @@ struct StokesArgs {
   int vcompact;
   const int32_t *pmap;      // pressure flagged map [nelem][p^3]
   int pcompact;
-  const double *cq;         // coupling factors [nelem][9][q^3]
+  const double *geo;        // trilinear coefficients of the elements [nelem][kGeoStride] (geom.h)
   const double *u;          // [3][nv]
   const double *pres;       // [np]
   int64_t nv;
@@ -46,7 +45,7 @@ struct ConvArgs {
   const int32_t *vmap;
   const int32_t *vpos;
   int vcompact;
-  const double *cq;         // coupling factors [nelem][9][q^3]
+  const double *geo;        // trilinear coefficients of the elements [nelem][kGeoStride] (geom.h)
   const double *u;          // [3][nv]
   int64_t nv;
   double *Yv;               // [3][vestride]
@@ -64,8 +63,5 @@ struct LinComb {
 };
 hipError_t launch_lincomb(const LinComb &lc, const double *scale, const uint8_t *mask, double *y,
                           int64_t n, int nb, hipStream_t s);
-// coupling factors C = w |J| J^{-T} at the q^3 Gauss points, [nelem][9][q^3], slot 3c + d
-hipError_t launch_coupling_setup(int q, const double *gx, const double *gw, const double *xyz,
-                                 int64_t nei, double *cq, hipStream_t s);
 
 }  // namespace sfem

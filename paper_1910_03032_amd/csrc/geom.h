@@ -133,6 +133,39 @@ struct LineMetric {
   }
 };
 
+// Component d (physical direction) of adj(J)'s three rows along a thread's xi_3 line, for
+// kernels that take one physical direction after the other: 7 coefficients at a time.
+// Sixty-four threads of a wave read the element's coefficients g from LDS.
+struct LineAdjComp {
+  double a1, b1, a2, b2, a3, b3, c3;
+
+  __device__ __forceinline__ void init(const double *g, int d, double x1, double x2) {
+    double P1[2], Q1[2], P2[2], Q2[2], J3[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {  // the two other components, in cyclic order
+      const int r = d + 1 + k < 3 ? d + 1 + k : d - 2 + k;
+      P1[k] = g[r] + g[9 + r] * x2;
+      Q1[k] = g[12 + r] + g[18 + r] * x2;
+      P2[k] = g[3 + r] + g[9 + r] * x1;
+      Q2[k] = g[15 + r] + g[18 + r] * x1;
+      J3[k] = (g[6 + r] + g[12 + r] * x1) + Q2[k] * x2;
+    }
+    auto cross = [](const double (&u)[2], const double (&v)[2]) { return u[0] * v[1] - u[1] * v[0]; };
+    a1 = cross(P2, J3);
+    b1 = cross(Q2, J3);
+    a2 = cross(J3, P1);
+    b2 = cross(J3, Q1);
+    a3 = cross(P1, P2);
+    b3 = cross(P1, Q2) + cross(Q1, P2);
+    c3 = cross(Q1, Q2);
+  }
+  __device__ __forceinline__ void at(double x, double &r1, double &r2, double &r3) const {
+    r1 = a1 + x * b1;
+    r2 = a2 + x * b2;
+    r3 = (a3 + (x * x) * c3) + x * b3;
+  }
+};
+
 // 1 / d for the positive |J| of a valid element: the hardware estimate and Newton steps.
 __device__ __forceinline__ double recip(double d) {
   double r = __builtin_amdgcn_rcp(d);

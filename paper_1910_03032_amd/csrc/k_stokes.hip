@@ -1,7 +1,8 @@
 // Coupling blocks of the Taylor-Hood Stokes operator (Section 3, eq. gradient and
 // eq. divergence): velocity in (Q_p)^3, pressure in Q_{p-1}, both nodal on the GLL
-// points, on the same elements and the same q = p + 2 Gauss points.  With the stored
-// coupling factor C = w |J| J^{-T} at each point (C_cd = w adj(J)_dc), the physical
+// points, on the same elements and the same q = p + 2 Gauss points.  With the
+// coupling factor C = w |J| J^{-T} at each point (C_cd = w adj(J)_dc, formed from the
+// element's trilinear map, geom.h), the physical
 // gradient of a scalar f integrated against w|J| is C grad_ref f, so
 //
 //   (G p)_{l, c} = sum_Q phi_l(Q) (C_Q grad_ref p(Q))_c
@@ -17,6 +18,7 @@
 
 #include "apply_impl.h"
 #include "flow.h"
+#include "geom.h"
 
 namespace sfem {
 namespace {
@@ -125,33 +127,30 @@ __device__ __forceinline__ void fwd_grad_xy(double *buf, int t) {
   }
 }
 
-// Transposed mass-type contractions of NF fields given at the q^3 points (each thread
-// holds its xi_3 line v[f][c]) down to nodal fields of order PO (NO = PO + 1 nodes per
-// direction), field f at buf + f * NO^3 ([k][j][i]); even-odd form.  Ends with a barrier.
+// Transposed mass-type contractions along xi_2 and xi_1 of NF fields given by their
+// contracted xi_3 lines (r[f][k] of line (a, b)), down to nodal fields of order PO (NO = PO + 1
+// nodes per direction), field f at buf + f * NO^3 ([k][j][i]); even-odd form.  Starts and ends
+// with a barrier.
+template <int PO, int Q>
+__device__ __forceinline__ void mass_line(const double (&in)[Q], double (&out)[PO + 1]) {
+  using BT = TabEO<PO, Q, 0>;
+  eo::Acc<PO + 1, double> A;
+  A.zero();
+#pragma unroll
+  for (int c = 0; c < Q / 2; ++c) A.template add_pair<BT>(c, in[c], in[Q - 1 - c]);
+  if constexpr (Q % 2 == 1) A.template add_mid<BT>(in[Q / 2]);
+  A.finish(out);
+}
 template <int PO, int Q, int NF>
-__device__ __forceinline__ void bwd_mass(double *buf, int t, const double (&v)[NF][Q]) {
+__device__ __forceinline__ void bwd_mass_xy(double *buf, int t, const double (&p)[NF][PO + 1]) {
   constexpr int NO = PO + 1;
   constexpr int NQ2 = NO * Q * Q, N2Q = NO * NO * Q, N3 = NO * NO * NO;
-  using BT = TabEO<PO, Q, 0>;
-  auto line = [](const double (&in)[Q], double (&out)[NO]) {
-    eo::Acc<NO, double> A;
-    A.zero();
+  __syncthreads();
 #pragma unroll
-    for (int c = 0; c < Q / 2; ++c) A.template add_pair<BT>(c, in[c], in[Q - 1 - c]);
-    if constexpr (Q % 2 == 1) A.template add_mid<BT>(in[Q / 2]);
-    A.finish(out);
-  };
-  {  // xi_3: [c] -> [k][b][a]
-    double r[NF][NO];
+  for (int f = 0; f < NF; ++f)
 #pragma unroll
-    for (int f = 0; f < NF; ++f) line(v[f], r[f]);
-    __syncthreads();
-#pragma unroll
-    for (int f = 0; f < NF; ++f)
-#pragma unroll
-      for (int k = 0; k < NO; ++k) buf[f * NQ2 + k * Q * Q + t] = r[f][k];
-    __syncthreads();
-  }
+    for (int k = 0; k < NO; ++k) buf[f * NQ2 + k * Q * Q + t] = p[f][k];
+  __syncthreads();
   {  // xi_2: [k][b][a] -> [k][j][a]
     const bool w = t < Q * NO;
     const int a = t % Q, k = t / Q;
@@ -162,7 +161,7 @@ __device__ __forceinline__ void bwd_mass(double *buf, int t, const double (&v)[N
         double in[Q];
 #pragma unroll
         for (int b = 0; b < Q; ++b) in[b] = buf[f * NQ2 + (k * Q + b) * Q + a];
-        line(in, r[f]);
+        mass_line<PO, Q>(in, r[f]);
       }
     }
     __syncthreads();
@@ -184,7 +183,7 @@ __device__ __forceinline__ void bwd_mass(double *buf, int t, const double (&v)[N
         double in[Q];
 #pragma unroll
         for (int a = 0; a < Q; ++a) in[a] = buf[f * N2Q + (k * NO + j) * Q + a];
-        line(in, r[f]);
+        mass_line<PO, Q>(in, r[f]);
       }
     }
     __syncthreads();
@@ -196,6 +195,15 @@ __device__ __forceinline__ void bwd_mass(double *buf, int t, const double (&v)[N
     }
     __syncthreads();
   }
+}
+
+// The same from the fields at the q^3 points (each thread holds its xi_3 line v[f][c]).
+template <int PO, int Q, int NF>
+__device__ __forceinline__ void bwd_mass(double *buf, int t, const double (&v)[NF][Q]) {
+  double r[NF][PO + 1];
+#pragma unroll
+  for (int f = 0; f < NF; ++f) mass_line<PO, Q>(v[f], r[f]);
+  bwd_mass_xy<PO, Q, NF>(buf, t, r);
 }
 
 // Gather of a pressure-space element (order P - 1, no essential DoFs) into buf and its
@@ -247,14 +255,6 @@ __device__ __forceinline__ void emit_pres(const double *buf, int t, bool active,
   }
 }
 
-// Offset of slot z at slice c (points a + q b follow) within an element's coupling
-// factors, stored by slice pair (c, q-1-c), then slice, then slot.
-template <int Q>
-__device__ __forceinline__ int cq_at(int c, int z) {
-  const int pc = c <= Q - 1 - c ? c : Q - 1 - c;
-  return ((2 * pc + (c > Q - 1 - c ? 1 : 0)) * 9 + z) * Q * Q;
-}
-
 template <int P>
 struct SDims {
   using D = Dims<P>;
@@ -262,11 +262,8 @@ struct SDims {
   static constexpr int TPE = D::TPE, E = D::E, THREADS = D::THREADS;
   static_assert(D::BUF >= 3 * N * Q * Q && D::BUF >= 3 * Q * Q * NP && D::BUF >= 2 * Q * N * N,
                 "element buffer");
-  // minimum waves per SIMD the kernels below are compiled for: 2 (at most 256 registers)
-  // up to p = 7, where the second wave outweighs a small spill (convection at 28^3 p = 5:
-  // 338 -> 302 us, 24^3 p = 7: 577 -> 472 us); at p = 8 the spill is large and one wave
-  // with more registers is faster
-  static constexpr int OCC = P <= 7 ? 2 : 1;
+  // minimum waves per SIMD the kernels below are compiled for
+  static constexpr int OCC = 2;
 };
 
 // Output of a velocity element vector that adds into an apply's output: sole DoFs
@@ -298,24 +295,64 @@ __device__ __forceinline__ void emit_add_vel(const double *buf, int t, bool acti
   }
 }
 
-// Both coupling blocks in one pass over the elements, so that the coupling factors are
-// read once: G p added into the three velocity components (the sole DoFs of yv directly,
-// the shared nodes through the E-vector, members at stride vestride, as emit_add_vel
-// describes) and -D P u into the pressure space (element-ordered E-vector Yp, sole DoFs
-// of yp).  cq: [nelem][9 q^3]
-// (cq_at order), slot 3c + d holds C_cd.
+// The elements' trilinear coefficients into LDS (sg: [E][kGeoStride]); no barrier.
+template <int P>
+__device__ __forceinline__ void load_geo(double *sg, const double *geo, int64_t e0, uint32_t rel, int t) {
+  constexpr int TPE = Dims<P>::TPE;
+#pragma unroll
+  for (int k = 0; k * TPE < kGeoStride; ++k) {
+    const int i = t + k * TPE < kGeoStride ? t + k * TPE : kGeoStride - 1;
+    sg[i] = ld<double>(geo + e0 * kGeoStride, (rel * kGeoStride + i) * 8u);
+  }
+}
+
+// Nodal values held in registers (Nodes::load_values) into buf[k][j][i], essential DoFs as 0
+// unless ESS; no barrier.
+template <int P, bool ESS>
+__device__ __forceinline__ void put_nodal(double *buf, int t, bool active, const Nodes<P> &nd,
+                                          const double (&v)[Nodes<P>::NL]) {
+#pragma unroll
+  for (int k = 0; k < Nodes<P>::NL; ++k)
+    buf[Nodes<P>::node(t, k)] = (active && (ESS || nd.c[k] >= 0)) ? v[k] : 0.0;
+}
+
+// Even-odd xi_3 lines of the three fields fwd_grad_xy leaves for order PO.
+template <int PO, int Q>
+__device__ __forceinline__ void read_z3(const double *buf, int t, eo::Split<PO + 1, double> &bb,
+                                        eo::Split<PO + 1, double> &gb, eo::Split<PO + 1, double> &bg) {
+  constexpr int NI = PO + 1, NQ2 = NI * Q * Q;
+  double zb[NI], zg[NI], zx[NI];
+#pragma unroll
+  for (int k = 0; k < NI; ++k) {
+    zb[k] = buf[k * Q * Q + t];
+    zg[k] = buf[NQ2 + k * Q * Q + t];
+    zx[k] = buf[2 * NQ2 + k * Q * Q + t];
+  }
+  bb = eo::split(zb);
+  gb = eo::split(zg);
+  bg = eo::split(zx);
+}
+
+// Both coupling blocks in one pass over the elements: G p added into the three velocity
+// components (the sole DoFs of yv directly, the shared nodes through the E-vector, members
+// at stride vestride, as emit_add_vel describes) and -D P u into the pressure space
+// (element-ordered E-vector Yp, sole DoFs of yp).  Component r needs the components
+// C_rd = w adj(J)_dr of the three adjugate rows, formed along the thread's xi_3 line (the
+// Stokes apply at 28 x 29 x 27 p = 3: 200 -> 152 us with the Helmholtz part's factors formed too).
 template <int P, bool POS>
 __global__ void __launch_bounds__(Dims<P>::THREADS, SDims<P>::OCC)
 coupling_kernel(const int32_t *__restrict__ vmap, const int32_t *__restrict__ vpos, int vcompact,
-                const int32_t *__restrict__ pmap, int pcompact, const double *__restrict__ cq,
+                const int32_t *__restrict__ pmap, int pcompact, const double *__restrict__ geo,
                 int64_t nelem, const double *__restrict__ u, const double *__restrict__ pres,
                 int64_t nv, double *__restrict__ Yv, int64_t vestride, double *__restrict__ yv,
                 double *__restrict__ Yp, double *__restrict__ yp) {
   using S = SDims<P>;
   using D = Dims<P>;
-  constexpr int N = S::N, NP = S::NP, Q = S::Q, Q2 = S::Q2, Q3 = S::Q3, TPE = S::TPE, E = S::E;
+  constexpr int N = S::N, NP = S::NP, Q = S::Q, TPE = S::TPE, E = S::E;
   constexpr int N3 = N * N * N, NP3 = NP * NP * NP;
+  constexpr rules::GaussRule<Q> gr = rules::gauss<Q>();
   __shared__ __align__(16) double smem[E * D::BUF];
+  __shared__ __align__(16) double sgeo[E * kGeoStride];
   __shared__ int32_t smap_all[E * N3];
   const int le = threadIdx.x / TPE;
   const int t0 = threadIdx.x - le * TPE;
@@ -324,71 +361,53 @@ coupling_kernel(const int32_t *__restrict__ vmap, const int32_t *__restrict__ vp
   const int64_t e = e0 + le;
   const bool active = e < nelem;
   const int64_t es = active ? e : e0;
+  const uint32_t rel = (uint32_t)(es - e0);
   double *buf = smem + le * D::BUF;
+  const double *sg = sgeo + le * kGeoStride;
   int32_t *smap = smap_all + le * N3;
+  const ElemTab z = elem_tab<P>(vmap, vpos, vcompact, e0);
+  Nodes<P> nd;
+  nd.load_map(z, t, rel);
+  nd.load_rank(z, t);
+  load_geo<P>(sgeo + le * kGeoStride, geo, e0, rel, t);
   // pressure element: the xi_3 lines of its reference gradient
   gather_pres<P>(buf, t, active, pmap + (int64_t)es * NP3, pres, smap);
+  nd.template load_dest<POS>(z, rel);
+  double v[Nodes<P>::NL];  // the next component's nodal values
+  nd.load_values(u, v);
   fwd_grad_xy<P - 1, Q>(buf, t);
   eo::Split<NP, double> pbb, pgb, pbg;  // xi_3 lines of the pressure, even-odd split
-  {
-    double zb[NP], zg[NP], zx[NP];
-#pragma unroll
-    for (int k = 0; k < NP; ++k) {
-      zb[k] = buf[k * Q2 + t];
-      zg[k] = buf[NP * Q2 + k * Q2 + t];
-      zx[k] = buf[2 * NP * Q2 + k * Q2 + t];
-    }
-    pbb = eo::split(zb);
-    pgb = eo::split(zg);
-    pbg = eo::split(zx);
-  }
-  // the velocity element's destinations for the output
-  const ElemTab z = elem_tab<P>(vmap, vpos, vcompact, e0);
-  {
-    Nodes<P> nd;
-    nd.load_map(z, t, (uint32_t)(es - e0));
-    nd.load_rank(z, t);
-    nd.template load_dest<POS>(z, (uint32_t)(es - e0));
-    nd.keep(smap, t);
-    __syncthreads();
-  }
-  const double *ce = cq + (int64_t)es * (9 * Q3) + t;
+  read_z3<P - 1, Q>(buf, t, pbb, pgb, pbg);
+  nd.keep(smap, t);  // the velocity nodes' destinations
   double s[1][Q];
 #pragma unroll
   for (int c = 0; c < Q; ++c) s[0][c] = 0.0;
+  const double x1 = kGaussRule<Q>.x[t % Q], x2 = kGaussRule<Q>.x[t / Q];
+  const double wab = kGaussRule<Q>.w[t % Q] * kGaussRule<Q>.w[t / Q];
   // (one component at a time, not unrolled: fewer live registers)
 #pragma unroll 1
   for (int r = 0; r < 3; ++r) {
     // indices derived from the thread are recomputed per component rather than kept live
     int t = t0;
     asm volatile("" : "+v"(t));
+    __syncthreads();  // buf was read by the last component's output (or the pressure lines)
     // velocity component r (essential DoFs read as 0)
-    {
-      Nodes<P> nd;
-      nd.load_map(z, t, (uint32_t)(es - e0));
-      gather_e<P, double>(buf, t, active, nd, u + r * nv);
-    }
+    put_nodal<P, false>(buf, t, active, nd, v);
+    __syncthreads();
+    if (r < 2) nd.load_values(u + (r + 1) * nv, v);
     fwd_grad_xy<P, Q>(buf, t);
     eo::Split<N, double> ubb, ugb, ubg;
-    {
-      double zb[N], zg[N], zx[N];
-#pragma unroll
-      for (int k = 0; k < N; ++k) {
-        zb[k] = buf[k * Q2 + t];
-        zg[k] = buf[N * Q2 + k * Q2 + t];
-        zx[k] = buf[2 * N * Q2 + k * Q2 + t];
-      }
-      ubb = eo::split(zb);
-      ugb = eo::split(zg);
-      ubg = eo::split(zx);
-    }
-    double v[1][Q];
+    read_z3<P, Q>(buf, t, ubb, ugb, ubg);
+    LineAdjComp L;
+    L.init(sg, r, x1, x2);
+    double n[1][Q];
     // row r of C times grad_ref p (G) and times grad_ref u_r (D) at slice c
     auto point = [&](int c, double ux, double uy, double uz, double px, double py, double pz) {
-      const double *cr = ce + cq_at<Q>(c, 3 * r);
-      const double c0 = cr[0], c1 = cr[Q2], c2 = cr[2 * Q2];
-      v[0][c] = c0 * px + c1 * py + c2 * pz;
-      s[0][c] -= c0 * ux + c1 * uy + c2 * uz;
+      double c0, c1, c2;
+      L.at(gr.x[c], c0, c1, c2);
+      const double w = wab * gr.w[c];
+      n[0][c] = w * (c0 * px + c1 * py + c2 * pz);
+      s[0][c] -= w * (c0 * ux + c1 * uy + c2 * uz);
     };
     using VB = TabEO<P, Q, 0>;
     using VG = TabEO<P, Q, 1>;
@@ -410,10 +429,10 @@ coupling_kernel(const int32_t *__restrict__ vmap, const int32_t *__restrict__ vp
       point(Q / 2, row_mid<VB>(ubg), row_mid<VB>(ugb), row_mid<VG>(ubb), row_mid<PB>(pbg),
             row_mid<PB>(pgb), row_mid<PG>(pbb));
     // G p, component r: added into yv / the velocity E-vector
-    bwd_mass<P, Q, 1>(buf, t, v);
+    bwd_mass<P, Q, 1>(buf, t, n);
     emit_add_vel<P, POS>(buf, t, active, smap, Yv + r * vestride, yv + r * nv);
-    __syncthreads();  // buf is reused by the next gather
   }
+  __syncthreads();
   // -D P u: one pressure field
   bwd_mass<P - 1, Q, 1>(buf, t, s);
   {
@@ -429,194 +448,302 @@ coupling_kernel(const int32_t *__restrict__ vmap, const int32_t *__restrict__ vp
   emit_pres<P>(buf, t, active, smap, es, pcompact != 0, Yp, yp);
 }
 
-// Interpolation of a nodal field of order P to the points, stages xi_1 and xi_2 (B only):
-// afterwards buf holds [k][b][a] and each thread reads its xi_3 line.
+// Interpolation of the three nodal fields in buf (field f at f n^3) to the points, stages
+// xi_1 and xi_2 (B only): afterwards buf holds the fields [k][b][a] at f n q^2.
 template <int P, int Q>
-__device__ __forceinline__ void fwd_val_xy(double *buf, int t) {
-  constexpr int NI = P + 1, N2 = NI * NI;
+__device__ __forceinline__ void fwd_val3_xy(double *buf, int t) {
+  constexpr int NI = P + 1, N2 = NI * NI, N3 = N2 * NI;
   using BT = TabEO<P, Q, 0>;
   {
     const bool w = t < N2;
     const int j = t % NI, k = t / NI;
-    double ob[Q];
+    double ob[3][Q];
     if (w) {
-      double in[NI];
 #pragma unroll
-      for (int i = 0; i < NI; ++i) in[i] = buf[(k * NI + j) * NI + i];
-      eo::apply<BT>(eo::split(in), ob);
+      for (int f = 0; f < 3; ++f) {
+        double in[NI];
+#pragma unroll
+        for (int i = 0; i < NI; ++i) in[i] = buf[f * N3 + (k * NI + j) * NI + i];
+        eo::apply<BT>(eo::split(in), ob[f]);
+      }
     }
     __syncthreads();
     if (w) {
 #pragma unroll
-      for (int a = 0; a < Q; ++a) buf[(k * NI + j) * Q + a] = ob[a];
+      for (int f = 0; f < 3; ++f)
+#pragma unroll
+        for (int a = 0; a < Q; ++a) buf[f * N2 * Q + (k * NI + j) * Q + a] = ob[f][a];
     }
     __syncthreads();
   }
   {
     const bool w = t < Q * NI;
     const int a = t % Q, k = t / Q;
-    double ob[Q];
-    if (w) {
-      double in[NI];
-#pragma unroll
-      for (int j = 0; j < NI; ++j) in[j] = buf[(k * NI + j) * Q + a];
-      eo::apply<BT>(eo::split(in), ob);
-    }
-    __syncthreads();
+    double ob[3][Q];
     if (w) {
 #pragma unroll
-      for (int b = 0; b < Q; ++b) buf[(k * Q + b) * Q + a] = ob[b];
-    }
-    __syncthreads();
-  }
-}
-
-// Pointwise products of the element kernels below that test against the basis values
-// (the three outputs are tested against phi): with the coupling factor C = w |J| J^{-T}
-// and Gamma_dr = sum_k C_dk d_ref_k u_r = w |J| d u_r / d x_d,
-//   kConvection:   n_c = sum_d u_d Gamma_dc               (eq. nonlinear)
-//   kCurl:         n_c = eps_cde Gamma_de                  (w |J| (curl u)_c)
-//   kGradient:     n_c = Gamma_c0 (one input field s)      (w |J| (grad s)_c)
-enum PointMode { kConvection = 0, kCurl = 1, kGradient = 2 };
-
-// Convection term N(u) (eq. nonlinear) on the velocity space, and the equal-order weak
-// curl and gradient of the projection step (Section 4.2), which share its stages: one
-// gather and forward pass per input component (value and reference gradient from the
-// same xi_1/xi_2 stages), the components' xi_3 lines held per thread, C read once per
-// point, then the three outputs (member c of the velocity E-vector and of y; essential
-// rows get nothing).  (For the convection term, two passes, values first and then per
-// component its gradient, hold fewer registers but measured 441 vs 264 us at 32^3 p = 4
-// and 620 vs 576 us at 24^3 p = 7.)
-template <int P, bool POS, int MODE>
-__device__ __forceinline__ void phi_test_body(const int32_t *__restrict__ vmap,
-                                              const int32_t *__restrict__ vpos, int vcompact,
-                                              const double *__restrict__ cq, int64_t nelem,
-                                              const double *__restrict__ u, int64_t nv,
-                                              double *__restrict__ Yv, int64_t vestride,
-                                              double *__restrict__ yv) {
-  using S = SDims<P>;
-  using D = Dims<P>;
-  constexpr int N = S::N, Q = S::Q, Q2 = S::Q2, Q3 = S::Q3, TPE = S::TPE, E = S::E;
-  constexpr int N3 = N * N * N;
-  constexpr int NIN = MODE == kGradient ? 1 : 3;
-  using VB = TabEO<P, Q, 0>;
-  using VG = TabEO<P, Q, 1>;
-  __shared__ __align__(16) double smem[E * D::BUF];
-  __shared__ int32_t smap_all[E * N3];
-  const int le = threadIdx.x / TPE;
-  const int t0 = threadIdx.x - le * TPE;
-  const int64_t e0 = (int64_t)xcd_block() * E;
-  const int64_t e = e0 + le;
-  const bool active = e < nelem;
-  const int64_t es = active ? e : e0;
-  double *buf = smem + le * D::BUF;
-  int32_t *smap = smap_all + le * N3;
-  // the nodes' map entries and destinations (the terms take u as it is, essential DoFs
-  // included)
-  Nodes<P> nd;
-  {
-    const ElemTab z = elem_tab<P>(vmap, vpos, vcompact, e0);
-    nd.load_map(z, t0, (uint32_t)(es - e0));
-    nd.load_rank(z, t0);
-    nd.template load_dest<POS>(z, (uint32_t)(es - e0));
-    nd.keep(smap, t0);
-  }
-  // the input components' xi_3 lines (value and reference-gradient fields, even-odd
-  // split), one gather and one forward pass each
-  eo::Split<N, double> sbb[NIN], sgb[NIN], sbg[NIN];
+      for (int f = 0; f < 3; ++f) {
+        double in[NI];
 #pragma unroll
-  for (int r = 0; r < NIN; ++r) {
-    gather_e<P, double, true>(buf, t0, active, nd, u + r * nv);
-    fwd_grad_xy<P, Q>(buf, t0);
-    double zb[N], zg[N], zx[N];
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
-      zb[k] = buf[k * Q2 + t0];
-      zg[k] = buf[N * Q2 + k * Q2 + t0];
-      zx[k] = buf[2 * N * Q2 + k * Q2 + t0];
-    }
-    sbb[r] = eo::split(zb);
-    sgb[r] = eo::split(zg);
-    sbg[r] = eo::split(zx);
-    __syncthreads();  // buf is reused by the next gather
-  }
-  const double *ce = cq + (int64_t)es * (9 * Q3) + t0;
-  // the three outputs at the points of the line
-  double n[3][Q];
-  auto point = [&](int c, const double (&uv)[NIN], const double (&g)[NIN][3]) {
-    const double *cp = ce + cq_at<Q>(c, 0);
-    double cm[9];
-#pragma unroll
-    for (int z = 0; z < 9; ++z) cm[z] = cp[z * Q2];
-    // Gamma_dr = (C grad_ref u_r)_d
-    auto gam = [&](int d, int r) {
-      return cm[3 * d] * g[r][0] + cm[3 * d + 1] * g[r][1] + cm[3 * d + 2] * g[r][2];
-    };
-    if constexpr (MODE == kConvection) {
-#pragma unroll
-      for (int r = 0; r < 3; ++r) {
-        double acc = 0.0;
-#pragma unroll
-        for (int d = 0; d < 3; ++d) acc += uv[d] * gam(d, r);
-        n[r][c] = acc;
+        for (int j = 0; j < NI; ++j) in[j] = buf[f * N2 * Q + (k * NI + j) * Q + a];
+        eo::apply<BT>(eo::split(in), ob[f]);
       }
-    } else if constexpr (MODE == kCurl) {
-      n[0][c] = gam(1, 2) - gam(2, 1);
-      n[1][c] = gam(2, 0) - gam(0, 2);
-      n[2][c] = gam(0, 1) - gam(1, 0);
-    } else {
-#pragma unroll
-      for (int d = 0; d < 3; ++d) n[d][c] = gam(d, 0);
     }
-  };
+    __syncthreads();
+    if (w) {
 #pragma unroll
-  for (int c = 0; c < Q / 2; ++c) {
-    double u0[NIN], u1[NIN], g0[NIN][3], g1[NIN][3];
+      for (int f = 0; f < 3; ++f)
 #pragma unroll
-    for (int r = 0; r < NIN; ++r) {
-      row_pair<VB>(sbb[r], c, u0[r], u1[r]);
-      row_pair<VB>(sbg[r], c, g0[r][0], g1[r][0]);
-      row_pair<VB>(sgb[r], c, g0[r][1], g1[r][1]);
-      row_pair<VG>(sbb[r], c, g0[r][2], g1[r][2]);
+        for (int b = 0; b < Q; ++b) buf[f * NI * Q * Q + (k * Q + b) * Q + a] = ob[f][b];
     }
-    point(c, u0, g0);
-    point(Q - 1 - c, u1, g1);
+    __syncthreads();
   }
-  if constexpr (Q % 2 == 1) {
-    double um[NIN], gm[NIN][3];
-#pragma unroll
-    for (int r = 0; r < NIN; ++r) {
-      um[r] = row_mid<VB>(sbb[r]);
-      gm[r][0] = row_mid<VB>(sbg[r]);
-      gm[r][1] = row_mid<VB>(sgb[r]);
-      gm[r][2] = row_mid<VG>(sbb[r]);
-    }
-    point(Q / 2, um, gm);
-  }
-  // the three outputs
-  bwd_mass<P, Q, 3>(buf, t0, n);
-#pragma unroll
-  for (int r = 0; r < 3; ++r)
-    emit_e<P, double, false>(buf + r * N3, t0, active, smap, u, Yv + r * vestride, yv + r * nv);
 }
 
+// h_k = sum_d C_dk u_d at the points of the thread's xi_3 line (C = w |J| J^{-T}: w |J| times
+// the reference-direction components of the vector field u), from its three nodal fields in
+// buf.  Ends without a barrier (buf has been read).
+template <int P, int Q>
+__device__ __forceinline__ void contravariant(double *buf, int t, const double *sg, double (&h)[3][Q]) {
+  constexpr int N = P + 1, Q2 = Q * Q;
+  constexpr rules::GaussRule<Q> gr = rules::gauss<Q>();
+  using VB = TabEO<P, Q, 0>;
+  fwd_val3_xy<P, Q>(buf, t);
+  const double x1 = kGaussRule<Q>.x[t % Q], x2 = kGaussRule<Q>.x[t / Q];
+  const double wab = kGaussRule<Q>.w[t % Q] * kGaussRule<Q>.w[t / Q];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    double z[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) z[k] = buf[d * N * Q2 + k * Q2 + t];
+    const auto sv = eo::split(z);
+    LineAdjComp L;
+    L.init(sg, d, x1, x2);
+    auto point = [&](int c, double v) {
+      double r1, r2, r3;
+      L.at(gr.x[c], r1, r2, r3);
+      const double wv = (wab * gr.w[c]) * v;
+      h[0][c] = (d == 0 ? 0.0 : h[0][c]) + r1 * wv;
+      h[1][c] = (d == 0 ? 0.0 : h[1][c]) + r2 * wv;
+      h[2][c] = (d == 0 ? 0.0 : h[2][c]) + r3 * wv;
+    };
+#pragma unroll
+    for (int c = 0; c < Q / 2; ++c) {
+      double v0, v1;
+      row_pair<VB>(sv, c, v0, v1);
+      point(c, v0);
+      point(Q - 1 - c, v1);
+    }
+    if constexpr (Q % 2 == 1) point(Q / 2, row_mid<VB>(sv));
+  }
+}
+
+// What the element kernels below begin with: the nodes' map entries and destinations and the
+// element's trilinear coefficients (loads in flight together; no barrier).
+template <int P, bool POS>
+__device__ __forceinline__ void begin_vel(Nodes<P> &nd, const int32_t *vmap, const int32_t *vpos,
+                                          int vcompact, const double *geo, int64_t e0, uint32_t rel, int t,
+                                          double *sg, int32_t *smap) {
+  const ElemTab z = elem_tab<P>(vmap, vpos, vcompact, e0);
+  nd.load_map(z, t, rel);
+  nd.load_rank(z, t);
+  load_geo<P>(sg, geo, e0, rel, t);
+  nd.template load_dest<POS>(z, rel);
+  nd.keep(smap, t);
+}
+
+// The three nodal components of u (essential DoFs included) into buf (component f at f n^3).
+// Ends with a barrier.
+template <int P>
+__device__ __forceinline__ void gather3(double *buf, int t, bool active, const Nodes<P> &nd,
+                                        const double *u, int64_t nv) {
+  double v[3][Nodes<P>::NL];
+#pragma unroll
+  for (int r = 0; r < 3; ++r) nd.load_values(u + r * nv, v[r]);
+#pragma unroll
+  for (int r = 0; r < 3; ++r) put_nodal<P, true>(buf + r * Dims<P>::N3, t, active, nd, v[r]);
+  __syncthreads();
+}
+
+// Convection term N(u) (eq. nonlinear) on the velocity space: n_c = sum_d u_d w |J| d u_c / d x_d
+// = sum_k h_k d_ref_k u_c with h = contravariant(u), so that the geometric factors are needed
+// once per point and not per component, and a component's gradient lines live only while it is
+// processed and the loop over components stays rolled.  What bounds it: VALU issue and LDS.
+// (With 9 stored factors read per point and the three components' lines held together it took
+// 230 registers at p = 4 and twice the HBM bytes: 28 x 27 x 29 p = 5 291 -> 195 us, 84 x 85 x 83
+// p = 1 361 -> 224 us.  Unrolled over the components: 202 registers, 21 x 22 x 20 p = 4 58 us
+// against 52.)
 template <int P, bool POS>
 __global__ void __launch_bounds__(Dims<P>::THREADS, SDims<P>::OCC)
 convection_kernel(const int32_t *__restrict__ vmap, const int32_t *__restrict__ vpos,
-                  int vcompact, const double *__restrict__ cq, int64_t nelem,
+                  int vcompact, const double *__restrict__ geo, int64_t nelem,
                   const double *__restrict__ u, int64_t nv, double *__restrict__ Yv,
                   int64_t vestride, double *__restrict__ yv) {
-  phi_test_body<P, POS, kConvection>(vmap, vpos, vcompact, cq, nelem, u, nv, Yv, vestride, yv);
+  using S = SDims<P>;
+  using D = Dims<P>;
+  constexpr int N = S::N, Q = S::Q, TPE = S::TPE, E = S::E, N3 = N * N * N;
+  using VB = TabEO<P, Q, 0>;
+  using VG = TabEO<P, Q, 1>;
+  __shared__ __align__(16) double smem[E * D::BUF];
+  __shared__ __align__(16) double sgeo[E * kGeoStride];
+  __shared__ int32_t smap_all[E * N3];
+  const int le = threadIdx.x / TPE;
+  const int t = threadIdx.x - le * TPE;
+  const int64_t e0 = (int64_t)xcd_block() * E;
+  const bool active = e0 + le < nelem;
+  double *buf = smem + le * D::BUF;
+  double *sg = sgeo + le * kGeoStride;
+  int32_t *smap = smap_all + le * N3;
+  Nodes<P> nd;
+  begin_vel<P, POS>(nd, vmap, vpos, vcompact, geo, e0, active ? le : 0, t, sg, smap);
+  gather3<P>(buf, t, active, nd, u, nv);
+  double v[Nodes<P>::NL];  // the next component's nodal values
+  nd.load_values(u, v);
+  double h[3][Q];
+  contravariant<P, Q>(buf, t, sg, h);
+  // (one component at a time, not unrolled: fewer live registers)
+#pragma unroll 1
+  for (int r = 0; r < 3; ++r) {
+    __syncthreads();  // buf has been read
+    put_nodal<P, true>(buf, t, active, nd, v);
+    __syncthreads();
+    if (r < 2) nd.load_values(u + (r + 1) * nv, v);
+    fwd_grad_xy<P, Q>(buf, t);
+    double p[1][N];
+    {
+      eo::Split<N, double> bb, gb, bg;
+      read_z3<P, Q>(buf, t, bb, gb, bg);
+      eo::Acc<N, double> A;
+      A.zero();
+#pragma unroll
+      for (int c = 0; c < Q / 2; ++c) {
+        double x0, x1, y0, y1, z0, z1;
+        row_pair<VB>(bg, c, x0, x1);
+        row_pair<VB>(gb, c, y0, y1);
+        row_pair<VG>(bb, c, z0, z1);
+        A.template add_pair<VB>(c, h[0][c] * x0 + h[1][c] * y0 + h[2][c] * z0,
+                                h[0][Q - 1 - c] * x1 + h[1][Q - 1 - c] * y1 + h[2][Q - 1 - c] * z1);
+      }
+      if constexpr (Q % 2 == 1) {
+        constexpr int M = Q / 2;
+        A.template add_mid<VB>(h[0][M] * row_mid<VB>(bg) + h[1][M] * row_mid<VB>(gb) +
+                               h[2][M] * row_mid<VG>(bb));
+      }
+      A.finish(p[0]);
+    }
+    bwd_mass_xy<P, Q, 1>(buf, t, p);
+    emit_e<P, double, false>(buf, t, active, smap, u, Yv + r * vestride, yv + r * nv);
+  }
 }
 
-// Weak curl (MODE = kCurl) or weak gradient (MODE = kGradient) of the projection step.
-template <int P, bool POS, int MODE>
+// Weak curl (CURL) or weak gradient of the projection step, tested against phi: with
+// Gamma_dr = sum_k C_dk d_ref_k u_r = w |J| d u_r / d x_d,
+//   curl      n_c = eps_cde Gamma_de                (w |J| (curl u)_c)
+//   gradient  n_c = Gamma_c0 (one input field s)    (w |J| (grad s)_c)
+// One input component after the other, its derivatives added into the three outputs at the
+// points (rolled loop; the outputs' roles rotate with it).  21 x 22 x 20 p = 4 against 9 stored
+// factors per point: curl 79 -> 49 us, gradient 61 -> 32 us.
+template <int P, bool POS, bool CURL>
 __global__ void __launch_bounds__(Dims<P>::THREADS, SDims<P>::OCC)
 weak_phi_kernel(const int32_t *__restrict__ vmap, const int32_t *__restrict__ vpos,
-                int vcompact, const double *__restrict__ cq, int64_t nelem,
+                int vcompact, const double *__restrict__ geo, int64_t nelem,
                 const double *__restrict__ u, int64_t nv, double *__restrict__ Yv,
                 int64_t vestride, double *__restrict__ yv) {
-  phi_test_body<P, POS, MODE>(vmap, vpos, vcompact, cq, nelem, u, nv, Yv, vestride, yv);
+  using S = SDims<P>;
+  using D = Dims<P>;
+  constexpr int N = S::N, Q = S::Q, TPE = S::TPE, E = S::E, N3 = N * N * N;
+  constexpr int NIN = CURL ? 3 : 1;
+  constexpr rules::GaussRule<Q> gr = rules::gauss<Q>();
+  using VB = TabEO<P, Q, 0>;
+  using VG = TabEO<P, Q, 1>;
+  __shared__ __align__(16) double smem[E * D::BUF];
+  __shared__ __align__(16) double sgeo[E * kGeoStride];
+  __shared__ int32_t smap_all[E * N3];
+  const int le = threadIdx.x / TPE;
+  const int t = threadIdx.x - le * TPE;
+  const int64_t e0 = (int64_t)xcd_block() * E;
+  const bool active = e0 + le < nelem;
+  double *buf = smem + le * D::BUF;
+  double *sg = sgeo + le * kGeoStride;
+  int32_t *smap = smap_all + le * N3;
+  Nodes<P> nd;
+  begin_vel<P, POS>(nd, vmap, vpos, vcompact, geo, e0, active ? le : 0, t, sg, smap);
+  double v[Nodes<P>::NL];  // the next component's nodal values
+  nd.load_values(u, v);
+  // n[k]: output r + 1 + k of the current input component r (curl), output k (gradient)
+  double n[3][Q];
+#pragma unroll
+  for (int d = 0; d < 3; ++d)
+#pragma unroll
+    for (int c = 0; c < Q; ++c) n[d][c] = 0.0;
+  const double x1 = kGaussRule<Q>.x[t % Q], x2 = kGaussRule<Q>.x[t / Q];
+  // (one component at a time, not unrolled: fewer live registers)
+#pragma unroll 1
+  for (int r = 0; r < NIN; ++r) {
+    if (r > 0) __syncthreads();  // buf has been read
+    put_nodal<P, true>(buf, t, active, nd, v);
+    __syncthreads();
+    if (r + 1 < NIN) nd.load_values(u + (r + 1) * nv, v);
+    fwd_grad_xy<P, Q>(buf, t);
+    eo::Split<N, double> bb, gb, bg;
+    read_z3<P, Q>(buf, t, bb, gb, bg);
+    // curl: d u_r / d x_d enters output r + 1 for d = r + 2 and, negated, output r + 2 for d = r + 1
+    constexpr int ND = CURL ? 2 : 3;
+    LineAdjComp L[ND];
+#pragma unroll
+    for (int k = 0; k < ND; ++k) {
+      const int d = CURL ? (r + 2 - k < 3 ? r + 2 - k : r - 1 - k) : k;
+      L[k].init(sg, d, x1, x2);
+    }
+    auto point = [&](int c, double dx, double dy, double dz) {
+#pragma unroll
+      for (int k = 0; k < ND; ++k) {
+        double r1, r2, r3;
+        L[k].at(gr.x[c], r1, r2, r3);
+        const double g = r1 * dx + r2 * dy + r3 * dz;
+        if (CURL) n[k][c] += k == 0 ? g : -g;
+        else n[k][c] = g;
+      }
+    };
+#pragma unroll
+    for (int c = 0; c < Q / 2; ++c) {
+      double x0, x1c, y0, y1, z0, z1;
+      row_pair<VB>(bg, c, x0, x1c);
+      row_pair<VB>(gb, c, y0, y1);
+      row_pair<VG>(bb, c, z0, z1);
+      point(c, x0, y0, z0);
+      point(Q - 1 - c, x1c, y1, z1);
+    }
+    if constexpr (Q % 2 == 1) point(Q / 2, row_mid<VB>(bg), row_mid<VB>(gb), row_mid<VG>(bb));
+    if constexpr (CURL) {
+#pragma unroll
+      for (int c = 0; c < Q; ++c) {
+        const double first = n[0][c];
+        n[0][c] = n[1][c];
+        n[1][c] = n[2][c];
+        n[2][c] = first;
+      }
+    }
+  }
+  // (curl: after r = 0, 1, 2 the outputs are in the order 1, 2, 0)
+  const double wab = kGaussRule<Q>.w[t % Q] * kGaussRule<Q>.w[t / Q];
+  double p[3][N];
+#pragma unroll
+  for (int f = 0; f < 3; ++f) {
+    eo::Acc<N, double> A;
+    A.zero();
+#pragma unroll
+    for (int c = 0; c < Q / 2; ++c)
+      A.template add_pair<VB>(c, (wab * gr.w[c]) * n[f][c], (wab * gr.w[c]) * n[f][Q - 1 - c]);
+    if constexpr (Q % 2 == 1) A.template add_mid<VB>((wab * gr.w[Q / 2]) * n[f][Q / 2]);
+    A.finish(p[f]);
+  }
+  bwd_mass_xy<P, Q, 3>(buf, t, p);
+#pragma unroll
+  for (int f = 0; f < 3; ++f) {
+    const int o = CURL ? (f + 1) % 3 : f;
+    emit_e<P, double, false>(buf + f * N3, t, active, smap, u, Yv + o * vestride, yv + o * nv);
+  }
 }
 
 // Transposed reference-gradient contraction: from the three channels v_k at the points
@@ -711,77 +838,37 @@ __device__ __forceinline__ void bwd_grad(double *buf, int t, const double (&v)[3
 
 // Weak divergence of a nodal vector field V (the pressure right-hand side of the
 // projection step, Section 4.2): r_l = sum_Q w |J| grad phi_l . V = sum_Q
-// grad_ref phi_l . (C^T V) with C = w |J| J^{-T}.  The three components are gathered
-// and interpolated (values only), C^T V is formed per point, and one backward
+// grad_ref phi_l . (C^T V) with C = w |J| J^{-T}: C^T V is formed per point and one backward
 // reference-gradient pass gives the single output (member 0 of the E-vector and of y).
+// 21 x 22 x 20 p = 4 against 9 stored factors per point: 54 -> 25 us.
 template <int P, bool POS>
 __global__ void __launch_bounds__(Dims<P>::THREADS, SDims<P>::OCC)
 weak_div_kernel(const int32_t *__restrict__ vmap, const int32_t *__restrict__ vpos,
-                int vcompact, const double *__restrict__ cq, int64_t nelem,
+                int vcompact, const double *__restrict__ geo, int64_t nelem,
                 const double *__restrict__ u, int64_t nv, double *__restrict__ Yv,
                 double *__restrict__ yv) {
   using S = SDims<P>;
   using D = Dims<P>;
-  constexpr int N = S::N, Q = S::Q, Q2 = S::Q2, Q3 = S::Q3, TPE = S::TPE, E = S::E;
-  constexpr int N3 = N * N * N;
-  using VB = TabEO<P, Q, 0>;
+  constexpr int N = S::N, Q = S::Q, TPE = S::TPE, E = S::E, N3 = N * N * N;
   __shared__ __align__(16) double smem[E * D::BUF];
+  __shared__ __align__(16) double sgeo[E * kGeoStride];
   __shared__ int32_t smap_all[E * N3];
   const int le = threadIdx.x / TPE;
-  const int t0 = threadIdx.x - le * TPE;
+  const int t = threadIdx.x - le * TPE;
   const int64_t e0 = (int64_t)xcd_block() * E;
-  const int64_t e = e0 + le;
-  const bool active = e < nelem;
-  const int64_t es = active ? e : e0;
+  const bool active = e0 + le < nelem;
   double *buf = smem + le * D::BUF;
+  double *sg = sgeo + le * kGeoStride;
   int32_t *smap = smap_all + le * N3;
-  // the nodes' map entries and destinations (the terms take u as it is, essential DoFs
-  // included)
-  Nodes<P> nd;
   {
-    const ElemTab z = elem_tab<P>(vmap, vpos, vcompact, e0);
-    nd.load_map(z, t0, (uint32_t)(es - e0));
-    nd.load_rank(z, t0);
-    nd.template load_dest<POS>(z, (uint32_t)(es - e0));
-    nd.keep(smap, t0);
+    Nodes<P> nd;
+    begin_vel<P, POS>(nd, vmap, vpos, vcompact, geo, e0, active ? le : 0, t, sg, smap);
+    gather3<P>(buf, t, active, nd, u, nv);
   }
-  eo::Split<N, double> sv[3];
-#pragma unroll
-  for (int r = 0; r < 3; ++r) {
-    gather_e<P, double, true>(buf, t0, active, nd, u + r * nv);
-    fwd_val_xy<P, Q>(buf, t0);
-    double z[N];
-#pragma unroll
-    for (int k = 0; k < N; ++k) z[k] = buf[k * Q2 + t0];
-    sv[r] = eo::split(z);
-    __syncthreads();
-  }
-  const double *ce = cq + (int64_t)es * (9 * Q3) + t0;
   double h[3][Q];  // (C^T V)_k at the points of the line
-  auto point = [&](int c, const double (&vv)[3]) {
-    const double *cp = ce + cq_at<Q>(c, 0);
-    double cm[9];
-#pragma unroll
-    for (int z = 0; z < 9; ++z) cm[z] = cp[z * Q2];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) h[k][c] = cm[k] * vv[0] + cm[3 + k] * vv[1] + cm[6 + k] * vv[2];
-  };
-#pragma unroll
-  for (int c = 0; c < Q / 2; ++c) {
-    double v0[3], v1[3];
-#pragma unroll
-    for (int r = 0; r < 3; ++r) row_pair<VB>(sv[r], c, v0[r], v1[r]);
-    point(c, v0);
-    point(Q - 1 - c, v1);
-  }
-  if constexpr (Q % 2 == 1) {
-    double vm[3];
-#pragma unroll
-    for (int r = 0; r < 3; ++r) vm[r] = row_mid<VB>(sv[r]);
-    point(Q / 2, vm);
-  }
-  bwd_grad<P, Q>(buf, t0, h);
-  emit_e<P, double, false>(buf, t0, active, smap, u, Yv, yv);
+  contravariant<P, Q>(buf, t, sg, h);
+  bwd_grad<P, Q>(buf, t, h);
+  emit_e<P, double, false>(buf, t, active, smap, u, Yv, yv);
 }
 
 template <int P>
@@ -796,7 +883,7 @@ hipError_t launch_stokes_pt(const StokesArgs &a, hipStream_t s) {
     dim3 grid((unsigned)((a.nelem + D::E - 1) / D::E));
     dim3 block(D::THREADS);
     hipLaunchKernelGGL((coupling_kernel<P, POS>), grid, block, 0, s, a.vmap, a.vpos, a.vcompact,
-                       a.pmap, a.pcompact, a.cq, a.nelem, a.u, a.pres, a.nv, a.Yv, a.vestride,
+                       a.pmap, a.pcompact, a.geo, a.nelem, a.u, a.pres, a.nv, a.Yv, a.vestride,
                        a.yv, a.Yp, a.yp);
     return hipGetLastError();
   }
@@ -813,19 +900,19 @@ hipError_t launch_convection_pt(const ConvArgs &a, hipStream_t s) {
   switch (a.kind) {
     case kWeakConvection:
       hipLaunchKernelGGL((convection_kernel<P, POS>), grid, block, 0, s, a.vmap, a.vpos,
-                         a.vcompact, a.cq, a.nelem, a.u, a.nv, a.Yv, a.vestride, a.yv);
+                         a.vcompact, a.geo, a.nelem, a.u, a.nv, a.Yv, a.vestride, a.yv);
       break;
     case kWeakCurl:
-      hipLaunchKernelGGL((weak_phi_kernel<P, POS, kCurl>), grid, block, 0, s, a.vmap, a.vpos,
-                         a.vcompact, a.cq, a.nelem, a.u, a.nv, a.Yv, a.vestride, a.yv);
+      hipLaunchKernelGGL((weak_phi_kernel<P, POS, true>), grid, block, 0, s, a.vmap, a.vpos,
+                         a.vcompact, a.geo, a.nelem, a.u, a.nv, a.Yv, a.vestride, a.yv);
       break;
     case kWeakGradient:
-      hipLaunchKernelGGL((weak_phi_kernel<P, POS, kGradient>), grid, block, 0, s, a.vmap, a.vpos,
-                         a.vcompact, a.cq, a.nelem, a.u, a.nv, a.Yv, a.vestride, a.yv);
+      hipLaunchKernelGGL((weak_phi_kernel<P, POS, false>), grid, block, 0, s, a.vmap, a.vpos,
+                         a.vcompact, a.geo, a.nelem, a.u, a.nv, a.Yv, a.vestride, a.yv);
       break;
     case kWeakDivergence:
       hipLaunchKernelGGL((weak_div_kernel<P, POS>), grid, block, 0, s, a.vmap, a.vpos, a.vcompact,
-                         a.cq, a.nelem, a.u, a.nv, a.Yv, a.yv);
+                         a.geo, a.nelem, a.u, a.nv, a.Yv, a.yv);
       break;
     default:
       return hipErrorInvalidValue;
