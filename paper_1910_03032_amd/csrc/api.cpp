@@ -77,7 +77,6 @@ struct sfem_ctx {
   int32_t *d_map = nullptr;        // [nelem][n^3] flagged (sole / essential bits)
   double *d_xyz = nullptr;         // [nelem][8][3]
   double *d_geo = nullptr;         // [nelem][kGeoStride] trilinear coefficients (geom.h)
-  double *d_qd = nullptr;          // [nelem][7][q^3]
   // assembly of the shared and essential DoFs
   int compact = 0;                 // E-vector over surface nodes only
   int64_t epe = 0;                 // E-vector entries per element (surface nodes or n^3)
@@ -240,7 +239,6 @@ void free_all(sfem_ctx *c) {
   c->d_map = nullptr;
   c->d_xyz = nullptr;
   c->d_geo = nullptr;
-  c->d_qd = nullptr;
   c->d_alist = nullptr;
   c->d_aoff = nullptr;
   c->d_pos = nullptr;
@@ -336,8 +334,8 @@ sfem_status ensure_diag(sfem_ctx *c, int op) {
     DiagArgs da;
     da.p = c->p;
     da.map = c->d_map;
-    da.qd = c->d_qd;
-    da.nu = (op != SFEM_MASS && c->has_nu) ? c->d_nu64 + (int64_t)f * c->nelem * q3_of(c) : nullptr;
+    da.geo = c->d_geo;
+    da.cw = (op != SFEM_MASS && c->has_nu) ? c->d_cw + (int64_t)f * c->nelem * q3_of(c) : nullptr;
     da.alpha = a;
     da.beta = b;
     da.nelem = c->nelem;
@@ -921,7 +919,6 @@ static sfem_status sfem_setup_body(sfem_ctx *c, int p, int q, int64_t nelem, con
   const int64_t q3 = (int64_t)q * q * q;
   if ((st = dalloc(c, &c->d_map, nelem * n3)) != SFEM_OK) return st;
   if ((st = dalloc(c, &c->d_xyz, nelem * 24)) != SFEM_OK) return st;
-  if ((st = dalloc(c, &c->d_qd, nelem * q3 * kQdSlots)) != SFEM_OK) return st;
   if ((st = dalloc(c, &c->d_geo, nelem * kGeoStride)) != SFEM_OK) return st;
   if ((st = dalloc(c, &c->d_alist, na)) != SFEM_OK) return st;
   if ((st = dalloc(c, &c->d_aoff, na + 1)) != SFEM_OK) return st;
@@ -951,8 +948,8 @@ static sfem_status sfem_setup_body(sfem_ctx *c, int p, int q, int64_t nelem, con
   int h_bad = 0;
   if (d_bad) {
     HIPCHK(c, VecOps<float>::fill((float *)d_bad, 0.0f, 1, c->stream));
-    HIPCHK(c, launch_qdata_setup(q, c->rules.gauss_x.data(), c->rules.gauss_w.data(), c->d_xyz,
-                                 nelem, c->d_qd, d_bad, c->stream));
+    HIPCHK(c, launch_check_det(q, c->rules.gauss_x.data(), c->rules.gauss_w.data(), c->d_xyz, nelem,
+                               d_bad, c->stream));
     HIPCHK(c, launch_geo_setup(c->d_xyz, nelem, c->d_geo, c->stream));
     HIPCHK(c, hipMemcpyAsync(&h_bad, d_bad, sizeof(int), hipMemcpyDeviceToHost, c->stream));
   }
@@ -1123,7 +1120,7 @@ sfem_status sfem_load(sfem_ctx *c, int nbatch, const double *f_q, double *b) {
   LoadArgs a;
   a.p = c->p;
   a.map = c->d_map;
-  a.qd = c->d_qd;
+  a.geo = c->d_geo;
   a.ndof = c->ndof;
   a.nei = c->nelem;
   a.nbatch = nbatch;
@@ -1161,7 +1158,7 @@ sfem_status sfem_grad_nu(sfem_ctx *c, int nbatch, const double *u, const double 
   GradArgs a;
   a.p = c->p;
   a.map = c->d_map;
-  a.qd = c->d_qd;
+  a.geo = c->d_geo;
   a.beta = c->beta;
   a.ndof = c->ndof;
   a.nei = c->nelem;

@@ -17,10 +17,6 @@ namespace sfem {
 // sums to y at the other listed DoFs and leaves the essential entries as they are).
 enum EssKind { kEssCopyX = 0, kEssOne = 1, kEssZero = 2, kEssAdd = 3 };
 
-// Quadrature-data slots per point, layout [elem][kQdSlots][q^3]:
-//   0: w|J|      1..6: w|J| (J^-1 J^-T) as (11, 22, 33, 12, 13, 23)
-constexpr int kQdSlots = 7;
-
 // 1D tables for order P (n = P + 1 GLL nodes, q = P + 2 Gauss points), row-major
 // [q][n]: B(a, i) = phi_i(xi_a), G(a, i) = phi_i'(xi_a).
 struct Rules1D {
@@ -104,8 +100,8 @@ hipError_t launch_assemble(const AsmPlan &pl, const T *evec, int64_t estride, co
 struct DiagArgs {
   int p;
   const int32_t *map;
-  const double *qd;         // base quadrature data (FP64)
-  const double *nu;         // [nelem][q^3] or null
+  const double *geo;        // trilinear coefficients (geom.h)
+  const double *cw;         // w nu / |J|, [nelem][q^3], or null (nu = 1)
   double alpha, beta;       // coefficients of the mass and diffusion terms
   int64_t nelem;
   double *diag;             // [ndof], written at the sole DoFs
@@ -115,8 +111,9 @@ struct DiagArgs {
 };
 hipError_t launch_diag(const DiagArgs &a, hipStream_t s);
 
-hipError_t launch_qdata_setup(int q, const double *gx, const double *gw, const double *xyz,
-                              int64_t nei, double *qd, int *bad, hipStream_t s);
+// *bad = 1 if |J| is not positive at some quadrature point.
+hipError_t launch_check_det(int q, const double *gx, const double *gw, const double *xyz, int64_t nei,
+                            int *bad, hipStream_t s);
 // Collocated (GLL-integrated) mass contributions of every element node: sole DoFs into
 // diag, shared nodes into their E-vector entry (then assembled with ess rows = 1).
 hipError_t launch_colloc_mass(int p, const double *gll_x, const double *gll_w, const double *xyz,
@@ -134,7 +131,7 @@ hipError_t launch_cast_f32(const double *src, float *dst, int64_t n, hipStream_t
 struct GradArgs {
   int p;
   const int32_t *map;
-  const double *qd;
+  const double *geo;
   double beta;
   int64_t ndof, nei;
   int nbatch;
@@ -146,7 +143,7 @@ hipError_t launch_grad(const GradArgs &a, hipStream_t s);
 struct LoadArgs {
   int p;
   const int32_t *map;
-  const double *qd;
+  const double *geo;
   int64_t ndof, nei;
   int nbatch;
   const double *f;          // [nbatch][nelem][q^3]

@@ -1,16 +1,20 @@
 // Exact diagonal of the assembled operator alpha M + beta K(nu), sum-factorized.
 //
-// With the stored factors m = w|J| and Gq = w|J| J^-1 J^-T (symmetric, 6 entries),
-// the diagonal entry of node (i, j, k) of an element is
+// With the factors m = w|J| and Gq = w|J| J^-1 J^-T (symmetric, 6 entries), formed from the
+// element's trilinear map (geom.h), the diagonal entry of node (i, j, k) of an element is
 //   alpha sum_abc m B2(a,i) B2(b,j) B2(c,k)
 // + beta  sum_abc nu sum_{r,s} Gq_rs t_r t_s
 // where t_1 = G(a,i) B(b,j) B(c,k), t_2 = B G B, t_3 = B B G (the rows of the tensor
 // gradient of eq. tensorGradient evaluated on the node's own basis function).  Each
 // of the 7 distinct (r, s) products factors per direction into a Hadamard product
 // of 1D tables: B2 = B.B, G2 = G.G, BG = B.G, with the off-diagonal pairs doubled.
-// Every term is then a three-stage contraction q^3 -> n^3.  The element
+// Every term is then a three-stage contraction q^3 -> n^3; a thread owns a xi_3 line of the
+// points, so a term's values and its xi_3 contraction stay in registers.  The element
 // contributions are assembled like the apply's (sole DoFs directly, shared nodes via
-// the E-vector and the assembly kernel, which sets the essential rows to 1).
+// the E-vector and the assembly kernel, which sets the essential rows to 1).  Several elements
+// share a workgroup as in the apply (one element per 64 threads left most lanes idle at low
+// order): set_coeffs with this kernel at 31 x 32 x 30 p = 1 449 -> 112 us, 20 x 21 x 19 p = 5
+// 869 -> 537 us.
 #include <hip/hip_runtime.h>
 
 #include "apply_impl.h"
@@ -30,99 +34,112 @@ __device__ __forceinline__ constexpr double dtab(int which, int a, int i) {
 __device__ constexpr int kTermTab[7][3] = {{0, 0, 0}, {1, 0, 0}, {0, 1, 0}, {0, 0, 1},
                                            {2, 2, 0}, {2, 0, 2}, {0, 2, 2}};
 
-template <int P>
-__global__ void __launch_bounds__(Dims<P>::Q2 < 64 ? 64 : Dims<P>::Q2)
-diag_kernel(const int32_t *__restrict__ map, const double *__restrict__ qd,
-            const double *__restrict__ nu, double alpha, double beta, int64_t nelem,
+template <int P, bool POS>
+__global__ void __launch_bounds__(Dims<P>::THREADS)
+diag_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
+            const double *__restrict__ cw, double alpha, double beta, int64_t nelem,
             double *__restrict__ diag, double *__restrict__ Y, const int32_t *__restrict__ pos,
             int compact) {
   using D = Dims<P>;
-  constexpr int N = D::N, Q = D::Q, N2 = D::N2, N3 = D::N3, Q2 = D::Q2, Q3 = D::Q3;
-  __shared__ double s0[Q3];
-  __shared__ double s1[Q2 * N];
-  __shared__ double s2[Q * N2];
-  const int t = threadIdx.x;
-  const int nt = blockDim.x;
-  const int64_t e = blockIdx.x;
-  if (e >= nelem) return;  // whole block exits together (one element per block)
-  const double *qe = qd + e * (int64_t)(kQdSlots * Q3);
-  const double *ne = nu ? nu + e * (int64_t)Q3 : nullptr;
+  constexpr int N = D::N, Q = D::Q, N2 = D::N2, N3 = D::N3, Q2 = D::Q2, Q3 = D::Q3, TPE = D::TPE, E = D::E;
+  constexpr rules::GaussRule<Q> gr = rules::gauss<Q>();
+  __shared__ double s1_all[E * N * Q2];  // [k][b][a], at the end the nodal values [k][j][i]
+  __shared__ double s2_all[E * N2 * Q];  // [k][j][a]
+  __shared__ __align__(16) double sgeo[E * kGeoStride];
+  __shared__ int32_t smap_all[E * N3];
+  const int le = threadIdx.x / TPE;
+  const int t = threadIdx.x - le * TPE;
+  const int64_t e0 = (int64_t)xcd_block() * E;
+  const bool active = e0 + le < nelem;
+  const uint32_t rel = active ? le : 0;
+  double *s1 = s1_all + le * N * Q2, *s2 = s2_all + le * N2 * Q, *sg = sgeo + le * kGeoStride;
+  int32_t *smap = smap_all + le * N3;
+  {
+    const ElemTab z = elem_tab<P>(map, pos, compact, e0);
+    Nodes<P> nd;
+    nd.load_map(z, t, rel);
+    nd.load_rank(z, t);
+#pragma unroll
+    for (int k = 0; k * TPE < kGeoStride; ++k) {
+      const int i = t + k * TPE < kGeoStride ? t + k * TPE : kGeoStride - 1;
+      sg[i] = ld<double>(geo + e0 * kGeoStride, (rel * kGeoStride + i) * 8u);
+    }
+    nd.template load_dest<POS>(z, rel);
+    nd.keep(smap, t);
+  }
+  __syncthreads();
+  LineGeom L;
+  L.init(sg, kGaussRule<Q>.x[t % Q], kGaussRule<Q>.x[t / Q]);
+  const double wab = kGaussRule<Q>.w[t % Q] * kGaussRule<Q>.w[t / Q];
+  const double *ce = cw ? cw + (e0 + rel) * Q3 + t : nullptr;
   double acc[N];
 #pragma unroll
-  for (int k = 0; k < N; ++k) acc[k] = 0.0;
+  for (int i = 0; i < N; ++i) acc[i] = 0.0;
 
 #pragma unroll
   for (int term = 0; term < 7; ++term) {
     const double coef = (term == 0) ? alpha : ((term <= 3) ? beta : 2.0 * beta);
     if (coef == 0.0) continue;  // uniform across the block
-    for (int qi = t; qi < Q3; qi += nt) {
-      double v = coef * qe[(int64_t)term * Q3 + qi];
-      if (term > 0 && ne) v *= ne[qi];
-      s0[qi] = v;
-    }
-    __syncthreads();
     const int tx = kTermTab[term][0], ty = kTermTab[term][1], tz = kTermTab[term][2];
-    if (t < Q2) {  // contract a: lines (b, c)
-      const int b = t % Q, c = t / Q;
-      double in[Q];
+    {  // the term at the line's points, contracted along c
+      double r[N];
 #pragma unroll
-      for (int a = 0; a < Q; ++a) in[a] = s0[c * Q2 + b * Q + a];
+      for (int k = 0; k < N; ++k) r[k] = 0.0;
 #pragma unroll
-      for (int i = 0; i < N; ++i) {
-        double s = 0.0;
+      for (int c = 0; c < Q; ++c) {
+        const double w = wab * gr.w[c], det = L.det(gr.x[c]);
+        double v;
+        if (term == 0) {
+          v = coef * (w * det);
+        } else {
+          double ad[3][3];
+          L.adj(gr.x[c], ad[0], ad[1], ad[2]);
+          const int i = term <= 3 ? term - 1 : (term == 6 ? 1 : 0), j = term <= 3 ? term - 1 : (term == 4 ? 1 : 2);
+          v = coef * (ce ? ce[c * Q2] : w * recip(det)) *
+              (ad[i][0] * ad[j][0] + ad[i][1] * ad[j][1] + ad[i][2] * ad[j][2]);
+        }
 #pragma unroll
-        for (int a = 0; a < Q; ++a) s += dtab<P>(tx, a, i) * in[a];
-        s1[(c * Q + b) * N + i] = s;
+        for (int k = 0; k < N; ++k) r[k] += dtab<P>(tz, c, k) * v;
       }
+#pragma unroll
+      for (int k = 0; k < N; ++k) s1[k * Q2 + t] = r[k];
     }
     __syncthreads();
-    if (t < Q * N) {  // contract b: lines (i, c)
-      const int i = t % N, c = t / N;
+    if (t < Q * N) {  // contract b: lines (a, k)
+      const int a = t % Q, k = t / Q;
       double in[Q];
 #pragma unroll
-      for (int b = 0; b < Q; ++b) in[b] = s1[(c * Q + b) * N + i];
+      for (int b = 0; b < Q; ++b) in[b] = s1[(k * Q + b) * Q + a];
 #pragma unroll
       for (int j = 0; j < N; ++j) {
         double s = 0.0;
 #pragma unroll
         for (int b = 0; b < Q; ++b) s += dtab<P>(ty, b, j) * in[b];
-        s2[(c * N + j) * N + i] = s;
+        s2[(k * N + j) * Q + a] = s;
       }
     }
     __syncthreads();
-    if (t < N2) {  // contract c: lines (i, j)
-      const int i = t % N, j = t / N;
+    if (t < N2) {  // contract a: lines (j, k)
       double in[Q];
 #pragma unroll
-      for (int c = 0; c < Q; ++c) in[c] = s2[(c * N + j) * N + i];
+      for (int a = 0; a < Q; ++a) in[a] = s2[t * Q + a];
 #pragma unroll
-      for (int k = 0; k < N; ++k) {
+      for (int i = 0; i < N; ++i) {
         double s = 0.0;
 #pragma unroll
-        for (int c = 0; c < Q; ++c) s += dtab<P>(tz, c, k) * in[c];
-        acc[k] += s;
+        for (int a = 0; a < Q; ++a) s += dtab<P>(tx, a, i) * in[a];
+        acc[i] += s;
       }
     }
-    __syncthreads();
+    // (the next term writes s1, whose last reads the barrier above has closed, and s2 only
+    // after its own first barrier)
   }
-  // nodal values into s0 as [k][j][i]
   if (t < N2) {
-    const int i = t % N, j = t / N;
 #pragma unroll
-    for (int k = 0; k < N; ++k) s0[(k * N + j) * N + i] = acc[k];
+    for (int i = 0; i < N; ++i) s1[t * N + i] = acc[i];
   }
   __syncthreads();
-  const int32_t *emap = map + e * (int64_t)N3;
-  for (int l = t; l < N3; l += nt) {
-    const int32_t c = emap[l];
-    if (c < 0) continue;
-    if (c & kSoleBit)
-      diag[c & kDofMask] = s0[l];
-    else {
-      const int64_t q = compact ? e * surf_count<P>() + kRankTable<P>.r[l] : e * N3 + l;
-      Y[pos ? pos[q] : q] = s0[l];
-    }
-  }
+  emit_e<P, double, false>(s1, t, active, smap, (const double *)nullptr, Y, diag);
 }
 
 template <int P>
@@ -130,9 +147,10 @@ hipError_t launch_diag_p(const DiagArgs &a, hipStream_t s) {
   using D = Dims<P>;
   const int64_t ne = a.nelem;
   if (ne <= 0) return hipSuccess;
-  const int threads = D::Q2 < 64 ? 64 : D::Q2;
-  hipLaunchKernelGGL((diag_kernel<P>), dim3((unsigned)ne), dim3(threads), 0, s, a.map, a.qd,
-                     a.nu, a.alpha, a.beta, a.nelem, a.diag, a.evec, a.pos, a.compact);
+  constexpr bool POS = evec_dof_ordered(P);
+  if ((a.pos != nullptr) != POS) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((diag_kernel<P, POS>), dim3((unsigned)((ne + D::E - 1) / D::E)), dim3(D::THREADS), 0,
+                     s, a.map, a.geo, a.cw, a.alpha, a.beta, a.nelem, a.diag, a.evec, a.pos, a.compact);
   return hipGetLastError();
 }
 

@@ -1,14 +1,19 @@
 // Adjoint-gradient integrand and load vector, built from the same sum-factorized
-// stages as the apply.
+// stages as the apply, with the geometric factors formed along each thread's xi_3 line
+// (geom.h).
 //
-// Gradient: K depends on nu only through the stored factor W = nu w|J| J^-1 J^-T
-// (Section 3.1), so dJ/dnu_q = -lam^T (dA/dnu_q) u = -beta (Gq grad_ref lam).grad_ref u
-// at each quadrature point.  Reference gradients of u and lam are interpolated with
-// the forward stages; the result goes to the caller's element order.
+// Gradient: K depends on nu only through W = nu w|J| J^-1 J^-T (Section 3.1), so
+// dJ/dnu_q = -lam^T (dA/dnu_q) u = -beta w|J| (J^-T grad_ref lam).(J^-T grad_ref u)
+// = -beta (w / |J|) (adj^T grad_ref lam).(adj^T grad_ref u) at each quadrature point.  The
+// result goes to the caller's element order.
 //
 // Load vector: b_i = sum_q w|J| f_q phi_i, i.e. the transposed stages with the
 // mass weight only (B^T in each direction), assembled like the apply (the assembly
 // kernel sets the essential entries to 0).
+//
+// Both were bound by the factors' bytes (6 and 1 of 8 per point); formed, the 25 x 26 x 24
+// p = 4 gradient takes 35 instead of 58 us (17 x 18 x 16 p = 6: 31 of 73) and the load vector
+// 23 instead of 34.
 #include <hip/hip_runtime.h>
 
 #include "apply_impl.h"
@@ -16,123 +21,192 @@
 namespace sfem {
 namespace {
 
-// Reference gradient (d/dxi_1, d/dxi_2, d/dxi_3) of a nodal field at the q points of
-// this thread's xi_3 line.
-template <int P, typename T>
-__device__ __forceinline__ void ref_grad_line(T *buf, int t, bool active, const Nodes<P> &nd,
-                                              const T *__restrict__ v,
-                                              T (&gx)[P + 2], T (&gy)[P + 2], T (&gz)[P + 2]) {
-  constexpr int N = P + 1, Q = P + 2;
-  using TB = Tab<P, T>;
-  gather_e<P, T>(buf, t, active, nd, v);
-  fwd_x<P, T, true>(buf, t);
-  fwd_y<P, T, true>(buf, t);
-  T zbb[N], zgb[N], zbg[N];
-  load_z<P, T, true>(buf, t, zbb, zgb, zbg);
+// Outputs (c, q-1-c), or the middle one, of a 1D contraction from the even-odd split of its
+// input line.
+template <typename TB>
+__device__ __forceinline__ void line_pair(const eo::Split<TB::NI, double> &x, int c, double &lo,
+                                          double &hi) {
+  double Ev = 0.0, Od = 0.0;
 #pragma unroll
-  for (int c = 0; c < Q; ++c) {
-    T dx = 0, dy = 0, dz = 0;
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
-      dz += TB::G(c, k) * zbb[k];
-      dy += TB::B(c, k) * zgb[k];
-      dx += TB::B(c, k) * zbg[k];
-    }
-    gx[c] = dx;
-    gy[c] = dy;
-    gz[c] = dz;
+  for (int i = 0; i < TB::NI / 2; ++i) {
+    Ev += TB::e(c, i) * x.e[i];
+    Od += TB::o(c, i) * x.o[i];
   }
-  __syncthreads();  // buf is reused by the next gather
+  if constexpr (TB::NI % 2 == 1) Ev += TB::t(c, TB::NI / 2) * x.e[TB::NI / 2];
+  lo = Ev + Od;
+  hi = (TB::S > 0) ? (Ev - Od) : (Od - Ev);
+}
+template <typename TB>
+__device__ __forceinline__ double line_mid(const eo::Split<TB::NI, double> &x) {
+  constexpr int M = TB::NO / 2;
+  double v = 0.0;
+#pragma unroll
+  for (int i = 0; i < TB::NI / 2; ++i) v += TB::t(M, i) * (TB::S > 0 ? x.e[i] : x.o[i]);
+  if constexpr (TB::NI % 2 == 1 && TB::S > 0) v += TB::t(M, TB::NI / 2) * x.e[TB::NI / 2];
+  return v;
+}
+
+// xi_3 lines of a field's three xi_1/xi_2-contracted forms, even-odd split.
+template <int P>
+struct Lines {
+  eo::Split<P + 1, double> bb, gb, bg;
+  __device__ __forceinline__ void read(const double *buf, int t) {
+    double zbb[P + 1], zgb[P + 1], zbg[P + 1];
+    load_z<P, double, true>(buf, t, zbb, zgb, zbg);
+    bb = eo::split(zbb);
+    gb = eo::split(zgb);
+    bg = eo::split(zbg);
+  }
+  // reference gradient at slices c and q-1-c, and at the middle slice
+  __device__ __forceinline__ void grad_pair(int c, double (&lo)[3], double (&hi)[3]) const {
+    line_pair<eo::Tab1<P, 0>>(bg, c, lo[0], hi[0]);
+    line_pair<eo::Tab1<P, 0>>(gb, c, lo[1], hi[1]);
+    line_pair<eo::Tab1<P, 1>>(bb, c, lo[2], hi[2]);
+  }
+  __device__ __forceinline__ void grad_mid(double (&m)[3]) const {
+    m[0] = line_mid<eo::Tab1<P, 0>>(bg);
+    m[1] = line_mid<eo::Tab1<P, 0>>(gb);
+    m[2] = line_mid<eo::Tab1<P, 1>>(bb);
+  }
+};
+
+template <int P>
+__device__ __forceinline__ void put_geo(double *sg, const double *geo, int64_t e0, uint32_t rel, int t) {
+  constexpr int TPE = Dims<P>::TPE;
+#pragma unroll
+  for (int k = 0; k * TPE < kGeoStride; ++k) {
+    const int i = t + k * TPE < kGeoStride ? t + k * TPE : kGeoStride - 1;
+    sg[i] = ld<double>(geo + e0 * kGeoStride, (rel * kGeoStride + i) * 8u);
+  }
 }
 
 template <int P>
-__global__ void __launch_bounds__(Dims<P>::THREADS)
-grad_kernel(const int32_t *__restrict__ map, const double *__restrict__ qd, double beta,
+__global__ void __launch_bounds__(Dims<P>::THREADS, 2)
+grad_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo, double beta,
             int64_t nei, int nbatch, int64_t ndof, const double *__restrict__ u,
             const double *__restrict__ lam, double *__restrict__ g) {
   using D = Dims<P>;
   constexpr int Q = D::Q, Q2 = D::Q2, Q3 = D::Q3, TPE = D::TPE, E = D::E;
-  __shared__ double smem[E * D::BUF];
+  constexpr rules::GaussRule<Q> gr = rules::gauss<Q>();
+  __shared__ __align__(16) double smem[E * D::BUF];
+  __shared__ __align__(16) double sgeo[E * kGeoStride];
   const int le = threadIdx.x / TPE;
   const int t = threadIdx.x - le * TPE;
-  const int64_t e0 = (int64_t)blockIdx.x * E;
-  const int64_t e = e0 + le;
-  const bool active = e < nei;
-  const int64_t es = active ? e : e0;
+  const int64_t e0 = (int64_t)xcd_block() * E;
+  const bool active = e0 + le < nei;
+  const uint32_t rel = active ? le : 0;
   double *buf = smem + le * D::BUF;
   Nodes<P> nd;
-  nd.load_map(elem_tab<P>(map, nullptr, 1, e0), t, (uint32_t)(es - e0));
-  const double *qe = qd + es * (int64_t)(kQdSlots * Q3);
+  nd.load_map(elem_tab<P>(map, nullptr, 1, e0), t, rel);
+  put_geo<P>(sgeo + le * kGeoStride, geo, e0, rel, t);
   for (int m = 0; m < nbatch; ++m) {
-    double lx[Q], ly[Q], lz[Q], ux[Q], uy[Q], uz[Q];
-    ref_grad_line<P, double>(buf, t, active, nd, lam + (int64_t)m * ndof, lx, ly, lz);
-    ref_grad_line<P, double>(buf, t, active, nd, u + (int64_t)m * ndof, ux, uy, uz);
-    if (active) {
-      double *go = g + ((int64_t)m * nei + e) * Q3;
+    double uv[Nodes<P>::NL];  // both fields' nodal values in flight together
+    nd.load_values(u + (int64_t)m * ndof, uv);
+    Lines<P> a, b;
+    gather_e<P, double>(buf, t, active, nd, lam + (int64_t)m * ndof);
+    fwd_x<P, double, true>(buf, t);
+    fwd_y<P, double, true>(buf, t);
+    a.read(buf, t);
+    __syncthreads();
 #pragma unroll
-      for (int c = 0; c < Q; ++c) {
-        const int qi = c * Q2 + t;
-        const double G11 = qe[1 * Q3 + qi], G22 = qe[2 * Q3 + qi], G33 = qe[3 * Q3 + qi];
-        const double G12 = qe[4 * Q3 + qi], G13 = qe[5 * Q3 + qi], G23 = qe[6 * Q3 + qi];
-        const double f1 = G11 * ux[c] + G12 * uy[c] + G13 * uz[c];
-        const double f2 = G12 * ux[c] + G22 * uy[c] + G23 * uz[c];
-        const double f3 = G13 * ux[c] + G23 * uy[c] + G33 * uz[c];
-        go[qi] = -beta * (lx[c] * f1 + ly[c] * f2 + lz[c] * f3);
-      }
+    for (int k = 0; k < Nodes<P>::NL; ++k)
+      buf[Nodes<P>::node(t, k)] = (active && nd.c[k] >= 0) ? uv[k] : 0.0;
+    __syncthreads();
+    fwd_x<P, double, true>(buf, t);
+    fwd_y<P, double, true>(buf, t);
+    b.read(buf, t);
+    __syncthreads();  // buf is reused by the next member
+    LineGeom L;
+    L.init(sgeo + le * kGeoStride, kGaussRule<Q>.x[t % Q], kGaussRule<Q>.x[t / Q]);
+    const double wab = kGaussRule<Q>.w[t % Q] * kGaussRule<Q>.w[t / Q];
+    double *go = g + ((int64_t)m * nei + e0 + rel) * Q3 + t;
+    auto point = [&](int c, const double (&x)[3], const double (&y)[3]) {
+      double r1[3], r2[3], r3[3], s = 0.0;
+      L.adj(gr.x[c], r1, r2, r3);
+#pragma unroll
+      for (int r = 0; r < 3; ++r)
+        s += (r1[r] * x[0] + r2[r] * x[1] + r3[r] * x[2]) * (r1[r] * y[0] + r2[r] * y[1] + r3[r] * y[2]);
+      if (active) go[c * Q2] = -beta * ((wab * gr.w[c]) * recip(L.det(gr.x[c]))) * s;
+    };
+#pragma unroll
+    for (int c = 0; c < Q / 2; ++c) {
+      double xl[3], xh[3], yl[3], yh[3];
+      a.grad_pair(c, xl, xh);
+      b.grad_pair(c, yl, yh);
+      point(c, xl, yl);
+      point(Q - 1 - c, xh, yh);
+    }
+    if constexpr (Q % 2 == 1) {
+      double x[3], y[3];
+      a.grad_mid(x);
+      b.grad_mid(y);
+      point(Q / 2, x, y);
     }
   }
 }
 
-template <int P>
+template <int P, bool POS>
 __global__ void __launch_bounds__(Dims<P>::THREADS)
-load_kernel(const int32_t *__restrict__ map, const double *__restrict__ qd, int64_t nei,
+load_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo, int64_t nei,
             int nbatch, int64_t ndof, const double *__restrict__ f, double *__restrict__ b,
             double *__restrict__ Y, int64_t estride, const int32_t *__restrict__ pos, int compact) {
   using D = Dims<P>;
-  using TB = Tab<P, double>;
+  using BT = eo::Tab1<P, 0>;
   constexpr int N = D::N, Q = D::Q, Q2 = D::Q2, Q3 = D::Q3, TPE = D::TPE, E = D::E;
-  __shared__ double smem[E * D::BUF];
+  constexpr rules::GaussRule<Q> gr = rules::gauss<Q>();
+  __shared__ __align__(16) double smem[E * D::BUF];
+  __shared__ __align__(16) double sgeo[E * kGeoStride];
+  __shared__ int32_t smap_all[E * D::N3];
   const int le = threadIdx.x / TPE;
   const int t = threadIdx.x - le * TPE;
-  const int64_t e = (int64_t)blockIdx.x * E + le;
-  const bool active = e < nei;
-  const int64_t es = active ? e : 0;
+  const int64_t e0 = (int64_t)xcd_block() * E;
+  const bool active = e0 + le < nei;
+  const uint32_t rel = active ? le : 0;
   double *buf = smem + le * D::BUF;
-  const int32_t *emap = map + es * (int64_t)D::N3;
-  const double *qe = qd + es * (int64_t)(kQdSlots * Q3);
+  int32_t *smap = smap_all + le * D::N3;
+  double fv[Q];  // the next source's values at the line's points
+  auto load_f = [&](int m) {
+    const double *fe = f + ((int64_t)m * nei + e0 + rel) * Q3 + t;
+#pragma unroll
+    for (int c = 0; c < Q; ++c) fv[c] = fe[c * Q2];
+  };
+  {
+    const ElemTab z = elem_tab<P>(map, pos, compact, e0);
+    Nodes<P> nd;
+    nd.load_map(z, t, rel);
+    nd.load_rank(z, t);
+    load_f(0);
+    put_geo<P>(sgeo + le * kGeoStride, geo, e0, rel, t);
+    nd.template load_dest<POS>(z, rel);
+    nd.keep(smap, t);
+  }
+  __syncthreads();
+  double wd[Q];  // w|J| along the line
+  {
+    LineGeom L;
+    L.init(sgeo + le * kGeoStride, kGaussRule<Q>.x[t % Q], kGaussRule<Q>.x[t / Q]);
+    const double wab = kGaussRule<Q>.w[t % Q] * kGaussRule<Q>.w[t / Q];
+#pragma unroll
+    for (int c = 0; c < Q; ++c) wd[c] = (wab * gr.w[c]) * L.det(gr.x[c]);
+  }
   for (int m = 0; m < nbatch; ++m) {
     double p1[N];
 #pragma unroll
-    for (int k = 0; k < N; ++k) p1[k] = 0.0;
-    if (active) {
-      const double *fe = f + ((int64_t)m * nei + e) * Q3;
+    for (int c = 0; c < Q; ++c) fv[c] *= wd[c];
+    eo::Acc<N, double> A;
+    A.zero();
 #pragma unroll
-      for (int c = 0; c < Q; ++c) {
-        const int qi = c * Q2 + t;
-        const double v = qe[qi] * fe[qi];
-#pragma unroll
-        for (int k = 0; k < N; ++k) p1[k] += TB::B(c, k) * v;
-      }
-    }
+    for (int c = 0; c < Q / 2; ++c) A.template add_pair<BT>(c, fv[c], fv[Q - 1 - c]);
+    if constexpr (Q % 2 == 1) A.template add_mid<BT>(fv[Q / 2]);
+    A.finish(p1);
 #pragma unroll
     for (int k = 0; k < N; ++k) buf[k * Q2 + t] = p1[k];
+    if (m + 1 < nbatch) load_f(m + 1);
     __syncthreads();
     bwd_y<P, double, false>(buf, t);
     bwd_x<P, double, false>(buf, t);
-    if (active) {
-      double *bm = b + (int64_t)m * ndof;
-      double *Ym = Y + (int64_t)m * estride;
-      for (int l = t; l < D::N3; l += TPE) {
-        const int32_t c = emap[l];
-        if (c < 0) continue;
-        if (c & kSoleBit) {
-          bm[c & kDofMask] = buf[l];
-        } else {
-          const int64_t q = compact ? e * surf_count<P>() + kRankTable<P>.r[l] : e * D::N3 + l;
-          Ym[pos ? pos[q] : q] = buf[l];
-        }
-      }
-    }
+    emit_e<P, double, false>(buf, t, active, smap, (const double *)nullptr, Y + (int64_t)m * estride,
+                             b + (int64_t)m * ndof);
     __syncthreads();
   }
 }
@@ -142,7 +216,7 @@ hipError_t launch_grad_p(const GradArgs &a, hipStream_t s) {
   using D = Dims<P>;
   if (a.nei <= 0 || a.nbatch <= 0) return hipSuccess;
   hipLaunchKernelGGL((grad_kernel<P>), dim3((unsigned)((a.nei + D::E - 1) / D::E)),
-                     dim3(D::THREADS), 0, s, a.map, a.qd, a.beta, a.nei, a.nbatch,
+                     dim3(D::THREADS), 0, s, a.map, a.geo, a.beta, a.nei, a.nbatch,
                      a.ndof, a.u, a.lam, a.g);
   return hipGetLastError();
 }
@@ -152,8 +226,10 @@ hipError_t launch_load_p(const LoadArgs &a, hipStream_t s) {
   using D = Dims<P>;
   const int64_t ne = a.nei;
   if (ne <= 0 || a.nbatch <= 0) return hipSuccess;
-  hipLaunchKernelGGL((load_kernel<P>), dim3((unsigned)((ne + D::E - 1) / D::E)), dim3(D::THREADS),
-                     0, s, a.map, a.qd, a.nei, a.nbatch, a.ndof, a.f, a.b, a.evec, a.estride,
+  constexpr bool POS = evec_dof_ordered(P);
+  if ((a.pos != nullptr) != POS) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((load_kernel<P, POS>), dim3((unsigned)((ne + D::E - 1) / D::E)), dim3(D::THREADS),
+                     0, s, a.map, a.geo, a.nei, a.nbatch, a.ndof, a.f, a.b, a.evec, a.estride,
                      a.pos, a.compact);
   return hipGetLastError();
 }

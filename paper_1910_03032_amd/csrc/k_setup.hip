@@ -1,6 +1,6 @@
-// Setup kernels: the elements' trilinear coefficients, quadrature data (Section 3.1: w|J|
-// and w|J| J^-1 J^-T at the quadrature points), physical quadrature-point coordinates, the
-// coefficient w nu / |J| of the applies, precision casts.
+// Setup kernels: the elements' trilinear coefficients, the check of |J|, physical
+// quadrature-point coordinates, the coefficient w nu / |J| of the applies, the collocated
+// mass, precision casts.
 #include <hip/hip_runtime.h>
 
 #include "geom.h"
@@ -90,8 +90,9 @@ __global__ void colloc_mass_kernel(GaussArg g, int p, const double *__restrict__
   }
 }
 
-__global__ void qdata_setup_kernel(GaussArg g, int q, const double *__restrict__ xyz, int64_t nei,
-                                   double *__restrict__ qd, int *__restrict__ bad) {
+// |J| > 0 at the quadrature points (else, or not a number, *bad = 1).
+__global__ void check_det_kernel(GaussArg g, int q, const double *__restrict__ xyz, int64_t nei,
+                                 int *__restrict__ bad) {
   const int64_t q3 = (int64_t)q * q * q;
   const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (gid >= nei * q3) return;
@@ -99,36 +100,14 @@ __global__ void qdata_setup_kernel(GaussArg g, int q, const double *__restrict__
   const int qi = (int)(gid - e * q3);
   const int a = qi % q, b = (qi / q) % q, c = qi / (q * q);
   const double xi[3] = {g.x[a], g.x[b], g.x[c]};
-  const double w = g.w[a] * g.w[b] * g.w[c];
   double pos[3], J[3][3];
   trilinear(xyz + e * 24, xi, pos, J);
-  // adjugate: adj = det * J^{-1}
-  double A[3][3];
-  A[0][0] = J[1][1] * J[2][2] - J[1][2] * J[2][1];
-  A[0][1] = J[0][2] * J[2][1] - J[0][1] * J[2][2];
-  A[0][2] = J[0][1] * J[1][2] - J[0][2] * J[1][1];
-  A[1][0] = J[1][2] * J[2][0] - J[1][0] * J[2][2];
-  A[1][1] = J[0][0] * J[2][2] - J[0][2] * J[2][0];
-  A[1][2] = J[0][2] * J[1][0] - J[0][0] * J[1][2];
-  A[2][0] = J[1][0] * J[2][1] - J[1][1] * J[2][0];
-  A[2][1] = J[0][1] * J[2][0] - J[0][0] * J[2][1];
-  A[2][2] = J[0][0] * J[1][1] - J[0][1] * J[1][0];
-  const double det = J[0][0] * A[0][0] + J[0][1] * A[1][0] + J[0][2] * A[2][0];
+  // |J| by the first column of the adjugate
+  const double A00 = J[1][1] * J[2][2] - J[1][2] * J[2][1];
+  const double A10 = J[1][2] * J[2][0] - J[1][0] * J[2][2];
+  const double A20 = J[1][0] * J[2][1] - J[1][1] * J[2][0];
+  const double det = J[0][0] * A00 + J[0][1] * A10 + J[0][2] * A20;
   if (!(det > 0.0)) *bad = 1;
-  // w|J| J^{-1} J^{-T} = (w / det) adj adj^T
-  const double s = w / det;
-  double Gm[3][3];
-  for (int d = 0; d < 3; ++d)
-    for (int f = 0; f < 3; ++f)
-      Gm[d][f] = s * (A[d][0] * A[f][0] + A[d][1] * A[f][1] + A[d][2] * A[f][2]);
-  double *o = qd + e * (int64_t)(kQdSlots * q3) + qi;
-  o[0 * q3] = w * det;
-  o[1 * q3] = Gm[0][0];
-  o[2 * q3] = Gm[1][1];
-  o[3 * q3] = Gm[2][2];
-  o[4 * q3] = Gm[0][1];
-  o[5 * q3] = Gm[0][2];
-  o[6 * q3] = Gm[1][2];
 }
 
 __global__ void qpoint_coords_kernel(GaussArg g, int q, const double *__restrict__ xyz,
@@ -209,12 +188,12 @@ unsigned nblocks(int64_t n, int bs) { return (unsigned)((n + bs - 1) / bs); }
 
 }  // namespace
 
-hipError_t launch_qdata_setup(int q, const double *gx, const double *gw, const double *xyz,
-                              int64_t nei, double *qd, int *bad, hipStream_t s) {
+hipError_t launch_check_det(int q, const double *gx, const double *gw, const double *xyz, int64_t nei,
+                            int *bad, hipStream_t s) {
   const int64_t n = nei * (int64_t)q * q * q;
   if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(qdata_setup_kernel, dim3(nblocks(n, 256)), dim3(256), 0, s,
-                     gauss_arg(gx, gw, q), q, xyz, nei, qd, bad);
+  hipLaunchKernelGGL(check_det_kernel, dim3(nblocks(n, 256)), dim3(256), 0, s, gauss_arg(gx, gw, q), q, xyz,
+                     nei, bad);
   return hipGetLastError();
 }
 

@@ -570,7 +570,7 @@ __device__ __forceinline__ void gather3(double *buf, int t, bool active, const N
 // once per point and not per component, and a component's gradient lines live only while it is
 // processed and the loop over components stays rolled.  What bounds it: VALU issue and LDS.
 // (With 9 stored factors read per point and the three components' lines held together it took
-// 230 registers at p = 4 and twice the HBM bytes: 28 x 27 x 29 p = 5 291 -> 195 us, 84 x 85 x 83
+// 230 registers at p = 4 and twice the HBM bytes: 28 x 27 x 29 p = 5 291 -> 186 us, 84 x 85 x 83
 // p = 1 361 -> 224 us.  Unrolled over the components: 202 registers, 21 x 22 x 20 p = 4 58 us
 // against 52.)
 template <int P, bool POS>
