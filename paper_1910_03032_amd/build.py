@@ -24,6 +24,8 @@ LIB = os.path.join(PKG, "libsfem.so")
 SOURCES = [
     "k_apply_f64.hip",
     "k_apply_f32.hip",
+    "k_apply_cg64.hip",
+    "k_apply_cg32.hip",
     "k_diag.hip",
     "k_grad_load.hip",
     "k_setup.hip",

@@ -85,6 +85,7 @@ struct sfem_ctx {
   int32_t *d_aoff = nullptr;       // [na + 1] CSR offsets of their E-vector entries
   int32_t *d_pos = nullptr;        // DoF-ordered E-vector: [nelem][epe] entry of each node
   int32_t *d_slot = nullptr;       // element-ordered E-vector: entries of the contributions
+  int32_t *d_doff = nullptr;       // [ndof + 1] per DoF the offset of its entries and flags (CgDofs)
   int64_t nentries = 0;            // E-vector entries per member
   int64_t n_ess = 0;               // essential DoFs
   // geometry-only vectors, computed on first use
@@ -243,6 +244,7 @@ void free_all(sfem_ctx *c) {
   c->d_aoff = nullptr;
   c->d_pos = nullptr;
   c->d_slot = nullptr;
+  c->d_doff = nullptr;
   c->nentries = 0;
   c->n_ess = 0;
   c->d_cm = c->d_cminv = c->d_m1 = nullptr;
@@ -379,8 +381,10 @@ sfem_status ensure_cmass(sfem_ctx *c) {
 
 // (assemble = false: the element kernel only; y holds the sole DoFs and evec the shared
 // nodes' contributions, for a caller that adds more before assembling)
+// (cg: the first launch of a CG iteration instead, x unused; no assembly)
 sfem_status do_apply(sfem_ctx *c, int op, bool f32, int nbatch, const void *x, void *y,
-                     double *part = nullptr, void *evec = nullptr, bool assemble = true);
+                     double *part = nullptr, void *evec = nullptr, bool assemble = true,
+                     const CgIn *cg = nullptr);
 
 // m1 = M 1 and 1^T M 1 (geometry only), for the mean-zero condition int x = m1^T x.
 sfem_status ensure_m1(sfem_ctx *c, double *tmp_ones, double *tmp_part, double *tmp_out) {
@@ -433,7 +437,7 @@ int apply_final_count(const sfem_ctx *c, bool f32, int nb) {
 // evec: E-vector storage of at least nbatch * nentries values given by the caller, or
 // null for the context's own (grown on demand).
 sfem_status do_apply(sfem_ctx *c, int op, bool f32, int nbatch, const void *x, void *y,
-                     double *part, void *evec, bool assemble) {
+                     double *part, void *evec, bool assemble, const CgIn *cg) {
   if (nbatch == 0 || c->ndof == 0) return SFEM_OK;
   const int64_t estride = c->nentries;
   const size_t esz = f32 ? sizeof(float) : sizeof(double);
@@ -442,8 +446,8 @@ sfem_status do_apply(sfem_ctx *c, int op, bool f32, int nbatch, const void *x, v
     if ((st = ensure_evec(c, (size_t)estride * nbatch * esz)) != SFEM_OK) return st;
     evec = c->evec.p;
   }
-  const int nparts = apply_nparts(c, f32, nbatch);
   const int nblk_e = apply_nparts_elem(c, f32, nbatch);
+  const int nparts = cg ? nblk_e : apply_nparts(c, f32, nbatch);
   ApplyArgs a;
   a.p = c->p;
   a.op = op;
@@ -464,9 +468,11 @@ sfem_status do_apply(sfem_ctx *c, int op, bool f32, int nbatch, const void *x, v
   a.cw_mstride = c->nfield > 1 ? c->nelem * q3_of(c) : 0;
   a.alpha = op == SFEM_HELMHOLTZ ? c->alpha : (op == SFEM_MASS ? 1.0 : 0.0);
   a.beta = op == SFEM_HELMHOLTZ ? c->beta : (op == SFEM_MASS ? 0.0 : 1.0);
-  hipError_t e = f32 ? launch_apply_f32(a, c->stream) : launch_apply_f64(a, c->stream);
+  hipError_t e;
+  if (cg) e = f32 ? launch_apply_cg32(a, *cg, c->stream) : launch_apply_cg64(a, *cg, c->stream);
+  else e = f32 ? launch_apply_f32(a, c->stream) : launch_apply_f64(a, c->stream);
   if (e != hipSuccess) return fail(c, SFEM_E_HIP, std::string("apply launch: ") + hipGetErrorString(e));
-  if (!assemble) return SFEM_OK;
+  if (cg || !assemble) return SFEM_OK;
   double *pa = part ? part + nblk_e : nullptr;
   if (f32)
     e = launch_assemble<float>(c->plan, (const float *)evec, estride, (const float *)x, (float *)y,
@@ -525,7 +531,7 @@ struct PcgWork {
   T *r, *p, *w;
   double *part;   // vector-kernel partials [nb][5][nblk]
   double *dpart;  // p^T A p partials of the apply [nb][nparts]
-  PcgScalars *sc;  // [2][nb]: the current and the next iteration's scalars
+  PcgScalars *sc;  // [2][nb]: the state after the update, the state after the element kernel
   int nblk, nparts;
 };
 
@@ -551,7 +557,8 @@ PcgWork<T> carve_pcg(const sfem_ctx *c, Carver &cv, int64_t n, int nb) {
   return w;
 }
 
-// Jacobi-PCG on the context stream.  On return hs[] holds the final scalars.
+// Jacobi-PCG on the context stream, two launches per iteration (pcg.h).  On return hs[] holds
+// the final scalars.
 template <typename T>
 sfem_status run_pcg(sfem_ctx *c, int op, int nb, const T *b, T *x, bool x0_zero, double rtol,
                     int maxit, int check_every, const T *dinv, int64_t dms, PcgWork<T> &w,
@@ -567,11 +574,8 @@ sfem_status run_pcg(sfem_ctx *c, int op, int nb, const T *b, T *x, bool x0_zero,
     HIPCHK(c, VecOps<T>::start(b, w.w, nullptr, w.r, dinv, dms, w.p, w.part, w.nblk, n, nb, s));
   }
   HIPCHK(c, launch_pcg_init(w.part, w.nblk, nb, rtol, w.sc, s, nullspace, n));
-  if (nullspace) HIPCHK(c, launch_zshift<T>(w.p, w.sc, n, nb, s));
-  int cur = 0;  // slot of the current scalars in w.sc
   auto all_done = [&]() -> sfem_status {
-    HIPCHK(c, hipMemcpyAsync(hs, w.sc + (int64_t)cur * nb, sizeof(PcgScalars) * nb,
-                             hipMemcpyDeviceToHost, s));
+    HIPCHK(c, hipMemcpyAsync(hs, w.sc, sizeof(PcgScalars) * nb, hipMemcpyDeviceToHost, s));
     HIPCHK(c, hipStreamSynchronize(s));
     return SFEM_OK;
   };
@@ -584,17 +588,27 @@ sfem_status run_pcg(sfem_ctx *c, int op, int nb, const T *b, T *x, bool x0_zero,
     return false;
   };
   if (!any_active()) return SFEM_OK;
+  const int nelem_parts = apply_nparts_elem(c, f32, nb), unblk = cg_update_nblk(n);
+  const CgDofs dofs{c->d_doff, c->d_slot};
+  CgIn g{};
+  g.r = w.r;
+  g.dinv = dinv;
+  g.p = w.p;
+  g.dinv_mstride = dms;
+  g.sc = w.sc;
+  g.sc_next = w.sc + nb;
+  g.upart = w.part;
+  g.unblk = unblk;
+  g.ready = 1;
+  g.nullspace = nullspace;
   for (int it = 0; it < maxit; ++it) {
-    if ((st = do_apply(c, op, f32, nb, w.p, w.w, w.dpart)) != SFEM_OK) return st;
-    const double *dp = w.dpart + apply_final_off(c, f32, nb);
-    const int dcount = apply_final_count(c, f32, nb);
-    PcgScalars *sc = w.sc + (int64_t)cur * nb, *sc_next = w.sc + (int64_t)(1 - cur) * nb;
-    HIPCHK(c, VecOps<T>::update(x, w.p, w.r, w.w, dinv, dms, sc, dp, w.nparts, dcount, w.part,
-                                w.nblk, n, nb, s));
-    HIPCHK(c, VecOps<T>::newdir(w.r, dinv, dms, w.p, sc, sc_next, dp, w.nparts, dcount, w.part,
-                                w.nblk, nullspace, n, nb, s));
-    cur = 1 - cur;
+    if ((st = do_apply(c, op, f32, nb, nullptr, w.w, w.dpart, nullptr, false, &g)) != SFEM_OK) return st;
+    HIPCHK(c, VecOps<T>::update(dofs, (const T *)c->evec.p, c->nentries, w.w, x, w.p, w.r, dinv, dms, w.sc + nb,
+                                w.sc, w.dpart, nelem_parts, nelem_parts, w.part, unblk, n, nb, s));
+    g.ready = 0;
     if ((it + 1) % check_every == 0 || it + 1 == maxit) {
+      HIPCHK(c, launch_cg_finish(w.sc, w.part, unblk, nb, nullspace, n, s));
+      g.ready = 1;
       if ((st = all_done()) != SFEM_OK) return st;
       if (!any_active()) break;
     }
@@ -894,12 +908,30 @@ static sfem_status sfem_setup_body(sfem_ctx *c, int p, int q, int64_t nelem, con
   const bool compact = hp.compact;
   const int64_t epe = hp.epe;
   const int64_t na = hp.na;
-  const std::vector<int32_t> &imap = hp.imap;
+  std::vector<int32_t> &imap = hp.imap;
   const std::vector<int32_t> &alist = hp.alist;
   const std::vector<int32_t> &aoff = hp.aoff;
   const std::vector<int32_t> &pos = hp.pos;
   const std::vector<int32_t> &slots = hp.slots;
   if (hp.nentries >= (int64_t)kDofMask) return fail(c, SFEM_E_ARG, "mesh too large");
+  // per DoF the offset of its E-vector entries, with the map's flags (CgDofs); and one
+  // element node per essential DoF marked (kEssOwnerBit)
+  std::vector<int32_t> doff((size_t)ndof + 1);
+  {
+    int64_t i = 0;
+    for (int64_t gd = 0; gd < ndof; ++gd) {
+      const bool listed = i < na && alist[(size_t)i] == gd;
+      doff[(size_t)gd] = aoff[(size_t)i] | (listed ? 0 : kSoleBit) | (ess[(size_t)gd] ? INT32_MIN : 0);
+      if (listed) ++i;
+    }
+    doff[(size_t)ndof] = aoff[(size_t)na];
+    std::vector<uint8_t> seen((size_t)ndof, 0);
+    for (int32_t &v : imap)
+      if (v < 0 && !seen[(size_t)(v & kDofMask)]) {
+        seen[(size_t)(v & kDofMask)] = 1;
+        v |= kEssOwnerBit;
+      }
+  }
 
   // ---- rules
   if (!make_rules(p, q, c->rules)) return fail(c, SFEM_E_HIP, "1D rule construction failed");
@@ -924,6 +956,7 @@ static sfem_status sfem_setup_body(sfem_ctx *c, int p, int q, int64_t nelem, con
   if ((st = dalloc(c, &c->d_aoff, na + 1)) != SFEM_OK) return st;
   if ((st = dalloc(c, &c->d_pos, (int64_t)pos.size())) != SFEM_OK) return st;
   if ((st = dalloc(c, &c->d_slot, (int64_t)slots.size())) != SFEM_OK) return st;
+  if ((st = dalloc(c, &c->d_doff, ndof + 1)) != SFEM_OK) return st;
   int *d_bad = nullptr;
   if ((st = dalloc(c, &d_bad, 1)) != SFEM_OK) return st;
   if (na > 0) {
@@ -934,6 +967,7 @@ static sfem_status sfem_setup_body(sfem_ctx *c, int p, int q, int64_t nelem, con
     HIPCHK(c, hipMemcpyAsync(c->d_pos, pos.data(), pos.size() * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));
   if (!slots.empty())
     HIPCHK(c, hipMemcpyAsync(c->d_slot, slots.data(), slots.size() * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));
+  HIPCHK(c, hipMemcpyAsync(c->d_doff, doff.data(), doff.size() * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));
   c->plan.alist = c->d_alist;
   c->plan.aoff = c->d_aoff;
   c->plan.slot = c->d_slot;

@@ -44,6 +44,7 @@
 #include "eo.h"
 #include "geom.h"
 #include "internal.h"
+#include "pcg.h"
 #include "rules.h"
 
 namespace sfem {
@@ -238,20 +239,19 @@ __device__ __forceinline__ double emit_e(const T *buf, int t, bool active, const
   return dot;
 }
 
-// Deterministic block sum, result on thread 0.  Every thread stores its value in LDS
-// (sh holds blockDim.x entries); the lanes of wave 0 each add a fixed strided subset,
-// then a wave64 butterfly.  Only values of existing threads are read, so a block whose
-// size is not a multiple of 64 needs no special case.
+// Deterministic sum over a block of THREADS threads, result on thread 0 (sh: THREADS / 64 + 1
+// doubles): a wave total each (the last wave may be partial), then the waves in order.
+template <int THREADS>
 __device__ __forceinline__ double block_sum_d(double v, double *sh) {
+  constexpr int NW = (THREADS + 63) / 64;
+  const int wave = threadIdx.x >> 6;
+  v = wave_total(v, wave == NW - 1 ? THREADS - 1 - 64 * (NW - 1) : 63);
   __syncthreads();
-  sh[threadIdx.x] = v;
+  if ((threadIdx.x & 63) == 0) sh[wave] = v;
   __syncthreads();
   double s = 0.0;
-  if (threadIdx.x < 64) {
-    for (int i = threadIdx.x; i < (int)blockDim.x; i += 64) s += sh[i];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-  }
+  if (threadIdx.x == 0)
+    for (int w = 0; w < NW; ++w) s += sh[w];
   return s;
 }
 
@@ -446,7 +446,7 @@ struct ApplyCfg {
   static constexpr int E = Dims<P>::E;
   static constexpr int THREADS = E * Dims<P>::TPE;
   static constexpr bool ZLDS = F64 ? (P >= 5) : (P == 6 || P == 8);
-  static constexpr int OCC = Dims<P>::OCC;
+  static constexpr int OCC = F64 ? Dims<P>::OCC : (P <= 6 ? 4 : 3);
 };
 
 // OP: 0 mass, 1 diffusion, 2 helmholtz (matches sfem_op).  Writes y at the sole DoFs
@@ -471,14 +471,17 @@ struct ApplyCfg {
 // members of one element run side by side (in the same workgroup or in neighbouring
 // ones, on one XCD) and read the element's coefficients, which all members share unless
 // cw_mstride != 0, from the same cache lines.
-template <int P, typename T, int OP, bool NU>
+// CG: the first launch of a CG iteration (pcg.h); x is unused and part required.  The partials
+// of p.Ap are then the element energies at the quadrature points, sum v u + g . grad_ref u, plus
+// p^2 of the essential DoFs at the element that carries their flag (kEssOwnerBit).
+template <int P, typename T, int OP, bool NU, bool CG>
 __global__ void __launch_bounds__((ApplyCfg<P, T>::THREADS), (ApplyCfg<P, T>::OCC))
 apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
              const double *__restrict__ cw, int64_t cw_mstride, double alpha, double beta, int64_t nelem,
              int nbatch, int64_t ndof, const T *__restrict__ x, T *__restrict__ Y,
              int64_t estride, const int32_t *__restrict__ pos, int compact, T *__restrict__ y,
              double *__restrict__ part,
-             int64_t part_mstride) {
+             int64_t part_mstride, CgIn cg) {
   using D = Dims<P>;
   constexpr int N = D::N, Q = D::Q, Q2 = D::Q2, Q3 = D::Q3, N3 = D::N3;
   constexpr int TPE = D::TPE, E = ApplyCfg<P, T>::E, THREADS = ApplyCfg<P, T>::THREADS;
@@ -487,8 +490,7 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
 
   constexpr bool POS = evec_dof_ordered(P);
   // element buffers; after the output step also the block sum of the fused dot product
-  // (E * BUF * sizeof(T) >= THREADS * 8 bytes)
-  static_assert(E * D::BUF * sizeof(T) >= THREADS * sizeof(double), "block sum space");
+  static_assert(E * D::BUF * sizeof(T) >= 8 * sizeof(double), "block sum space");
   __shared__ __align__(16) T smem[E * D::BUF];
   __shared__ __align__(16) double sgeo[E * kGeoStride];  // the elements' trilinear coefficients
   __shared__ int32_t smap_all[E * N3];  // the elements' map entries, kept for the output
@@ -510,15 +512,20 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
     m = rr - rel * (uint32_t)nbatch;
   }
   T *buf = smem + le * D::BUF;
+  double dot = 0.0;  // CG: the thread's part of p.Ap
 
   {
-    const T *xm = x + (int64_t)m * ndof;
+    const T *xm = CG ? nullptr : x + (int64_t)m * ndof;
     // first group of loads: the map, the entry order, the coefficients of the element and
     // of the thread's points; then what the map leads to
     const ElemTab z = elem_tab<P>(map, pos, compact, e0);
     Nodes<P> nd;
     nd.load_map(z, t, rel);
     nd.load_rank(z, t);
+    constexpr int NW = THREADS / 64;
+    PartLoads<NW, 2> up;  // CG: the update's partials of the workgroup's first member
+    if constexpr (CG)
+      if (!cg.ready) up.load(cg.upart + (int64_t)r0 * 4 * cg.unblk, cg.unblk);
     constexpr int NG = (kGeoStride + TPE - 1) / TPE;
     double gv[NG];
 #pragma unroll
@@ -538,7 +545,62 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
     for (int k = 0; k < NG; ++k)
       sgeo[le * kGeoStride + (t + k * TPE < kGeoStride ? t + k * TPE : kGeoStride - 1)] = gv[k];
     nd.keep(smap, t);
-    gather_e<P, T>(buf, t, active, nd, xm);
+    if constexpr (!CG) {
+      gather_e<P, T>(buf, t, active, nd, xm);
+    } else {
+      constexpr int NL = Nodes<P>::NL;
+      T zr[NL], zd[NL], zp[NL];
+      nd.load_values((const T *)cg.r + (int64_t)m * ndof, zr);
+      nd.load_values((const T *)cg.dinv + (int64_t)m * cg.dinv_mstride, zd);
+      nd.load_values((const T *)cg.p + (int64_t)m * ndof, zp);
+      // the states of the workgroup's members: here distinct ones, the k-th (r0 + k) mod nbatch
+      __shared__ double sums[E][4][NW];
+      const int here = nbatch < count ? nbatch : count;
+      const int k = le < here ? le : le % here;
+      PcgScalars s;
+      copy_state(s, cg.sc[m]);
+      auto other_parts = [&](double (&sh)[4][NW], int64_t mm, bool all) {
+        const double *p = cg.upart + mm * 4 * cg.unblk;
+        PartLoads<NW, 2> q;
+        if (all) {
+          q.load(p, cg.unblk);
+          q.parts(sh, cg.unblk);
+        }
+        if (cg.nullspace) {
+          q.load(p + 2 * (int64_t)cg.unblk, cg.unblk);
+          q.parts(*reinterpret_cast<double(*)[4][NW]>(&sh[2]), cg.unblk);
+        }
+      };
+      if (!cg.ready) {
+        up.parts(sums[0], cg.unblk);
+        other_parts(sums[0], r0, false);
+        for (int i = 1; i < here; ++i) other_parts(sums[i], (r0 + (uint32_t)i) % (uint32_t)nbatch, true);
+        __syncthreads();
+        cg_next_from<NW>(s, sums[k], cg.nullspace, ndof);
+      }
+      if (blockIdx.x == 0) {  // the first workgroup passes the states on (r0 = 0)
+        if (t == 0 && le < here) copy_state(cg.sc_next[m], s);
+        for (int mm = here; mm < nbatch; ++mm) {
+          PcgScalars o;
+          copy_state(o, cg.sc[mm]);
+          if (!cg.ready) {
+            __syncthreads();
+            other_parts(sums[0], mm, true);
+            __syncthreads();
+            cg_next_from<NW>(o, sums[0], cg.nullspace, ndof);
+          }
+          if (threadIdx.x == 0) copy_state(cg.sc_next[mm], o);
+        }
+      }
+      const T beta = (T)s.beta, zs = (T)s.zshift;
+#pragma unroll
+      for (int j = 0; j < NL; ++j) {
+        const T pv = cg_dir(zd[j], zr[j], zs, beta, zp[j]);
+        buf[Nodes<P>::node(t, j)] = (active && nd.c[j] >= 0) ? pv : T(0);
+        if (active && t + j * TPE < N3 && nd.c[j] < 0 && (nd.c[j] & kEssOwnerBit)) dot += (double)pv * (double)pv;
+      }
+      __syncthreads();
+    }
     using C = ApplyCfg<P, T>;
     fwd_x<P, T, DIFF>(buf, t);
     fwd_y<P, T, DIFF>(buf, t);
@@ -627,6 +689,10 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
             g3 = G[4] * dx + G[5] * dy + G[2] * dz;
           }
         }
+        if constexpr (CG) {
+          dot += (double)(v * u + g1 * dx + g2 * dy + g3 * dz);
+          asm volatile("" : "+v"(dot));  // summed here: postponed, its operands would stay live
+        }
       };
 #pragma unroll
       for (int c = 0; c < Q / 2; ++c) {
@@ -688,47 +754,47 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
 
     bwd_y<P, T, DIFF>(buf, t);
     bwd_x<P, T, DIFF>(buf, t);
-    if (part) {
-      const double dot =
-          emit_e<P, T, true>(buf, t, active, smap, xm, Y + (int64_t)m * estride, y + (int64_t)m * ndof);
+    T *Ym = Y + (int64_t)m * estride, *ym = y + (int64_t)m * ndof;
+    bool sum_dot = CG;
+    if constexpr (CG) {
+      emit_e<P, T, false>(buf, t, active, smap, xm, Ym, ym);
+    } else {
+      sum_dot = part != nullptr;
+      if (sum_dot) dot = emit_e<P, T, true>(buf, t, active, smap, xm, Ym, ym);
+      else emit_e<P, T, false>(buf, t, active, smap, xm, Ym, ym);
+    }
+    if (sum_dot) {
       // one sum per member; the block's pairs v_lo.. hold members (v_lo + k) mod nbatch,
       // k < count (a uniform test: members without a pair here get 0 without a sum)
       for (int mm = 0; mm < nbatch; ++mm) {
         const bool here = ((mm - (int)r0 + nbatch) % nbatch) < count;
         double sum = 0.0;
         if (here)
-          sum = block_sum_d((active && (int)m == mm) ? dot : 0.0, reinterpret_cast<double *>(smem));
+          sum = block_sum_d<THREADS>((active && (int)m == mm) ? dot : 0.0, reinterpret_cast<double *>(smem));
         if (threadIdx.x == 0) part[(int64_t)mm * part_mstride + blockIdx.x] = sum;
       }
-    } else {
-      emit_e<P, T, false>(buf, t, active, smap, xm, Y + (int64_t)m * estride, y + (int64_t)m * ndof);
     }
   }
 }
 
-template <int P, typename T>
-hipError_t launch_apply_pt(const ApplyArgs &a, hipStream_t s) {
-  using D = Dims<P>;
+template <int P, typename T, bool CG>
+hipError_t launch_apply_pt(const ApplyArgs &a, const CgIn &g, hipStream_t s) {
   if (a.nelem <= 0 || a.nbatch <= 0) return hipSuccess;
   if ((a.pos != nullptr) != evec_dof_ordered(P)) return hipErrorInvalidValue;
+  if (CG && !a.part) return hipErrorInvalidValue;
   using C = ApplyCfg<P, T>;
   dim3 grid((unsigned)((a.nelem * a.nbatch + C::E - 1) / C::E));
   dim3 block(C::THREADS);
-  const T *x = (const T *)a.x;
-  T *Y = (T *)a.evec;
-  T *y = (T *)a.y;
-#define SFEM_APPLY_ARGS                                                                    \
-  a.map, a.geo, a.cw, a.cw_mstride, a.alpha, a.beta, a.nelem, a.nbatch, a.ndof, x, Y, a.estride, \
-      a.pos, a.compact, y, a.part, a.part_mstride
-#define SFEM_APPLY(OP, NU) \
-  hipLaunchKernelGGL((apply_kernel<P, T, OP, NU>), grid, block, 0, s, SFEM_APPLY_ARGS)
+#define SFEM_APPLY(OP, NU)                                                                              \
+  hipLaunchKernelGGL((apply_kernel<P, T, OP, NU, CG>), grid, block, 0, s, a.map, a.geo, a.cw,           \
+                     a.cw_mstride, a.alpha, a.beta, a.nelem, a.nbatch, a.ndof, (const T *)a.x,          \
+                     (T *)a.evec, a.estride, a.pos, a.compact, (T *)a.y, a.part, a.part_mstride, g)
   if (a.op == SFEM_MASS) SFEM_APPLY(0, false);
   else if (a.op == SFEM_DIFFUSION && a.cw) SFEM_APPLY(1, true);
   else if (a.op == SFEM_DIFFUSION) SFEM_APPLY(1, false);
   else if (a.cw) SFEM_APPLY(2, true);
   else SFEM_APPLY(2, false);
 #undef SFEM_APPLY
-#undef SFEM_APPLY_ARGS
   return hipGetLastError();
 }
 

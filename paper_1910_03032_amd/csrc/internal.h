@@ -72,6 +72,21 @@ struct ApplyArgs {
 // Element phase of the apply over all elements (writes the E-vector).
 hipError_t launch_apply_f64(const ApplyArgs &a, hipStream_t s);
 hipError_t launch_apply_f32(const ApplyArgs &a, hipStream_t s);
+// The same as the first launch of a CG iteration (pcg.h): the direction is formed from r, dinv
+// and the old direction p (all in the apply's precision, [nb][ndof]; dinv member stride
+// dinv_mstride), a.x is unused, a.part ([nb][part_mstride], one partial of p.Ap per workgroup)
+// is required.  sc: the state after the last update; unless ready (it already holds beta) the
+// update's partials upart ([nb][4][unblk]) complete it; the completed state goes to sc_next.
+struct CgIn {
+  const void *r, *dinv, *p;
+  int64_t dinv_mstride;
+  const PcgScalars *sc;
+  PcgScalars *sc_next;
+  const double *upart;
+  int unblk, ready, nullspace;
+};
+hipError_t launch_apply_cg64(const ApplyArgs &a, const CgIn &g, hipStream_t s);
+hipError_t launch_apply_cg32(const ApplyArgs &a, const CgIn &g, hipStream_t s);
 // elements per workgroup of the apply kernel (one dot partial per workgroup)
 int apply_group_elems_f64(int p);
 int apply_group_elems_f32(int p);
@@ -155,6 +170,14 @@ struct LoadArgs {
 };
 hipError_t launch_load(const LoadArgs &a, hipStream_t s);
 
+// Where the update kernel of the CG finds (A p)_g: doff[g] holds the offset of g's E-vector
+// entries (the next DoF's offset ends them) with the map's sole and essential flags; slot: as
+// in AsmPlan.
+struct CgDofs {
+  const int32_t *doff;      // [ndof + 1]
+  const int32_t *slot;
+};
+
 // Vector kernels of the PCG (T = double or float).  Partial-sum buffers hold
 // [nb][nv][nblk] doubles.  dinv may be shared by all members (dms = 0) or per member
 // (dms = n).
@@ -166,17 +189,14 @@ struct VecOps {
   // one vector shared by all members, or null for the all-ones vector)
   static hipError_t dot(const T *a, const T *c, int64_t c_mstride, double *part, int nblk,
                         int64_t n, int nb, hipStream_t s);
-  // One CG step after the apply w = A p, whose partial sums of p.Ap are dpart[m * dmstride
-  // + i], i < dcount: update forms alpha and updates x and r, leaving the partials of
-  // r.z, r.r, sum z, sum r in part ([nb][4][nblk]); newdir forms beta from them, updates
-  // p and writes the next scalars to sc_next (the scalars are double-buffered).
-  static hipError_t update(T *x, const T *p, T *r, const T *w, const T *dinv, int64_t dms,
-                           const PcgScalars *sc, const double *dpart, int64_t dmstride,
-                           int dcount, double *part, int nblk, int64_t n, int nb, hipStream_t s);
-  static hipError_t newdir(const T *r, const T *dinv, int64_t dms, T *p, const PcgScalars *sc,
-                           PcgScalars *sc_next, const double *dpart, int64_t dmstride, int dcount,
-                           const double *upart, int unblk, int nullspace, int64_t n, int nb,
-                           hipStream_t s);
+  // The second launch of a CG iteration (pcg.h) after the element kernel in CG mode: dpart[m *
+  // dmstride + i], i < dcount, are its partials of p.Ap, y and evec its outputs; leaves the
+  // partials of r.z, r.r, sum z, sum r in part ([nb][4][nblk], nblk = cg_update_nblk) and the
+  // state with alpha in sc_next.
+  static hipError_t update(const CgDofs &dofs, const T *evec, int64_t estride, const T *y, T *x, T *p, T *r,
+                           const T *dinv, int64_t dms, const PcgScalars *sc, PcgScalars *sc_next,
+                           const double *dpart, int64_t dmstride, int dcount, double *part, int nblk,
+                           int64_t n, int nb, hipStream_t s);
   static hipError_t fill(T *p, T v, int64_t n, hipStream_t s);
   static hipError_t recip(const double *d, T *out, int64_t n, hipStream_t s);
 };
@@ -188,9 +208,10 @@ hipError_t launch_sub_norm(const double *b, const double *w, double *r, double *
 // z - mean(z) 1, and rho = r^T z of that vector (Section 5.3).
 hipError_t launch_pcg_init(const double *part, int nblk, int nb, double rtol, PcgScalars *sc,
                            hipStream_t s, int nullspace = 0, int64_t n = 0);
-// v[m][i] -= sc[m].zshift (the initial direction of a null-space solve)
-template <typename T>
-hipError_t launch_zshift(T *v, const PcgScalars *sc, int64_t n, int nb, hipStream_t s);
+int cg_update_nblk(int64_t n);
+// In place, the state of the next iteration from the update's partials.
+hipError_t launch_cg_finish(PcgScalars *sc, const double *part, int nblk, int nb, int nullspace, int64_t n,
+                            hipStream_t s);
 // v[m][i] -= c[m] * scale (member-wise constant shift)
 hipError_t launch_shift(double *v, const double *c, double scale, int64_t n, int nb, hipStream_t s);
 hipError_t launch_reduce1(const double *part, int nblk, int nb, double *out, hipStream_t s);

@@ -11,28 +11,29 @@
 #include <cmath>
 
 #include "internal.h"
+#include "pcg.h"
 
 namespace sfem {
 namespace {
 
 constexpr int VB = 256;
 
+// Sums over a block of VB threads, in every thread: wave totals, then the waves in order.
 template <int NV>
 __device__ __forceinline__ void block_sum(double (&v)[NV]) {
-  __shared__ double sh[NV][VB];
+  __shared__ double sh[NV][VB / 64];
 #pragma unroll
-  for (int k = 0; k < NV; ++k) sh[k][threadIdx.x] = v[k];
+  for (int k = 0; k < NV; ++k) {
+    const double t = wave_total(v[k]);
+    if ((threadIdx.x & 63) == 0) sh[k][threadIdx.x >> 6] = t;
+  }
   __syncthreads();
 #pragma unroll
-  for (int s = VB / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) {
+  for (int k = 0; k < NV; ++k) {
+    v[k] = 0.0;
 #pragma unroll
-      for (int k = 0; k < NV; ++k) sh[k][threadIdx.x] += sh[k][threadIdx.x + s];
-    }
-    __syncthreads();
+    for (int w = 0; w < VB / 64; ++w) v[k] += sh[k][w];
   }
-#pragma unroll
-  for (int k = 0; k < NV; ++k) v[k] = sh[k][0];
 }
 
 template <int NV>
@@ -47,8 +48,8 @@ __device__ __forceinline__ void write_part(double (&v)[NV], double *part, int nb
 
 // Sum of the nblk partials of quantity k (NV quantities per member, part[(m NV + k) nblk
 // + i]) of member m by a block of NT threads: each thread sums a fixed strided subset
-// (4 independent loads per step), then a wave64 butterfly and the waves in order.  The
-// order depends only on nblk and NT.  Result broadcast to all threads.
+// (4 independent loads per step), then wave totals and the waves in order.  The order
+// depends only on nblk and NT.  Result broadcast to all threads.
 template <int NV, int NT>
 __device__ __forceinline__ void reduce_parts_m(const double *part, int nblk, int m, double (&v)[NV]) {
   __shared__ double sh[NV][NT / 64];
@@ -56,17 +57,17 @@ __device__ __forceinline__ void reduce_parts_m(const double *part, int nblk, int
   for (int k = 0; k < NV; ++k) {
     const double *pk = part + ((int64_t)m * NV + k) * nblk;
     double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-    int i = threadIdx.x;
-    for (; i + 3 * NT < nblk; i += 4 * NT) {
-      s0 += pk[i];
-      s1 += pk[i + NT];
-      s2 += pk[i + 2 * NT];
-      s3 += pk[i + 3 * NT];
+    for (int i = threadIdx.x; i < nblk; i += 4 * NT) {
+      // clamped, not predicated: the four loads are in flight together also in the last step
+      const int i1 = i + NT, i2 = i + 2 * NT, i3 = i + 3 * NT, last = nblk - 1;
+      const double v0 = pk[i], v1 = pk[i1 < nblk ? i1 : last], v2 = pk[i2 < nblk ? i2 : last],
+                   v3 = pk[i3 < nblk ? i3 : last];
+      s0 += v0;
+      s1 += i1 < nblk ? v1 : 0.0;
+      s2 += i2 < nblk ? v2 : 0.0;
+      s3 += i3 < nblk ? v3 : 0.0;
     }
-    for (; i < nblk; i += NT) s0 += pk[i];
-    double s = (s0 + s1) + (s2 + s3);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    const double s = wave_total((s0 + s1) + (s2 + s3));
     if ((threadIdx.x & 63) == 0) sh[k][threadIdx.x >> 6] = s;
   }
   __syncthreads();
@@ -85,42 +86,8 @@ __device__ __forceinline__ void reduce_parts(const double *part, int nblk, doubl
   reduce_parts_m<NV, RB>(part, nblk, blockIdx.x, v);
 }
 
-// CG step length from p.Ap (or the failure state).
-__device__ __forceinline__ void set_alpha(PcgScalars &s, double pw) {
-  s.pw = pw;
-  s.alpha = 0.0;
-  if (s.active) {
-    if (!isfinite(pw)) {
-      s.status = SFEM_E_NAN;
-      s.active = 0;
-    } else if (!(pw > 0.0)) {
-      s.status = SFEM_E_BREAKDOWN;
-      s.active = 0;
-    } else {
-      s.alpha = s.rho / pw;
-    }
-  }
-}
-
-// New direction coefficient from r.z and r.r, and the stopping test.
-__device__ __forceinline__ void set_beta(PcgScalars &s, double rz, double rr) {
-  s.beta = 0.0;
-  if (s.active) {
-    s.iters += 1;
-    if (!isfinite(rz) || !isfinite(rr)) {
-      s.status = SFEM_E_NAN;
-      s.active = 0;
-    } else {
-      s.beta = rz / s.rho;
-      s.rho = rz;
-      s.rr = rr;
-      if (rr <= s.tol2) s.active = 0;
-    }
-  }
-}
-
-// r = b - w (w may be null: r = b); x = 0 if xzero; p = dinv r;
-// partials: r.p (rho), r.r, b.b, sum p, sum r
+// r = b - w (w may be null: r = b); x = 0 if xzero; p = 0 (the first direction is z = dinv r);
+// partials: r.z (rho), r.r, b.b, sum z, sum r
 template <typename T>
 __global__ void start_kernel(const T *__restrict__ b, const T *__restrict__ w, T *__restrict__ x,
                              T *__restrict__ r, const T *__restrict__ dinv, int64_t dinv_mstride,
@@ -133,7 +100,7 @@ __global__ void start_kernel(const T *__restrict__ b, const T *__restrict__ w, T
     const T ri = w ? (T)(bi - w[off + i]) : bi;
     const T pi = dm[i] * ri;
     r[off + i] = ri;
-    p[off + i] = pi;
+    p[off + i] = T(0);
     if (x) x[off + i] = T(0);
     v[0] += (double)ri * (double)pi;
     v[1] += (double)ri * (double)ri;
@@ -162,75 +129,130 @@ __device__ __forceinline__ double step_alpha(const PcgScalars &s, double pw) {
   return (s.active && isfinite(pw) && pw > 0.0) ? s.rho / pw : 0.0;
 }
 
-// x += alpha p; r -= alpha w; partials: r.z, r.r, sum z, sum r (z = dinv r).  alpha is
-// formed by every block from the apply's partials.
+// The second launch of a CG iteration (pcg.h): per DoF, w = (A p)_g -- the element kernel's y
+// at a DoF of one element, p itself at an essential DoF, else the sum of the DoF's E-vector
+// entries in element order (as assemble_kernel) -- then p, x += alpha p, r -= alpha w and the
+// partials of r.z, r.r, sum z, sum r of the new r.  doff: per DoF the offset of its entries,
+// with the map's flags (the count follows from the next DoF's offset).  Bound by HBM (or the
+// last-level cache): 7 vector streams, the offsets and the entries, in one pass where an
+// assembly, an update and a direction kernel made three.  Blocks of 512 threads, at most 512 of
+// them: few partials for every block of the next launch to sum, and 16 waves per CU in flight.
+constexpr int CU_NT = 512;
+constexpr int CU_MAXB = 512;  // (at most 4 * 192: PartLoads of the element kernels' 3 full waves)
+
 template <typename T>
-__global__ void update_kernel(T *__restrict__ x, const T *__restrict__ p, T *__restrict__ r,
-                              const T *__restrict__ w, const T *__restrict__ dinv,
-                              int64_t dinv_mstride, const PcgScalars *__restrict__ sc,
-                              const double *__restrict__ dpart, int64_t dmstride, int dcount,
-                              double *__restrict__ part, int nblk, int64_t n) {
+__global__ void __launch_bounds__(CU_NT)
+cg_update_kernel(CgDofs dofs, const T *__restrict__ Y, int64_t estride, const T *__restrict__ y,
+                 T *__restrict__ x, T *__restrict__ p, T *__restrict__ r,
+                 const T *__restrict__ dinv, int64_t dinv_mstride, const PcgScalars *__restrict__ sc,
+                 PcgScalars *__restrict__ sc_next, const double *__restrict__ dpart, int64_t dmstride,
+                 int dcount, double *__restrict__ part, int nblk, int64_t n) {
   const int m = blockIdx.y;
   const int64_t off = (int64_t)m * n;
-  const T *dm = dinv + (int64_t)m * dinv_mstride;
-  // the operands of the first entry are requested before the partial sums are read
-  const int64_t i0 = (int64_t)blockIdx.x * VB + threadIdx.x, stride = (int64_t)nblk * VB;
-  const bool has0 = i0 < n;
-  const int64_t j0 = has0 ? i0 : 0;
-  const T x0 = x[off + j0], p0 = p[off + j0], r0 = r[off + j0], w0 = w[off + j0], d0 = dm[j0];
-  double pw[1];
-  reduce_parts_m<1, VB>(dpart + (int64_t)m * dmstride, dcount, 0, pw);
-  const T alpha = (T)step_alpha(sc[m], pw[0]);
-  double v[4] = {0.0, 0.0, 0.0, 0.0};
-  auto step = [&](int64_t i, T xi, T pi, T ri, T wi, T di) {
-    x[off + i] = xi + alpha * pi;
-    ri = ri - alpha * wi;
-    r[off + i] = ri;
-    const T zi = di * ri;
-    v[0] += (double)ri * (double)zi;
-    v[1] += (double)ri * (double)ri;
-    v[2] += (double)zi;
-    v[3] += (double)ri;
+  const T *dm = dinv + (int64_t)m * dinv_mstride, *Ym = Y + (int64_t)m * estride, *ym = y + off;
+  T *xm = x + off, *pm = p + off, *rm = r + off;
+  // U entries per thread and pass, all their loads in flight together; those of the first
+  // pass are requested before the partial sums are read
+  constexpr int U = 2;
+  int32_t o[U], o1[U];
+  T ex[U], ep[U], er[U], ed[U];
+  const int64_t stride = (int64_t)nblk * CU_NT;
+  auto fetch = [&](int64_t i) {
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const int64_t j = i + k * stride < n ? i + k * stride : n - 1;
+      o[k] = dofs.doff[j];
+      o1[k] = dofs.doff[j + 1];
+      ex[k] = xm[j];
+      ep[k] = pm[j];
+      er[k] = rm[j];
+      ed[k] = dm[j];
+    }
   };
-  if (has0) step(i0, x0, p0, r0, w0, d0);
-  for (int64_t i = i0 + stride; i < n; i += stride)
-    step(i, x[off + i], p[off + i], r[off + i], w[off + i], dm[i]);
-  write_part<4>(v, part, nblk);
+  int64_t i = (int64_t)blockIdx.x * CU_NT + threadIdx.x;
+  fetch(i);
+  double pw[1];
+  reduce_parts_m<1, CU_NT>(dpart + (int64_t)m * dmstride, dcount, 0, pw);
+  PcgScalars s;
+  copy_state(s, sc[m]);
+  set_alpha(s, pw[0]);
+  if (blockIdx.x == 0 && threadIdx.x == 0) copy_state(sc_next[m], s);
+  const T alpha = (T)s.alpha, beta = (T)s.beta, zs = (T)s.zshift;
+  double v[4] = {0.0, 0.0, 0.0, 0.0};
+  for (; i < n; i += U * stride) {
+    T w[U];
+    int32_t a[U], cnt[U];
+    {
+      T val[U][8], yi[U];
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        const int64_t j = i + k * stride;
+        a[k] = o[k] & kDofMask;
+        cnt[k] = j < n ? (o1[k] & kDofMask) - a[k] : 0;
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+          val[k][q] = (q < cnt[k]) ? Ym[dofs.slot ? dofs.slot[a[k] + q] : a[k] + q] : T(0);
+        yi[k] = (j < n && (o[k] & kSoleBit)) ? ym[j] : T(0);
+      }
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        w[k] = val[k][0];
+#pragma unroll
+        for (int q = 1; q < 8; ++q)
+          if (q < cnt[k]) w[k] += val[k][q];
+        for (int q = 8; q < cnt[k]; ++q) w[k] += Ym[dofs.slot ? dofs.slot[a[k] + q] : a[k] + q];
+        if (o[k] & kSoleBit) w[k] = yi[k];
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const int64_t j = i + k * stride;
+      if (j >= n) continue;
+      const T pi = cg_dir(ed[k], er[k], zs, beta, ep[k]);
+      if (o[k] < 0) w[k] = pi;  // essential
+      const T ri = er[k] - alpha * w[k];
+      pm[j] = pi;
+      xm[j] = ex[k] + alpha * pi;
+      rm[j] = ri;
+      const T zi = ed[k] * ri;
+      v[0] += (double)ri * (double)zi;
+      v[1] += (double)ri * (double)ri;
+      v[2] += (double)zi;
+      v[3] += (double)ri;
+    }
+    if (i + U * stride < n) fetch(i + U * stride);
+  }
+  // block sums: wave totals, then the waves in order
+  __shared__ double sh[4][CU_NT / 64];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    v[k] = wave_total(v[k]);
+    if ((threadIdx.x & 63) == 0) sh[k][threadIdx.x >> 6] = v[k];
+  }
+  __syncthreads();
+  if (threadIdx.x < 4) {
+    double t = 0.0;
+    for (int w = 0; w < CU_NT / 64; ++w) t += sh[threadIdx.x][w];
+    part[((int64_t)m * 4 + threadIdx.x) * nblk + blockIdx.x] = t;
+  }
 }
 
-// New direction p = (dinv r - zshift) + beta p, with beta (and the null-space shift)
-// formed by every block from the update's partials.  Block 0 of each member also
-// writes the next iteration's scalars to sc_next (the scalars are double-buffered, so
-// no block reads a value another block of the same launch writes).
-template <typename T>
-__global__ void newdir_kernel(const T *__restrict__ r, const T *__restrict__ dinv,
-                              int64_t dinv_mstride, T *__restrict__ p,
-                              const PcgScalars *__restrict__ sc, PcgScalars *__restrict__ sc_next,
-                              const double *__restrict__ dpart, int64_t dmstride, int dcount,
-                              const double *__restrict__ upart, int unblk, int nullspace,
-                              int64_t n) {
-  const int m = blockIdx.y;
-  const int64_t off = (int64_t)m * n;
-  const T *dm = dinv + (int64_t)m * dinv_mstride;
-  // the operands of the first entry are requested before the partial sums are read
-  const int64_t i0 = (int64_t)blockIdx.x * VB + threadIdx.x, stride = (int64_t)gridDim.x * VB;
-  const bool has0 = i0 < n;
-  const int64_t j0 = has0 ? i0 : 0;
-  const T r0 = r[off + j0], d0 = dm[j0], p0 = p[off + j0];
-  double pw[1], u[4];
-  reduce_parts_m<1, VB>(dpart + (int64_t)m * dmstride, dcount, 0, pw);
-  reduce_parts_m<4, VB>(upart, unblk, m, u);
-  PcgScalars s = sc[m];
-  set_alpha(s, pw[0]);
-  const double zs = nullspace ? u[2] / (double)n : 0.0;
-  if (s.active) s.zshift = zs;
-  set_beta(s, u[0] - zs * u[3], u[1]);
-  if (blockIdx.x == 0 && threadIdx.x == 0) sc_next[m] = s;
-  const T beta = (T)s.beta;
-  const T zst = (T)s.zshift;
-  if (has0) p[off + i0] = (d0 * r0 - zst) + beta * p0;
-  for (int64_t i = i0 + stride; i < n; i += stride)
-    p[off + i] = (dm[i] * r[off + i] - zst) + beta * p[off + i];
+// The state of the next iteration from the update's partials (a block per member), where the
+// host reads it before the next element kernel runs.
+__global__ void __launch_bounds__(256)
+cg_finish_kernel(PcgScalars *__restrict__ sc, const double *__restrict__ part, int nblk, int nullspace,
+                 int64_t n) {
+  const int m = blockIdx.x;
+  __shared__ double sums[4][4];
+  PcgScalars s;
+  copy_state(s, sc[m]);
+  const double *p = part + (int64_t)m * 4 * nblk;
+  PartLoads<4, 4> up;
+  up.load(p, nblk);
+  up.parts(sums, nblk);
+  __syncthreads();
+  cg_next_from<4>(s, sums, nullspace, n);
+  if (threadIdx.x == 0) copy_state(sc[m], s);
 }
 
 // ---- CG steps around a preconditioner applied between the launches (z given), one member:
@@ -337,15 +359,6 @@ __global__ void __launch_bounds__(RB) init_scalars_kernel(const double *__restri
     s.status = finite ? 0 : SFEM_E_NAN;
     s.active = (finite && v[2] > 0.0 && v[1] > s.tol2) ? 1 : 0;
   }
-}
-
-// v[m][i] -= sc[m].zshift
-template <typename T>
-__global__ void zshift_kernel(T *__restrict__ v, const PcgScalars *__restrict__ sc, int64_t n) {
-  const int m = blockIdx.y;
-  const T zs = (T)sc[m].zshift;
-  for (int64_t i = (int64_t)blockIdx.x * VB + threadIdx.x; i < n; i += (int64_t)gridDim.x * VB)
-    v[(int64_t)m * n + i] -= zs;
 }
 
 // v[m][i] -= c[m] * scale
@@ -535,22 +548,12 @@ hipError_t VecOps<T>::dot(const T *a, const T *c, int64_t c_mstride, double *par
 }
 
 template <typename T>
-hipError_t VecOps<T>::update(T *x, const T *p, T *r, const T *w, const T *dinv, int64_t dms,
-                             const PcgScalars *sc, const double *dpart, int64_t dmstride,
-                             int dcount, double *part, int nblk, int64_t n, int nb,
-                             hipStream_t s) {
-  hipLaunchKernelGGL((update_kernel<T>), dim3(nblk, nb), dim3(VB), 0, s, x, p, r, w, dinv, dms, sc,
-                     dpart, dmstride, dcount, part, nblk, n);
-  return hipGetLastError();
-}
-
-template <typename T>
-hipError_t VecOps<T>::newdir(const T *r, const T *dinv, int64_t dms, T *p, const PcgScalars *sc,
-                             PcgScalars *sc_next, const double *dpart, int64_t dmstride,
-                             int dcount, const double *upart, int unblk, int nullspace, int64_t n,
-                             int nb, hipStream_t s) {
-  hipLaunchKernelGGL((newdir_kernel<T>), dim3(vec_nblk(n), nb), dim3(VB), 0, s, r, dinv, dms, p, sc,
-                     sc_next, dpart, dmstride, dcount, upart, unblk, nullspace, n);
+hipError_t VecOps<T>::update(const CgDofs &dofs, const T *evec, int64_t estride, const T *y, T *x, T *p, T *r,
+                             const T *dinv, int64_t dms, const PcgScalars *sc, PcgScalars *sc_next,
+                             const double *dpart, int64_t dmstride, int dcount, double *part, int nblk,
+                             int64_t n, int nb, hipStream_t s) {
+  hipLaunchKernelGGL((cg_update_kernel<T>), dim3(nblk, nb), dim3(CU_NT), 0, s, dofs, evec, estride, y, x, p,
+                     r, dinv, dms, sc, sc_next, dpart, dmstride, dcount, part, nblk, n);
   return hipGetLastError();
 }
 
@@ -649,14 +652,18 @@ hipError_t launch_pcg_init(const double *part, int nblk, int nb, double rtol, Pc
   return hipGetLastError();
 }
 
-template <typename T>
-hipError_t launch_zshift(T *v, const PcgScalars *sc, int64_t n, int nb, hipStream_t s) {
-  if (n <= 0 || nb <= 0) return hipSuccess;
-  hipLaunchKernelGGL((zshift_kernel<T>), dim3(grid_for(n), nb), dim3(VB), 0, s, v, sc, n);
+int cg_update_nblk(int64_t n) {
+  int64_t b = (n + CU_NT - 1) / CU_NT;
+  if (b < 1) b = 1;
+  if (b > CU_MAXB) b = CU_MAXB;
+  return (int)b;
+}
+
+hipError_t launch_cg_finish(PcgScalars *sc, const double *part, int nblk, int nb, int nullspace, int64_t n,
+                            hipStream_t s) {
+  hipLaunchKernelGGL(cg_finish_kernel, dim3(nb), dim3(256), 0, s, sc, part, nblk, nullspace, n);
   return hipGetLastError();
 }
-template hipError_t launch_zshift<double>(double *, const PcgScalars *, int64_t, int, hipStream_t);
-template hipError_t launch_zshift<float>(float *, const PcgScalars *, int64_t, int, hipStream_t);
 
 hipError_t launch_shift(double *v, const double *c, double scale, int64_t n, int nb, hipStream_t s) {
   if (n <= 0 || nb <= 0) return hipSuccess;

@@ -16,6 +16,9 @@ namespace sfem {
 //   bit 31      essential DoF (entry is negative)
 constexpr int32_t kDofMask = 0x3fffffff;
 constexpr int32_t kSoleBit = 0x40000000;
+// In the uploaded map, bit 30 of an essential entry marks one element node per essential DoF
+// (the first): the node that stands for the DoF in a sum over elements.
+constexpr int32_t kEssOwnerBit = 0x40000000;
 
 // E-vector layout used for order p (see HostPlan): DoF-ordered up to p = 4, where the
 // assembly kernel's share of the apply is largest; element-ordered above, where the
