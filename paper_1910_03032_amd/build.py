@@ -26,6 +26,7 @@ SOURCES = [
     "k_apply_f32.hip",
     "k_apply_cg64.hip",
     "k_apply_cg32.hip",
+    "k_apply_cgz.hip",
     "k_diag.hip",
     "k_grad_load.hip",
     "k_setup.hip",

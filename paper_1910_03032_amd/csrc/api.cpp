@@ -123,8 +123,8 @@ struct sfem_ctx {
   std::vector<uint8_t> h_ess;
   bool lor_ok[3] = {false, false, false};
   Amg lor[3];
-  double *lor_work = nullptr;      // [5][ndof] vectors of the LOR-preconditioned CG
-  double *lor_scal = nullptr;      // device scalars: [kLorScalarSlots] doubles, then 2 PcgScalars
+  double *lor_work = nullptr;      // [4][ndof] vectors of the LOR-preconditioned CG
+  double *lor_scal = nullptr;      // device scalars: 2 PcgScalars
   float *lor_work32 = nullptr;     // [2][ndof] FP32 residual and V-cycle output
 
   // ---- E-vector of the apply and solver workspace (grown on demand)
@@ -347,7 +347,7 @@ sfem_status ensure_diag(sfem_ctx *c, int op) {
     da.compact = c->compact;
     HIPCHK(c, launch_diag(da, c->stream));
     HIPCHK(c, launch_assemble<double>(c->plan, (const double *)c->evec.p, 0, nullptr, da.diag, c->ndof,
-                                      1, kEssOne, nullptr, 0, c->stream));
+                                      1, kEssOne, c->stream));
   }
   HIPCHK(c, VecOps<double>::recip(c->d_diag[op], c->d_dinv[op], n, c->stream));
   HIPCHK(c, VecOps<float>::recip(c->d_diag[op], c->d_dinv32[op], n, c->stream));
@@ -369,8 +369,7 @@ sfem_status ensure_cmass(sfem_ctx *c) {
   if ((st = ensure_evec(c, (size_t)c->nentries * sizeof(double))) != SFEM_OK) return st;
   HIPCHK(c, launch_colloc_mass(c->p, c->rules.gll_x.data(), c->rules.gll_w.data(), c->d_xyz, c->d_map,
                                c->d_pos, c->compact, c->nelem, cm, (double *)c->evec.p, c->stream));
-  HIPCHK(c, launch_assemble<double>(c->plan, (const double *)c->evec.p, 0, nullptr, cm, n, 1, kEssOne,
-                                    nullptr, 0, c->stream));
+  HIPCHK(c, launch_assemble<double>(c->plan, (const double *)c->evec.p, 0, nullptr, cm, n, 1, kEssOne, c->stream));
   HIPCHK(c, VecOps<double>::recip(cm, cminv, n, c->stream));
   HIPCHK(c, VecOps<float>::recip(cm, cminv32, n, c->stream));
   c->d_cm = cm;
@@ -413,27 +412,15 @@ sfem_status check_op_batch(sfem_ctx *c, int op, int nbatch) {
   return SFEM_OK;
 }
 
-// Per-block dot partials of one apply of nb members, per member: the element kernel's
-// blocks (one per group of (element, member) pairs), then the assembly's (which fold the
-// element partials in, so that the apply's sum is the sum of the assembly partials alone
-// when there is an assembly phase).
-int apply_nparts_elem(const sfem_ctx *c, bool f32, int nb) {
+// Partials of p.Ap per member that the element kernel of a CG iteration of nb members leaves:
+// one per workgroup (a group of (element, member) pairs).
+int cg_nparts(const sfem_ctx *c, bool f32, int nb) {
   const int e = f32 ? apply_group_elems_f32(c->p) : apply_group_elems_f64(c->p);
   return (int)((c->nelem * nb + e - 1) / e);
 }
-int apply_nparts(const sfem_ctx *c, bool f32, int nb) {
-  return apply_nparts_elem(c, f32, nb) + (c->na > 0 ? assemble_nblk_dot(c->na) : 0);
-}
-// Offset and count of the partials that sum to the apply's x . y.
-int apply_final_off(const sfem_ctx *c, bool f32, int nb) {
-  return c->na > 0 ? apply_nparts_elem(c, f32, nb) : 0;
-}
-int apply_final_count(const sfem_ctx *c, bool f32, int nb) {
-  return c->na > 0 ? assemble_nblk_dot(c->na) : apply_nparts_elem(c, f32, nb);
-}
 
-// Enqueue y = A x on the context stream (no argument checks).  With part != null the
-// two launches also leave the per-block partial sums of x . y in part[m][0..nparts).
+// Enqueue y = A x on the context stream (no argument checks).  With cg: the first launch of a CG
+// iteration, which leaves its partials of p.Ap in part[m][0..cg_nparts).
 // evec: E-vector storage of at least nbatch * nentries values given by the caller, or
 // null for the context's own (grown on demand).
 sfem_status do_apply(sfem_ctx *c, int op, bool f32, int nbatch, const void *x, void *y,
@@ -446,8 +433,6 @@ sfem_status do_apply(sfem_ctx *c, int op, bool f32, int nbatch, const void *x, v
     if ((st = ensure_evec(c, (size_t)estride * nbatch * esz)) != SFEM_OK) return st;
     evec = c->evec.p;
   }
-  const int nblk_e = apply_nparts_elem(c, f32, nbatch);
-  const int nparts = cg ? nblk_e : apply_nparts(c, f32, nbatch);
   ApplyArgs a;
   a.p = c->p;
   a.op = op;
@@ -462,25 +447,24 @@ sfem_status do_apply(sfem_ctx *c, int op, bool f32, int nbatch, const void *x, v
   a.pos = c->d_pos;
   a.compact = c->compact;
   a.part = part;
-  a.part_mstride = nparts;
+  a.part_mstride = cg ? cg_nparts(c, f32, nbatch) : 0;
   a.geo = c->d_geo;
   a.cw = op != SFEM_MASS ? c->d_cw : nullptr;
   a.cw_mstride = c->nfield > 1 ? c->nelem * q3_of(c) : 0;
   a.alpha = op == SFEM_HELMHOLTZ ? c->alpha : (op == SFEM_MASS ? 1.0 : 0.0);
   a.beta = op == SFEM_HELMHOLTZ ? c->beta : (op == SFEM_MASS ? 0.0 : 1.0);
   hipError_t e;
-  if (cg) e = f32 ? launch_apply_cg32(a, *cg, c->stream) : launch_apply_cg64(a, *cg, c->stream);
+  if (cg) e = cg->z ? launch_apply_cgz(a, *cg, c->stream)
+                    : (f32 ? launch_apply_cg32(a, *cg, c->stream) : launch_apply_cg64(a, *cg, c->stream));
   else e = f32 ? launch_apply_f32(a, c->stream) : launch_apply_f64(a, c->stream);
   if (e != hipSuccess) return fail(c, SFEM_E_HIP, std::string("apply launch: ") + hipGetErrorString(e));
   if (cg || !assemble) return SFEM_OK;
-  double *pa = part ? part + nblk_e : nullptr;
   if (f32)
     e = launch_assemble<float>(c->plan, (const float *)evec, estride, (const float *)x, (float *)y,
-                               c->ndof, nbatch, kEssCopyX, pa, nparts, c->stream, part, nblk_e);
+                               c->ndof, nbatch, kEssCopyX, c->stream);
   else
     e = launch_assemble<double>(c->plan, (const double *)evec, estride, (const double *)x,
-                                (double *)y, c->ndof, nbatch, kEssCopyX, pa, nparts, c->stream, part,
-                                nblk_e);
+                                (double *)y, c->ndof, nbatch, kEssCopyX, c->stream);
   if (e != hipSuccess) return fail(c, SFEM_E_HIP, std::string("assembly launch: ") + hipGetErrorString(e));
   return SFEM_OK;
 }
@@ -539,7 +523,7 @@ template <typename T>
 size_t pcg_work_bytes(const sfem_ctx *c, int64_t n, int nb) {
   const int nblk = vec_nblk(n);
   return 3 * align_up((size_t)n * nb * sizeof(T)) + align_up((size_t)nb * 5 * nblk * sizeof(double)) +
-         align_up((size_t)nb * apply_nparts(c, sizeof(T) == 4, nb) * sizeof(double)) +
+         align_up((size_t)nb * cg_nparts(c, sizeof(T) == 4, nb) * sizeof(double)) +
          align_up((size_t)2 * nb * sizeof(PcgScalars));
 }
 
@@ -547,7 +531,7 @@ template <typename T>
 PcgWork<T> carve_pcg(const sfem_ctx *c, Carver &cv, int64_t n, int nb) {
   PcgWork<T> w;
   w.nblk = vec_nblk(n);
-  w.nparts = apply_nparts(c, sizeof(T) == 4, nb);
+  w.nparts = cg_nparts(c, sizeof(T) == 4, nb);
   w.r = cv.take<T>(n * nb);
   w.p = cv.take<T>(n * nb);
   w.w = cv.take<T>(n * nb);
@@ -557,8 +541,8 @@ PcgWork<T> carve_pcg(const sfem_ctx *c, Carver &cv, int64_t n, int nb) {
   return w;
 }
 
-// Jacobi-PCG on the context stream, two launches per iteration (pcg.h).  On return hs[] holds
-// the final scalars.
+// Jacobi-PCG on the context stream, two launches per iteration (pcg.h).  On return hs[] (pinned
+// host memory) holds the final scalars.
 template <typename T>
 sfem_status run_pcg(sfem_ctx *c, int op, int nb, const T *b, T *x, bool x0_zero, double rtol,
                     int maxit, int check_every, const T *dinv, int64_t dms, PcgWork<T> &w,
@@ -574,12 +558,8 @@ sfem_status run_pcg(sfem_ctx *c, int op, int nb, const T *b, T *x, bool x0_zero,
     HIPCHK(c, VecOps<T>::start(b, w.w, nullptr, w.r, dinv, dms, w.p, w.part, w.nblk, n, nb, s));
   }
   HIPCHK(c, launch_pcg_init(w.part, w.nblk, nb, rtol, w.sc, s, nullspace, n));
-  auto all_done = [&]() -> sfem_status {
-    HIPCHK(c, hipMemcpyAsync(hs, w.sc, sizeof(PcgScalars) * nb, hipMemcpyDeviceToHost, s));
-    HIPCHK(c, hipStreamSynchronize(s));
-    return SFEM_OK;
-  };
-  if ((st = all_done()) != SFEM_OK) return st;
+  HIPCHK(c, hipMemcpyAsync(hs, w.sc, sizeof(PcgScalars) * nb, hipMemcpyDeviceToHost, s));
+  HIPCHK(c, hipStreamSynchronize(s));
   for (int m = 0; m < nb; ++m)  // b = 0: the solution is x = 0
     if (hs[m].bb == 0.0 && !x0_zero) HIPCHK(c, VecOps<T>::fill(x + (int64_t)m * n, T(0), n, s));
   auto any_active = [&]() {
@@ -588,7 +568,7 @@ sfem_status run_pcg(sfem_ctx *c, int op, int nb, const T *b, T *x, bool x0_zero,
     return false;
   };
   if (!any_active()) return SFEM_OK;
-  const int nelem_parts = apply_nparts_elem(c, f32, nb), unblk = cg_update_nblk(n);
+  const int nelem_parts = cg_nparts(c, f32, nb), unblk = cg_update_nblk(n);
   const CgDofs dofs{c->d_doff, c->d_slot};
   CgIn g{};
   g.r = w.r;
@@ -607,9 +587,9 @@ sfem_status run_pcg(sfem_ctx *c, int op, int nb, const T *b, T *x, bool x0_zero,
                                 w.sc, w.dpart, nelem_parts, nelem_parts, w.part, unblk, n, nb, s));
     g.ready = 0;
     if ((it + 1) % check_every == 0 || it + 1 == maxit) {
-      HIPCHK(c, launch_cg_finish(w.sc, w.part, unblk, nb, nullspace, n, s));
+      HIPCHK(c, launch_cg_finish(w.sc, hs, w.part, unblk, nb, nullspace, n, s));
       g.ready = 1;
-      if ((st = all_done()) != SFEM_OK) return st;
+      HIPCHK(c, hipStreamSynchronize(s));
       if (!any_active()) break;
     }
   }
@@ -623,8 +603,6 @@ constexpr double kLorTheta = 0.02;
 constexpr int64_t kLorCoarse = 200;
 constexpr int kLorMaxLevels = 12;
 constexpr int kLorSweeps = 1;
-// device scalar doubles of the LOR solves ahead of the CG scalars (the null-space mean)
-constexpr int64_t kLorScalarSlots = 8;
 static_assert(sizeof(PcgScalars) % sizeof(double) == 0, "PcgScalars packs into doubles");
 
 // Build (once per operator kind and coefficients) A_LOR of op and its multigrid hierarchy.
@@ -665,8 +643,8 @@ sfem_status ensure_lor_f64(sfem_ctx *c, int op) {
   }
   if (!c->lor_work) {
     sfem_status st;
-    if ((st = dalloc(c, &c->lor_work, 5 * c->ndof)) != SFEM_OK) return st;
-    if ((st = dalloc(c, &c->lor_scal, kLorScalarSlots + 2 * (int64_t)(sizeof(PcgScalars) / sizeof(double)))) != SFEM_OK) return st;
+    if ((st = dalloc(c, &c->lor_work, 4 * c->ndof)) != SFEM_OK) return st;
+    if ((st = dalloc(c, &c->lor_scal, 2 * (int64_t)(sizeof(PcgScalars) / sizeof(double)))) != SFEM_OK) return st;
   }
   c->lor_ok[op] = true;
   return SFEM_OK;
@@ -694,37 +672,29 @@ hipError_t lor_vcycle(sfem_ctx *c, int op, bool f32, const double *r, double *z)
   return launch_convert<float, double>(z32, z, n, c->stream);
 }
 
-sfem_status lor_precond(sfem_ctx *c, int op, bool f32, const double *r, double *z, int nullspace,
-                        double *part) {
-  HIPCHK(c, lor_vcycle(c, op, f32, r, z));
-  if (nullspace) {
-    const int64_t n = c->ndof;
-    const int nblk = vec_nblk(n);
-    HIPCHK(c, VecOps<double>::dot(z, nullptr, 0, part, nblk, n, 1, c->stream));
-    HIPCHK(c, launch_reduce1(part, nblk, 1, c->lor_scal, c->stream));
-    HIPCHK(c, launch_shift(z, c->lor_scal, 1.0 / (double)n, n, 1, c->stream));
-  }
-  return SFEM_OK;
-}
-
-// CG for one member preconditioned by the LOR multigrid V-cycle.  The scalars stay on the
-// device (step length, direction and stopping test formed by the kernels from partial
-// sums); after each iteration they are copied to pinned host memory behind an event, and
-// the host reads the previous iteration's copy once the next iteration is queued, so the
-// GPU never waits for the host.  When that copy shows the solve stopped, the iteration
-// queued after it changes nothing (alpha = 0 once inactive).  dpart: the apply's partials;
-// part: [5][vec_nblk(n)] partials.  On return hs holds the final scalars.
-sfem_status run_pcg_lor(sfem_ctx *c, int op, bool f32, const double *b, double *x, bool x0_zero,
-                        double rtol, int maxit, int nullspace, double *dpart, double *part,
-                        PcgScalars &hs) {
+// CG for one member preconditioned by the LOR multigrid V-cycle, the scalars on the device
+// (pcg.h).  The element kernel writes the state it completes to pinned host memory; the host
+// waits for it behind an event with the rest of the iteration already queued, so the GPU never
+// waits for the host.  When the state shows that the solve stopped, that iteration changes
+// nothing (alpha = 0 once inactive).  dpart: the element kernel's partials; part: those of the
+// dots ([5][vec_nblk(n)]).  On return hs holds the final scalars.
+template <typename TZ>
+sfem_status run_pcg_lor_z(sfem_ctx *c, int op, const double *b, double *x, bool x0_zero, double rtol, int maxit,
+                          int nullspace, double *dpart, double *part, TZ *z, PcgScalars &hs) {
+  constexpr bool f32 = sizeof(TZ) == 4;
   const int64_t n = c->ndof;
   hipStream_t s = c->stream;
-  double *r = c->lor_work, *z = r + n, *pv = z + n, *w = pv + n;
-  PcgScalars *sc = reinterpret_cast<PcgScalars *>(c->lor_scal + kLorScalarSlots);  // [2]
-  PcgScalars *h = reinterpret_cast<PcgScalars *>(c->h_pinned);                       // [2]
-  const int nblk = vec_nblk(n);
+  const Amg &amg = c->lor[op];
+  double *r = c->lor_work, *pv = r + 2 * n, *w = pv + n;
+  float *r32 = f32 ? c->lor_work32 : nullptr;
+  PcgScalars *sc = reinterpret_cast<PcgScalars *>(c->lor_scal);  // [2]
+  PcgScalars *h = reinterpret_cast<PcgScalars *>(c->h_pinned);   // [2]
+  const int unblk = cg_update_nblk(n);
   sfem_status st;
   hs = PcgScalars{};
+  const TZ *bz;  // the V-cycle's input
+  if constexpr (f32) bz = r32;
+  else bz = r;
   if (x0_zero) {
     HIPCHK(c, VecOps<double>::fill(x, 0.0, n, s));
     HIPCHK(c, hipMemcpyAsync(r, b, (size_t)n * sizeof(double), hipMemcpyDeviceToDevice, s));
@@ -732,10 +702,11 @@ sfem_status run_pcg_lor(sfem_ctx *c, int op, bool f32, const double *b, double *
     if ((st = do_apply(c, op, false, 1, x, w)) != SFEM_OK) return st;
     HIPCHK(c, launch_axpby(n, 1.0, b, -1.0, w, r, s));  // r = b - A x
   }
-  if ((st = lor_precond(c, op, f32, r, z, nullspace, part)) != SFEM_OK) return st;
-  HIPCHK(c, hipMemcpyAsync(pv, z, (size_t)n * sizeof(double), hipMemcpyDeviceToDevice, s));
-  HIPCHK(c, launch_gpcg_dots<double>(r, z, b, 0, part, nblk, n, s));
-  HIPCHK(c, launch_pcg_init(part, nblk, 1, rtol, sc, s));
+  if (f32) HIPCHK(c, (launch_convert<double, float>(r, r32, n, s)));
+  HIPCHK(c, amg_vcycle<TZ>(amg, bz, z, s));
+  HIPCHK(c, VecOps<double>::fill(pv, 0.0, n, s));
+  HIPCHK(c, launch_cgz_dots<TZ>(r, z, b, part, unblk, n, s));
+  HIPCHK(c, launch_pcg_init(part, unblk, 1, rtol, sc, s, nullspace, n));
   HIPCHK(c, hipMemcpyAsync(h, sc, sizeof(PcgScalars), hipMemcpyDeviceToHost, s));
   HIPCHK(c, hipStreamSynchronize(s));
   hs = h[0];
@@ -743,52 +714,58 @@ sfem_status run_pcg_lor(sfem_ctx *c, int op, bool f32, const double *b, double *
     HIPCHK(c, VecOps<double>::fill(x, 0.0, n, s));
     return SFEM_OK;
   }
-  if (!hs.active) return SFEM_OK;
-  const double *dp = dpart + apply_final_off(c, false, 1);
-  const int dcount = apply_final_count(c, false, 1);
-  hipEvent_t ev[2] = {nullptr, nullptr};
-  for (hipEvent_t &e : ev)
-    if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
-      (void)hipGetLastError();
-      for (hipEvent_t &d : ev)
-        if (d) (void)hipEventDestroy(d);
-      return fail(c, SFEM_E_HIP, "LOR CG: event creation failed");
-    }
-  // in the loop the V-cycle's FP32 input comes from the update and its output is read by
-  // the dots and the new direction as it is; the null-space shift is folded into those
-  float *r32 = f32 ? c->lor_work32 : nullptr, *z32 = f32 ? c->lor_work32 + n : nullptr;
+  if (!hs.active || maxit <= 0) return SFEM_OK;
+  hipEvent_t ev = nullptr;
+  if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) {
+    (void)hipGetLastError();
+    return fail(c, SFEM_E_HIP, "LOR CG: event creation failed");
+  }
+  const int nparts = cg_nparts(c, false, 1);
+  const CgDofs dofs{c->d_doff, c->d_slot};
+  const FirstSweep<TZ> fs = amg_first_sweep<TZ>(amg);
+  CgIn g{};
+  g.p = pv;
+  g.z = z;
+  g.z32 = f32 ? 1 : 0;
+  g.sc = sc;
+  g.sc_next = sc + 1;
+  g.upart = part;
+  g.unblk = unblk;
+  g.ready = 1;
+  g.nullspace = nullspace;
   auto body = [&]() -> sfem_status {
-    int cur = 0, last = -1;
     for (int it = 0; it < maxit; ++it) {
-      if ((st = do_apply(c, op, false, 1, pv, w, dpart)) != SFEM_OK) return st;
-      HIPCHK(c, launch_gpcg_update(x, pv, r, w, r32, sc + cur, dp, dcount, n, s));
-      if (f32) {
-        HIPCHK(c, amg_vcycle<float>(c->lor[op], r32, z32, s));
-        HIPCHK(c, launch_gpcg_dots<float>(r, z32, nullptr, nullspace, part, nblk, n, s));
-        HIPCHK(c, launch_gpcg_newdir<float>(z32, pv, sc + cur, sc + 1 - cur, dp, dcount, part, nblk, nullspace,
-                                            n, s));
-      } else {
-        HIPCHK(c, amg_vcycle<double>(c->lor[op], r, z, s));
-        HIPCHK(c, launch_gpcg_dots<double>(r, z, nullptr, nullspace, part, nblk, n, s));
-        HIPCHK(c, launch_gpcg_newdir<double>(z, pv, sc + cur, sc + 1 - cur, dp, dcount, part, nblk, nullspace,
-                                             n, s));
-      }
-      cur = 1 - cur;
-      HIPCHK(c, hipMemcpyAsync(h + (it & 1), sc + cur, sizeof(PcgScalars), hipMemcpyDeviceToHost, s));
-      HIPCHK(c, hipEventRecord(ev[it & 1], s));
-      last = it;
-      if (it > 0) {
-        HIPCHK(c, hipEventSynchronize(ev[(it - 1) & 1]));
-        if (!h[(it - 1) & 1].active) break;
+      g.host = h + (it & 1);
+      if ((st = do_apply(c, op, false, 1, nullptr, w, dpart, nullptr, false, &g)) != SFEM_OK) return st;
+      HIPCHK(c, hipEventRecord(ev, s));
+      g.ready = 0;
+      HIPCHK(c, launch_cgz_update<TZ>(dofs, (const double *)c->evec.p, w, x, pv, r, z, r32, fs.t, fs.dinv, fs.omega,
+                                      sc + 1, sc, dpart, nparts, n, s));
+      HIPCHK(c, amg_vcycle<TZ>(amg, bz, z, s, fs.t != nullptr));
+      HIPCHK(c, launch_cgz_dots<TZ>(r, z, nullptr, part, unblk, n, s));
+      HIPCHK(c, hipEventSynchronize(ev));
+      if (!h[it & 1].active) {
+        hs = h[it & 1];
+        return SFEM_OK;
       }
     }
-    HIPCHK(c, hipEventSynchronize(ev[last & 1]));
-    hs = h[last & 1];
+    HIPCHK(c, launch_cg_finish(sc, h, part, unblk, 1, nullspace, n, s));
+    HIPCHK(c, hipStreamSynchronize(s));
+    hs = h[0];
     return SFEM_OK;
   };
   st = body();
-  for (hipEvent_t &e : ev) (void)hipEventDestroy(e);
+  (void)hipEventDestroy(ev);
   return st;
+}
+
+sfem_status run_pcg_lor(sfem_ctx *c, int op, bool f32, const double *b, double *x, bool x0_zero,
+                        double rtol, int maxit, int nullspace, double *dpart, double *part,
+                        PcgScalars &hs) {
+  if (f32)
+    return run_pcg_lor_z<float>(c, op, b, x, x0_zero, rtol, maxit, nullspace, dpart, part,
+                                c->lor_work32 + c->ndof, hs);
+  return run_pcg_lor_z<double>(c, op, b, x, x0_zero, rtol, maxit, nullspace, dpart, part, c->lor_work + c->ndof, hs);
 }
 
 sfem_status require_ready(sfem_ctx *c) {
@@ -948,7 +925,6 @@ static sfem_status sfem_setup_body(sfem_ctx *c, int p, int q, int64_t nelem, con
 
   // ---- upload + geometric factors
   sfem_status st;
-  const int64_t q3 = (int64_t)q * q * q;
   if ((st = dalloc(c, &c->d_map, nelem * n3)) != SFEM_OK) return st;
   if ((st = dalloc(c, &c->d_xyz, nelem * 24)) != SFEM_OK) return st;
   if ((st = dalloc(c, &c->d_geo, nelem * kGeoStride)) != SFEM_OK) return st;
@@ -1166,7 +1142,7 @@ sfem_status sfem_load(sfem_ctx *c, int nbatch, const double *f_q, double *b) {
   a.compact = c->compact;
   HIPCHK(c, launch_load(a, c->stream));
   HIPCHK(c, launch_assemble<double>(c->plan, (const double *)c->evec.p, estride, nullptr, b, c->ndof,
-                                    nbatch, kEssZero, nullptr, 0, c->stream));
+                                    nbatch, kEssZero, c->stream));
   return SFEM_OK;
 }
 
@@ -1529,9 +1505,8 @@ sfem_status sfem_stokes_apply(sfem_ctx *c, const double *u, const double *pres, 
   a.yp = yp;
   HIPCHK(c, launch_stokes(a, c->stream));
   HIPCHK(c, launch_assemble<double>(c->plan, (const double *)c->evec.p, c->nentries, one_asm ? u : nullptr,
-                                    yu, nv, 3, one_asm ? kEssCopyX : kEssAdd, nullptr, 0, c->stream));
-  HIPCHK(c, launch_assemble<double>(c->pplan, Yp, 0, nullptr, yp, np, 1, kEssZero, nullptr, 0,
-                                    c->stream));
+                                    yu, nv, 3, one_asm ? kEssCopyX : kEssAdd, c->stream));
+  HIPCHK(c, launch_assemble<double>(c->pplan, Yp, 0, nullptr, yp, np, 1, kEssZero, c->stream));
   return SFEM_OK;
 }
 
@@ -1558,7 +1533,7 @@ sfem_status sfem_convection(sfem_ctx *c, const double *u, double *y) {
   a.yv = y;
   HIPCHK(c, launch_convection(a, c->stream));
   HIPCHK(c, launch_assemble<double>(c->plan, (const double *)c->evec.p, c->nentries, nullptr, y, nv, 3,
-                                    kEssZero, nullptr, 0, c->stream));
+                                    kEssZero, c->stream));
   return SFEM_OK;
 }
 
@@ -1590,7 +1565,7 @@ sfem_status sfem_weak_op(sfem_ctx *c, int kind, const double *x, double *y) {
   HIPCHK(c, launch_convection(a, c->stream));
   const int nout = kind == SFEM_WEAK_DIVERGENCE ? 1 : 3;
   HIPCHK(c, launch_assemble<double>(c->plan, (const double *)c->evec.p, c->nentries, nullptr, y, nv,
-                                    nout, kEssZero, nullptr, 0, c->stream));
+                                    nout, kEssZero, c->stream));
   return SFEM_OK;
 }
 

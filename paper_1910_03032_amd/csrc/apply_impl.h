@@ -212,31 +212,20 @@ __device__ __forceinline__ void gather_e(T *buf, int t, bool active, const Nodes
 }
 
 // Output of the element vector buf[l]: sole DoFs -> y, shared nodes -> their E-vector
-// entry, essential -> nothing.  The destinations come from LDS, kept by the gather.  With
-// DOT, returns this thread's part of sum x_g y_g over the sole DoFs (x read again from xm).
-template <int P, typename T, bool DOT>
-__device__ __forceinline__ double emit_e(const T *buf, int t, bool active, const int32_t *smap,
-                                         const T *__restrict__ xm, T *__restrict__ Y,
-                                         T *__restrict__ y) {
+// entry, essential -> nothing.  The destinations come from LDS, kept by the gather.
+template <int P, typename T>
+__device__ __forceinline__ void emit_e(const T *buf, int t, bool active, const int32_t *smap,
+                                       T *__restrict__ Y, T *__restrict__ y) {
   using D = Dims<P>;
   constexpr int NL = Per<P>::NL;
-  double dot = 0.0;
 #pragma unroll
   for (int k = 0; k < NL; ++k) {
     const int l = Nodes<P>::node(t, k);
     const int32_t c = smap[l];
     const T v = buf[l];
     // one predicated store per node: the destination is selected, not branched to
-    const bool ok = active && t + k * D::TPE < D::N3 && c >= 0;
-    const bool sole = (c & kSoleBit) != 0;
-    const int32_t g = c & kDofMask;
-    if (ok) (sole ? y : Y)[g] = v;
-    if constexpr (DOT) {
-      const T xv = xm[sole ? g : 0];  // in range for every entry
-      if (ok && sole) dot += (double)xv * (double)v;
-    }
+    if (active && t + k * D::TPE < D::N3 && c >= 0) ((c & kSoleBit) ? y : Y)[c & kDofMask] = v;
   }
-  return dot;
 }
 
 // Deterministic sum over a block of THREADS threads, result on thread 0 (sh: THREADS / 64 + 1
@@ -450,9 +439,7 @@ struct ApplyCfg {
 };
 
 // OP: 0 mass, 1 diffusion, 2 helmholtz (matches sfem_op).  Writes y at the sole DoFs
-// and the E-vector Y[m] at the shared nodes; with part != null also the per-block sums
-// of x_g y_g over the sole DoFs (part[m * part_mstride + block], 0 for a member with no
-// element in the block).
+// and the E-vector Y[m] at the shared nodes.
 //
 // The geometric factors are formed from the element's trilinear coefficients (geom.h) along
 // each thread's xi_3 line; with NU the kernel reads one value per point, cw = w nu / |J|
@@ -471,10 +458,11 @@ struct ApplyCfg {
 // members of one element run side by side (in the same workgroup or in neighbouring
 // ones, on one XCD) and read the element's coefficients, which all members share unless
 // cw_mstride != 0, from the same cache lines.
-// CG: the first launch of a CG iteration (pcg.h); x is unused and part required.  The partials
+// CG = 1: the first launch of a CG iteration (pcg.h) with z = dinv r; CG = 2: with z given; x is
+// unused and part required.  The partials
 // of p.Ap are then the element energies at the quadrature points, sum v u + g . grad_ref u, plus
 // p^2 of the essential DoFs at the element that carries their flag (kEssOwnerBit).
-template <int P, typename T, int OP, bool NU, bool CG>
+template <int P, typename T, int OP, bool NU, int CG>
 __global__ void __launch_bounds__((ApplyCfg<P, T>::THREADS), (ApplyCfg<P, T>::OCC))
 apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
              const double *__restrict__ cw, int64_t cw_mstride, double alpha, double beta, int64_t nelem,
@@ -550,8 +538,19 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
     } else {
       constexpr int NL = Nodes<P>::NL;
       T zr[NL], zd[NL], zp[NL];
-      nd.load_values((const T *)cg.r + (int64_t)m * ndof, zr);
-      nd.load_values((const T *)cg.dinv + (int64_t)m * cg.dinv_mstride, zd);
+      if constexpr (CG == 1) {
+        nd.load_values((const T *)cg.r + (int64_t)m * ndof, zr);
+        nd.load_values((const T *)cg.dinv + (int64_t)m * cg.dinv_mstride, zd);
+      } else {
+        if (cg.z32) {
+#pragma unroll
+          for (int j = 0; j < NL; ++j) zr[j] = (T)((const float *)cg.z)[nd.c[j] & kDofMask];
+        } else {
+          nd.load_values((const T *)cg.z, zr);
+        }
+#pragma unroll
+        for (int j = 0; j < NL; ++j) zd[j] = T(1);
+      }
       nd.load_values((const T *)cg.p + (int64_t)m * ndof, zp);
       // the states of the workgroup's members: here distinct ones, the k-th (r0 + k) mod nbatch
       __shared__ double sums[E][4][NW];
@@ -579,7 +578,10 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
         cg_next_from<NW>(s, sums[k], cg.nullspace, ndof);
       }
       if (blockIdx.x == 0) {  // the first workgroup passes the states on (r0 = 0)
-        if (t == 0 && le < here) copy_state(cg.sc_next[m], s);
+        if (t == 0 && le < here) {
+          copy_state(cg.sc_next[m], s);
+          if (cg.host) copy_state(cg.host[m], s);
+        }
         for (int mm = here; mm < nbatch; ++mm) {
           PcgScalars o;
           copy_state(o, cg.sc[mm]);
@@ -589,7 +591,10 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
             __syncthreads();
             cg_next_from<NW>(o, sums[0], cg.nullspace, ndof);
           }
-          if (threadIdx.x == 0) copy_state(cg.sc_next[mm], o);
+          if (threadIdx.x == 0) {
+            copy_state(cg.sc_next[mm], o);
+            if (cg.host) copy_state(cg.host[mm], o);
+          }
         }
       }
       const T beta = (T)s.beta, zs = (T)s.zshift;
@@ -755,15 +760,8 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
     bwd_y<P, T, DIFF>(buf, t);
     bwd_x<P, T, DIFF>(buf, t);
     T *Ym = Y + (int64_t)m * estride, *ym = y + (int64_t)m * ndof;
-    bool sum_dot = CG;
+    emit_e<P, T>(buf, t, active, smap, Ym, ym);
     if constexpr (CG) {
-      emit_e<P, T, false>(buf, t, active, smap, xm, Ym, ym);
-    } else {
-      sum_dot = part != nullptr;
-      if (sum_dot) dot = emit_e<P, T, true>(buf, t, active, smap, xm, Ym, ym);
-      else emit_e<P, T, false>(buf, t, active, smap, xm, Ym, ym);
-    }
-    if (sum_dot) {
       // one sum per member; the block's pairs v_lo.. hold members (v_lo + k) mod nbatch,
       // k < count (a uniform test: members without a pair here get 0 without a sum)
       for (int mm = 0; mm < nbatch; ++mm) {
@@ -777,7 +775,7 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
   }
 }
 
-template <int P, typename T, bool CG>
+template <int P, typename T, int CG>
 hipError_t launch_apply_pt(const ApplyArgs &a, const CgIn &g, hipStream_t s) {
   if (a.nelem <= 0 || a.nbatch <= 0) return hipSuccess;
   if ((a.pos != nullptr) != evec_dof_ordered(P)) return hipErrorInvalidValue;

@@ -66,28 +66,32 @@ struct ApplyArgs {
   const int32_t *pos;       // DoF-ordered E-vector: [nelem][epe] entry of each element
                             // node; null: element-ordered, node r of element e -> e*epe + r
   int compact;              // nodes indexed by surface rank (1, epe = S) or local node (0)
-  double *part;             // per-block dot partials (or null)
+  double *part;             // CG: one partial of p.Ap per workgroup, [nb][part_mstride]
   int64_t part_mstride;
 };
 // Element phase of the apply over all elements (writes the E-vector).
 hipError_t launch_apply_f64(const ApplyArgs &a, hipStream_t s);
 hipError_t launch_apply_f32(const ApplyArgs &a, hipStream_t s);
-// The same as the first launch of a CG iteration (pcg.h): the direction is formed from r, dinv
-// and the old direction p (all in the apply's precision, [nb][ndof]; dinv member stride
-// dinv_mstride), a.x is unused, a.part ([nb][part_mstride], one partial of p.Ap per workgroup)
-// is required.  sc: the state after the last update; unless ready (it already holds beta) the
-// update's partials upart ([nb][4][unblk]) complete it; the completed state goes to sc_next.
+// The same as the first launch of a CG iteration (pcg.h): a.x is unused, a.part is required.  The
+// direction is formed from the preconditioned residual -- dinv r (launch_apply_cg*: r and dinv in
+// the apply's precision, [nb][ndof], dinv member stride dinv_mstride), or z given (launch_apply_cgz,
+// float64 or, with z32, float32) -- and the old direction p.  sc: the state after the last update;
+// unless ready (it already holds beta) the partials upart ([nb][4][unblk]) complete it; the
+// completed state goes to sc_next and, if given, to host (device-visible host memory).
 struct CgIn {
   const void *r, *dinv, *p;
+  const void *z;
+  int z32;
   int64_t dinv_mstride;
   const PcgScalars *sc;
-  PcgScalars *sc_next;
+  PcgScalars *sc_next, *host;
   const double *upart;
   int unblk, ready, nullspace;
 };
 hipError_t launch_apply_cg64(const ApplyArgs &a, const CgIn &g, hipStream_t s);
 hipError_t launch_apply_cg32(const ApplyArgs &a, const CgIn &g, hipStream_t s);
-// elements per workgroup of the apply kernel (one dot partial per workgroup)
+hipError_t launch_apply_cgz(const ApplyArgs &a, const CgIn &g, hipStream_t s);
+// elements per workgroup of the apply kernel (one partial of p.Ap per workgroup)
 int apply_group_elems_f64(int p);
 int apply_group_elems_f32(int p);
 // Assembly list on the device (see HostPlan): the assembled DoFs, ascending, the CSR
@@ -100,17 +104,11 @@ struct AsmPlan {
   int64_t na;
 };
 // Assembly phase over the list: y[g] = sum of g's E-vector entries in element order;
-// essential DoFs get x[g], 1 or 0 per ess_kind.  With part != null also the per-block
-// sums of x_g y_g (part[m * part_mstride + block], assemble_nblk_dot blocks), each
-// including a fixed range of the ne element-kernel partials epart[m * part_mstride + i]:
-// the partials the assembly leaves are then the whole apply's.
+// essential DoFs get x[g], 1 or 0 per ess_kind.
 constexpr int kMaxParts = 1024;  // cap of the partial-sum count of a reduction
-int assemble_nblk(int64_t na);
-int assemble_nblk_dot(int64_t na);
 template <typename T>
 hipError_t launch_assemble(const AsmPlan &pl, const T *evec, int64_t estride, const T *x, T *y,
-                           int64_t n, int nb, int ess_kind, double *part, int64_t part_mstride,
-                           hipStream_t s, const double *epart = nullptr, int ne = 0);
+                           int64_t n, int nb, int ess_kind, hipStream_t s);
 
 struct DiagArgs {
   int p;
@@ -209,30 +207,26 @@ hipError_t launch_sub_norm(const double *b, const double *w, double *r, double *
 hipError_t launch_pcg_init(const double *part, int nblk, int nb, double rtol, PcgScalars *sc,
                            hipStream_t s, int nullspace = 0, int64_t n = 0);
 int cg_update_nblk(int64_t n);
-// In place, the state of the next iteration from the update's partials.
-hipError_t launch_cg_finish(PcgScalars *sc, const double *part, int nblk, int nb, int nullspace, int64_t n,
-                            hipStream_t s);
+// The same update around a preconditioner applied between the launches (one member, z given in
+// the preconditioner's precision TZ); no partials.  TZ = float: r32 = (float) r, its input.  With
+// t also the preconditioner's first smoothing sweep, t = omega tdinv r.
+template <typename TZ>
+hipError_t launch_cgz_update(const CgDofs &dofs, const double *evec, const double *y, double *x, double *p,
+                             double *r, const TZ *z, float *r32, TZ *t, const TZ *tdinv, TZ omega,
+                             const PcgScalars *sc, PcgScalars *sc_next, const double *dpart, int dcount,
+                             int64_t n, hipStream_t s);
+// Partials of r.z, r.r, sum z, sum r ([4][nblk], nblk = cg_update_nblk); with b of r.z, r.r, b.b,
+// sum z, sum r ([5][nblk], the input of launch_pcg_init).
+template <typename TZ>
+hipError_t launch_cgz_dots(const double *r, const TZ *z, const double *b, double *part, int nblk, int64_t n,
+                           hipStream_t s);
+// In place, the state of the next iteration from the update's partials; also written to host
+// (device-visible host memory, [nb]).
+hipError_t launch_cg_finish(PcgScalars *sc, PcgScalars *host, const double *part, int nblk, int nb,
+                            int nullspace, int64_t n, hipStream_t s);
 // v[m][i] -= c[m] * scale (member-wise constant shift)
 hipError_t launch_shift(double *v, const double *c, double scale, int64_t n, int nb, hipStream_t s);
 hipError_t launch_reduce1(const double *part, int nblk, int nb, double *out, hipStream_t s);
-// CG around a preconditioner applied between the launches (one member, z given in FP64
-// or FP32):
-//   update  x += alpha p, r -= alpha w (alpha from sc and the apply's partials dpart[0..dcount));
-//           r32 != null: also r32 = (float) r
-//   dots    partials of r.z, r.r ([2][nblk]); nullspace: also sum z, sum r ([4][nblk]); with
-//           b != null of r.z, r.r, b.b, 0, 0 ([5][nblk], the input of launch_pcg_init)
-//   newdir  p = (z - zs) + beta p with zs = mean(z) when nullspace (else 0); scalars of the
-//           next iteration to sc_next
-hipError_t launch_gpcg_update(double *x, const double *p, double *r, const double *w, float *r32,
-                              const PcgScalars *sc, const double *dpart, int dcount, int64_t n,
-                              hipStream_t s);
-template <typename TZ>
-hipError_t launch_gpcg_dots(const double *r, const TZ *z, const double *b, int nullspace, double *part,
-                            int nblk, int64_t n, hipStream_t s);
-template <typename TZ>
-hipError_t launch_gpcg_newdir(const TZ *z, double *p, const PcgScalars *sc, PcgScalars *sc_next,
-                              const double *dpart, int dcount, const double *upart, int unblk,
-                              int nullspace, int64_t n, hipStream_t s);
 hipError_t launch_ir_norm(const double *part, int nblk, int nb, int set_bb, double rtol, double *ir,
                           hipStream_t s);
 hipError_t launch_ir_cast(const double *r, const double *ir, float *r32, int64_t n, int nb,

@@ -4,7 +4,7 @@
 namespace sfem {
 
 hipError_t launch_apply_cg32(const ApplyArgs &a, const CgIn &g, hipStream_t s) {
-#define SFEM_CALL(P) launch_apply_pt<P, float, true>(a, g, s)
+#define SFEM_CALL(P) launch_apply_pt<P, float, 1>(a, g, s)
   SFEM_DISPATCH_P(a.p, SFEM_CALL)
 #undef SFEM_CALL
 }

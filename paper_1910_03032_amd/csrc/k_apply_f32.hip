@@ -4,7 +4,7 @@
 namespace sfem {
 
 hipError_t launch_apply_f32(const ApplyArgs &a, hipStream_t s) {
-#define SFEM_CALL(P) launch_apply_pt<P, float, false>(a, CgIn{}, s)
+#define SFEM_CALL(P) launch_apply_pt<P, float, 0>(a, CgIn{}, s)
   SFEM_DISPATCH_P(a.p, SFEM_CALL)
 #undef SFEM_CALL
 }

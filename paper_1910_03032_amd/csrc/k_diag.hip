@@ -139,7 +139,7 @@ diag_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
     for (int i = 0; i < N; ++i) s1[t * N + i] = acc[i];
   }
   __syncthreads();
-  emit_e<P, double, false>(s1, t, active, smap, (const double *)nullptr, Y, diag);
+  emit_e<P, double>(s1, t, active, smap, Y, diag);
 }
 
 template <int P>

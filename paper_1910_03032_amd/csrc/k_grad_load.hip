@@ -205,7 +205,7 @@ load_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo, int
     __syncthreads();
     bwd_y<P, double, false>(buf, t);
     bwd_x<P, double, false>(buf, t);
-    emit_e<P, double, false>(buf, t, active, smap, (const double *)nullptr, Y + (int64_t)m * estride,
+    emit_e<P, double>(buf, t, active, smap, Y + (int64_t)m * estride,
                              b + (int64_t)m * ndof);
     __syncthreads();
   }

@@ -18,7 +18,7 @@ namespace {
 constexpr int kRowBlock = 256;
 static_assert(kRowBlock % kSellRows == 0 && kSellRows == 64, "a wave per slice");
 
-enum CsrMode { kSpmv = 0, kSpmvAdd = 1, kResidual = 2, kJacobi = 3 };
+enum CsrMode { kSpmv = 0, kSpmvAdd = 1, kResidual = 2, kJacobi = 3, kResidual0 = 4, kSpmvBase = 5 };
 
 // Block index remapped so that each of the 8 XCDs (workgroups are dispatched to them in
 // turn) takes one contiguous range of the grid's blocks, i.e. of the rows: the rows of a
@@ -37,6 +37,8 @@ __device__ __forceinline__ int64_t row_block() {
 // y_i = (A x)_i combined per MODE:
 //   kSpmv      out = A x            kSpmvAdd  out += A x
 //   kResidual  out = b - A x        kJacobi   out = x + omega dinv (b - A x)
+// and, with x0 = omega dinv b (a Jacobi sweep from 0, formed where it is read instead of stored),
+//   kResidual0 out = b - A x0       kSpmvBase out = x0 + A x
 template <int LPR, int MODE, typename T>
 __global__ void __launch_bounds__(kRowBlock)
 csr_kernel(const int32_t *__restrict__ ptr, const int32_t *__restrict__ col,
@@ -47,13 +49,17 @@ csr_kernel(const int32_t *__restrict__ ptr, const int32_t *__restrict__ col,
   for (int64_t i = (row_block() * kRowBlock + threadIdx.x) / LPR; i < n; i += groups) {
     T s = T(0);
     const int32_t k1 = ptr[i + 1];
-    for (int32_t k = ptr[i] + lane; k < k1; k += LPR) s += val[k] * x[col[k]];
+    for (int32_t k = ptr[i] + lane; k < k1; k += LPR) {
+      const int32_t c = col[k];
+      s += val[k] * (MODE == kResidual0 ? omega * dinv[c] * b[c] : x[c]);
+    }
 #pragma unroll
     for (int off = LPR / 2; off > 0; off >>= 1) s += __shfl_down(s, off, LPR);
     if (lane == 0) {
       if constexpr (MODE == kSpmv) out[i] = s;
       else if constexpr (MODE == kSpmvAdd) out[i] += s;
-      else if constexpr (MODE == kResidual) out[i] = b[i] - s;
+      else if constexpr (MODE == kResidual || MODE == kResidual0) out[i] = b[i] - s;
+      else if constexpr (MODE == kSpmvBase) out[i] = omega * dinv[i] * b[i] + s;
       else out[i] = x[i] + omega * dinv[i] * (b[i] - s);
     }
   }
@@ -83,19 +89,23 @@ sell_kernel(const int32_t *__restrict__ off, const int32_t *__restrict__ pinfo,
   if (pi >= 0) {
     const int32_t *c = col + pi + lane;
 #pragma unroll 4
-    for (int k = 0; k < len; ++k) s += v[(int64_t)k * kSellRows] * x[c[(int64_t)k * kSellRows]];
+    for (int k = 0; k < len; ++k) {
+      const int32_t j = c[(int64_t)k * kSellRows];
+      s += v[(int64_t)k * kSellRows] * (MODE == kResidual0 ? omega * dinv[j] * b[j] : x[j]);
+    }
   } else {
     const int32_t *po = pat + (-1 - pi);
 #pragma unroll 4
     for (int k = 0; k < len; ++k) {
       int64_t c = i + po[k];
       c = c < 0 ? 0 : (c >= ncols ? ncols - 1 : c);  // absent entries (value 0) of edge rows
-      s += v[(int64_t)k * kSellRows] * x[c];
+      s += v[(int64_t)k * kSellRows] * (MODE == kResidual0 ? omega * dinv[c] * b[c] : x[c]);
     }
   }
   if constexpr (MODE == kSpmv) out[i] = s;
   else if constexpr (MODE == kSpmvAdd) out[i] += s;
-  else if constexpr (MODE == kResidual) out[i] = b[i] - s;
+  else if constexpr (MODE == kResidual || MODE == kResidual0) out[i] = b[i] - s;
+  else if constexpr (MODE == kSpmvBase) out[i] = omega * dinv[i] * b[i] + s;
   else out[i] = x[i] + omega * dinv[i] * (b[i] - s);
 }
 
@@ -212,6 +222,17 @@ hipError_t launch_mat_spmv(const DevMat &M, const T *x, T *y, bool accumulate, h
 }
 
 template <typename T>
+hipError_t launch_mat_residual0(const DevMat &A, const T *dinv, T omega, const T *b, T *r, hipStream_t s) {
+  return launch_mat<kResidual0, T>(A, b, b, dinv, omega, r, s);
+}
+
+template <typename T>
+hipError_t launch_mat_spmv_base(const DevMat &M, const T *x, const T *dinv, T omega, const T *b, T *y,
+                                hipStream_t s) {
+  return launch_mat<kSpmvBase, T>(M, x, b, dinv, omega, y, s);
+}
+
+template <typename T>
 hipError_t launch_dense_matvec(const T *C, int64_t n, const T *x, T *y, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL((dense_matvec_kernel<T>), dim3(grid_for_rows(n, 64)), dim3(kRowBlock), 0, s, C, n, x,
@@ -232,6 +253,9 @@ hipError_t launch_convert(const TI *in, TO *out, int64_t n, hipStream_t s) {
                                            hipStream_t);                                            \
   template hipError_t launch_mat_residual<T>(const DevMat &, const T *, const T *, T *, hipStream_t); \
   template hipError_t launch_mat_spmv<T>(const DevMat &, const T *, T *, bool, hipStream_t);          \
+  template hipError_t launch_mat_residual0<T>(const DevMat &, const T *, T, const T *, T *, hipStream_t); \
+  template hipError_t launch_mat_spmv_base<T>(const DevMat &, const T *, const T *, T, const T *, T *, \
+                                              hipStream_t);                                          \
   template hipError_t launch_dense_matvec<T>(const T *, int64_t, const T *, T *, hipStream_t);
 SFEM_LOR_INST(double)
 SFEM_LOR_INST(float)

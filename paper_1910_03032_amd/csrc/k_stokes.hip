@@ -632,7 +632,7 @@ convection_kernel(const int32_t *__restrict__ vmap, const int32_t *__restrict__ 
       A.finish(p[0]);
     }
     bwd_mass_xy<P, Q, 1>(buf, t, p);
-    emit_e<P, double, false>(buf, t, active, smap, u, Yv + r * vestride, yv + r * nv);
+    emit_e<P, double>(buf, t, active, smap, Yv + r * vestride, yv + r * nv);
   }
 }
 
@@ -742,7 +742,7 @@ weak_phi_kernel(const int32_t *__restrict__ vmap, const int32_t *__restrict__ vp
 #pragma unroll
   for (int f = 0; f < 3; ++f) {
     const int o = CURL ? (f + 1) % 3 : f;
-    emit_e<P, double, false>(buf + f * N3, t, active, smap, u, Yv + o * vestride, yv + o * nv);
+    emit_e<P, double>(buf + f * N3, t, active, smap, Yv + o * vestride, yv + o * nv);
   }
 }
 
@@ -868,7 +868,7 @@ weak_div_kernel(const int32_t *__restrict__ vmap, const int32_t *__restrict__ vp
   double h[3][Q];  // (C^T V)_k at the points of the line
   contravariant<P, Q>(buf, t, sg, h);
   bwd_grad<P, Q>(buf, t, h);
-  emit_e<P, double, false>(buf, t, active, smap, u, Yv, yv);
+  emit_e<P, double>(buf, t, active, smap, Yv, yv);
 }
 
 template <int P>

@@ -122,13 +122,6 @@ __global__ void dot_kernel(const T *__restrict__ a, const T *__restrict__ c, int
   write_part<1>(v, part, nblk);
 }
 
-// The step length of the current iteration from the scalars sc (rho, active) and the
-// apply's partial sums of p.Ap (member m: dpart[m * dmstride + i], i < dcount), summed
-// in a fixed order by every block that needs it -- the same value in each.
-__device__ __forceinline__ double step_alpha(const PcgScalars &s, double pw) {
-  return (s.active && isfinite(pw) && pw > 0.0) ? s.rho / pw : 0.0;
-}
-
 // The second launch of a CG iteration (pcg.h): per DoF, w = (A p)_g -- the element kernel's y
 // at a DoF of one element, p itself at an essential DoF, else the sum of the DoF's E-vector
 // entries in element order (as assemble_kernel) -- then p, x += alpha p, r -= alpha w and the
@@ -140,16 +133,26 @@ __device__ __forceinline__ double step_alpha(const PcgScalars &s, double pw) {
 constexpr int CU_NT = 512;
 constexpr int CU_MAXB = 512;  // (at most 4 * 192: PartLoads of the element kernels' 3 full waves)
 
-template <typename T>
+// With Z (one member) the preconditioned residual z is given instead of dinv r, there are no
+// partials, and what the preconditioner starts from is written too (CgzOut).
+template <typename TZ>
+struct CgzOut {
+  float *r32;       // (float) r, or null
+  TZ *t;            // first smoothing sweep omega tdinv r, or null
+  const TZ *tdinv;
+  TZ omega;
+};
+template <typename T, typename TZ, bool Z>
 __global__ void __launch_bounds__(CU_NT)
 cg_update_kernel(CgDofs dofs, const T *__restrict__ Y, int64_t estride, const T *__restrict__ y,
                  T *__restrict__ x, T *__restrict__ p, T *__restrict__ r,
-                 const T *__restrict__ dinv, int64_t dinv_mstride, const PcgScalars *__restrict__ sc,
+                 const TZ *__restrict__ dinv, int64_t dinv_mstride, const PcgScalars *__restrict__ sc,
                  PcgScalars *__restrict__ sc_next, const double *__restrict__ dpart, int64_t dmstride,
-                 int dcount, double *__restrict__ part, int nblk, int64_t n) {
+                 int dcount, double *__restrict__ part, int nblk, int64_t n, CgzOut<TZ> zo) {
   const int m = blockIdx.y;
   const int64_t off = (int64_t)m * n;
-  const T *dm = dinv + (int64_t)m * dinv_mstride, *Ym = Y + (int64_t)m * estride, *ym = y + off;
+  const TZ *dm = dinv + (int64_t)m * dinv_mstride;  // (Z: the given z)
+  const T *Ym = Y + (int64_t)m * estride, *ym = y + off;
   T *xm = x + off, *pm = p + off, *rm = r + off;
   // U entries per thread and pass, all their loads in flight together; those of the first
   // pass are requested before the partial sums are read
@@ -166,7 +169,7 @@ cg_update_kernel(CgDofs dofs, const T *__restrict__ Y, int64_t estride, const T 
       ex[k] = xm[j];
       ep[k] = pm[j];
       er[k] = rm[j];
-      ed[k] = dm[j];
+      ed[k] = (T)dm[j];
     }
   };
   int64_t i = (int64_t)blockIdx.x * CU_NT + threadIdx.x;
@@ -208,12 +211,17 @@ cg_update_kernel(CgDofs dofs, const T *__restrict__ Y, int64_t estride, const T 
     for (int k = 0; k < U; ++k) {
       const int64_t j = i + k * stride;
       if (j >= n) continue;
-      const T pi = cg_dir(ed[k], er[k], zs, beta, ep[k]);
+      const T pi = Z ? cg_dir(T(1), ed[k], zs, beta, ep[k]) : cg_dir(ed[k], er[k], zs, beta, ep[k]);
       if (o[k] < 0) w[k] = pi;  // essential
       const T ri = er[k] - alpha * w[k];
       pm[j] = pi;
       xm[j] = ex[k] + alpha * pi;
       rm[j] = ri;
+      if constexpr (Z) {
+        if (zo.r32) zo.r32[j] = (float)ri;
+        if (zo.t) zo.t[j] = zo.omega * zo.tdinv[j] * (TZ)ri;
+        continue;
+      }
       const T zi = ed[k] * ri;
       v[0] += (double)ri * (double)zi;
       v[1] += (double)ri * (double)ri;
@@ -222,6 +230,7 @@ cg_update_kernel(CgDofs dofs, const T *__restrict__ Y, int64_t estride, const T 
     }
     if (i + U * stride < n) fetch(i + U * stride);
   }
+  if constexpr (Z) return;
   // block sums: wave totals, then the waves in order
   __shared__ double sh[4][CU_NT / 64];
 #pragma unroll
@@ -240,8 +249,8 @@ cg_update_kernel(CgDofs dofs, const T *__restrict__ Y, int64_t estride, const T 
 // The state of the next iteration from the update's partials (a block per member), where the
 // host reads it before the next element kernel runs.
 __global__ void __launch_bounds__(256)
-cg_finish_kernel(PcgScalars *__restrict__ sc, const double *__restrict__ part, int nblk, int nullspace,
-                 int64_t n) {
+cg_finish_kernel(PcgScalars *__restrict__ sc, PcgScalars *__restrict__ host, const double *__restrict__ part,
+                 int nblk, int nullspace, int64_t n) {
   const int m = blockIdx.x;
   __shared__ double sums[4][4];
   PcgScalars s;
@@ -252,78 +261,53 @@ cg_finish_kernel(PcgScalars *__restrict__ sc, const double *__restrict__ part, i
   up.parts(sums, nblk);
   __syncthreads();
   cg_next_from<4>(s, sums, nullspace, n);
-  if (threadIdx.x == 0) copy_state(sc[m], s);
-}
-
-// ---- CG steps around a preconditioner applied between the launches (z given), one member:
-// the step length, the next direction and the next scalars come from device-side partial
-// sums, as in the Jacobi CG, so that the host only reads the scalars to stop.
-
-// x += alpha p; r -= alpha w, alpha formed by every block from the scalars and the apply's
-// partials of p.Ap; with r32 also r32 = (float) r (the input of an FP32 preconditioner).
-__global__ void gpcg_update_kernel(double *__restrict__ x, const double *__restrict__ p,
-                                   double *__restrict__ r, const double *__restrict__ w,
-                                   float *__restrict__ r32, const PcgScalars *__restrict__ sc,
-                                   const double *__restrict__ dpart, int dcount, int64_t n) {
-  double pw[1];
-  reduce_parts_m<1, VB>(dpart, dcount, 0, pw);
-  const double alpha = step_alpha(sc[0], pw[0]);
-  for (int64_t i = (int64_t)blockIdx.x * VB + threadIdx.x; i < n; i += (int64_t)gridDim.x * VB) {
-    x[i] += alpha * p[i];
-    const double ri = r[i] - alpha * w[i];
-    r[i] = ri;
-    if (r32) r32[i] = (float)ri;
+  if (threadIdx.x == 0) {
+    copy_state(sc[m], s);
+    copy_state(host[m], s);
   }
 }
 
-// Partials of r.z and r.r, then by NV: 4, sum z and sum r (for the null-space shift);
-// 5, b.b and two zeros (the five quantities the scalar initialization reads).
-template <int NV, typename TZ>
-__global__ void gpcg_dots_kernel(const double *__restrict__ r, const TZ *__restrict__ z,
-                                 const double *__restrict__ b, double *__restrict__ part, int nblk,
-                                 int64_t n) {
+// Partials of r.z, r.r, (BB: b.b,) sum z, sum r.
+template <typename TZ, bool BB>
+__global__ void __launch_bounds__(CU_NT)
+cgz_dots_kernel(const double *__restrict__ r, const TZ *__restrict__ z, const double *__restrict__ b,
+                double *__restrict__ part, int nblk, int64_t n) {
+  constexpr int NV = BB ? 5 : 4, U = 2;
   double v[NV];
 #pragma unroll
   for (int k = 0; k < NV; ++k) v[k] = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * VB + threadIdx.x; i < n; i += (int64_t)nblk * VB) {
-    const double ri = r[i], zi = (double)z[i];
-    v[0] += ri * zi;
-    v[1] += ri * ri;
-    if constexpr (NV == 4) {
-      v[2] += zi;
-      v[3] += ri;
+  const int64_t stride = (int64_t)nblk * CU_NT;
+  for (int64_t i = (int64_t)blockIdx.x * CU_NT + threadIdx.x; i < n; i += U * stride) {
+    double ri[U], zi[U], bi[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const int64_t j = i + k * stride < n ? i + k * stride : n - 1;
+      ri[k] = r[j];
+      zi[k] = (double)z[j];
+      bi[k] = BB ? b[j] : 0.0;
     }
-    if constexpr (NV == 5) v[2] += b[i] * b[i];
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      if (i + k * stride >= n) continue;
+      v[0] += ri[k] * zi[k];
+      v[1] += ri[k] * ri[k];
+      if constexpr (BB) v[2] += bi[k] * bi[k];
+      v[NV - 2] += zi[k];
+      v[NV - 1] += ri[k];
+    }
   }
-  write_part<NV>(v, part, nblk);
-}
-
-// p = (z - zs) + beta p, with alpha (for the failure state), beta and the stopping test
-// formed by every block from the scalars and the partials of p.Ap and of r.z, r.r (and,
-// with NS, sum z and sum r: zs = mean(z), the preconditioned residual orthogonalized
-// against the constants, whose r.(z - zs) = r.z - zs sum r); block 0 writes the next
-// scalars to sc_next (double-buffered).
-template <typename TZ, bool NS>
-__global__ void gpcg_newdir_kernel(const TZ *__restrict__ z, double *__restrict__ p,
-                                   const PcgScalars *__restrict__ sc, PcgScalars *__restrict__ sc_next,
-                                   const double *__restrict__ dpart, int dcount,
-                                   const double *__restrict__ upart, int unblk, int64_t n) {
-  constexpr int NU = NS ? 4 : 2;
-  double pw[1], u[NU];
-  reduce_parts_m<1, VB>(dpart, dcount, 0, pw);
-  reduce_parts_m<NU, VB>(upart, unblk, 0, u);
-  PcgScalars s = sc[0];
-  set_alpha(s, pw[0]);
-  double zs = 0.0, rz = u[0];
-  if constexpr (NS) {
-    zs = u[2] / (double)n;
-    rz = u[0] - zs * u[3];
+  __shared__ double sh[NV][CU_NT / 64];
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    v[k] = wave_total(v[k]);
+    if ((threadIdx.x & 63) == 0) sh[k][threadIdx.x >> 6] = v[k];
   }
-  set_beta(s, rz, u[1]);
-  if (blockIdx.x == 0 && threadIdx.x == 0) sc_next[0] = s;
-  const double beta = s.beta;
-  for (int64_t i = (int64_t)blockIdx.x * VB + threadIdx.x; i < n; i += (int64_t)gridDim.x * VB)
-    p[i] = ((double)z[i] - zs) + beta * p[i];
+  __syncthreads();
+  if (threadIdx.x < NV) {
+    double t = 0.0;
+    for (int w = 0; w < CU_NT / 64; ++w) t += sh[threadIdx.x][w];
+    part[(int64_t)threadIdx.x * nblk + blockIdx.x] = t;
+  }
 }
 
 // r = b - w with partial r.r (w may be null: r = b); r may be null (norm only)
@@ -421,71 +405,39 @@ __global__ void ir_accum_kernel(double *__restrict__ x, const float *__restrict_
 // entries of list entry i in element order -- [aoff[i], aoff[i+1]) for the DoF-ordered
 // E-vector (consecutive threads then read consecutive runs), slot[aoff[i]..aoff[i+1])
 // for the element-ordered one; essential DoFs (no entries) get x[g], 1 or 0 (kEssAdd:
-// y[g] += the sum at the other DoFs, essential entries untouched).  DOT: also
-// the per-block sums of x_g y_g.  Each thread takes AU list entries per pass (stride
-// VB); the first KS entries of each are loaded together, longer lists fall back to a
-// loop.  Index arithmetic is 32-bit (entries below 2^30, checked at set-up).
-constexpr int AU = 1;
+// y[g] += the sum at the other DoFs, essential entries untouched).  The first KS entries of
+// each are loaded together, longer lists fall back to a loop.  Index arithmetic is 32-bit
+// (entries below 2^30, checked at set-up).
 constexpr int KS = 8;
 
-template <typename T, bool DOT>
+template <typename T>
 __global__ void __launch_bounds__(VB)
 assemble_kernel(AsmPlan pl, const T *__restrict__ Y, int64_t estride, const T *__restrict__ x,
-                T *__restrict__ y, int64_t n, int ess_kind, double *__restrict__ part,
-                int64_t part_mstride, int nblk, const double *__restrict__ epart, int ne) {
+                T *__restrict__ y, int64_t n, int ess_kind, int nblk) {
   const int mb = blockIdx.y;
   const T *Ym = Y + (int64_t)mb * estride;
   const T *xm = x ? x + (int64_t)mb * n : nullptr;
   T *ym = y + (int64_t)mb * n;
   const int na = (int)pl.na;
-  double v[1] = {0.0};
-  for (int base = (int)blockIdx.x * (VB * AU) + (int)threadIdx.x; base < na; base += nblk * (VB * AU)) {
-    int32_t g[AU], a[AU], d[AU];
+  for (int i = (int)blockIdx.x * VB + (int)threadIdx.x; i < na; i += nblk * VB) {
+    const int32_t g = pl.alist[i], a = pl.aoff[i], d = pl.aoff[i + 1] - a;
+    int32_t sl[KS];
 #pragma unroll
-    for (int k = 0; k < AU; ++k) {
-      const int i = base + k * VB;
-      const bool in = i < na;
-      g[k] = in ? pl.alist[i] : 0;
-      a[k] = in ? pl.aoff[i] : 0;
-      d[k] = in ? pl.aoff[i + 1] - a[k] : -1;
+    for (int j = 0; j < KS; ++j) sl[j] = (j < d) ? (pl.slot ? pl.slot[a + j] : a + j) : 0;
+    T val[KS];
+#pragma unroll
+    for (int j = 0; j < KS; ++j) val[j] = (j < d) ? Ym[sl[j]] : T(0);
+    T acc = val[0];
+#pragma unroll
+    for (int j = 1; j < KS; ++j)
+      if (j < d) acc += val[j];
+    for (int j = KS; j < d; ++j) acc += Ym[pl.slot ? pl.slot[a + j] : a + j];
+    if (ess_kind == kEssAdd) {
+      if (d > 0) ym[g] += acc;
+      continue;
     }
-    int32_t sl[AU][KS];
-#pragma unroll
-    for (int k = 0; k < AU; ++k)
-#pragma unroll
-      for (int j = 0; j < KS; ++j) sl[k][j] = (j < d[k]) ? (pl.slot ? pl.slot[a[k] + j] : a[k] + j) : 0;
-    T val[AU][KS];
-#pragma unroll
-    for (int k = 0; k < AU; ++k)
-#pragma unroll
-      for (int j = 0; j < KS; ++j) val[k][j] = (j < d[k]) ? Ym[sl[k][j]] : T(0);
-#pragma unroll
-    for (int k = 0; k < AU; ++k) {
-      if (d[k] < 0) continue;
-      T acc = val[k][0];
-#pragma unroll
-      for (int j = 1; j < KS; ++j)
-        if (j < d[k]) acc += val[k][j];
-      for (int j = KS; j < d[k]; ++j) acc += Ym[pl.slot ? pl.slot[a[k] + j] : a[k] + j];
-      const T xg = (DOT || (d[k] == 0 && ess_kind == kEssCopyX)) ? xm[g[k]] : T(0);
-      if (ess_kind == kEssAdd) {
-        if (d[k] > 0) ym[g[k]] += acc;
-        continue;
-      }
-      if (d[k] == 0) acc = (ess_kind == kEssCopyX) ? xg : (ess_kind == kEssOne ? T(1) : T(0));
-      ym[g[k]] = acc;
-      if constexpr (DOT) v[0] += (double)xg * (double)acc;
-    }
-  }
-  if constexpr (DOT) {
-    // this block's share of the element kernel's partial sums (a fixed range), so that
-    // the apply leaves one partial per assembly block
-    const double *ep = epart + (int64_t)mb * part_mstride;
-    const int lo = (int)((int64_t)ne * blockIdx.x / nblk);
-    const int hi = (int)((int64_t)ne * (blockIdx.x + 1) / nblk);
-    for (int i = lo + (int)threadIdx.x; i < hi; i += VB) v[0] += ep[i];
-    block_sum<1>(v);
-    if (threadIdx.x == 0) part[(int64_t)mb * part_mstride + blockIdx.x] = v[0];
+    if (d == 0) acc = (ess_kind == kEssCopyX) ? xm[g] : (ess_kind == kEssOne ? T(1) : T(0));
+    ym[g] = acc;
   }
 }
 
@@ -511,19 +463,6 @@ unsigned grid_for(int64_t n) {
 }
 
 }  // namespace
-
-int assemble_nblk(int64_t na) {
-  int64_t b = (na + VB * AU - 1) / (VB * AU);
-  if (b < 1) b = 1;
-  if (b > 8192) b = 8192;
-  return (int)b;
-}
-
-
-int assemble_nblk_dot(int64_t na) {
-  const int b = assemble_nblk(na);
-  return b < kMaxParts ? b : kMaxParts;
-}
 
 int vec_nblk(int64_t n) {
   int64_t b = (n + VB * 2 - 1) / (VB * 2);
@@ -552,8 +491,8 @@ hipError_t VecOps<T>::update(const CgDofs &dofs, const T *evec, int64_t estride,
                              const T *dinv, int64_t dms, const PcgScalars *sc, PcgScalars *sc_next,
                              const double *dpart, int64_t dmstride, int dcount, double *part, int nblk,
                              int64_t n, int nb, hipStream_t s) {
-  hipLaunchKernelGGL((cg_update_kernel<T>), dim3(nblk, nb), dim3(CU_NT), 0, s, dofs, evec, estride, y, x, p,
-                     r, dinv, dms, sc, sc_next, dpart, dmstride, dcount, part, nblk, n);
+  hipLaunchKernelGGL((cg_update_kernel<T, T, false>), dim3(nblk, nb), dim3(CU_NT), 0, s, dofs, evec, estride,
+                     y, x, p, r, dinv, dms, sc, sc_next, dpart, dmstride, dcount, part, nblk, n, CgzOut<T>{});
   return hipGetLastError();
 }
 
@@ -573,72 +512,56 @@ hipError_t VecOps<T>::recip(const double *d, T *out, int64_t n, hipStream_t s) {
 
 template <typename T>
 hipError_t launch_assemble(const AsmPlan &pl, const T *evec, int64_t estride, const T *x, T *y,
-                           int64_t n, int nb, int ess_kind, double *part, int64_t part_mstride,
-                           hipStream_t s, const double *epart, int ne) {
+                           int64_t n, int nb, int ess_kind, hipStream_t s) {
   if (pl.na <= 0 || nb <= 0) return hipSuccess;
-  const int nblk = part ? assemble_nblk_dot(pl.na) : assemble_nblk(pl.na);
-  if (part)
-    hipLaunchKernelGGL((assemble_kernel<T, true>), dim3(nblk, nb), dim3(VB), 0, s, pl, evec, estride,
-                       x, y, n, ess_kind, part, part_mstride, nblk, epart, ne);
-  else
-    hipLaunchKernelGGL((assemble_kernel<T, false>), dim3(nblk, nb), dim3(VB), 0, s, pl, evec, estride,
-                       x, y, n, ess_kind, part, part_mstride, nblk, epart, ne);
+  int64_t nblk = (pl.na + VB - 1) / VB;
+  if (nblk > 8192) nblk = 8192;
+  hipLaunchKernelGGL((assemble_kernel<T>), dim3((unsigned)nblk, nb), dim3(VB), 0, s, pl, evec, estride, x, y,
+                     n, ess_kind, (int)nblk);
   return hipGetLastError();
 }
 template hipError_t launch_assemble<double>(const AsmPlan &, const double *, int64_t, const double *,
-                                            double *, int64_t, int, int, double *, int64_t,
-                                            hipStream_t, const double *, int);
+                                            double *, int64_t, int, int, hipStream_t);
 template hipError_t launch_assemble<float>(const AsmPlan &, const float *, int64_t, const float *,
-                                           float *, int64_t, int, int, double *, int64_t, hipStream_t,
-                                           const double *, int);
+                                           float *, int64_t, int, int, hipStream_t);
 
 template struct VecOps<double>;
 template struct VecOps<float>;
 
-hipError_t launch_gpcg_update(double *x, const double *p, double *r, const double *w, float *r32,
-                              const PcgScalars *sc, const double *dpart, int dcount, int64_t n,
-                              hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(gpcg_update_kernel, dim3(vec_nblk(n)), dim3(VB), 0, s, x, p, r, w, r32, sc, dpart,
-                     dcount, n);
-  return hipGetLastError();
-}
-
 template <typename TZ>
-hipError_t launch_gpcg_dots(const double *r, const TZ *z, const double *b, int nullspace, double *part,
-                            int nblk, int64_t n, hipStream_t s) {
-  if (b)
-    hipLaunchKernelGGL((gpcg_dots_kernel<5, TZ>), dim3(nblk), dim3(VB), 0, s, r, z, b, part, nblk, n);
-  else if (nullspace)
-    hipLaunchKernelGGL((gpcg_dots_kernel<4, TZ>), dim3(nblk), dim3(VB), 0, s, r, z, b, part, nblk, n);
-  else
-    hipLaunchKernelGGL((gpcg_dots_kernel<2, TZ>), dim3(nblk), dim3(VB), 0, s, r, z, b, part, nblk, n);
-  return hipGetLastError();
-}
-
-template <typename TZ>
-hipError_t launch_gpcg_newdir(const TZ *z, double *p, const PcgScalars *sc, PcgScalars *sc_next,
-                              const double *dpart, int dcount, const double *upart, int unblk,
-                              int nullspace, int64_t n, hipStream_t s) {
+hipError_t launch_cgz_update(const CgDofs &dofs, const double *evec, const double *y, double *x, double *p,
+                             double *r, const TZ *z, float *r32, TZ *t, const TZ *tdinv, TZ omega,
+                             const PcgScalars *sc, PcgScalars *sc_next, const double *dpart, int dcount,
+                             int64_t n, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  if (nullspace)
-    hipLaunchKernelGGL((gpcg_newdir_kernel<TZ, true>), dim3(vec_nblk(n)), dim3(VB), 0, s, z, p, sc, sc_next,
-                       dpart, dcount, upart, unblk, n);
-  else
-    hipLaunchKernelGGL((gpcg_newdir_kernel<TZ, false>), dim3(vec_nblk(n)), dim3(VB), 0, s, z, p, sc,
-                       sc_next, dpart, dcount, upart, unblk, n);
+  const int nblk = cg_update_nblk(n);
+  hipLaunchKernelGGL((cg_update_kernel<double, TZ, true>), dim3(nblk), dim3(CU_NT), 0, s, dofs, evec, (int64_t)0,
+                     y, x, p, r, z, (int64_t)0, sc, sc_next, dpart, (int64_t)0, dcount, (double *)nullptr, nblk, n,
+                     CgzOut<TZ>{r32, t, tdinv, omega});
   return hipGetLastError();
 }
-template hipError_t launch_gpcg_dots<double>(const double *, const double *, const double *, int, double *,
-                                             int, int64_t, hipStream_t);
-template hipError_t launch_gpcg_dots<float>(const double *, const float *, const double *, int, double *,
-                                            int, int64_t, hipStream_t);
-template hipError_t launch_gpcg_newdir<double>(const double *, double *, const PcgScalars *, PcgScalars *,
-                                               const double *, int, const double *, int, int, int64_t,
-                                               hipStream_t);
-template hipError_t launch_gpcg_newdir<float>(const float *, double *, const PcgScalars *, PcgScalars *,
-                                              const double *, int, const double *, int, int, int64_t,
+template hipError_t launch_cgz_update<double>(const CgDofs &, const double *, const double *, double *, double *,
+                                              double *, const double *, float *, double *, const double *, double,
+                                              const PcgScalars *, PcgScalars *, const double *, int, int64_t,
                                               hipStream_t);
+template hipError_t launch_cgz_update<float>(const CgDofs &, const double *, const double *, double *, double *,
+                                             double *, const float *, float *, float *, const float *, float,
+                                             const PcgScalars *, PcgScalars *, const double *, int, int64_t,
+                                             hipStream_t);
+
+template <typename TZ>
+hipError_t launch_cgz_dots(const double *r, const TZ *z, const double *b, double *part, int nblk, int64_t n,
+                           hipStream_t s) {
+  if (b)
+    hipLaunchKernelGGL((cgz_dots_kernel<TZ, true>), dim3(nblk), dim3(CU_NT), 0, s, r, z, b, part, nblk, n);
+  else
+    hipLaunchKernelGGL((cgz_dots_kernel<TZ, false>), dim3(nblk), dim3(CU_NT), 0, s, r, z, b, part, nblk, n);
+  return hipGetLastError();
+}
+template hipError_t launch_cgz_dots<double>(const double *, const double *, const double *, double *, int, int64_t,
+                                            hipStream_t);
+template hipError_t launch_cgz_dots<float>(const double *, const float *, const double *, double *, int, int64_t,
+                                           hipStream_t);
 
 hipError_t launch_sub_norm(const double *b, const double *w, double *r, double *part, int nblk,
                            int64_t n, int nb, hipStream_t s) {
@@ -659,9 +582,9 @@ int cg_update_nblk(int64_t n) {
   return (int)b;
 }
 
-hipError_t launch_cg_finish(PcgScalars *sc, const double *part, int nblk, int nb, int nullspace, int64_t n,
-                            hipStream_t s) {
-  hipLaunchKernelGGL(cg_finish_kernel, dim3(nb), dim3(256), 0, s, sc, part, nblk, nullspace, n);
+hipError_t launch_cg_finish(PcgScalars *sc, PcgScalars *host, const double *part, int nblk, int nb,
+                            int nullspace, int64_t n, hipStream_t s) {
+  hipLaunchKernelGGL(cg_finish_kernel, dim3(nb), dim3(256), 0, s, sc, host, part, nblk, nullspace, n);
   return hipGetLastError();
 }
 

@@ -192,7 +192,7 @@ std::string amg_make_f32(Amg &amg, hipStream_t s) {
 namespace {
 
 template <typename T>
-hipError_t vcycle_level(const Amg &amg, size_t l, const T *b, T *x, hipStream_t s) {
+hipError_t vcycle_level(const Amg &amg, size_t l, const T *b, T *x, hipStream_t s, bool presmoothed) {
   const AmgLevel &v = amg.lv[l];
   if (l + 1 == amg.lv.size()) {
     const T *C;
@@ -202,11 +202,22 @@ hipError_t vcycle_level(const Amg &amg, size_t l, const T *b, T *x, hipStream_t 
   }
   const LevelVecs<T> &w = v.vecs<T>();
   const T omega = (T)v.omega;
+  const LevelVecs<T> &c = amg.lv[l + 1].vecs<T>();
   hipError_t e;
+  if (l > 0 && amg.nu == 1) {
+    // a small level's time is its launches: the first sweep is formed where it is read
+    // instead of stored by a launch of its own (on the finest level the second gathered
+    // vector would cost more than it saves)
+    if ((e = launch_mat_residual0<T>(v.A, w.dinv, omega, b, x, s)) != hipSuccess) return e;
+    if ((e = launch_mat_spmv<T>(v.R, x, c.b, false, s)) != hipSuccess) return e;
+    if ((e = vcycle_level<T>(amg, l + 1, c.b, c.x, s, false)) != hipSuccess) return e;
+    if ((e = launch_mat_spmv_base<T>(v.P, c.x, w.dinv, omega, b, w.t, s)) != hipSuccess) return e;
+    return launch_mat_jacobi<T>(v.A, w.dinv, omega, b, w.t, x, s);
+  }
   // pre-smoothing from x = 0: the first sweep is omega D^-1 b.  It goes to the work
   // vector, so that after the 2 nu - 1 alternations between the two vectors the last
   // post-smoothing sweep lands in x (x serves as scratch until then).
-  if ((e = launch_mat_jacobi<T>(v.A, w.dinv, omega, b, nullptr, w.t, s)) != hipSuccess) return e;
+  if (!presmoothed && (e = launch_mat_jacobi<T>(v.A, w.dinv, omega, b, nullptr, w.t, s)) != hipSuccess) return e;
   T *cur = w.t, *oth = x;
   for (int it = 1; it < amg.nu; ++it) {
     if ((e = launch_mat_jacobi<T>(v.A, w.dinv, omega, b, cur, oth, s)) != hipSuccess) return e;
@@ -214,9 +225,8 @@ hipError_t vcycle_level(const Amg &amg, size_t l, const T *b, T *x, hipStream_t 
   }
   // residual, restriction, coarse correction, prolongation
   if ((e = launch_mat_residual<T>(v.A, b, cur, oth, s)) != hipSuccess) return e;
-  const LevelVecs<T> &c = amg.lv[l + 1].vecs<T>();
   if ((e = launch_mat_spmv<T>(v.R, oth, c.b, false, s)) != hipSuccess) return e;
-  if ((e = vcycle_level<T>(amg, l + 1, c.b, c.x, s)) != hipSuccess) return e;
+  if ((e = vcycle_level<T>(amg, l + 1, c.b, c.x, s, false)) != hipSuccess) return e;
   if ((e = launch_mat_spmv<T>(v.P, c.x, cur, true, s)) != hipSuccess) return e;
   for (int it = 0; it < amg.nu; ++it) {
     if ((e = launch_mat_jacobi<T>(v.A, w.dinv, omega, b, cur, oth, s)) != hipSuccess) return e;
@@ -229,13 +239,22 @@ hipError_t vcycle_level(const Amg &amg, size_t l, const T *b, T *x, hipStream_t 
 }  // namespace
 
 template <typename T>
-hipError_t amg_vcycle(const Amg &amg, const T *b, T *x, hipStream_t s) {
+hipError_t amg_vcycle(const Amg &amg, const T *b, T *x, hipStream_t s, bool presmoothed) {
   if (amg.lv.empty()) return hipErrorInvalidValue;
   if (sizeof(T) == 4 && !amg.has32) return hipErrorInvalidValue;
-  return vcycle_level<T>(amg, 0, b, x, s);
+  return vcycle_level<T>(amg, 0, b, x, s, presmoothed);
 }
-template hipError_t amg_vcycle<double>(const Amg &, const double *, double *, hipStream_t);
-template hipError_t amg_vcycle<float>(const Amg &, const float *, float *, hipStream_t);
+template hipError_t amg_vcycle<double>(const Amg &, const double *, double *, hipStream_t, bool);
+template hipError_t amg_vcycle<float>(const Amg &, const float *, float *, hipStream_t, bool);
+
+template <typename T>
+FirstSweep<T> amg_first_sweep(const Amg &amg) {
+  if (amg.lv.size() < 2 || (sizeof(T) == 4 && !amg.has32)) return FirstSweep<T>{nullptr, nullptr, T(0)};
+  const LevelVecs<T> &w = amg.lv[0].vecs<T>();
+  return FirstSweep<T>{w.t, w.dinv, (T)amg.lv[0].omega};
+}
+template FirstSweep<double> amg_first_sweep<double>(const Amg &);
+template FirstSweep<float> amg_first_sweep<float>(const Amg &);
 
 hipError_t amg_apply_fine(const Amg &amg, const double *x, double *y, hipStream_t s) {
   if (amg.lv.empty()) return hipErrorInvalidValue;

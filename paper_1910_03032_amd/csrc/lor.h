@@ -107,9 +107,20 @@ void amg_free(Amg &amg);
 // vectors, for amg_vcycle<float> (the FP64 data stays).  Empty string or an error message.
 std::string amg_make_f32(Amg &amg, hipStream_t s);
 // x = V-cycle(b) on the finest level in precision T (b, x: device [n], distinct; T = float
-// after amg_make_f32).
+// after amg_make_f32).  presmoothed: the finest level's first sweep omega D^-1 b is already in
+// amg_first_sweep(...).t (only where that is not null).
 template <typename T>
-hipError_t amg_vcycle(const Amg &amg, const T *b, T *x, hipStream_t s);
+hipError_t amg_vcycle(const Amg &amg, const T *b, T *x, hipStream_t s, bool presmoothed = false);
+// Where a caller that computes b can leave the first sweep t = omega dinv b; t null if the
+// cycle has no use for it.
+template <typename T>
+struct FirstSweep {
+  T *t;
+  const T *dinv;
+  T omega;
+};
+template <typename T>
+FirstSweep<T> amg_first_sweep(const Amg &amg);
 // y = A_0 x (the finest operator).
 hipError_t amg_apply_fine(const Amg &amg, const double *x, double *y, hipStream_t s);
 
@@ -124,6 +135,12 @@ hipError_t launch_mat_residual(const DevMat &A, const T *b, const T *x, T *r, hi
 // y = M x (accumulate: y += M x)
 template <typename T>
 hipError_t launch_mat_spmv(const DevMat &M, const T *x, T *y, bool accumulate, hipStream_t s);
+// r = b - A x0 and y = x0 + M x with x0 = omega dinv b
+template <typename T>
+hipError_t launch_mat_residual0(const DevMat &A, const T *dinv, T omega, const T *b, T *r, hipStream_t s);
+template <typename T>
+hipError_t launch_mat_spmv_base(const DevMat &M, const T *x, const T *dinv, T omega, const T *b, T *y,
+                                hipStream_t s);
 // out = (TO) in
 template <typename TI, typename TO>
 hipError_t launch_convert(const TI *in, TO *out, int64_t n, hipStream_t s);
