@@ -30,7 +30,7 @@
 // elements in that XCD's L2.
 //
 // LDS layouts inside an element buffer (a, b, c: quadrature indices along
-// xi_1..3; i, j, k: node indices):
+// xi_1..3; i, j, k: node indices), with the strides of Lds<P>:
 //   nodal         [k][j][i]
 //   after xi_1    [k][j][a]      (two fields: B- and G-contracted)
 //   after xi_2    [k][b][a]      (three fields)
@@ -61,8 +61,58 @@ struct Dims {
   static constexpr int THREADS = E * TPE;
   // minimum waves per SIMD the element kernels are compiled for: the largest that
   // the Helmholtz kernels reach without spilling registers (p = 8 spills slightly)
-  static constexpr int OCC = P <= 2 ? 4 : (P <= 4 ? 3 : 2);
+  static constexpr int OCC = P <= 2 ? 4 : (P <= 6 ? 3 : 2);
 };
+
+// Layout of the apply kernels' element buffer.  A half-wave's 32 lanes are served in one
+// cycle when they touch different banks, and the bank is the element index modulo 32 for
+// 4- and 8-byte elements alike; with dense strides the stages' accesses took about twice
+// the cycles of that (2.7 times at p = 6, where every stride is even).  LQ (line of
+// [k][j][a]), SK (its plane), SP (plane of [k][b][a]) and BUF modulo 32 (element to element)
+// are the strides with the fewest conflicts, counted over all accesses of a workgroup, that
+// take at most 12 % more LDS than the dense ones and keep the workgroups per CU (p = 6, 7);
+// mass kernels keep one field each (DIFF false).  24^3 p = 6 in float32: 65 -> 60 us; mass at
+// 36^3 p = 4: 68 -> 61 us.  The nodal vectors have a place of their own past the [k][j][a]
+// fields, so that the xi_1 stages need no barrier between their reads and writes.
+template <int P, bool DIFF = true>
+struct Lds {
+  static constexpr int N = P + 1, Q = P + 2;
+  static constexpr int pick(int a1, int a2, int a3, int a4, int a5, int a6, int a7, int a8) {
+    return P == 1 ? a1 : P == 2 ? a2 : P == 3 ? a3 : P == 4 ? a4 : P == 5 ? a5 : P == 6 ? a6 : P == 7 ? a7 : a8;
+  }
+  static constexpr int LN = pick(2, 3, 5, 5, 7, 7, 9, 9);
+  static constexpr int LQ = pick(3, 5, 6, 7, 7, 9, 9, 11);
+  static constexpr int SK = pick(12, 20, 24, 38, 42, 72, 72, 103);
+  static constexpr int SP = pick(11, 20, 25, 38, 56, 68, 81, 106);
+  static constexpr int XF = N * SK, YF = N * SP;  // fields of [k][j][a] and of [k][b][a]
+  static constexpr int NOD = DIFF ? 2 * XF : XF;
+  static constexpr int FULL = pick(72, 188, 325, 580, 1009, 1428, 1952, 2884);
+  static constexpr int MASS = NOD + N * N * LN > YF ? NOD + N * N * LN : YF;
+  static constexpr int BUF = DIFF ? FULL : MASS + (FULL % 32 - MASS % 32 + 32) % 32;
+  static_assert(LN >= N && LQ >= Q && SK >= N * LQ && SP >= Q * Q, "strides");
+  static_assert(BUF >= NOD + N * N * LN && BUF >= (DIFF ? 3 : 1) * YF, "element buffer");
+  static __device__ __forceinline__ int nodal(int l) { return NOD + (LN == N ? l : l + l / N); }
+  static_assert(LN == N || LN == N + 1, "nodal()");
+};
+// The dense nodal vector at the start of a buffer.
+struct DenseNodal {
+  static __device__ __forceinline__ int nodal(int l) { return l; }
+};
+
+// Barrier between the stages of one element's threads.  Where a wave holds whole elements,
+// they exchange data inside it only, and LDS keeps a wave's accesses in order (p = 2 and 6
+// without the workgroup's barriers: 201 -> 185 us at 72^3 p = 2, float64).
+// (TH: threads of the workgroup)
+template <int P, int TH = Dims<P>::THREADS>
+__device__ __forceinline__ void elem_sync() {
+  if constexpr (64 % Dims<P>::TPE == 0 || TH <= 64) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  } else {
+    __syncthreads();
+  }
+}
 
 // The 1D tables as compile-time constants of the order P (q = P + 2): after loop
 // unrolling every table entry is a literal, so no table lives in registers or memory.
@@ -192,28 +242,36 @@ struct Nodes {
 #pragma unroll
     for (int k = 0; k < NL; ++k) v[k] = xm[c[k] & kDofMask];
   }
+  // Keep the loads of v where they were written: under the condition of their use, each would
+  // be issued in a branch of its own after whatever is waited for before it.
+  template <typename T>
+  static __device__ __forceinline__ void pin(T (&v)[NL]) {
+#pragma unroll
+    for (int k = 0; k < NL; ++k) asm volatile("" : "+v"(v[k]));
+  }
   __device__ __forceinline__ void keep(int32_t *smap, int t) const {
 #pragma unroll
     for (int k = 0; k < NL; ++k) smap[node(t, k)] = d[k];
   }
 };
 
-// Gather the element's nodal values (essential DoFs as 0, unless ESS) into buf[k][j][i].
-// Ends with a barrier.
-template <int P, typename T, bool ESS = false>
+// Gather the element's nodal values (essential DoFs as 0) into the nodal vector of layout
+// Lds<P>.  Ends with a barrier.
+template <int P, typename T>
 __device__ __forceinline__ void gather_e(T *buf, int t, bool active, const Nodes<P> &nd,
                                          const T *__restrict__ xm) {
   T v[Nodes<P>::NL];
   nd.load_values(xm, v);
+  nd.pin(v);
 #pragma unroll
   for (int k = 0; k < Nodes<P>::NL; ++k)
-    buf[Nodes<P>::node(t, k)] = (active && (ESS || nd.c[k] >= 0)) ? v[k] : T(0);
-  __syncthreads();
+    buf[Lds<P>::nodal(Nodes<P>::node(t, k))] = (active && nd.c[k] >= 0) ? v[k] : T(0);
+  elem_sync<P>();
 }
 
-// Output of the element vector buf[l]: sole DoFs -> y, shared nodes -> their E-vector
+// Output of the element vector at L::nodal: sole DoFs -> y, shared nodes -> their E-vector
 // entry, essential -> nothing.  The destinations come from LDS, kept by the gather.
-template <int P, typename T>
+template <int P, typename T, class L = DenseNodal>
 __device__ __forceinline__ void emit_e(const T *buf, int t, bool active, const int32_t *smap,
                                        T *__restrict__ Y, T *__restrict__ y) {
   using D = Dims<P>;
@@ -222,7 +280,7 @@ __device__ __forceinline__ void emit_e(const T *buf, int t, bool active, const i
   for (int k = 0; k < NL; ++k) {
     const int l = Nodes<P>::node(t, k);
     const int32_t c = smap[l];
-    const T v = buf[l];
+    const T v = buf[L::nodal(l)];
     // one predicated store per node: the destination is selected, not branched to
     if (active && t + k * D::TPE < D::N3 && c >= 0) ((c & kSoleBit) ? y : Y)[c & kDofMask] = v;
   }
@@ -245,9 +303,10 @@ __device__ __forceinline__ double block_sum_d(double v, double *sh) {
 }
 
 // xi_1 contraction: [k][j][i] -> [k][j][a] with B (field 0) and, if DIFF, G (field 1).
-template <int P, typename T, bool DIFF>
+template <int P, typename T, bool DIFF, int TH = Dims<P>::THREADS>
 __device__ __forceinline__ void fwd_x(T *buf, int t) {
   using D = Dims<P>;
+  using L = Lds<P, DIFF>;
   constexpr int N = D::N, Q = D::Q;
   const bool w = t < D::N2;
   const int j = t % N, k = t / N;
@@ -255,27 +314,27 @@ __device__ __forceinline__ void fwd_x(T *buf, int t) {
   if (w) {
     T in[N];
 #pragma unroll
-    for (int i = 0; i < N; ++i) in[i] = buf[(k * N + j) * N + i];
+    for (int i = 0; i < N; ++i) in[i] = buf[L::NOD + (k * N + j) * L::LN + i];
     const auto sp = eo::split(in);
     eo::apply<eo::Tab1<P, 0>>(sp, ob);
     if constexpr (DIFF) eo::apply<eo::Tab1<P, 1>>(sp, og);
   }
-  __syncthreads();
   if (w) {
 #pragma unroll
     for (int a = 0; a < Q; ++a) {
-      buf[(k * N + j) * Q + a] = ob[a];
-      if constexpr (DIFF) buf[D::QN2 + (k * N + j) * Q + a] = og[a];
+      buf[k * L::SK + j * L::LQ + a] = ob[a];
+      if constexpr (DIFF) buf[L::XF + k * L::SK + j * L::LQ + a] = og[a];
     }
   }
-  __syncthreads();
+  elem_sync<P, TH>();
 }
 
 // xi_2 contraction: [k][j][a] -> [k][b][a]: field 0 = B(B x), and if DIFF
 // field 1 = G_y(B_x x) (for d/dxi_2), field 2 = B_y(G_x x) (for d/dxi_1).
-template <int P, typename T, bool DIFF>
+template <int P, typename T, bool DIFF, int TH = Dims<P>::THREADS>
 __device__ __forceinline__ void fwd_y(T *buf, int t) {
   using D = Dims<P>;
+  using L = Lds<P, DIFF>;
   constexpr int N = D::N, Q = D::Q;
   const bool w = t < Q * N;
   const int a = t % Q, k = t / Q;
@@ -284,8 +343,8 @@ __device__ __forceinline__ void fwd_y(T *buf, int t) {
     T ib[N], ig[N];
 #pragma unroll
     for (int j = 0; j < N; ++j) {
-      ib[j] = buf[(k * N + j) * Q + a];
-      if constexpr (DIFF) ig[j] = buf[D::QN2 + (k * N + j) * Q + a];
+      ib[j] = buf[k * L::SK + j * L::LQ + a];
+      if constexpr (DIFF) ig[j] = buf[L::XF + k * L::SK + j * L::LQ + a];
     }
     const auto sb = eo::split(ib);
     eo::apply<eo::Tab1<P, 0>>(sb, obb);
@@ -294,40 +353,41 @@ __device__ __forceinline__ void fwd_y(T *buf, int t) {
       eo::apply<eo::Tab1<P, 0>>(eo::split(ig), obg);
     }
   }
-  __syncthreads();
+  elem_sync<P, TH>();
   if (w) {
 #pragma unroll
     for (int b = 0; b < Q; ++b) {
-      buf[(k * Q + b) * Q + a] = obb[b];
+      buf[k * L::SP + b * Q + a] = obb[b];
       if constexpr (DIFF) {
-        buf[D::NQ2 + (k * Q + b) * Q + a] = ogb[b];
-        buf[2 * D::NQ2 + (k * Q + b) * Q + a] = obg[b];
+        buf[L::YF + k * L::SP + b * Q + a] = ogb[b];
+        buf[2 * L::YF + k * L::SP + b * Q + a] = obg[b];
       }
     }
   }
-  __syncthreads();
+  elem_sync<P, TH>();
 }
 
 // Read the xi_3 lines of thread t = a + q b (no barrier).
 template <int P, typename T, bool DIFF>
 __device__ __forceinline__ void load_z(const T *buf, int t, T (&zbb)[P + 1], T (&zgb)[P + 1],
                                        T (&zbg)[P + 1]) {
-  using D = Dims<P>;
+  using L = Lds<P, DIFF>;
 #pragma unroll
-  for (int k = 0; k < D::N; ++k) {
-    zbb[k] = buf[k * D::Q2 + t];
+  for (int k = 0; k < L::N; ++k) {
+    zbb[k] = buf[k * L::SP + t];
     if constexpr (DIFF) {
-      zgb[k] = buf[D::NQ2 + k * D::Q2 + t];
-      zbg[k] = buf[2 * D::NQ2 + k * D::Q2 + t];
+      zgb[k] = buf[L::YF + k * L::SP + t];
+      zbg[k] = buf[2 * L::YF + k * L::SP + t];
     }
   }
 }
 
 // Transposed xi_2: [k][b][a] (fields p1, p2, p3) -> [k][j][a] (fields r1, r2) with
 // r1 = B^T p1 + G^T p2 and r2 = B^T p3.
-template <int P, typename T, bool DIFF>
+template <int P, typename T, bool DIFF, int TH = Dims<P>::THREADS>
 __device__ __forceinline__ void bwd_y(T *buf, int t) {
   using D = Dims<P>;
+  using L = Lds<P, DIFF>;
   using BT = eo::Tab1<P, 0>;
   using GT = eo::Tab1<P, 1>;
   constexpr int N = D::N, Q = D::Q;
@@ -338,10 +398,10 @@ __device__ __forceinline__ void bwd_y(T *buf, int t) {
     T i1[Q], i2[Q], i3[Q];
 #pragma unroll
     for (int b = 0; b < Q; ++b) {
-      i1[b] = buf[(k * Q + b) * Q + a];
+      i1[b] = buf[k * L::SP + b * Q + a];
       if constexpr (DIFF) {
-        i2[b] = buf[D::NQ2 + (k * Q + b) * Q + a];
-        i3[b] = buf[2 * D::NQ2 + (k * Q + b) * Q + a];
+        i2[b] = buf[L::YF + k * L::SP + b * Q + a];
+        i3[b] = buf[2 * L::YF + k * L::SP + b * Q + a];
       }
     }
     eo::Acc<N, T> A1, A2;
@@ -365,21 +425,22 @@ __device__ __forceinline__ void bwd_y(T *buf, int t) {
     A1.finish(r1);
     if constexpr (DIFF) A2.finish(r2);
   }
-  __syncthreads();
+  elem_sync<P, TH>();
   if (w) {
 #pragma unroll
     for (int j = 0; j < N; ++j) {
-      buf[(k * N + j) * Q + a] = r1[j];
-      if constexpr (DIFF) buf[D::QN2 + (k * N + j) * Q + a] = r2[j];
+      buf[k * L::SK + j * L::LQ + a] = r1[j];
+      if constexpr (DIFF) buf[L::XF + k * L::SK + j * L::LQ + a] = r2[j];
     }
   }
-  __syncthreads();
+  elem_sync<P, TH>();
 }
 
 // Transposed xi_1: [k][j][a] (r1, r2) -> nodal [k][j][i] = B^T r1 + G^T r2.
-template <int P, typename T, bool DIFF>
+template <int P, typename T, bool DIFF, int TH = Dims<P>::THREADS>
 __device__ __forceinline__ void bwd_x(T *buf, int t) {
   using D = Dims<P>;
+  using L = Lds<P, DIFF>;
   using BT = eo::Tab1<P, 0>;
   using GT = eo::Tab1<P, 1>;
   constexpr int N = D::N, Q = D::Q;
@@ -390,8 +451,8 @@ __device__ __forceinline__ void bwd_x(T *buf, int t) {
     T i1[Q], i2[Q];
 #pragma unroll
     for (int a = 0; a < Q; ++a) {
-      i1[a] = buf[(k * N + j) * Q + a];
-      if constexpr (DIFF) i2[a] = buf[D::QN2 + (k * N + j) * Q + a];
+      i1[a] = buf[k * L::SK + j * L::LQ + a];
+      if constexpr (DIFF) i2[a] = buf[L::XF + k * L::SK + j * L::LQ + a];
     }
     eo::Acc<N, T> A;
     A.zero();
@@ -406,12 +467,11 @@ __device__ __forceinline__ void bwd_x(T *buf, int t) {
     }
     A.finish(yo);
   }
-  __syncthreads();
   if (w) {
 #pragma unroll
-    for (int i = 0; i < N; ++i) buf[(k * N + j) * N + i] = yo[i];
+    for (int i = 0; i < N; ++i) buf[L::NOD + (k * N + j) * L::LN + i] = yo[i];
   }
-  __syncthreads();
+  elem_sync<P, TH>();
 }
 
 // Index of the element batch of this workgroup such that XCD k (workgroups are
@@ -425,14 +485,21 @@ __device__ __forceinline__ int xcd_block() {
 
 // How the element kernel of order P and precision T is built (chosen by measurement on
 // MI355X):
-//   ZLDS   the xi_3 stage's input lines are read from LDS again for every slice pair
-//          instead of being held in registers for the whole stage (fewer registers);
-//   OCC    minimum waves per SIMD the kernel is compiled for (launch bound);
-//   E      elements per workgroup (q^2 threads each).
-template <int P, typename T>
+//   ZLDS   the xi_3 stage's input lines are read from LDS again for every slice pair, one at
+//          a time, instead of being held in registers for the whole stage;
+//   OCC    minimum waves per SIMD the kernel is compiled for (launch bound): three float64
+//          ones at p = 5 and 6 as well (29^3 p = 5 115 -> 101 us, 24^3 p = 6 101 -> 82 us,
+//          Helmholtz with nu), although p = 5 spills 24 bytes for it (12^3: 16.6 -> 17.0 us).
+//          Four at p = 3 and 4 would spill 12 and 52 bytes (1.00 and 0.85 times as fast);
+//   E      elements per workgroup (q^2 threads each).  The applies take as many as fill one
+//          wave at p = 1, whose stages then need no barriers, and two waves at p = 3 (1.05
+//          and 1.03 - 1.06 times as fast as four waves); one to three waves were slower at p = 4, 5 and 8
+//          (0.90 - 0.98), and the CG iteration's kernels read the partial sums once per
+//          workgroup.  Eight waves at p = 8, which leave few lanes idle: 0.94 (float32 0.79).
+template <int P, typename T, int CG>
 struct ApplyCfg {
   static constexpr bool F64 = sizeof(T) == 8;
-  static constexpr int E = Dims<P>::E;
+  static constexpr int E = CG ? Dims<P>::E : P == 1 ? 7 : P == 3 ? 5 : Dims<P>::E;
   static constexpr int THREADS = E * Dims<P>::TPE;
   static constexpr bool ZLDS = F64 ? (P >= 5) : (P == 6 || P == 8);
   static constexpr int OCC = F64 ? Dims<P>::OCC : (P <= 6 ? 4 : 3);
@@ -452,7 +519,10 @@ struct ApplyCfg {
 // at 32^3 p = 4 in float64, 396 MB were factors.  Formed, they cost 35 to 40 operations a
 // point, and the kernel is bound by VALU issue, LDS and the latency between its barriers:
 // 120.3 -> 77.3 us there, 212 -> 126 us for nu = 1 at 63 x 61 x 59 p = 2, float32 32^3 p = 8
-// 341 -> 290 us.
+// 341 -> 290 us.  With the layouts of Lds, eight barriers a workgroup instead of eleven, and
+// every load of the prologue issued before the first wait for the map's followers: 72, 107 and
+// 288 us.  Of 107 us at 36^3 p = 4 the loads, stores and the assembly alone took 68 and the
+// quadrature function 20; of a workgroup's 20000 cycles, its loads took 7000 and VALU issue 3900.
 //
 // Work items are (element, member) pairs, pair v = e * nbatch + m, E per workgroup: the
 // members of one element run side by side (in the same workgroup or in neighbouring
@@ -463,7 +533,7 @@ struct ApplyCfg {
 // of p.Ap are then the element energies at the quadrature points, sum v u + g . grad_ref u, plus
 // p^2 of the essential DoFs at the element that carries their flag (kEssOwnerBit).
 template <int P, typename T, int OP, bool NU, int CG>
-__global__ void __launch_bounds__((ApplyCfg<P, T>::THREADS), (ApplyCfg<P, T>::OCC))
+__global__ void __launch_bounds__((ApplyCfg<P, T, CG>::THREADS), (ApplyCfg<P, T, CG>::OCC))
 apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
              const double *__restrict__ cw, int64_t cw_mstride, double alpha, double beta, int64_t nelem,
              int nbatch, int64_t ndof, const T *__restrict__ x, T *__restrict__ Y,
@@ -472,15 +542,17 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
              int64_t part_mstride, CgIn cg) {
   using D = Dims<P>;
   constexpr int N = D::N, Q = D::Q, Q2 = D::Q2, Q3 = D::Q3, N3 = D::N3;
-  constexpr int TPE = D::TPE, E = ApplyCfg<P, T>::E, THREADS = ApplyCfg<P, T>::THREADS;
+  constexpr int TPE = D::TPE, E = ApplyCfg<P, T, CG>::E, THREADS = ApplyCfg<P, T, CG>::THREADS;
   constexpr bool MASS = (OP == 0) || (OP == 2);
   constexpr bool DIFF = (OP == 1) || (OP == 2);
+  using LD = Lds<P, DIFF>;
 
   constexpr bool POS = evec_dof_ordered(P);
   // element buffers; after the output step also the block sum of the fused dot product
-  static_assert(E * D::BUF * sizeof(T) >= 8 * sizeof(double), "block sum space");
-  __shared__ __align__(16) T smem[E * D::BUF];
+  static_assert(E * LD::BUF * sizeof(T) >= 8 * sizeof(double), "block sum space");
+  __shared__ __align__(16) T smem[E * LD::BUF];
   __shared__ __align__(16) double sgeo[E * kGeoStride];  // the elements' trilinear coefficients
+  __shared__ __align__(16) double sgauss[E * 2 * Q];     // the Gauss rule, for each element's threads
   __shared__ int32_t smap_all[E * N3];  // the elements' map entries, kept for the output
   const int le = threadIdx.x / TPE;
   const int t = threadIdx.x - le * TPE;
@@ -499,7 +571,7 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
     rel = rr / (uint32_t)nbatch;
     m = rr - rel * (uint32_t)nbatch;
   }
-  T *buf = smem + le * D::BUF;
+  T *buf = smem + le * LD::BUF;
   double dot = 0.0;  // CG: the thread's part of p.Ap
 
   {
@@ -510,7 +582,7 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
     Nodes<P> nd;
     nd.load_map(z, t, rel);
     nd.load_rank(z, t);
-    constexpr int NW = THREADS / 64;
+    constexpr int NW = CG ? THREADS / 64 : 1;
     PartLoads<NW, 2> up;  // CG: the update's partials of the workgroup's first member
     if constexpr (CG)
       if (!cg.ready) up.load(cg.upart + (int64_t)r0 * 4 * cg.unblk, cg.unblk);
@@ -527,15 +599,27 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
 #pragma unroll
       for (int c = 0; c < Q; ++c) cv[c] = ce[c * Q2];
     }
-    nd.template load_dest<POS>(z, rel);
+    static_assert(sizeof(rules::GaussRule<Q>) == 2 * Q * sizeof(double) && TPE >= 2 * Q, "points, then weights");
+    const int gi = t < 2 * Q ? t : 2 * Q - 1;
+    const double gq = ld<double>(&kGaussRule<Q>, (uint32_t)gi * 8u);
     int32_t *smap = smap_all + le * N3;
+    T v[CG ? 1 : Nodes<P>::NL];
+    if constexpr (!CG) nd.load_values(xm, v);
+    nd.template load_dest<POS>(z, rel);
 #pragma unroll
     for (int k = 0; k < NG; ++k)
       sgeo[le * kGeoStride + (t + k * TPE < kGeoStride ? t + k * TPE : kGeoStride - 1)] = gv[k];
-    nd.keep(smap, t);
+    double *sgq = sgauss + le * 2 * Q;
+    sgq[gi] = gq;
     if constexpr (!CG) {
-      gather_e<P, T>(buf, t, active, nd, xm);
+      nd.pin(v);
+      nd.keep(smap, t);
+#pragma unroll
+      for (int k = 0; k < Nodes<P>::NL; ++k)
+        buf[LD::nodal(Nodes<P>::node(t, k))] = (active && nd.c[k] >= 0) ? v[k] : T(0);
+      elem_sync<P, THREADS>();
     } else {
+      nd.keep(smap, t);
       constexpr int NL = Nodes<P>::NL;
       T zr[NL], zd[NL], zp[NL];
       if constexpr (CG == 1) {
@@ -552,6 +636,9 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
         for (int j = 0; j < NL; ++j) zd[j] = T(1);
       }
       nd.load_values((const T *)cg.p + (int64_t)m * ndof, zp);
+      nd.pin(zr);
+      nd.pin(zd);
+      nd.pin(zp);
       // the states of the workgroup's members: here distinct ones, the k-th (r0 + k) mod nbatch
       __shared__ double sums[E][4][NW];
       const int here = nbatch < count ? nbatch : count;
@@ -601,14 +688,14 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
 #pragma unroll
       for (int j = 0; j < NL; ++j) {
         const T pv = cg_dir(zd[j], zr[j], zs, beta, zp[j]);
-        buf[Nodes<P>::node(t, j)] = (active && nd.c[j] >= 0) ? pv : T(0);
+        buf[LD::nodal(Nodes<P>::node(t, j))] = (active && nd.c[j] >= 0) ? pv : T(0);
         if (active && t + j * TPE < N3 && nd.c[j] < 0 && (nd.c[j] & kEssOwnerBit)) dot += (double)pv * (double)pv;
       }
-      __syncthreads();
+      elem_sync<P, THREADS>();
     }
-    using C = ApplyCfg<P, T>;
-    fwd_x<P, T, DIFF>(buf, t);
-    fwd_y<P, T, DIFF>(buf, t);
+    using C = ApplyCfg<P, T, CG>;
+    fwd_x<P, T, DIFF, THREADS>(buf, t);
+    fwd_y<P, T, DIFF, THREADS>(buf, t);
 
     // xi_3 contraction, quadrature function, transposed xi_3: thread = line (a, b),
     // processed by symmetric slice pairs (c, q-1-c).
@@ -618,31 +705,29 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
       constexpr rules::GaussRule<Q> gr = rules::gauss<Q>();
       std::conditional_t<sizeof(T) == 8, LineGeom, LineMetric> L;
       const int la = t % Q, lb = t / Q;
-      L.init(sgeo + le * kGeoStride, kGaussRule<Q>.x[la], kGaussRule<Q>.x[lb]);
-      const double wab = kGaussRule<Q>.w[la] * kGaussRule<Q>.w[lb];
+      L.init(sgeo + le * kGeoStride, sgq[la], sgq[lb]);
+      const double wab = sgq[Q + la] * sgq[Q + lb];
       const double wm = alpha * wab;             // mass weight of the line
       const double ws = NU ? beta : beta * wab;  // diffusion weight (cw holds w)
       // the stage's input lines (split into even and odd parts), held in registers or,
       // with ZLDS, read from LDS again for every slice pair
-      eo::Split<N, T> rbb{}, rgb{}, rbg{};
-      auto read_lines = [&](eo::Split<N, T> &sbb, eo::Split<N, T> &sgb, eo::Split<N, T> &sbg) {
-        T zbb[N], zgb[N], zbg[N];
-        load_z<P, T, DIFF>(buf, t, zbb, zgb, zbg);
-        sbb = eo::split(zbb);
-        if constexpr (DIFF) {
-          sgb = eo::split(zgb);
-          sbg = eo::split(zbg);
-        }
+      eo::Split<N, T> held[DIFF ? 3 : 1];
+      auto read_line = [&](int f) {
+        T z[N];
+#pragma unroll
+        for (int k = 0; k < N; ++k) z[k] = buf[f * LD::YF + k * LD::SP + t];
+        return eo::split(z);
       };
-      if constexpr (!C::ZLDS) read_lines(rbb, rgb, rbg);
-      auto zlines = [&](eo::Split<N, T> &sbb, eo::Split<N, T> &sgb, eo::Split<N, T> &sbg) {
+      if constexpr (!C::ZLDS) {
+#pragma unroll
+        for (int f = 0; f < (DIFF ? 3 : 1); ++f) held[f] = read_line(f);
+      }
+      auto zline = [&](int f) {
         if constexpr (C::ZLDS) {
           asm volatile("" ::: "memory");  // a fresh LDS read, not a reuse of the last one
-          read_lines(sbb, sgb, sbg);
+          return read_line(f);
         } else {
-          sbb = rbb;
-          sgb = rgb;
-          sbg = rbg;
+          return held[f];
         }
       };
       eo::Acc<N, T> A1, A2, A3;
@@ -702,13 +787,12 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
 #pragma unroll
       for (int c = 0; c < Q / 2; ++c) {
         T u0 = 0, u1 = 0, dx0 = 0, dx1 = 0, dy0 = 0, dy1 = 0, dz0 = 0, dz1 = 0;
-        eo::Split<N, T> sbb, sgb, sbg;
-        zlines(sbb, sgb, sbg);
+        const eo::Split<N, T> sbb = zline(0);
         if constexpr (MASS) row_pair(BT{}, sbb, c, u0, u1);
         if constexpr (DIFF) {
           row_pair(GT{}, sbb, c, dz0, dz1);
-          row_pair(BT{}, sgb, c, dy0, dy1);
-          row_pair(BT{}, sbg, c, dx0, dx1);
+          row_pair(BT{}, zline(1), c, dy0, dy1);
+          row_pair(BT{}, zline(2), c, dx0, dx1);
         }
         T v0, g10, g20, g30, v1, g11, g21, g31;
         qfun(c, u0, dx0, dy0, dz0, v0, g10, g20, g30);
@@ -722,13 +806,12 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
       }
       if constexpr (Q % 2 == 1) {
         T u = 0, dx = 0, dy = 0, dz = 0;
-        eo::Split<N, T> sbb, sgb, sbg;
-        zlines(sbb, sgb, sbg);
+        const eo::Split<N, T> sbb = zline(0);
         if constexpr (MASS) u = row_mid(BT{}, sbb);
         if constexpr (DIFF) {
           dz = row_mid(GT{}, sbb);
-          dy = row_mid(BT{}, sgb);
-          dx = row_mid(BT{}, sbg);
+          dy = row_mid(BT{}, zline(1));
+          dx = row_mid(BT{}, zline(2));
         }
         T v, g1, g2, g3;
         qfun(Q / 2, u, dx, dy, dz, v, g1, g2, g3);
@@ -745,22 +828,22 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
         A2.finish(p2);
         A3.finish(p3);
       }
-      __syncthreads();
+      // a thread's lines replace those it read: no barrier before the stores
 #pragma unroll
       for (int k = 0; k < N; ++k) {
-        buf[k * Q2 + t] = p1[k];
+        buf[k * LD::SP + t] = p1[k];
         if constexpr (DIFF) {
-          buf[D::NQ2 + k * Q2 + t] = p2[k];
-          buf[2 * D::NQ2 + k * Q2 + t] = p3[k];
+          buf[LD::YF + k * LD::SP + t] = p2[k];
+          buf[2 * LD::YF + k * LD::SP + t] = p3[k];
         }
       }
-      __syncthreads();
+      elem_sync<P, THREADS>();
     }
 
-    bwd_y<P, T, DIFF>(buf, t);
-    bwd_x<P, T, DIFF>(buf, t);
+    bwd_y<P, T, DIFF, THREADS>(buf, t);
+    bwd_x<P, T, DIFF, THREADS>(buf, t);
     T *Ym = Y + (int64_t)m * estride, *ym = y + (int64_t)m * ndof;
-    emit_e<P, T>(buf, t, active, smap, Ym, ym);
+    emit_e<P, T, LD>(buf, t, active, smap, Ym, ym);
     if constexpr (CG) {
       // one sum per member; the block's pairs v_lo.. hold members (v_lo + k) mod nbatch,
       // k < count (a uniform test: members without a pair here get 0 without a sum)
@@ -780,7 +863,7 @@ hipError_t launch_apply_pt(const ApplyArgs &a, const CgIn &g, hipStream_t s) {
   if (a.nelem <= 0 || a.nbatch <= 0) return hipSuccess;
   if ((a.pos != nullptr) != evec_dof_ordered(P)) return hipErrorInvalidValue;
   if (CG && !a.part) return hipErrorInvalidValue;
-  using C = ApplyCfg<P, T>;
+  using C = ApplyCfg<P, T, CG>;
   dim3 grid((unsigned)((a.nelem * a.nbatch + C::E - 1) / C::E));
   dim3 block(C::THREADS);
 #define SFEM_APPLY(OP, NU)                                                                              \
@@ -796,10 +879,10 @@ hipError_t launch_apply_pt(const ApplyArgs &a, const CgIn &g, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Elements per workgroup of the apply kernel for order P and precision T.
+// Elements per workgroup of the CG iteration's apply kernel for order P and precision T.
 template <int P, typename T>
 int apply_group_elems_pt() {
-  return ApplyCfg<P, T>::E;
+  return ApplyCfg<P, T, 1>::E;
 }
 
 #define SFEM_DISPATCH_P(p, CALL) \

@@ -88,14 +88,14 @@ grad_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo, dou
   using D = Dims<P>;
   constexpr int Q = D::Q, Q2 = D::Q2, Q3 = D::Q3, TPE = D::TPE, E = D::E;
   constexpr rules::GaussRule<Q> gr = rules::gauss<Q>();
-  __shared__ __align__(16) double smem[E * D::BUF];
+  __shared__ __align__(16) double smem[E * Lds<P>::BUF];
   __shared__ __align__(16) double sgeo[E * kGeoStride];
   const int le = threadIdx.x / TPE;
   const int t = threadIdx.x - le * TPE;
   const int64_t e0 = (int64_t)xcd_block() * E;
   const bool active = e0 + le < nei;
   const uint32_t rel = active ? le : 0;
-  double *buf = smem + le * D::BUF;
+  double *buf = smem + le * Lds<P>::BUF;
   Nodes<P> nd;
   nd.load_map(elem_tab<P>(map, nullptr, 1, e0), t, rel);
   put_geo<P>(sgeo + le * kGeoStride, geo, e0, rel, t);
@@ -110,7 +110,7 @@ grad_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo, dou
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < Nodes<P>::NL; ++k)
-      buf[Nodes<P>::node(t, k)] = (active && nd.c[k] >= 0) ? uv[k] : 0.0;
+      buf[Lds<P>::nodal(Nodes<P>::node(t, k))] = (active && nd.c[k] >= 0) ? uv[k] : 0.0;
     __syncthreads();
     fwd_x<P, double, true>(buf, t);
     fwd_y<P, double, true>(buf, t);
@@ -154,7 +154,7 @@ load_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo, int
   using BT = eo::Tab1<P, 0>;
   constexpr int N = D::N, Q = D::Q, Q2 = D::Q2, Q3 = D::Q3, TPE = D::TPE, E = D::E;
   constexpr rules::GaussRule<Q> gr = rules::gauss<Q>();
-  __shared__ __align__(16) double smem[E * D::BUF];
+  __shared__ __align__(16) double smem[E * Lds<P, false>::BUF];
   __shared__ __align__(16) double sgeo[E * kGeoStride];
   __shared__ int32_t smap_all[E * D::N3];
   const int le = threadIdx.x / TPE;
@@ -162,7 +162,7 @@ load_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo, int
   const int64_t e0 = (int64_t)xcd_block() * E;
   const bool active = e0 + le < nei;
   const uint32_t rel = active ? le : 0;
-  double *buf = smem + le * D::BUF;
+  double *buf = smem + le * Lds<P, false>::BUF;
   int32_t *smap = smap_all + le * D::N3;
   double fv[Q];  // the next source's values at the line's points
   auto load_f = [&](int m) {
@@ -200,12 +200,12 @@ load_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo, int
     if constexpr (Q % 2 == 1) A.template add_mid<BT>(fv[Q / 2]);
     A.finish(p1);
 #pragma unroll
-    for (int k = 0; k < N; ++k) buf[k * Q2 + t] = p1[k];
+    for (int k = 0; k < N; ++k) buf[k * Lds<P, false>::SP + t] = p1[k];
     if (m + 1 < nbatch) load_f(m + 1);
     __syncthreads();
     bwd_y<P, double, false>(buf, t);
     bwd_x<P, double, false>(buf, t);
-    emit_e<P, double>(buf, t, active, smap, Y + (int64_t)m * estride,
+    emit_e<P, double, Lds<P, false>>(buf, t, active, smap, Y + (int64_t)m * estride,
                              b + (int64_t)m * ndof);
     __syncthreads();
   }
