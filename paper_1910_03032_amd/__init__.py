@@ -23,7 +23,13 @@ __all__ = ["Operator", "SfemError", "MASS", "DIFFUSION", "HELMHOLTZ", "F64", "F3
 
 
 def _ptr(t):
-    return C.c_void_p(t.data_ptr()) if t is not None and t.numel() > 0 else None
+    return t.data_ptr() if t is not None and t.numel() > 0 else None
+
+
+def _stream_handle(index):
+    """Handle of PyTorch's current stream on GPU index.  Every call passes it on; the Stream
+    object of torch.cuda.current_stream took 1.9 of a small apply's 12 us."""
+    return torch._C._cuda_getCurrentRawStream(index)
 
 
 def check_mesh_shapes(xyz_shape, dofs_shape, ndof, p, ess_shape=None):
@@ -118,8 +124,7 @@ class Operator:
         return st
 
     def _sync_stream(self):
-        s = torch.cuda.current_stream(self.device).cuda_stream
-        self._lib.sfem_set_stream(self._h, C.c_void_p(s))
+        self._lib.sfem_set_stream(self._h, _stream_handle(self.device.index))
 
     def _vec(self, t, dtype, name):
         if not isinstance(t, torch.Tensor):
@@ -176,10 +181,13 @@ class Operator:
         if xv.ndim not in (1, 2):
             raise ValueError("x must have shape [ndof] or [nbatch, ndof]")
         nb = 1 if xv.ndim == 1 else xv.shape[0]
-        y = torch.empty_like(xv) if out is None else out
-        aliased = xv.numel() > 0 and y.data_ptr() == xv.data_ptr()
-        if y.dtype != dtype or not y.is_contiguous() or y.shape != xv.shape or aliased:
-            raise ValueError("out must be a distinct contiguous tensor of x's shape and dtype")
+        if out is None:
+            y = torch.empty_like(xv)
+        else:
+            y = out
+            aliased = xv.numel() > 0 and y.data_ptr() == xv.data_ptr()
+            if y.dtype != dtype or not y.is_contiguous() or y.shape != xv.shape or aliased:
+                raise ValueError("out must be a distinct contiguous tensor of x's shape and dtype")
         prec = F32 if dtype == torch.float32 else F64
         self._check(self._lib.sfem_apply(self._h, op, prec, nb, _ptr(xv), _ptr(y)))
         return y

@@ -505,6 +505,9 @@ struct ApplyCfg {
   static constexpr int OCC = F64 ? Dims<P>::OCC : (P <= 6 ? 4 : 3);
 };
 
+// The plain applies pass no CG inputs (half of the launch's argument bytes).
+struct NoCg {};
+
 // OP: 0 mass, 1 diffusion, 2 helmholtz (matches sfem_op).  Writes y at the sole DoFs
 // and the E-vector Y[m] at the shared nodes.
 //
@@ -539,7 +542,7 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
              int nbatch, int64_t ndof, const T *__restrict__ x, T *__restrict__ Y,
              int64_t estride, const int32_t *__restrict__ pos, int compact, T *__restrict__ y,
              double *__restrict__ part,
-             int64_t part_mstride, CgIn cg) {
+             int64_t part_mstride, std::conditional_t<CG != 0, CgIn, NoCg> cg) {
   using D = Dims<P>;
   constexpr int N = D::N, Q = D::Q, Q2 = D::Q2, Q3 = D::Q3, N3 = D::N3;
   constexpr int TPE = D::TPE, E = ApplyCfg<P, T, CG>::E, THREADS = ApplyCfg<P, T, CG>::THREADS;
@@ -866,10 +869,12 @@ hipError_t launch_apply_pt(const ApplyArgs &a, const CgIn &g, hipStream_t s) {
   using C = ApplyCfg<P, T, CG>;
   dim3 grid((unsigned)((a.nelem * a.nbatch + C::E - 1) / C::E));
   dim3 block(C::THREADS);
+  std::conditional_t<CG != 0, CgIn, NoCg> cg;
+  if constexpr (CG != 0) cg = g;
 #define SFEM_APPLY(OP, NU)                                                                              \
   hipLaunchKernelGGL((apply_kernel<P, T, OP, NU, CG>), grid, block, 0, s, a.map, a.geo, a.cw,           \
                      a.cw_mstride, a.alpha, a.beta, a.nelem, a.nbatch, a.ndof, (const T *)a.x,          \
-                     (T *)a.evec, a.estride, a.pos, a.compact, (T *)a.y, a.part, a.part_mstride, g)
+                     (T *)a.evec, a.estride, a.pos, a.compact, (T *)a.y, a.part, a.part_mstride, cg)
   if (a.op == SFEM_MASS) SFEM_APPLY(0, false);
   else if (a.op == SFEM_DIFFUSION && a.cw) SFEM_APPLY(1, true);
   else if (a.op == SFEM_DIFFUSION) SFEM_APPLY(1, false);
