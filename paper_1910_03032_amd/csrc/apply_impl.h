@@ -488,21 +488,27 @@ __device__ __forceinline__ int xcd_block() {
 //   ZLDS   the xi_3 stage's input lines are read from LDS again for every slice pair, one at
 //          a time, instead of being held in registers for the whole stage;
 //   OCC    minimum waves per SIMD the kernel is compiled for (launch bound): three float64
-//          ones at p = 5 and 6 as well (29^3 p = 5 115 -> 101 us, 24^3 p = 6 101 -> 82 us,
-//          Helmholtz with nu), although p = 5 spills 24 bytes for it (12^3: 16.6 -> 17.0 us).
-//          Four at p = 3 and 4 would spill 12 and 52 bytes (1.00 and 0.85 times as fast);
+//          ones at p = 5 and 6 as well (29^3 p = 5 115 -> 100 us, 24^3 p = 6 101 -> 82 us,
+//          Helmholtz with nu).  Four at p = 3 and 4, and three at p = 7, would spill 44 to
+//          100 bytes (1.00, 0.85 and 0.85 times as fast);
+//   REFORM the output's addresses are formed anew: kept since the gather they cost the stages
+//          up to 15 registers, and with them spills, whose stores wait for the prologue's
+//          loads (12^3 p = 5 16.8 -> 16.3 us, float32 18^3 p = 8 61 -> 59 us with four waves;
+//          without a spill to save 0.5 to 3 % slower);
 //   E      elements per workgroup (q^2 threads each).  The applies take as many as fill one
 //          wave at p = 1, whose stages then need no barriers, and two waves at p = 3 (1.05
-//          and 1.03 - 1.06 times as fast as four waves); one to three waves were slower at p = 4, 5 and 8
-//          (0.90 - 0.98), and the CG iteration's kernels read the partial sums once per
-//          workgroup.  Eight waves at p = 8, which leave few lanes idle: 0.94 (float32 0.79).
+//          and 1.03 - 1.06 times as fast as four waves); one to three waves were slower at
+//          p = 4, 5 and 8 (0.90 - 0.98), and the CG iteration's kernels read the partial sums
+//          once per workgroup.  Eight waves at p = 8, which leave few lanes idle: 0.94
+//          (float32 0.79).
 template <int P, typename T, int CG>
 struct ApplyCfg {
   static constexpr bool F64 = sizeof(T) == 8;
   static constexpr int E = CG ? Dims<P>::E : P == 1 ? 7 : P == 3 ? 5 : Dims<P>::E;
   static constexpr int THREADS = E * Dims<P>::TPE;
-  static constexpr bool ZLDS = F64 ? (P >= 5) : (P == 6 || P == 8);
-  static constexpr int OCC = F64 ? Dims<P>::OCC : (P <= 6 ? 4 : 3);
+  static constexpr bool ZLDS = F64 ? (P >= 5) : (P == 6 || P == 8 || (CG && P >= 4));
+  static constexpr int OCC = F64 ? Dims<P>::OCC : (P <= 6 || (P == 8 && !CG) ? 4 : 3);
+  static constexpr bool REFORM = CG != 0 || P == (F64 ? 5 : 8);
 };
 
 // The plain applies pass no CG inputs (half of the launch's argument bytes).
@@ -545,7 +551,8 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
              int64_t part_mstride, std::conditional_t<CG != 0, CgIn, NoCg> cg) {
   using D = Dims<P>;
   constexpr int N = D::N, Q = D::Q, Q2 = D::Q2, Q3 = D::Q3, N3 = D::N3;
-  constexpr int TPE = D::TPE, E = ApplyCfg<P, T, CG>::E, THREADS = ApplyCfg<P, T, CG>::THREADS;
+  using C = ApplyCfg<P, T, CG>;
+  constexpr int TPE = D::TPE, E = C::E, THREADS = C::THREADS;
   constexpr bool MASS = (OP == 0) || (OP == 2);
   constexpr bool DIFF = (OP == 1) || (OP == 2);
   using LD = Lds<P, DIFF>;
@@ -586,9 +593,14 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
     nd.load_map(z, t, rel);
     nd.load_rank(z, t);
     constexpr int NW = CG ? THREADS / 64 : 1;
-    PartLoads<NW, 2> up;  // CG: the update's partials of the workgroup's first member
-    if constexpr (CG)
-      if (!cg.ready) up.load(cg.upart + (int64_t)r0 * 4 * cg.unblk, cg.unblk);
+    // CG: the update's partials of the workgroup's first member and the state; also when the
+    // state is ready, for loads under a condition are waited for where it ends
+    PartLoads<NW, 2> up;
+    PcgScalars s;
+    if constexpr (CG) {
+      up.load(cg.upart + (int64_t)r0 * 4 * cg.unblk, cg.unblk);
+      copy_state(s, cg.sc[m]);
+    }
     constexpr int NG = (kGeoStride + TPE - 1) / TPE;
     double gv[NG];
 #pragma unroll
@@ -606,25 +618,12 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
     const int gi = t < 2 * Q ? t : 2 * Q - 1;
     const double gq = ld<double>(&kGaussRule<Q>, (uint32_t)gi * 8u);
     int32_t *smap = smap_all + le * N3;
-    T v[CG ? 1 : Nodes<P>::NL];
-    if constexpr (!CG) nd.load_values(xm, v);
-    nd.template load_dest<POS>(z, rel);
-#pragma unroll
-    for (int k = 0; k < NG; ++k)
-      sgeo[le * kGeoStride + (t + k * TPE < kGeoStride ? t + k * TPE : kGeoStride - 1)] = gv[k];
-    double *sgq = sgauss + le * 2 * Q;
-    sgq[gi] = gq;
+    constexpr int NL = Nodes<P>::NL;
+    T v[CG ? 1 : NL];
+    T zr[CG ? NL : 1], zd[CG ? NL : 1], zp[CG ? NL : 1];
     if constexpr (!CG) {
-      nd.pin(v);
-      nd.keep(smap, t);
-#pragma unroll
-      for (int k = 0; k < Nodes<P>::NL; ++k)
-        buf[LD::nodal(Nodes<P>::node(t, k))] = (active && nd.c[k] >= 0) ? v[k] : T(0);
-      elem_sync<P, THREADS>();
+      nd.load_values(xm, v);
     } else {
-      nd.keep(smap, t);
-      constexpr int NL = Nodes<P>::NL;
-      T zr[NL], zd[NL], zp[NL];
       if constexpr (CG == 1) {
         nd.load_values((const T *)cg.r + (int64_t)m * ndof, zr);
         nd.load_values((const T *)cg.dinv + (int64_t)m * cg.dinv_mstride, zd);
@@ -639,15 +638,25 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
         for (int j = 0; j < NL; ++j) zd[j] = T(1);
       }
       nd.load_values((const T *)cg.p + (int64_t)m * ndof, zp);
-      nd.pin(zr);
-      nd.pin(zd);
-      nd.pin(zp);
+    }
+    nd.template load_dest<POS>(z, rel);
+#pragma unroll
+    for (int k = 0; k < NG; ++k)
+      sgeo[le * kGeoStride + (t + k * TPE < kGeoStride ? t + k * TPE : kGeoStride - 1)] = gv[k];
+    double *sgq = sgauss + le * 2 * Q;
+    sgq[gi] = gq;
+    if constexpr (!CG) {
+      nd.pin(v);
+      nd.keep(smap, t);
+#pragma unroll
+      for (int k = 0; k < NL; ++k)
+        buf[LD::nodal(Nodes<P>::node(t, k))] = (active && nd.c[k] >= 0) ? v[k] : T(0);
+      elem_sync<P, THREADS>();
+    } else {
       // the states of the workgroup's members: here distinct ones, the k-th (r0 + k) mod nbatch
       __shared__ double sums[E][4][NW];
       const int here = nbatch < count ? nbatch : count;
       const int k = le < here ? le : le % here;
-      PcgScalars s;
-      copy_state(s, cg.sc[m]);
       auto other_parts = [&](double (&sh)[4][NW], int64_t mm, bool all) {
         const double *p = cg.upart + mm * 4 * cg.unblk;
         PartLoads<NW, 2> q;
@@ -687,6 +696,10 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
           }
         }
       }
+      nd.pin(zr);
+      if constexpr (CG == 1) nd.pin(zd);
+      nd.pin(zp);
+      nd.keep(smap, t);
       const T beta = (T)s.beta, zs = (T)s.zshift;
 #pragma unroll
       for (int j = 0; j < NL; ++j) {
@@ -696,7 +709,6 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
       }
       elem_sync<P, THREADS>();
     }
-    using C = ApplyCfg<P, T, CG>;
     fwd_x<P, T, DIFF, THREADS>(buf, t);
     fwd_y<P, T, DIFF, THREADS>(buf, t);
 
@@ -846,7 +858,9 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
     bwd_y<P, T, DIFF, THREADS>(buf, t);
     bwd_x<P, T, DIFF, THREADS>(buf, t);
     T *Ym = Y + (int64_t)m * estride, *ym = y + (int64_t)m * ndof;
-    emit_e<P, T, LD>(buf, t, active, smap, Ym, ym);
+    int te = t;
+    if constexpr (C::REFORM) asm volatile("" : "+v"(te));
+    emit_e<P, T, LD>(buf, te, active, smap, Ym, ym);
     if constexpr (CG) {
       // one sum per member; the block's pairs v_lo.. hold members (v_lo + k) mod nbatch,
       // k < count (a uniform test: members without a pair here get 0 without a sum)
