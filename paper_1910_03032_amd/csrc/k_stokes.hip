@@ -67,13 +67,33 @@ __device__ __forceinline__ double row_mid(const eo::Split<TB::NI, double> &x) {
   return v;
 }
 
-// Forward reference gradient of a nodal field of order PO (NI = PO + 1 nodes per
-// direction, in buf as [k][j][i]) for the q x q threads of an element: stages xi_1 and
-// xi_2 through LDS (even-odd contractions); the xi_3 contraction is the caller's.
+// Where the stages keep a field of order PO in an element's buffer: [k][j][i] at NOD, then
+// [k][j][a] (line stride LQ, plane SK, field XF), then [k][b][a] (plane SP, field YF).  Dense
+// serves any (order, q); Padded the velocity, with the strides of Lds<P> and the nodal vector
+// past the [k][j][a] fields, where the xi_1 stages need no barrier between reads and writes.
 template <int PO, int Q>
+struct Dense {
+  static constexpr int NI = PO + 1, LQ = Q, SK = NI * Q, XF = NI * SK, SP = Q * Q, YF = NI * SP, NOD = 0;
+};
+template <int P>
+struct Padded {
+  static constexpr int LQ = Lds<P>::LQ, SK = Lds<P>::SK, XF = Lds<P>::XF, SP = Lds<P>::SP, YF = Lds<P>::YF,
+                       NOD = Lds<P>::NOD;
+  static_assert(Lds<P>::FULL >= NOD + (P + 1) * (P + 1) * (P + 1) && Lds<P>::FULL >= Dims<P>::BUF, "element buffer");
+};
+// (p = 8: the padded strides' addresses spill in the curl and coupling kernels, 11^3 curl 51.3 ->
+// 52.7 us; p = 2, where a wave holds its elements: 42^3 curl 86 -> 78, Stokes 205 -> 188 us; p = 6
+// 5 to 7 %, the others 0 to 3 %)
+template <int P>
+using VelLay = std::conditional_t<(P < 8), Padded<P>, Dense<P, P + 2>>;
+
+// Forward reference gradient of a nodal field of order PO (NI = PO + 1 nodes per
+// direction, in buf + NOD as [k][j][i]) for the q x q threads of an element: stages xi_1 and
+// xi_2 through LDS (even-odd contractions); the xi_3 contraction is the caller's.
+template <int PO, int Q, class L = Dense<PO, Q>>
 __device__ __forceinline__ void fwd_grad_xy(double *buf, int t) {
   constexpr int NI = PO + 1;
-  constexpr int N2 = NI * NI, QN2 = Q * N2, NQ2 = NI * Q * Q;
+  constexpr int N2 = NI * NI;
   using BT = TabEO<PO, Q, 0>;
   using GT = TabEO<PO, Q, 1>;
   {  // xi_1: [k][j][i] -> [k][j][a] (B and G)
@@ -83,20 +103,20 @@ __device__ __forceinline__ void fwd_grad_xy(double *buf, int t) {
     if (w) {
       double in[NI];
 #pragma unroll
-      for (int i = 0; i < NI; ++i) in[i] = buf[(k * NI + j) * NI + i];
+      for (int i = 0; i < NI; ++i) in[i] = buf[L::NOD + (k * NI + j) * NI + i];
       const auto sp = eo::split(in);
       eo::apply<BT>(sp, ob);
       eo::apply<GT>(sp, og);
     }
-    __syncthreads();
+    if constexpr (L::NOD == 0) elem_sync<Q - 2>();
     if (w) {
 #pragma unroll
       for (int a = 0; a < Q; ++a) {
-        buf[(k * NI + j) * Q + a] = ob[a];
-        buf[QN2 + (k * NI + j) * Q + a] = og[a];
+        buf[k * L::SK + j * L::LQ + a] = ob[a];
+        buf[L::XF + k * L::SK + j * L::LQ + a] = og[a];
       }
     }
-    __syncthreads();
+    elem_sync<Q - 2>();
   }
   {  // xi_2: [k][j][a] -> [k][b][a]: B(Bx), G(Bx), B(Gx)
     const bool w = t < Q * NI;
@@ -106,31 +126,31 @@ __device__ __forceinline__ void fwd_grad_xy(double *buf, int t) {
       double ib[NI], ig[NI];
 #pragma unroll
       for (int j = 0; j < NI; ++j) {
-        ib[j] = buf[(k * NI + j) * Q + a];
-        ig[j] = buf[QN2 + (k * NI + j) * Q + a];
+        ib[j] = buf[k * L::SK + j * L::LQ + a];
+        ig[j] = buf[L::XF + k * L::SK + j * L::LQ + a];
       }
       const auto sb = eo::split(ib);
       eo::apply<BT>(sb, obb);
       eo::apply<GT>(sb, ogb);
       eo::apply<BT>(eo::split(ig), obg);
     }
-    __syncthreads();
+    elem_sync<Q - 2>();
     if (w) {
 #pragma unroll
       for (int b = 0; b < Q; ++b) {
-        buf[(k * Q + b) * Q + a] = obb[b];
-        buf[NQ2 + (k * Q + b) * Q + a] = ogb[b];
-        buf[2 * NQ2 + (k * Q + b) * Q + a] = obg[b];
+        buf[k * L::SP + b * Q + a] = obb[b];
+        buf[L::YF + k * L::SP + b * Q + a] = ogb[b];
+        buf[2 * L::YF + k * L::SP + b * Q + a] = obg[b];
       }
     }
-    __syncthreads();
+    elem_sync<Q - 2>();
   }
 }
 
 // Transposed mass-type contractions along xi_2 and xi_1 of NF fields given by their
 // contracted xi_3 lines (r[f][k] of line (a, b)), down to nodal fields of order PO (NO = PO + 1
-// nodes per direction), field f at buf + f * NO^3 ([k][j][i]); even-odd form.  Starts and ends
-// with a barrier.
+// nodes per direction), field f at buf + NOD + f * NO^3 ([k][j][i]); even-odd form.  Ends with
+// a barrier and, with NOD = 0, starts with one (else a thread's lines replace lines of its own).
 template <int PO, int Q>
 __device__ __forceinline__ void mass_line(const double (&in)[Q], double (&out)[PO + 1]) {
   using BT = TabEO<PO, Q, 0>;
@@ -141,16 +161,17 @@ __device__ __forceinline__ void mass_line(const double (&in)[Q], double (&out)[P
   if constexpr (Q % 2 == 1) A.template add_mid<BT>(in[Q / 2]);
   A.finish(out);
 }
-template <int PO, int Q, int NF>
+template <int PO, int Q, int NF, class L = Dense<PO, Q>>
 __device__ __forceinline__ void bwd_mass_xy(double *buf, int t, const double (&p)[NF][PO + 1]) {
   constexpr int NO = PO + 1;
-  constexpr int NQ2 = NO * Q * Q, N2Q = NO * NO * Q, N3 = NO * NO * NO;
-  __syncthreads();
+  constexpr int N3 = NO * NO * NO;
+  static_assert(L::NOD == 0 || NF == 1, "one field past the [k][j][a] fields");
+  if constexpr (L::NOD == 0) elem_sync<Q - 2>();
 #pragma unroll
   for (int f = 0; f < NF; ++f)
 #pragma unroll
-    for (int k = 0; k < NO; ++k) buf[f * NQ2 + k * Q * Q + t] = p[f][k];
-  __syncthreads();
+    for (int k = 0; k < NO; ++k) buf[f * L::YF + k * L::SP + t] = p[f][k];
+  elem_sync<Q - 2>();
   {  // xi_2: [k][b][a] -> [k][j][a]
     const bool w = t < Q * NO;
     const int a = t % Q, k = t / Q;
@@ -160,18 +181,18 @@ __device__ __forceinline__ void bwd_mass_xy(double *buf, int t, const double (&p
       for (int f = 0; f < NF; ++f) {
         double in[Q];
 #pragma unroll
-        for (int b = 0; b < Q; ++b) in[b] = buf[f * NQ2 + (k * Q + b) * Q + a];
+        for (int b = 0; b < Q; ++b) in[b] = buf[f * L::YF + k * L::SP + b * Q + a];
         mass_line<PO, Q>(in, r[f]);
       }
     }
-    __syncthreads();
+    elem_sync<Q - 2>();
     if (w) {
 #pragma unroll
       for (int f = 0; f < NF; ++f)
 #pragma unroll
-        for (int j = 0; j < NO; ++j) buf[f * N2Q + (k * NO + j) * Q + a] = r[f][j];
+        for (int j = 0; j < NO; ++j) buf[f * L::XF + k * L::SK + j * L::LQ + a] = r[f][j];
     }
-    __syncthreads();
+    elem_sync<Q - 2>();
   }
   {  // xi_1: [k][j][a] -> [k][j][i]
     const bool w = t < NO * NO;
@@ -182,28 +203,28 @@ __device__ __forceinline__ void bwd_mass_xy(double *buf, int t, const double (&p
       for (int f = 0; f < NF; ++f) {
         double in[Q];
 #pragma unroll
-        for (int a = 0; a < Q; ++a) in[a] = buf[f * N2Q + (k * NO + j) * Q + a];
+        for (int a = 0; a < Q; ++a) in[a] = buf[f * L::XF + k * L::SK + j * L::LQ + a];
         mass_line<PO, Q>(in, r[f]);
       }
     }
-    __syncthreads();
+    if constexpr (L::NOD == 0) elem_sync<Q - 2>();
     if (w) {
 #pragma unroll
       for (int f = 0; f < NF; ++f)
 #pragma unroll
-        for (int i = 0; i < NO; ++i) buf[f * N3 + (k * NO + j) * NO + i] = r[f][i];
+        for (int i = 0; i < NO; ++i) buf[L::NOD + f * N3 + (k * NO + j) * NO + i] = r[f][i];
     }
-    __syncthreads();
+    elem_sync<Q - 2>();
   }
 }
 
 // The same from the fields at the q^3 points (each thread holds its xi_3 line v[f][c]).
-template <int PO, int Q, int NF>
+template <int PO, int Q, int NF, class L = Dense<PO, Q>>
 __device__ __forceinline__ void bwd_mass(double *buf, int t, const double (&v)[NF][Q]) {
   double r[NF][PO + 1];
 #pragma unroll
   for (int f = 0; f < NF; ++f) mass_line<PO, Q>(v[f], r[f]);
-  bwd_mass_xy<PO, Q, NF>(buf, t, r);
+  bwd_mass_xy<PO, Q, NF, L>(buf, t, r);
 }
 
 // Gather of a pressure-space element (order P - 1, no essential DoFs) into buf and its
@@ -264,6 +285,7 @@ struct SDims {
                 "element buffer");
   // minimum waves per SIMD the kernels below are compiled for
   static constexpr int OCC = 2;
+  static constexpr int CONV_OCC = P <= 4 ? 4 : (P <= 6 ? 3 : 2);  // the most without spilling
 };
 
 // Output of a velocity element vector that adds into an apply's output: sole DoFs
@@ -317,16 +339,16 @@ __device__ __forceinline__ void put_nodal(double *buf, int t, bool active, const
 }
 
 // Even-odd xi_3 lines of the three fields fwd_grad_xy leaves for order PO.
-template <int PO, int Q>
+template <int PO, int Q, class L = Dense<PO, Q>>
 __device__ __forceinline__ void read_z3(const double *buf, int t, eo::Split<PO + 1, double> &bb,
                                         eo::Split<PO + 1, double> &gb, eo::Split<PO + 1, double> &bg) {
-  constexpr int NI = PO + 1, NQ2 = NI * Q * Q;
+  constexpr int NI = PO + 1;
   double zb[NI], zg[NI], zx[NI];
 #pragma unroll
   for (int k = 0; k < NI; ++k) {
-    zb[k] = buf[k * Q * Q + t];
-    zg[k] = buf[NQ2 + k * Q * Q + t];
-    zx[k] = buf[2 * NQ2 + k * Q * Q + t];
+    zb[k] = buf[k * L::SP + t];
+    zg[k] = buf[L::YF + k * L::SP + t];
+    zx[k] = buf[2 * L::YF + k * L::SP + t];
   }
   bb = eo::split(zb);
   gb = eo::split(zg);
@@ -351,7 +373,7 @@ coupling_kernel(const int32_t *__restrict__ vmap, const int32_t *__restrict__ vp
   constexpr int N = S::N, NP = S::NP, Q = S::Q, TPE = S::TPE, E = S::E;
   constexpr int N3 = N * N * N, NP3 = NP * NP * NP;
   constexpr rules::GaussRule<Q> gr = rules::gauss<Q>();
-  __shared__ __align__(16) double smem[E * D::BUF];
+  __shared__ __align__(16) double smem[E * Lds<P>::FULL];
   __shared__ __align__(16) double sgeo[E * kGeoStride];
   __shared__ int32_t smap_all[E * N3];
   const int le = threadIdx.x / TPE;
@@ -362,7 +384,7 @@ coupling_kernel(const int32_t *__restrict__ vmap, const int32_t *__restrict__ vp
   const bool active = e < nelem;
   const int64_t es = active ? e : e0;
   const uint32_t rel = (uint32_t)(es - e0);
-  double *buf = smem + le * D::BUF;
+  double *buf = smem + le * Lds<P>::FULL;
   const double *sg = sgeo + le * kGeoStride;
   int32_t *smap = smap_all + le * N3;
   const ElemTab z = elem_tab<P>(vmap, vpos, vcompact, e0);
@@ -390,14 +412,14 @@ coupling_kernel(const int32_t *__restrict__ vmap, const int32_t *__restrict__ vp
     // indices derived from the thread are recomputed per component rather than kept live
     int t = t0;
     asm volatile("" : "+v"(t));
-    __syncthreads();  // buf was read by the last component's output (or the pressure lines)
+    elem_sync<P>();  // buf was read by the last component's output (or the pressure lines)
     // velocity component r (essential DoFs read as 0)
-    put_nodal<P, false>(buf, t, active, nd, v);
-    __syncthreads();
+    put_nodal<P, false>(buf + VelLay<P>::NOD, t, active, nd, v);
+    elem_sync<P>();
     if (r < 2) nd.load_values(u + (r + 1) * nv, v);
-    fwd_grad_xy<P, Q>(buf, t);
+    fwd_grad_xy<P, Q, VelLay<P>>(buf, t);
     eo::Split<N, double> ubb, ugb, ubg;
-    read_z3<P, Q>(buf, t, ubb, ugb, ubg);
+    read_z3<P, Q, VelLay<P>>(buf, t, ubb, ugb, ubg);
     LineAdjComp L;
     L.init(sg, r, x1, x2);
     double n[1][Q];
@@ -429,10 +451,9 @@ coupling_kernel(const int32_t *__restrict__ vmap, const int32_t *__restrict__ vp
       point(Q / 2, row_mid<VB>(ubg), row_mid<VB>(ugb), row_mid<VG>(ubb), row_mid<PB>(pbg),
             row_mid<PB>(pgb), row_mid<PG>(pbb));
     // G p, component r: added into yv / the velocity E-vector
-    bwd_mass<P, Q, 1>(buf, t, n);
-    emit_add_vel<P, POS>(buf, t, active, smap, Yv + r * vestride, yv + r * nv);
+    bwd_mass<P, Q, 1, VelLay<P>>(buf, t, n);
+    emit_add_vel<P, POS>(buf + VelLay<P>::NOD, t, active, smap, Yv + r * vestride, yv + r * nv);
   }
-  __syncthreads();
   // -D P u: one pressure field
   bwd_mass<P - 1, Q, 1>(buf, t, s);
   {
@@ -467,14 +488,14 @@ __device__ __forceinline__ void fwd_val3_xy(double *buf, int t) {
         eo::apply<BT>(eo::split(in), ob[f]);
       }
     }
-    __syncthreads();
+    elem_sync<P>();
     if (w) {
 #pragma unroll
       for (int f = 0; f < 3; ++f)
 #pragma unroll
         for (int a = 0; a < Q; ++a) buf[f * N2 * Q + (k * NI + j) * Q + a] = ob[f][a];
     }
-    __syncthreads();
+    elem_sync<P>();
   }
   {
     const bool w = t < Q * NI;
@@ -489,14 +510,14 @@ __device__ __forceinline__ void fwd_val3_xy(double *buf, int t) {
         eo::apply<BT>(eo::split(in), ob[f]);
       }
     }
-    __syncthreads();
+    elem_sync<P>();
     if (w) {
 #pragma unroll
       for (int f = 0; f < 3; ++f)
 #pragma unroll
         for (int b = 0; b < Q; ++b) buf[f * NI * Q * Q + (k * Q + b) * Q + a] = ob[f][b];
     }
-    __syncthreads();
+    elem_sync<P>();
   }
 }
 
@@ -539,31 +560,39 @@ __device__ __forceinline__ void contravariant(double *buf, int t, const double *
 }
 
 // What the element kernels below begin with: the nodes' map entries and destinations and the
-// element's trilinear coefficients (loads in flight together; no barrier).
-template <int P, bool POS>
+// element's trilinear coefficients (loads in flight together; no barrier).  values() loads what
+// the map leads to, before the destinations are waited for.
+template <int P, bool POS, typename F>
 __device__ __forceinline__ void begin_vel(Nodes<P> &nd, const int32_t *vmap, const int32_t *vpos,
                                           int vcompact, const double *geo, int64_t e0, uint32_t rel, int t,
-                                          double *sg, int32_t *smap) {
+                                          double *sg, int32_t *smap, F values) {
   const ElemTab z = elem_tab<P>(vmap, vpos, vcompact, e0);
   nd.load_map(z, t, rel);
   nd.load_rank(z, t);
   load_geo<P>(sg, geo, e0, rel, t);
+  values();
   nd.template load_dest<POS>(z, rel);
   nd.keep(smap, t);
 }
 
-// The three nodal components of u (essential DoFs included) into buf (component f at f n^3).
-// Ends with a barrier.
+// The three nodal components of u (essential DoFs included), loaded, and put into buf
+// (component f at f n^3).
 template <int P>
-__device__ __forceinline__ void gather3(double *buf, int t, bool active, const Nodes<P> &nd,
-                                        const double *u, int64_t nv) {
+struct Vec3 {
   double v[3][Nodes<P>::NL];
+  __device__ __forceinline__ void load(const Nodes<P> &nd, const double *u, int64_t nv) {
 #pragma unroll
-  for (int r = 0; r < 3; ++r) nd.load_values(u + r * nv, v[r]);
+    for (int r = 0; r < 3; ++r) nd.load_values(u + r * nv, v[r]);
+  }
+  // ends with a barrier
+  __device__ __forceinline__ void put(double *buf, int t, bool active, const Nodes<P> &nd) {
 #pragma unroll
-  for (int r = 0; r < 3; ++r) put_nodal<P, true>(buf + r * Dims<P>::N3, t, active, nd, v[r]);
-  __syncthreads();
-}
+    for (int r = 0; r < 3; ++r) nd.pin(v[r]);
+#pragma unroll
+    for (int r = 0; r < 3; ++r) put_nodal<P, true>(buf + r * Dims<P>::N3, t, active, nd, v[r]);
+    elem_sync<P>();
+  }
+};
 
 // Convection term N(u) (eq. nonlinear) on the velocity space: n_c = sum_d u_d w |J| d u_c / d x_d
 // = sum_k h_k d_ref_k u_c with h = contravariant(u), so that the geometric factors are needed
@@ -574,7 +603,7 @@ __device__ __forceinline__ void gather3(double *buf, int t, bool active, const N
 // p = 1 361 -> 224 us.  Unrolled over the components: 202 registers, 21 x 22 x 20 p = 4 58 us
 // against 52.)
 template <int P, bool POS>
-__global__ void __launch_bounds__(Dims<P>::THREADS, SDims<P>::OCC)
+__global__ void __launch_bounds__(Dims<P>::THREADS, SDims<P>::CONV_OCC)
 convection_kernel(const int32_t *__restrict__ vmap, const int32_t *__restrict__ vpos,
                   int vcompact, const double *__restrict__ geo, int64_t nelem,
                   const double *__restrict__ u, int64_t nv, double *__restrict__ Yv,
@@ -584,19 +613,21 @@ convection_kernel(const int32_t *__restrict__ vmap, const int32_t *__restrict__ 
   constexpr int N = S::N, Q = S::Q, TPE = S::TPE, E = S::E, N3 = N * N * N;
   using VB = TabEO<P, Q, 0>;
   using VG = TabEO<P, Q, 1>;
-  __shared__ __align__(16) double smem[E * D::BUF];
+  __shared__ __align__(16) double smem[E * Lds<P>::FULL];
   __shared__ __align__(16) double sgeo[E * kGeoStride];
   __shared__ int32_t smap_all[E * N3];
   const int le = threadIdx.x / TPE;
   const int t = threadIdx.x - le * TPE;
   const int64_t e0 = (int64_t)xcd_block() * E;
   const bool active = e0 + le < nelem;
-  double *buf = smem + le * D::BUF;
+  double *buf = smem + le * Lds<P>::FULL;
   double *sg = sgeo + le * kGeoStride;
   int32_t *smap = smap_all + le * N3;
   Nodes<P> nd;
-  begin_vel<P, POS>(nd, vmap, vpos, vcompact, geo, e0, active ? le : 0, t, sg, smap);
-  gather3<P>(buf, t, active, nd, u, nv);
+  Vec3<P> u3;
+  begin_vel<P, POS>(nd, vmap, vpos, vcompact, geo, e0, active ? le : 0, t, sg, smap,
+                    [&] { u3.load(nd, u, nv); });
+  u3.put(buf, t, active, nd);
   double v[Nodes<P>::NL];  // the next component's nodal values
   nd.load_values(u, v);
   double h[3][Q];
@@ -604,15 +635,15 @@ convection_kernel(const int32_t *__restrict__ vmap, const int32_t *__restrict__ 
   // (one component at a time, not unrolled: fewer live registers)
 #pragma unroll 1
   for (int r = 0; r < 3; ++r) {
-    __syncthreads();  // buf has been read
-    put_nodal<P, true>(buf, t, active, nd, v);
-    __syncthreads();
+    elem_sync<P>();  // buf has been read
+    put_nodal<P, true>(buf + VelLay<P>::NOD, t, active, nd, v);
+    elem_sync<P>();
     if (r < 2) nd.load_values(u + (r + 1) * nv, v);
-    fwd_grad_xy<P, Q>(buf, t);
+    fwd_grad_xy<P, Q, VelLay<P>>(buf, t);
     double p[1][N];
     {
       eo::Split<N, double> bb, gb, bg;
-      read_z3<P, Q>(buf, t, bb, gb, bg);
+      read_z3<P, Q, VelLay<P>>(buf, t, bb, gb, bg);
       eo::Acc<N, double> A;
       A.zero();
 #pragma unroll
@@ -631,8 +662,8 @@ convection_kernel(const int32_t *__restrict__ vmap, const int32_t *__restrict__ 
       }
       A.finish(p[0]);
     }
-    bwd_mass_xy<P, Q, 1>(buf, t, p);
-    emit_e<P, double>(buf, t, active, smap, Yv + r * vestride, yv + r * nv);
+    bwd_mass_xy<P, Q, 1, VelLay<P>>(buf, t, p);
+    emit_e<P, double>(buf + VelLay<P>::NOD, t, active, smap, Yv + r * vestride, yv + r * nv);
   }
 }
 
@@ -656,20 +687,21 @@ weak_phi_kernel(const int32_t *__restrict__ vmap, const int32_t *__restrict__ vp
   constexpr rules::GaussRule<Q> gr = rules::gauss<Q>();
   using VB = TabEO<P, Q, 0>;
   using VG = TabEO<P, Q, 1>;
-  __shared__ __align__(16) double smem[E * D::BUF];
+  __shared__ __align__(16) double smem[E * Lds<P>::FULL];
   __shared__ __align__(16) double sgeo[E * kGeoStride];
   __shared__ int32_t smap_all[E * N3];
   const int le = threadIdx.x / TPE;
   const int t = threadIdx.x - le * TPE;
   const int64_t e0 = (int64_t)xcd_block() * E;
   const bool active = e0 + le < nelem;
-  double *buf = smem + le * D::BUF;
+  double *buf = smem + le * Lds<P>::FULL;
   double *sg = sgeo + le * kGeoStride;
   int32_t *smap = smap_all + le * N3;
   Nodes<P> nd;
-  begin_vel<P, POS>(nd, vmap, vpos, vcompact, geo, e0, active ? le : 0, t, sg, smap);
   double v[Nodes<P>::NL];  // the next component's nodal values
-  nd.load_values(u, v);
+  begin_vel<P, POS>(nd, vmap, vpos, vcompact, geo, e0, active ? le : 0, t, sg, smap,
+                    [&] { nd.load_values(u, v); });
+  nd.pin(v);
   // n[k]: output r + 1 + k of the current input component r (curl), output k (gradient)
   double n[3][Q];
 #pragma unroll
@@ -680,13 +712,13 @@ weak_phi_kernel(const int32_t *__restrict__ vmap, const int32_t *__restrict__ vp
   // (one component at a time, not unrolled: fewer live registers)
 #pragma unroll 1
   for (int r = 0; r < NIN; ++r) {
-    if (r > 0) __syncthreads();  // buf has been read
-    put_nodal<P, true>(buf, t, active, nd, v);
-    __syncthreads();
+    if (r > 0) elem_sync<P>();  // buf has been read
+    put_nodal<P, true>(buf + VelLay<P>::NOD, t, active, nd, v);
+    elem_sync<P>();
     if (r + 1 < NIN) nd.load_values(u + (r + 1) * nv, v);
-    fwd_grad_xy<P, Q>(buf, t);
+    fwd_grad_xy<P, Q, VelLay<P>>(buf, t);
     eo::Split<N, double> bb, gb, bg;
-    read_z3<P, Q>(buf, t, bb, gb, bg);
+    read_z3<P, Q, VelLay<P>>(buf, t, bb, gb, bg);
     // curl: d u_r / d x_d enters output r + 1 for d = r + 2 and, negated, output r + 2 for d = r + 1
     constexpr int ND = CURL ? 2 : 3;
     LineAdjComp L[ND];
@@ -862,8 +894,10 @@ weak_div_kernel(const int32_t *__restrict__ vmap, const int32_t *__restrict__ vp
   int32_t *smap = smap_all + le * N3;
   {
     Nodes<P> nd;
-    begin_vel<P, POS>(nd, vmap, vpos, vcompact, geo, e0, active ? le : 0, t, sg, smap);
-    gather3<P>(buf, t, active, nd, u, nv);
+    Vec3<P> u3;
+    begin_vel<P, POS>(nd, vmap, vpos, vcompact, geo, e0, active ? le : 0, t, sg, smap,
+                      [&] { u3.load(nd, u, nv); });
+    u3.put(buf, t, active, nd);
   }
   double h[3][Q];  // (C^T V)_k at the points of the line
   contravariant<P, Q>(buf, t, sg, h);
