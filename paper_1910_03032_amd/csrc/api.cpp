@@ -893,6 +893,8 @@ static sfem_status sfem_setup_body(sfem_ctx *c, int p, int q, int64_t nelem, con
   if (hp.nentries >= (int64_t)kDofMask) return fail(c, SFEM_E_ARG, "mesh too large");
   // per DoF the offset of its E-vector entries, with the map's flags (CgDofs); and one
   // element node per essential DoF marked (kEssOwnerBit)
+  c->n_ess = 0;
+  for (int64_t gd = 0; gd < ndof; ++gd) c->n_ess += ess[(size_t)gd] ? 1 : 0;
   std::vector<int32_t> doff((size_t)ndof + 1);
   {
     int64_t i = 0;
@@ -902,12 +904,13 @@ static sfem_status sfem_setup_body(sfem_ctx *c, int p, int q, int64_t nelem, con
       if (listed) ++i;
     }
     doff[(size_t)ndof] = aoff[(size_t)na];
-    std::vector<uint8_t> seen((size_t)ndof, 0);
-    for (int32_t &v : imap)
-      if (v < 0 && !seen[(size_t)(v & kDofMask)]) {
-        seen[(size_t)(v & kDofMask)] = 1;
-        v |= kEssOwnerBit;
-      }
+    std::vector<uint8_t> owned((size_t)(c->n_ess > 0 ? ndof : 0), 0);
+    if (c->n_ess > 0)
+      for (int32_t &v : imap)
+        if (v < 0 && !owned[(size_t)(v & kDofMask)]) {
+          owned[(size_t)(v & kDofMask)] = 1;
+          v |= kEssOwnerBit;
+        }
   }
 
   // ---- rules
@@ -948,8 +951,6 @@ static sfem_status sfem_setup_body(sfem_ctx *c, int p, int q, int64_t nelem, con
   c->plan.aoff = c->d_aoff;
   c->plan.slot = c->d_slot;
   c->nentries = hp.nentries;
-  c->n_ess = 0;
-  for (int64_t gd = 0; gd < ndof; ++gd) c->n_ess += ess[(size_t)gd] ? 1 : 0;
   c->plan.na = na;
   if (nelem > 0) {
     HIPCHK(c, hipMemcpyAsync(c->d_map, imap.data(), imap.size() * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));

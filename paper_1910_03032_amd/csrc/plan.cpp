@@ -34,9 +34,9 @@ int build_host_plan(int p, int64_t nelem, const int32_t *dofs_ptr, int64_t ndof,
   auto dofs = [&](size_t k) { return dofs_ptr[k]; };
   std::vector<uint8_t> ess(ess_ptr, ess_ptr + ndof);
   // ---- validate the map: range, no repeated DoF inside an element, every DoF used
-  std::vector<int64_t> deg((size_t)ndof + 1, 0);
+  std::vector<int32_t> deg((size_t)ndof, 0);  // (nelem n^3 < 2^31: checked by the caller)
   {
-    std::vector<int64_t> stamp((size_t)ndof, -1);
+    std::vector<int32_t> stamp((size_t)ndof, -1);
     for (int64_t e = 0; e < nelem; ++e) {
       for (int64_t l = 0; l < n3; ++l) {
         const int32_t gd = dofs((size_t)(e * n3 + l));
@@ -46,7 +46,7 @@ int build_host_plan(int p, int64_t nelem, const int32_t *dofs_ptr, int64_t ndof,
         if (stamp[gd] == e)
           return set_err(err, SFEM_E_MESH, "element " + std::to_string(e) + " references DoF " +
                                           std::to_string(gd) + " twice");
-        stamp[gd] = e;
+        stamp[gd] = (int32_t)e;
         deg[gd]++;
       }
     }
