@@ -65,19 +65,20 @@ def log(*a):
 # assembly dispatch), from rocprofv3 FETCH_SIZE / WRITE_SIZE runs scaled by a plain
 # copy's readings; valid only for the kernel sources they were taken with (keyed by
 # the hash of those sources), otherwise the roofline reports traffic = null.
-KERNEL_SOURCES = ["apply_impl.h", "eo.h", "rules.h", "internal.h", "plan.h", "k_apply_f64.hip", "k_vec.hip"]
+KERNEL_SOURCES = ["apply_impl.h", "eo.h", "geom.h", "pcg.h", "wave.h", "rules.h", "internal.h", "plan.h",
+                  "k_apply_f64.hip", "k_vec.hip"]
 MEASURED_TRAFFIC = {
     # profiles/helmholtz_apply_p4_32e_hbm_bytes.md (FP64 apply, both dispatches)
-    ("a7986bae1c3cc88f", "helmholtz_p4_32e"): 553476720,
+    ("e3c3f7f9a6bb4d6e", "helmholtz_p4_32e"): 213103000,
     # profiles/vector_helmholtz_p7_24e_counters.md (three-member FP64 apply)
-    ("a7986bae1c3cc88f", "vector_helmholtz_p7_24e"): 1288660473,
+    ("e3c3f7f9a6bb4d6e", "vector_helmholtz_p7_24e"): 806559000,
 }
 # Executed floating-point operations of one apply (element kernel + assembly) from the
 # SQ_INSTS_VALU_FLOPS_FP64 / _FP32 counters (x 64 lanes), same keying as the traffic:
 # profiles/helmholtz_apply_p4_32e_counters.md, profiles/vector_helmholtz_p7_24e_counters.md.
 MEASURED_FLOPS = {
-    ("a7986bae1c3cc88f", "helmholtz_p4_32e"): {"fp64": 961714752, "fp32": 964111936},
-    ("a7986bae1c3cc88f", "vector_helmholtz_p7_24e"): {"fp64": 6564470208, "fp32": 6260121024},
+    ("e3c3f7f9a6bb4d6e", "helmholtz_p4_32e"): {"fp64": 1435158592, "fp32": 961714752},
+    ("e3c3f7f9a6bb4d6e", "vector_helmholtz_p7_24e"): {"fp64": 8450727360, "fp32": 6267198912},
 }
 FP32_PEAK_TFLOPS = 157.3  # MI355X dense FP32 vector
 
@@ -106,11 +107,15 @@ def kernel_source_hash(read=None):
     return h.hexdigest()[:16]
 
 
-def algorithmic_bytes(nelem, p, ndof, s, nb=1, nqd=7, nb_qd=1):
-    """Bytes an apply must move: quadrature data once (per distinct field), x read and
-    y written once per member, the element->DoF map once."""
+GEO_BYTES = 192  # an element's trilinear coefficients: the geometric factors are formed from them
+
+
+def algorithmic_bytes(nelem, p, ndof, s, nb=1, nb_qd=1):
+    """Bytes an apply must move: w nu / |J| at the points (float64 in both precisions, per
+    distinct field) and the elements' trilinear coefficients once, x read and y written once
+    per member, the element->DoF map once."""
     q = p + 2
-    return nb_qd * nelem * q ** 3 * nqd * s + nb * 2 * ndof * s + nelem * (p + 1) ** 3 * 4
+    return nelem * (nb_qd * q ** 3 * 8 + GEO_BYTES + (p + 1) ** 3 * 4) + nb * 2 * ndof * s
 
 
 def flops_helmholtz(nelem, p, nb=1):
@@ -402,7 +407,7 @@ def run_main(a, wl):
         out["ir_speedup"] = round(s64["ms"] / sir["ms"], 3)
         lam = xs.clone()
         msg = B.timed(lambda: B.op.grad_nu(xs, lam), 10, 2)
-        gbytes = m.nelem * q ** 3 * 6 * 8 + 2 * N * 8 + m.nelem * q ** 3 * 8 + m.nelem * (p + 1) ** 3 * 4
+        gbytes = m.nelem * (GEO_BYTES + q ** 3 * 8 + (p + 1) ** 3 * 4) + 2 * N * 8
         out["adjoint_grad_kernel"] = {"us": round(msg * 1e3, 1),
                                       "algorithmic_GBps": round(gbytes / (msg * 1e-3) / 1e9, 1)}
     if not a.no_sweep:
@@ -743,11 +748,11 @@ def run_size_sweep(a):
 
 
 def stokes_bytes(nelem, p, nv, npres):
-    """Bytes a Stokes block apply must move: the folded Helmholtz factors (7 per point) and
-    the coupling factors (9 per point) once, u and p read and y_u, y_p written once, both
-    element->DoF maps once."""
+    """Bytes a Stokes block apply must move: w nu / |J| at the points and the elements'
+    trilinear coefficients once, u and p read and y_u, y_p written once, both element->DoF
+    maps once."""
     q = p + 2
-    return nelem * q ** 3 * (7 + 9) * 8 + 2 * (3 * nv + npres) * 8 + nelem * ((p + 1) ** 3 + p ** 3) * 4
+    return nelem * (q ** 3 * 8 + GEO_BYTES + ((p + 1) ** 3 + p ** 3) * 4) + 2 * (3 * nv + npres) * 8
 
 
 def run_stokes(a):
@@ -873,8 +878,8 @@ def run_convection(a):
     """Convection term N(u) (three velocity components) over p = 1..8, the throughput-vs-order
     view of the nonlinear term (Section 6, figure on the shared-memory convection
     evaluation), 1.8-4.8 M DoFs per component (32^3 hexes at p = 4, 24^3 at p = 7): GDoF/s
-    over the 3 N velocity DoFs; bytes = coupling factors (9 per point) once, u read and N(u)
-    written once, the map once."""
+    over the 3 N velocity DoFs; bytes = the elements' trilinear coefficients once, u read and
+    N(u) written once, the map once."""
     import torch
     from paper_1910_03032_amd import Operator
     from workloads import BoxMesh, normal
@@ -896,8 +901,7 @@ def run_convection(a):
         e1.record(stream)
         torch.cuda.synchronize()
         ms = e0.elapsed_time(e1) / a.steps
-        q = p + 2
-        nbytes = m.nelem * q ** 3 * 9 * 8 + 2 * 3 * m.ndof * 8 + m.nelem * (p + 1) ** 3 * 4
+        nbytes = m.nelem * (GEO_BYTES + (p + 1) ** 3 * 4) + 2 * 3 * m.ndof * 8
         row = {"p": p, "elements": f"{ne}^3", "velocity_dofs": 3 * m.ndof, "us": round(ms * 1e3, 2),
                "GDoF/s": round(3 * m.ndof / (ms * 1e-3) / 1e9, 3), "algorithmic_bytes": nbytes,
                "hbm_frac": round(nbytes / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)}

@@ -4,9 +4,9 @@
  * the Poisson and Helmholtz solves of a projection step.
  *
  * The operations follow the method's statement of the problem:
- *   - mesh + order -> setup that stores the geometric factors at quadrature
- *     points (Section 3.1, after eq. tensorGradient: setup O(p^d), the Jacobian
- *     kept at quadrature points);
+ *   - mesh + order -> setup that stores each element's trilinear map, from which the
+ *     kernels form the geometric factors at the quadrature points (Section 3.1, after
+ *     eq. tensorGradient, keeps the Jacobian there instead);
  *   - operator action of the mass, diffusion and Helmholtz operators
  *     (eq. vectorMass, eq. vectorDiffusion, eq. localStiffnessMapped, the
  *     Helmholtz combination A = c M + L of Section 5.2 and eq. proj-helmholtz),
@@ -99,7 +99,7 @@ sfem_status sfem_set_stream(sfem_ctx *ctx, void *stream);
  * this process).  The string is owned by the library, valid until the next call. */
 const char *sfem_last_error(const sfem_ctx *ctx);
 
-/* Mesh + order setup (Section 3.1: geometric factors stored at quadrature points).
+/* Mesh + order setup.
  *   p          polynomial order, 1..SFEM_MAX_P;  q: Gauss points per direction (= p + 2)
  *   nelem      number of hexahedra (>= 0)
  *   elem_xyz   [nelem][8][3] float64 vertex coordinates (device)
@@ -107,8 +107,8 @@ const char *sfem_last_error(const sfem_ctx *ctx);
  *              values in [0, ndof), no DoF twice in one element, every DoF used
  *   ndof       number of global DoFs (< 2^30)
  *   ess_mask   [ndof] uint8, nonzero = essential DoF (device), or NULL (none)
- * Computes per quadrature point w|J| and w|J| J^{-1} J^{-T} (FP64), classifies the
- * DoFs (owned by one element, or shared and summed by an assembly pass without
+ * Stores the trilinear coefficients of every element (FP64; w|J| and w|J| J^{-1} J^{-T} are
+ * formed from them where they are needed), classifies the DoFs (owned by one element, or shared and summed by an assembly pass without
  * atomics), and resets the coefficients to alpha = 1, beta = 1, nu = 1.  Returns SFEM_E_MESH if some
  * det J <= 0 or the map is invalid.  May be called again to replace the mesh. */
 sfem_status sfem_setup(sfem_ctx *ctx, int p, int q, int64_t nelem, const double *elem_xyz,
@@ -123,13 +123,13 @@ sfem_status sfem_qpoint_coords(sfem_ctx *ctx, double *xq);
  *              (device, copied), or NULL for nu = 1
  *   nbatch_nu  number of nu fields (>= 1); with more than one field, a batched
  *              apply / solve must use nbatch == nbatch_nu and member m uses field m
- * Recomputes the folded quadrature data and the operator diagonals. */
+ * Recomputes w nu / |J| at the points and the operator diagonals. */
 sfem_status sfem_set_coeffs(sfem_ctx *ctx, double alpha, double beta, const double *nu_q,
                             int nbatch_nu);
 
 /* y = A x for nbatch vectors.  x, y: [nbatch][ndof] of float64 (SFEM_F64) or
  * float32 (SFEM_F32), device, not aliased.  FP32 uses float32 copies of the 1D
- * tables and the quadrature data rounded from FP64. */
+ * tables and geometric factors formed in FP64 and rounded once. */
 sfem_status sfem_apply(sfem_ctx *ctx, int op, int prec, int nbatch, const void *x, void *y);
 
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight
@@ -258,8 +258,8 @@ sfem_status sfem_grad_nu(sfem_ctx *ctx, int nbatch, const double *u, const doubl
 /* Taylor-Hood pressure space for the Stokes blocks (Section 3: velocity (Q_p)^3, pressure
  * Q_{p-1}, nodal GLL bases; p >= 2): the order-(p-1) element->DoF map of the same elements
  * as sfem_setup, pres_dofs [nelem][p^3] int32 (device, local l = i + p (j + p k)), with
- * npres pressure DoFs; the pressure space has no essential DoFs.  Also stores the
- * coupling factors w |J| J^{-T} at the quadrature points.  Once per sfem_setup.
+ * npres pressure DoFs; the pressure space has no essential DoFs.  Once per
+ * sfem_setup.
  * Errors: SFEM_E_UNSUPPORTED for p < 2, SFEM_E_MESH for an invalid map, SFEM_E_STATE
  * before sfem_setup or when called twice. */
 sfem_status sfem_setup_pressure(sfem_ctx *ctx, const int32_t *pres_dofs, int64_t npres);
@@ -280,8 +280,7 @@ sfem_status sfem_stokes_apply(sfem_ctx *ctx, const double *u, const double *p, d
  *   y_{c,i} = sum_e sum_q w|J| phi_i ((u . grad) u)_c,
  * u, y: [3][ndof] float64 (device, component-major).  u is taken with its boundary values;
  * rows of essential DoFs are set to 0 (the term is a right-hand side of the constrained
- * solves).  Uses the coupling factors w |J| J^{-T} (computed on first use).
- * Asynchronous on the context stream.  Errors: SFEM_E_ARG for NULL or aliased arrays. */
+ * solves).  Asynchronous on the context stream.  Errors: SFEM_E_ARG for NULL or aliased arrays. */
 sfem_status sfem_convection(sfem_ctx *ctx, const double *u, double *y);
 
 /* Equal-order weak vector operators of the projection step (Section 4.2, the pressure
@@ -295,8 +294,7 @@ sfem_status sfem_convection(sfem_ctx *ctx, const double *u, double *y);
  *                         x: [3][ndof], y: [ndof]
  * (float64, device, component-major; grad = J^{-T} grad_ref at the Gauss points.)  x is
  * taken with all its values; rows of essential DoFs are set to 0 (a context without
- * essential DoFs gives every row).  Uses the coupling factors w |J| J^{-T} (computed on
- * first use).  Asynchronous on the context stream.  Errors: SFEM_E_ARG for a bad kind or
+ * essential DoFs gives every row).  Asynchronous on the context stream.  Errors: SFEM_E_ARG for a bad kind or
  * NULL or aliased arrays. */
 #define SFEM_WEAK_GRADIENT 1
 #define SFEM_WEAK_CURL 2

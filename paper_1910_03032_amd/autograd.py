@@ -2,7 +2,7 @@
 
 Backward (adjoint method): with g = dJ/du, lam solves A lam = g (A is symmetric),
 then dJ/dnu_q = -lam^T (dA/dnu_q) u, which the library evaluates pointwise per
-quadrature point (K is linear in nu through the stored factor of Section 3.1), and
+quadrature point (K is linear in nu through the factor W of Section 3.1), and
 dJ/db = lam.  The forward solution u is kept as the checkpoint; the backward pass
 costs one more PCG solve and one gradient kernel.
 """

@@ -14,9 +14,9 @@
 // points are symmetric about 0, so B is centro-symmetric and G centro-antisymmetric),
 // which halves the multiply-adds; the xi_3 stage walks the quadrature slices in
 // symmetric pairs (c, q-1-c).  Intermediates between stages live in LDS, one buffer
-// per element.  Several (element, batch member) pairs share a workgroup (E = 256 / q^2),
+// per element.  Several (element, batch member) pairs share a workgroup (E of ApplyCfg),
 // the members of an element next to each other, so that a batched apply reads each
-// element's quadrature data from HBM once for all members.
+// element's coefficients from HBM once for all members.
 //
 // Assembly (no atomics, deterministic): one launch of the element kernel covers every
 // element.  A DoF that belongs to this element only (the element-interior nodes of a
