@@ -529,8 +529,8 @@ struct NoCg {};
 // point, and the kernel is bound by VALU issue, LDS and the latency between its barriers:
 // 120.3 -> 77.3 us there, 212 -> 126 us for nu = 1 at 63 x 61 x 59 p = 2, float32 32^3 p = 8
 // 341 -> 290 us.  With the layouts of Lds, eight barriers a workgroup instead of eleven, and
-// every load of the prologue issued before the first wait for the map's followers: 72, 107 and
-// 288 us.  Of 107 us at 36^3 p = 4 the loads, stores and the assembly alone took 68 and the
+// every load of the prologue issued before the first wait for the map's followers: 69, 100 and
+// 264 us.  Of 107 us at 36^3 p = 4 the loads, stores and the assembly alone took 68 and the
 // quadrature function 20; of a workgroup's 20000 cycles, its loads took 7000 and VALU issue 3900.
 //
 // Work items are (element, member) pairs, pair v = e * nbatch + m, E per workgroup: the
