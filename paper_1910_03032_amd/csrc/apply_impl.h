@@ -486,7 +486,9 @@ __device__ __forceinline__ int xcd_block() {
 // How the element kernel of order P and precision T is built (chosen by measurement on
 // MI355X):
 //   ZLDS   the xi_3 stage's input lines are read from LDS again for every slice pair, one at
-//          a time, instead of being held in registers for the whole stage;
+//          a time, instead of being held in registers for the whole stage: where that decides
+//          the waves per SIMD.  Float64 p = 7 has two either way and holds them (243 registers
+//          of 256, LDS half busy: three members at 24^3 377 -> 350 us);
 //   OCC    minimum waves per SIMD the kernel is compiled for (launch bound): three float64
 //          ones at p = 5 and 6 as well (29^3 p = 5 115 -> 100 us, 24^3 p = 6 101 -> 82 us,
 //          Helmholtz with nu).  Four at p = 3 and 4, and three at p = 7, would spill 44 to
@@ -506,7 +508,7 @@ struct ApplyCfg {
   static constexpr bool F64 = sizeof(T) == 8;
   static constexpr int E = CG ? Dims<P>::E : P == 1 ? 7 : P == 3 ? 5 : Dims<P>::E;
   static constexpr int THREADS = E * Dims<P>::TPE;
-  static constexpr bool ZLDS = F64 ? (P >= 5) : (P == 6 || P == 8 || (CG && P >= 4));
+  static constexpr bool ZLDS = F64 ? (P == 5 || P == 6 || P == 8) : (P == 6 || P == 8 || (CG && P >= 4));
   static constexpr int OCC = F64 ? Dims<P>::OCC : (P <= 6 || (P == 8 && !CG) ? 4 : 3);
   static constexpr bool REFORM = CG != 0 || P == (F64 ? 5 : 8);
 };
