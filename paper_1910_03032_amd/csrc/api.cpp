@@ -568,7 +568,7 @@ sfem_status run_pcg(sfem_ctx *c, int op, int nb, const T *b, T *x, bool x0_zero,
     return false;
   };
   if (!any_active()) return SFEM_OK;
-  const int nelem_parts = cg_nparts(c, f32, nb), unblk = cg_update_nblk(n);
+  const int nelem_parts = cg_nparts(c, f32, nb), unblk = cg_update_nblk(n, nb);
   const CgDofs dofs{c->d_doff, c->d_slot};
   CgIn g{};
   g.r = w.r;
@@ -689,7 +689,7 @@ sfem_status run_pcg_lor_z(sfem_ctx *c, int op, const double *b, double *x, bool 
   float *r32 = f32 ? c->lor_work32 : nullptr;
   PcgScalars *sc = reinterpret_cast<PcgScalars *>(c->lor_scal);  // [2]
   PcgScalars *h = reinterpret_cast<PcgScalars *>(c->h_pinned);   // [2]
-  const int unblk = cg_update_nblk(n);
+  const int unblk = cg_update_nblk(n, 1);
   sfem_status st;
   hs = PcgScalars{};
   const TZ *bz;  // the V-cycle's input

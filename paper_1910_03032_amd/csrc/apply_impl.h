@@ -674,7 +674,17 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
       if (!cg.ready) {
         up.parts(sums[0], cg.unblk);
         other_parts(sums[0], r0, false);
-        for (int i = 1; i < here; ++i) other_parts(sums[i], (r0 + (uint32_t)i) % (uint32_t)nbatch, true);
+        for (int i = 1; i < here; i += 2) {  // two members' loads together
+          const int i1 = i + 1 < here ? i + 1 : i;
+          const uint32_t ma = (r0 + (uint32_t)i) % (uint32_t)nbatch, mb = (r0 + (uint32_t)i1) % (uint32_t)nbatch;
+          PartLoads<NW, 2> qa, qb;
+          qa.load(cg.upart + (int64_t)ma * 4 * cg.unblk, cg.unblk);
+          qb.load(cg.upart + (int64_t)mb * 4 * cg.unblk, cg.unblk);
+          qa.parts(sums[i], cg.unblk);
+          qb.parts(sums[i1], cg.unblk);
+          other_parts(sums[i], ma, false);
+          if (i1 > i) other_parts(sums[i1], mb, false);
+        }
         __syncthreads();
         cg_next_from<NW>(s, sums[k], cg.nullspace, ndof);
       }

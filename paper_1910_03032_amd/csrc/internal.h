@@ -206,7 +206,7 @@ hipError_t launch_sub_norm(const double *b, const double *w, double *r, double *
 // z - mean(z) 1, and rho = r^T z of that vector (Section 5.3).
 hipError_t launch_pcg_init(const double *part, int nblk, int nb, double rtol, PcgScalars *sc,
                            hipStream_t s, int nullspace = 0, int64_t n = 0);
-int cg_update_nblk(int64_t n);
+int cg_update_nblk(int64_t n, int nb);
 // The same update around a preconditioner applied between the launches (one member, z given in
 // the preconditioner's precision TZ); no partials.  TZ = float: r32 = (float) r, its input.  With
 // t also the preconditioner's first smoothing sweep, t = omega tdinv r.

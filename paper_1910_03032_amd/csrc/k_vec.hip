@@ -534,7 +534,7 @@ hipError_t launch_cgz_update(const CgDofs &dofs, const double *evec, const doubl
                              const PcgScalars *sc, PcgScalars *sc_next, const double *dpart, int dcount,
                              int64_t n, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  const int nblk = cg_update_nblk(n);
+  const int nblk = cg_update_nblk(n, 1);
   hipLaunchKernelGGL((cg_update_kernel<double, TZ, true>), dim3(nblk), dim3(CU_NT), 0, s, dofs, evec, (int64_t)0,
                      y, x, p, r, z, (int64_t)0, sc, sc_next, dpart, (int64_t)0, dcount, (double *)nullptr, nblk, n,
                      CgzOut<TZ>{r32, t, tdinv, omega});
@@ -575,10 +575,14 @@ hipError_t launch_pcg_init(const double *part, int nblk, int nb, double rtol, Pc
   return hipGetLastError();
 }
 
-int cg_update_nblk(int64_t n) {
+// (all members together fill the chip: every workgroup of the update reads all partials of its
+// member's p.Ap, which number nb times those of one member, and every workgroup of the element
+// kernel the update's partials of its members)
+int cg_update_nblk(int64_t n, int nb) {
+  const int64_t most = nb < CU_MAXB ? CU_MAXB / nb : 1;
   int64_t b = (n + CU_NT - 1) / CU_NT;
   if (b < 1) b = 1;
-  if (b > CU_MAXB) b = CU_MAXB;
+  if (b > most) b = most;
   return (int)b;
 }
 
