@@ -887,6 +887,174 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
   }
 }
 
+// Outputs (c, q-1-c) and, for odd q, the middle output of a 1D contraction from a split line.
+template <typename TB, int N, typename T>
+__device__ __forceinline__ void line_pair_of(const eo::Split<N, T> &x, int c, T &lo, T &hi) {
+  T Ev = 0, Od = 0;
+#pragma unroll
+  for (int i = 0; i < N / 2; ++i) {
+    Ev += (T)TB::e(c, i) * x.e[i];
+    Od += (T)TB::o(c, i) * x.o[i];
+  }
+  if constexpr (N % 2 == 1) Ev += (T)TB::t(c, N / 2) * x.e[N / 2];
+  lo = Ev + Od;
+  hi = (TB::S > 0) ? (Ev - Od) : (Od - Ev);
+}
+template <typename TB, int N, typename T>
+__device__ __forceinline__ T line_mid_of(const eo::Split<N, T> &x) {
+  constexpr int M = (N + 1) / 2;  // q / 2
+  T v = 0;
+#pragma unroll
+  for (int i = 0; i < N / 2; ++i) v += (T)TB::t(M, i) * (TB::S > 0 ? x.e[i] : x.o[i]);
+  if constexpr (N % 2 == 1 && TB::S > 0) v += (T)TB::t(M, N / 2) * x.e[N / 2];
+  return v;
+}
+
+// The float32 apply of several members with one coefficient: a workgroup takes E elements and
+// all their members in turn.  The six factors and the mass weight of the thread's points are
+// formed in float64 once, rounded, and kept in 7 q registers, which the coefficients of the
+// line's metric and w nu / |J| took; formed for each member they are a quarter of the vector
+// instructions at p = 4: three members at 29^3 p = 2 30 -> 23.5 us, 29^3 p = 4 100 -> 81 us,
+// 114^3 p = 1 617 -> 388 us (Helmholtz with nu; by pairs at the left).
+template <int P, int OP, bool NU>
+__global__ void __launch_bounds__((ApplyCfg<P, float, 0>::THREADS), (ApplyCfg<P, float, 0>::OCC))
+apply_members_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo, const double *__restrict__ cw,
+                     double alpha, double beta, int64_t nelem, int nbatch, int64_t ndof,
+                     const float *__restrict__ x, float *__restrict__ Y, int64_t estride,
+                     const int32_t *__restrict__ pos, int compact, float *__restrict__ y) {
+  using D = Dims<P>;
+  using C = ApplyCfg<P, float, 0>;
+  using LD = Lds<P, true>;
+  using T = float;
+  constexpr int N = D::N, Q = D::Q, Q2 = D::Q2, Q3 = D::Q3, N3 = D::N3, TPE = D::TPE, E = C::E, THREADS = C::THREADS;
+  constexpr int NL = Nodes<P>::NL;
+  constexpr bool MASS = OP == 2, POS = evec_dof_ordered(P);
+  static_assert(OP == 1 || OP == 2, "diffusion or Helmholtz");
+  constexpr rules::GaussRule<Q> gr = rules::gauss<Q>();
+  using BT = eo::Tab1<P, 0>;
+  using GT = eo::Tab1<P, 1>;
+  __shared__ __align__(16) T smem[E * LD::BUF];
+  __shared__ __align__(16) double sgeo[E * kGeoStride];
+  __shared__ int32_t smap_all[E * N3];
+  const int le = threadIdx.x / TPE;
+  const int t = threadIdx.x - le * TPE;
+  const int64_t e0 = (int64_t)xcd_block() * E;
+  const bool active = e0 + le < nelem;
+  const uint32_t rel = active ? le : 0;
+  T *buf = smem + le * LD::BUF;
+  int32_t *smap = smap_all + le * N3;
+  const ElemTab z = elem_tab<P>(map, pos, compact, e0);
+  Nodes<P> nd;
+  nd.load_map(z, t, rel);
+  nd.load_rank(z, t);
+  constexpr int NG = (kGeoStride + TPE - 1) / TPE;
+  double gv[NG];
+#pragma unroll
+  for (int k = 0; k < NG; ++k) {
+    const int i = t + k * TPE < kGeoStride ? t + k * TPE : kGeoStride - 1;
+    gv[k] = ld<double>(geo + e0 * kGeoStride, (rel * kGeoStride + i) * 8u);
+  }
+  double cv[Q];  // w nu / |J| at the points of the thread's line
+  if constexpr (NU) {
+#pragma unroll
+    for (int c = 0; c < Q; ++c) cv[c] = ld<double>(cw + e0 * Q3, (rel * Q3 + t + c * Q2) * 8u);
+  }
+  T v[NL];
+  nd.load_values(x, v);
+  nd.template load_dest<POS>(z, rel);
+#pragma unroll
+  for (int k = 0; k < NG; ++k)
+    sgeo[le * kGeoStride + (t + k * TPE < kGeoStride ? t + k * TPE : kGeoStride - 1)] = gv[k];
+  nd.pin(v);
+  nd.keep(smap, t);
+#pragma unroll
+  for (int k = 0; k < NL; ++k) buf[LD::nodal(Nodes<P>::node(t, k))] = (active && nd.c[k] >= 0) ? v[k] : T(0);
+  elem_sync<P, THREADS>();
+  T G[Q][6], wd[Q];
+  {
+    LineMetric L;
+    const int la = t % Q, lb = t / Q;
+    L.init(sgeo + le * kGeoStride, kGaussRule<Q>.x[la], kGaussRule<Q>.x[lb]);
+    const double wab = kGaussRule<Q>.w[la] * kGaussRule<Q>.w[lb];
+    const double wm = alpha * wab, ws = NU ? beta : beta * wab;
+#pragma unroll
+    for (int c = 0; c < Q; ++c) {
+      double det = 0.0;
+      if constexpr (MASS || !NU) det = L.det(gr.x[c]);
+      wd[c] = MASS ? (T)((wm * gr.w[c]) * det) : T(0);
+      L.factors(gr.x[c], NU ? cv[c] * ws : (ws * gr.w[c]) * recip(det), G[c]);
+    }
+  }
+  for (int m = 0; m < nbatch; ++m) {
+    if (m + 1 < nbatch) nd.load_values(x + (int64_t)(m + 1) * ndof, v);
+    fwd_x<P, T, true, THREADS>(buf, t);
+    fwd_y<P, T, true, THREADS>(buf, t);
+    {
+      auto line = [&](int f) {
+        T u[N];
+#pragma unroll
+        for (int k = 0; k < N; ++k) u[k] = buf[f * LD::YF + k * LD::SP + t];
+        return eo::split(u);
+      };
+      const eo::Split<N, T> sb = line(0), sg = line(1), sx = line(2);
+      eo::Acc<N, T> A1, A2, A3;
+      A1.zero();
+      A2.zero();
+      A3.zero();
+      auto flux = [&](int c, T dx, T dy, T dz, T &g1, T &g2, T &g3) {
+        g1 = G[c][0] * dx + G[c][3] * dy + G[c][4] * dz;
+        g2 = G[c][3] * dx + G[c][1] * dy + G[c][5] * dz;
+        g3 = G[c][4] * dx + G[c][5] * dy + G[c][2] * dz;
+      };
+#pragma unroll
+      for (int c = 0; c < Q / 2; ++c) {
+        T u0, u1, dx0, dx1, dy0, dy1, dz0, dz1, a1, a2, a3, b1, b2, b3;
+        if constexpr (MASS) {
+          line_pair_of<BT>(sb, c, u0, u1);
+          A1.template add_pair<BT>(c, wd[c] * u0, wd[Q - 1 - c] * u1);
+        }
+        line_pair_of<GT>(sb, c, dz0, dz1);
+        line_pair_of<BT>(sg, c, dy0, dy1);
+        line_pair_of<BT>(sx, c, dx0, dx1);
+        flux(c, dx0, dy0, dz0, a1, a2, a3);
+        flux(Q - 1 - c, dx1, dy1, dz1, b1, b2, b3);
+        A1.template add_pair<GT>(c, a3, b3);
+        A2.template add_pair<BT>(c, a2, b2);
+        A3.template add_pair<BT>(c, a1, b1);
+      }
+      if constexpr (Q % 2 == 1) {
+        T g1, g2, g3;
+        if constexpr (MASS) A1.template add_mid<BT>(wd[Q / 2] * line_mid_of<BT>(sb));
+        flux(Q / 2, line_mid_of<BT>(sx), line_mid_of<BT>(sg), line_mid_of<GT>(sb), g1, g2, g3);
+        A1.template add_mid<GT>(g3);
+        A2.template add_mid<BT>(g2);
+        A3.template add_mid<BT>(g1);
+      }
+      T p1[N], p2[N], p3[N];
+      A1.finish(p1);
+      A2.finish(p2);
+      A3.finish(p3);
+      // a thread's lines replace those it read: no barrier before the stores
+#pragma unroll
+      for (int k = 0; k < N; ++k) {
+        buf[k * LD::SP + t] = p1[k];
+        buf[LD::YF + k * LD::SP + t] = p2[k];
+        buf[2 * LD::YF + k * LD::SP + t] = p3[k];
+      }
+      elem_sync<P, THREADS>();
+    }
+    bwd_y<P, T, true, THREADS>(buf, t);
+    bwd_x<P, T, true, THREADS>(buf, t);
+    emit_e<P, T, LD>(buf, t, active, smap, Y + (int64_t)m * estride, y + (int64_t)m * ndof);
+    if (m + 1 < nbatch) {
+      elem_sync<P, THREADS>();  // the nodal vector has been read
+#pragma unroll
+      for (int k = 0; k < NL; ++k) buf[LD::nodal(Nodes<P>::node(t, k))] = (active && nd.c[k] >= 0) ? v[k] : T(0);
+      elem_sync<P, THREADS>();
+    }
+  }
+}
+
 template <int P, typename T, int CG>
 hipError_t launch_apply_pt(const ApplyArgs &a, const CgIn &g, hipStream_t s) {
   if (a.nelem <= 0 || a.nbatch <= 0) return hipSuccess;
@@ -895,6 +1063,24 @@ hipError_t launch_apply_pt(const ApplyArgs &a, const CgIn &g, hipStream_t s) {
   using C = ApplyCfg<P, T, CG>;
   dim3 grid((unsigned)((a.nelem * a.nbatch + C::E - 1) / C::E));
   dim3 block(C::THREADS);
+  // (up to p = 4, where the members kernel's registers fit four waves per SIMD: three members
+  // there 1.05 - 1.8 times as fast as by (element, member) pairs; with its spills 0.43 - 0.9 at
+  // 2e5 DoFs at p = 5 to 8, 1.0 at 1.5e6)
+  if constexpr (sizeof(T) == 4 && CG == 0 && P <= 4) {
+    if (a.nbatch > 1 && a.op != SFEM_MASS && (!a.cw || a.cw_mstride == 0)) {
+      dim3 eg((unsigned)((a.nelem + C::E - 1) / C::E));
+#define SFEM_MEMBERS(OP, NU)                                                                             \
+  hipLaunchKernelGGL((apply_members_kernel<P, OP, NU>), eg, block, 0, s, a.map, a.geo, a.cw, a.alpha,    \
+                     a.beta, a.nelem, a.nbatch, a.ndof, (const float *)a.x, (float *)a.evec, a.estride,  \
+                     a.pos, a.compact, (float *)a.y)
+      if (a.op == SFEM_DIFFUSION && a.cw) SFEM_MEMBERS(1, true);
+      else if (a.op == SFEM_DIFFUSION) SFEM_MEMBERS(1, false);
+      else if (a.cw) SFEM_MEMBERS(2, true);
+      else SFEM_MEMBERS(2, false);
+#undef SFEM_MEMBERS
+      return hipGetLastError();
+    }
+  }
   std::conditional_t<CG != 0, CgIn, NoCg> cg;
   if constexpr (CG != 0) cg = g;
 #define SFEM_APPLY(OP, NU)                                                                              \
