@@ -568,7 +568,9 @@ sfem_status run_pcg(sfem_ctx *c, int op, int nb, const T *b, T *x, bool x0_zero,
     return false;
   };
   if (!any_active()) return SFEM_OK;
-  const int nelem_parts = cg_nparts(c, f32, nb), unblk = cg_update_nblk(n, nb);
+  // (by members a workgroup leaves one partial for each; cg_nparts is enough for both)
+  const bool members = f32 && f32_by_members(c->p, op, nb, c->nfield <= 1, true, cg_nparts(c, f32, 1));
+  const int nelem_parts = members ? cg_nparts(c, f32, 1) : cg_nparts(c, f32, nb), unblk = cg_update_nblk(n, nb);
   const CgDofs dofs{c->d_doff, c->d_slot};
   CgIn g{};
   g.r = w.r;
@@ -584,7 +586,7 @@ sfem_status run_pcg(sfem_ctx *c, int op, int nb, const T *b, T *x, bool x0_zero,
   for (int it = 0; it < maxit; ++it) {
     if ((st = do_apply(c, op, f32, nb, nullptr, w.w, w.dpart, nullptr, false, &g)) != SFEM_OK) return st;
     HIPCHK(c, VecOps<T>::update(dofs, (const T *)c->evec.p, c->nentries, w.w, x, w.p, w.r, dinv, dms, w.sc + nb,
-                                w.sc, w.dpart, nelem_parts, nelem_parts, w.part, unblk, n, nb, s));
+                                w.sc, w.dpart, cg_nparts(c, f32, nb), nelem_parts, w.part, unblk, n, nb, s));
     g.ready = 0;
     if ((it + 1) % check_every == 0 || it + 1 == maxit) {
       HIPCHK(c, launch_cg_finish(w.sc, hs, w.part, unblk, nb, nullspace, n, s));

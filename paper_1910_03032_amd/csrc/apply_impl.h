@@ -916,14 +916,18 @@ __device__ __forceinline__ T line_mid_of(const eo::Split<N, T> &x) {
 // line's metric and w nu / |J| took; formed for each member they are a quarter of the vector
 // instructions at p = 4: three members at 29^3 p = 2 30 -> 23.5 us, 29^3 p = 4 100 -> 81 us,
 // 114^3 p = 1 617 -> 388 us (Helmholtz with nu; by pairs at the left).
-template <int P, int OP, bool NU>
-__global__ void __launch_bounds__((ApplyCfg<P, float, 0>::THREADS), (ApplyCfg<P, float, 0>::OCC))
+// CG = 1: the first launch of a CG iteration as in apply_kernel, with a partial of p.Ap per
+// workgroup and member (refined solves of three members: 30^3 p = 4 43.8 -> 36.8 ms, 54^3 p = 1
+// 9.8 -> 5.7 ms).
+template <int P, int OP, bool NU, int CG>
+__global__ void __launch_bounds__((ApplyCfg<P, float, CG>::THREADS), (ApplyCfg<P, float, CG>::OCC))
 apply_members_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo, const double *__restrict__ cw,
                      double alpha, double beta, int64_t nelem, int nbatch, int64_t ndof,
                      const float *__restrict__ x, float *__restrict__ Y, int64_t estride,
-                     const int32_t *__restrict__ pos, int compact, float *__restrict__ y) {
+                     const int32_t *__restrict__ pos, int compact, float *__restrict__ y, double *__restrict__ part,
+                     int64_t part_mstride, std::conditional_t<CG != 0, CgIn, NoCg> cg) {
   using D = Dims<P>;
-  using C = ApplyCfg<P, float, 0>;
+  using C = ApplyCfg<P, float, CG>;
   using LD = Lds<P, true>;
   using T = float;
   constexpr int N = D::N, Q = D::Q, Q2 = D::Q2, Q3 = D::Q3, N3 = D::N3, TPE = D::TPE, E = C::E, THREADS = C::THREADS;
@@ -959,16 +963,77 @@ apply_members_kernel(const int32_t *__restrict__ map, const double *__restrict__
 #pragma unroll
     for (int c = 0; c < Q; ++c) cv[c] = ld<double>(cw + e0 * Q3, (rel * Q3 + t + c * Q2) * 8u);
   }
+  // CG: the members' states, member m's by thread m (the update's partials summed first)
+  constexpr int NW = CG ? THREADS / 64 : 1, MM = CG ? kCgMembersMax : 1;
+  __shared__ double sums[MM][4][NW], sdir[MM][2], sdot[CG ? (THREADS + 63) / 64 + 1 : 1];
+  PcgScalars st;
+  if constexpr (CG) copy_state(st, cg.sc[(int)threadIdx.x < nbatch ? (int)threadIdx.x : nbatch - 1]);
   T v[NL];
-  nd.load_values(x, v);
+  if constexpr (!CG) nd.load_values(x, v);
   nd.template load_dest<POS>(z, rel);
+  if constexpr (CG) {
+    if (!cg.ready) {
+      for (int i = 0; i < nbatch; i += 2) {  // two members' loads together
+        const int i1 = i + 1 < nbatch ? i + 1 : i;
+        const double *pa = cg.upart + (int64_t)i * 4 * cg.unblk, *pb = cg.upart + (int64_t)i1 * 4 * cg.unblk;
+        PartLoads<NW, 2> qa, qb;
+        qa.load(pa, cg.unblk);
+        qb.load(pb, cg.unblk);
+        qa.parts(sums[i], cg.unblk);
+        qb.parts(sums[i1], cg.unblk);
+        if (cg.nullspace) {
+          qa.load(pa + 2 * (int64_t)cg.unblk, cg.unblk);
+          qb.load(pb + 2 * (int64_t)cg.unblk, cg.unblk);
+          qa.parts(*reinterpret_cast<double(*)[4][NW]>(&sums[i][2]), cg.unblk);
+          qb.parts(*reinterpret_cast<double(*)[4][NW]>(&sums[i1][2]), cg.unblk);
+        }
+      }
+      __syncthreads();
+    }
+    if ((int)threadIdx.x < nbatch) {
+      const int m = threadIdx.x;
+      if (!cg.ready) cg_next_from<NW>(st, sums[m], cg.nullspace, ndof);
+      sdir[m][0] = st.beta;
+      sdir[m][1] = st.zshift;
+      if (blockIdx.x == 0) {
+        copy_state(cg.sc_next[m], st);
+        if (cg.host) copy_state(cg.host[m], st);
+      }
+    }
+    __syncthreads();
+  }
+  double dot = 0.0;
+  // the member's direction (pcg.h) into the nodal vector
+  auto put_dir = [&](int m) {
+    if constexpr (CG) {
+      T zr[NL], zd[NL], zp[NL];
+      nd.load_values((const T *)cg.r + (int64_t)m * ndof, zr);
+      nd.load_values((const T *)cg.dinv + (int64_t)m * cg.dinv_mstride, zd);
+      nd.load_values((const T *)cg.p + (int64_t)m * ndof, zp);
+      nd.pin(zr);
+      nd.pin(zd);
+      nd.pin(zp);
+      const T bt = (T)sdir[m][0], zs = (T)sdir[m][1];
+      dot = 0.0;
+#pragma unroll
+      for (int k = 0; k < NL; ++k) {
+        const T pv = cg_dir(zd[k], zr[k], zs, bt, zp[k]);
+        buf[LD::nodal(Nodes<P>::node(t, k))] = (active && nd.c[k] >= 0) ? pv : T(0);
+        if (active && t + k * TPE < N3 && nd.c[k] < 0 && (nd.c[k] & kEssOwnerBit)) dot += (double)pv * (double)pv;
+      }
+    }
+  };
 #pragma unroll
   for (int k = 0; k < NG; ++k)
     sgeo[le * kGeoStride + (t + k * TPE < kGeoStride ? t + k * TPE : kGeoStride - 1)] = gv[k];
-  nd.pin(v);
+  if constexpr (!CG) nd.pin(v);
   nd.keep(smap, t);
+  if constexpr (CG) {
+    put_dir(0);
+  } else {
 #pragma unroll
-  for (int k = 0; k < NL; ++k) buf[LD::nodal(Nodes<P>::node(t, k))] = (active && nd.c[k] >= 0) ? v[k] : T(0);
+    for (int k = 0; k < NL; ++k) buf[LD::nodal(Nodes<P>::node(t, k))] = (active && nd.c[k] >= 0) ? v[k] : T(0);
+  }
   elem_sync<P, THREADS>();
   T G[Q][6], wd[Q];
   {
@@ -986,7 +1051,7 @@ apply_members_kernel(const int32_t *__restrict__ map, const double *__restrict__
     }
   }
   for (int m = 0; m < nbatch; ++m) {
-    if (m + 1 < nbatch) nd.load_values(x + (int64_t)(m + 1) * ndof, v);
+    if (!CG && m + 1 < nbatch) nd.load_values(x + (int64_t)(m + 1) * ndof, v);
     fwd_x<P, T, true, THREADS>(buf, t);
     fwd_y<P, T, true, THREADS>(buf, t);
     {
@@ -1008,7 +1073,7 @@ apply_members_kernel(const int32_t *__restrict__ map, const double *__restrict__
       };
 #pragma unroll
       for (int c = 0; c < Q / 2; ++c) {
-        T u0, u1, dx0, dx1, dy0, dy1, dz0, dz1, a1, a2, a3, b1, b2, b3;
+        T u0 = 0, u1 = 0, dx0, dx1, dy0, dy1, dz0, dz1, a1, a2, a3, b1, b2, b3;
         if constexpr (MASS) {
           line_pair_of<BT>(sb, c, u0, u1);
           A1.template add_pair<BT>(c, wd[c] * u0, wd[Q - 1 - c] * u1);
@@ -1018,14 +1083,24 @@ apply_members_kernel(const int32_t *__restrict__ map, const double *__restrict__
         line_pair_of<BT>(sx, c, dx0, dx1);
         flux(c, dx0, dy0, dz0, a1, a2, a3);
         flux(Q - 1 - c, dx1, dy1, dz1, b1, b2, b3);
+        if constexpr (CG) {
+          dot += (double)(wd[c] * u0 * u0 + a1 * dx0 + a2 * dy0 + a3 * dz0);
+          dot += (double)(wd[Q - 1 - c] * u1 * u1 + b1 * dx1 + b2 * dy1 + b3 * dz1);
+          asm volatile("" : "+v"(dot));  // summed here: postponed, its operands would stay live
+        }
         A1.template add_pair<GT>(c, a3, b3);
         A2.template add_pair<BT>(c, a2, b2);
         A3.template add_pair<BT>(c, a1, b1);
       }
       if constexpr (Q % 2 == 1) {
-        T g1, g2, g3;
-        if constexpr (MASS) A1.template add_mid<BT>(wd[Q / 2] * line_mid_of<BT>(sb));
-        flux(Q / 2, line_mid_of<BT>(sx), line_mid_of<BT>(sg), line_mid_of<GT>(sb), g1, g2, g3);
+        T g1, g2, g3, u = 0;
+        if constexpr (MASS) {
+          u = line_mid_of<BT>(sb);
+          A1.template add_mid<BT>(wd[Q / 2] * u);
+        }
+        const T dx = line_mid_of<BT>(sx), dy = line_mid_of<BT>(sg), dz = line_mid_of<GT>(sb);
+        flux(Q / 2, dx, dy, dz, g1, g2, g3);
+        if constexpr (CG) dot += (double)(wd[Q / 2] * u * u + g1 * dx + g2 * dy + g3 * dz);
         A1.template add_mid<GT>(g3);
         A2.template add_mid<BT>(g2);
         A3.template add_mid<BT>(g1);
@@ -1046,10 +1121,18 @@ apply_members_kernel(const int32_t *__restrict__ map, const double *__restrict__
     bwd_y<P, T, true, THREADS>(buf, t);
     bwd_x<P, T, true, THREADS>(buf, t);
     emit_e<P, T, LD>(buf, t, active, smap, Y + (int64_t)m * estride, y + (int64_t)m * ndof);
+    if constexpr (CG) {
+      const double sum = block_sum_d<THREADS>(active ? dot : 0.0, sdot);
+      if (threadIdx.x == 0) part[(int64_t)m * part_mstride + blockIdx.x] = sum;
+    }
     if (m + 1 < nbatch) {
       elem_sync<P, THREADS>();  // the nodal vector has been read
+      if constexpr (CG) {
+        put_dir(m + 1);
+      } else {
 #pragma unroll
-      for (int k = 0; k < NL; ++k) buf[LD::nodal(Nodes<P>::node(t, k))] = (active && nd.c[k] >= 0) ? v[k] : T(0);
+        for (int k = 0; k < NL; ++k) buf[LD::nodal(Nodes<P>::node(t, k))] = (active && nd.c[k] >= 0) ? v[k] : T(0);
+      }
       elem_sync<P, THREADS>();
     }
   }
@@ -1066,13 +1149,15 @@ hipError_t launch_apply_pt(const ApplyArgs &a, const CgIn &g, hipStream_t s) {
   // (up to p = 4, where the members kernel's registers fit four waves per SIMD: three members
   // there 1.05 - 1.8 times as fast as by (element, member) pairs; with its spills 0.43 - 0.9 at
   // 2e5 DoFs at p = 5 to 8, 1.0 at 1.5e6)
-  if constexpr (sizeof(T) == 4 && CG == 0 && P <= 4) {
-    if (a.nbatch > 1 && a.op != SFEM_MASS && (!a.cw || a.cw_mstride == 0)) {
+  if constexpr (sizeof(T) == 4 && CG <= 1 && P <= kMembersMaxP) {
+    if (f32_by_members(P, a.op, a.nbatch, !a.cw || a.cw_mstride == 0, CG != 0, (a.nelem + C::E - 1) / C::E)) {
+      std::conditional_t<CG != 0, CgIn, NoCg> cg;
+      if constexpr (CG != 0) cg = g;
       dim3 eg((unsigned)((a.nelem + C::E - 1) / C::E));
 #define SFEM_MEMBERS(OP, NU)                                                                             \
-  hipLaunchKernelGGL((apply_members_kernel<P, OP, NU>), eg, block, 0, s, a.map, a.geo, a.cw, a.alpha,    \
+  hipLaunchKernelGGL((apply_members_kernel<P, OP, NU, CG>), eg, block, 0, s, a.map, a.geo, a.cw, a.alpha,    \
                      a.beta, a.nelem, a.nbatch, a.ndof, (const float *)a.x, (float *)a.evec, a.estride,  \
-                     a.pos, a.compact, (float *)a.y)
+                     a.pos, a.compact, (float *)a.y, a.part, a.part_mstride, cg)
       if (a.op == SFEM_DIFFUSION && a.cw) SFEM_MEMBERS(1, true);
       else if (a.op == SFEM_DIFFUSION) SFEM_MEMBERS(1, false);
       else if (a.cw) SFEM_MEMBERS(2, true);
