@@ -41,6 +41,7 @@
 
 #include <type_traits>
 
+#include "energy.h"
 #include "eo.h"
 #include "geom.h"
 #include "internal.h"
@@ -807,7 +808,12 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
           }
         }
         if constexpr (CG) {
-          dot += (double)(v * u + g1 * dx + g2 * dy + g3 * dz);
+          if constexpr (sizeof(T) == 8) {
+            dot += v * u + g1 * dx + g2 * dy + g3 * dz;
+          } else {
+            if constexpr (MASS) dot = add_energy(dot, v, u);
+            if constexpr (DIFF) dot = add_energy(dot, g1, dx, g2, dy, g3, dz);
+          }
           asm volatile("" : "+v"(dot));  // summed here: postponed, its operands would stay live
         }
       };
@@ -1074,19 +1080,28 @@ apply_members_kernel(const int32_t *__restrict__ map, const double *__restrict__
 #pragma unroll
       for (int c = 0; c < Q / 2; ++c) {
         T u0 = 0, u1 = 0, dx0, dx1, dy0, dy1, dz0, dz1, a1, a2, a3, b1, b2, b3;
+        // (CG: each energy is summed at once; postponed, its operands would stay live)
         if constexpr (MASS) {
           line_pair_of<BT>(sb, c, u0, u1);
-          A1.template add_pair<BT>(c, wd[c] * u0, wd[Q - 1 - c] * u1);
+          const T v0 = wd[c] * u0, v1 = wd[Q - 1 - c] * u1;
+          if constexpr (CG) {
+            dot = add_energy(add_energy(dot, v0, u0), v1, u1);
+            asm volatile("" : "+v"(dot));
+          }
+          A1.template add_pair<BT>(c, v0, v1);
         }
         line_pair_of<GT>(sb, c, dz0, dz1);
         line_pair_of<BT>(sg, c, dy0, dy1);
         line_pair_of<BT>(sx, c, dx0, dx1);
         flux(c, dx0, dy0, dz0, a1, a2, a3);
+        if constexpr (CG) {
+          dot = add_energy(dot, a1, dx0, a2, dy0, a3, dz0);
+          asm volatile("" : "+v"(dot));
+        }
         flux(Q - 1 - c, dx1, dy1, dz1, b1, b2, b3);
         if constexpr (CG) {
-          dot += (double)(wd[c] * u0 * u0 + a1 * dx0 + a2 * dy0 + a3 * dz0);
-          dot += (double)(wd[Q - 1 - c] * u1 * u1 + b1 * dx1 + b2 * dy1 + b3 * dz1);
-          asm volatile("" : "+v"(dot));  // summed here: postponed, its operands would stay live
+          dot = add_energy(dot, b1, dx1, b2, dy1, b3, dz1);
+          asm volatile("" : "+v"(dot));
         }
         A1.template add_pair<GT>(c, a3, b3);
         A2.template add_pair<BT>(c, a2, b2);
@@ -1100,7 +1115,7 @@ apply_members_kernel(const int32_t *__restrict__ map, const double *__restrict__
         }
         const T dx = line_mid_of<BT>(sx), dy = line_mid_of<BT>(sg), dz = line_mid_of<GT>(sb);
         flux(Q / 2, dx, dy, dz, g1, g2, g3);
-        if constexpr (CG) dot += (double)(wd[Q / 2] * u * u + g1 * dx + g2 * dy + g3 * dz);
+        if constexpr (CG) dot = add_energy(add_energy(dot, wd[Q / 2] * u, u), g1, dx, g2, dy, g3, dz);
         A1.template add_mid<GT>(g3);
         A2.template add_mid<BT>(g2);
         A3.template add_mid<BT>(g1);
