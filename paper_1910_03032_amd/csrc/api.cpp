@@ -73,6 +73,7 @@ struct sfem_ctx {
   bool ready = false;
   int p = 0, q = 0;
   int64_t nelem = 0, ndof = 0;
+  int thin = 0;                    // some element has nearly parallel edges (kMetricLimit of geom.h)
   Rules1D rules;
   int32_t *d_map = nullptr;        // [nelem][n^3] flagged (sole / essential bits)
   double *d_xyz = nullptr;         // [nelem][8][3]
@@ -453,6 +454,7 @@ sfem_status do_apply(sfem_ctx *c, int op, bool f32, int nbatch, const void *x, v
   a.cw_mstride = c->nfield > 1 ? c->nelem * q3_of(c) : 0;
   a.alpha = op == SFEM_HELMHOLTZ ? c->alpha : (op == SFEM_MASS ? 1.0 : 0.0);
   a.beta = op == SFEM_HELMHOLTZ ? c->beta : (op == SFEM_MASS ? 0.0 : 1.0);
+  a.thin = c->thin;
   hipError_t e;
   if (cg) e = cg->z ? launch_apply_cgz(a, *cg, c->stream)
                     : (f32 ? launch_apply_cg32(a, *cg, c->stream) : launch_apply_cg64(a, *cg, c->stream));
@@ -569,7 +571,7 @@ sfem_status run_pcg(sfem_ctx *c, int op, int nb, const T *b, T *x, bool x0_zero,
   };
   if (!any_active()) return SFEM_OK;
   // (by members a workgroup leaves one partial for each; cg_nparts is enough for both)
-  const bool members = f32 && f32_by_members(c->p, op, nb, c->nfield <= 1, true, cg_nparts(c, f32, 1));
+  const bool members = f32 && f32_by_members(c->p, op, nb, c->nfield <= 1, c->thin != 0, true, cg_nparts(c, f32, 1));
   const int nelem_parts = members ? cg_nparts(c, f32, 1) : cg_nparts(c, f32, nb), unblk = cg_update_nblk(n, nb);
   const CgDofs dofs{c->d_doff, c->d_slot};
   CgIn g{};
@@ -939,7 +941,7 @@ static sfem_status sfem_setup_body(sfem_ctx *c, int p, int q, int64_t nelem, con
   if ((st = dalloc(c, &c->d_slot, (int64_t)slots.size())) != SFEM_OK) return st;
   if ((st = dalloc(c, &c->d_doff, ndof + 1)) != SFEM_OK) return st;
   int *d_bad = nullptr;
-  if ((st = dalloc(c, &d_bad, 1)) != SFEM_OK) return st;
+  if ((st = dalloc(c, &d_bad, 2)) != SFEM_OK) return st;
   if (na > 0) {
     HIPCHK(c, hipMemcpyAsync(c->d_alist, alist.data(), alist.size() * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(c->d_aoff, aoff.data(), aoff.size() * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));
@@ -958,17 +960,18 @@ static sfem_status sfem_setup_body(sfem_ctx *c, int p, int q, int64_t nelem, con
     HIPCHK(c, hipMemcpyAsync(c->d_map, imap.data(), imap.size() * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(c->d_xyz, xyz.data(), xyz.size() * sizeof(double), hipMemcpyHostToDevice, c->stream));
   }
-  int h_bad = 0;
+  int h_bad[2] = {0, 0};
   if (d_bad) {
-    HIPCHK(c, VecOps<float>::fill((float *)d_bad, 0.0f, 1, c->stream));
+    HIPCHK(c, VecOps<float>::fill((float *)d_bad, 0.0f, 2, c->stream));
     HIPCHK(c, launch_check_det(q, c->rules.gauss_x.data(), c->rules.gauss_w.data(), c->d_xyz, nelem,
                                d_bad, c->stream));
     HIPCHK(c, launch_geo_setup(c->d_xyz, nelem, c->d_geo, c->stream));
-    HIPCHK(c, hipMemcpyAsync(&h_bad, d_bad, sizeof(int), hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipMemcpyAsync(h_bad, d_bad, sizeof(h_bad), hipMemcpyDeviceToHost, c->stream));
   }
   HIPCHK(c, hipStreamSynchronize(c->stream));
   dfree(c, d_bad);
-  if (h_bad) {
+  c->thin = h_bad[1];
+  if (h_bad[0]) {
     free_all(c);
     return fail(c, SFEM_E_MESH, "det J <= 0 (or not finite) at some quadrature point: inverted or degenerate element");
   }

@@ -525,7 +525,8 @@ struct NoCg {};
 // ([nelem][q^3] per field, float64 for both precisions), and without (nu = 1) none.  The
 // float64 operators multiply by adj(J) twice.  The float32 ones form the six factors in
 // float64 and round each once, so that they are those a stored float32 copy would hold
-// (forming them in float32 rounds adj(J) twice each: 5-15 % more error of the apply).
+// (forming them in float32 rounds adj(J) twice each: 5-15 % more error of the apply), THIN from
+// adj(J) where the metric would lose digits (kMetricLimit).
 //
 // Reading the factors (7 values per point) bound the kernel by HBM: of the 553 MB of an apply
 // at 32^3 p = 4 in float64, 396 MB were factors.  Formed, they cost 35 to 40 operations a
@@ -544,7 +545,7 @@ struct NoCg {};
 // unused and part required.  The partials
 // of p.Ap are then the element energies at the quadrature points, sum v u + g . grad_ref u, plus
 // p^2 of the essential DoFs at the element that carries their flag (kEssOwnerBit).
-template <int P, typename T, int OP, bool NU, int CG>
+template <int P, typename T, int OP, bool NU, int CG, bool THIN>
 __global__ void __launch_bounds__((ApplyCfg<P, T, CG>::THREADS), (ApplyCfg<P, T, CG>::OCC))
 apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
              const double *__restrict__ cw, int64_t cw_mstride, double alpha, double beta, int64_t nelem,
@@ -731,7 +732,7 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
       using BT = eo::Tab1<P, 0>;
       using GT = eo::Tab1<P, 1>;
       constexpr rules::GaussRule<Q> gr = rules::gauss<Q>();
-      std::conditional_t<sizeof(T) == 8, LineGeom, LineMetric> L;
+      std::conditional_t<sizeof(T) == 8 || THIN, LineGeom, LineMetric> L;
       const int la = t % Q, lb = t / Q;
       L.init(sgeo + le * kGeoStride, sgq[la], sgq[lb]);
       const double wab = sgq[Q + la] * sgq[Q + lb];
@@ -1165,7 +1166,8 @@ hipError_t launch_apply_pt(const ApplyArgs &a, const CgIn &g, hipStream_t s) {
   // there 1.05 - 1.8 times as fast as by (element, member) pairs; with its spills 0.43 - 0.9 at
   // 2e5 DoFs at p = 5 to 8, 1.0 at 1.5e6)
   if constexpr (sizeof(T) == 4 && CG <= 1 && P <= kMembersMaxP) {
-    if (f32_by_members(P, a.op, a.nbatch, !a.cw || a.cw_mstride == 0, CG != 0, (a.nelem + C::E - 1) / C::E)) {
+    if (f32_by_members(P, a.op, a.nbatch, !a.cw || a.cw_mstride == 0, a.thin != 0, CG != 0,
+                       (a.nelem + C::E - 1) / C::E)) {
       std::conditional_t<CG != 0, CgIn, NoCg> cg;
       if constexpr (CG != 0) cg = g;
       dim3 eg((unsigned)((a.nelem + C::E - 1) / C::E));
@@ -1183,16 +1185,26 @@ hipError_t launch_apply_pt(const ApplyArgs &a, const CgIn &g, hipStream_t s) {
   }
   std::conditional_t<CG != 0, CgIn, NoCg> cg;
   if constexpr (CG != 0) cg = g;
-#define SFEM_APPLY(OP, NU)                                                                              \
-  hipLaunchKernelGGL((apply_kernel<P, T, OP, NU, CG>), grid, block, 0, s, a.map, a.geo, a.cw,           \
+#define SFEM_APPLY_GEO(OP, NU, THIN)                                                                    \
+  hipLaunchKernelGGL((apply_kernel<P, T, OP, NU, CG, THIN>), grid, block, 0, s, a.map, a.geo, a.cw,     \
                      a.cw_mstride, a.alpha, a.beta, a.nelem, a.nbatch, a.ndof, (const T *)a.x,          \
                      (T *)a.evec, a.estride, a.pos, a.compact, (T *)a.y, a.part, a.part_mstride, cg)
+#define SFEM_APPLY(OP, NU)                                            \
+  do {                                                                \
+    if constexpr (sizeof(T) == 4 && OP != SFEM_MASS) {                \
+      if (a.thin) SFEM_APPLY_GEO(OP, NU, true);                       \
+      else SFEM_APPLY_GEO(OP, NU, false);                             \
+    } else {                                                          \
+      SFEM_APPLY_GEO(OP, NU, false);                                  \
+    }                                                                 \
+  } while (0)
   if (a.op == SFEM_MASS) SFEM_APPLY(0, false);
   else if (a.op == SFEM_DIFFUSION && a.cw) SFEM_APPLY(1, true);
   else if (a.op == SFEM_DIFFUSION) SFEM_APPLY(1, false);
   else if (a.cw) SFEM_APPLY(2, true);
   else SFEM_APPLY(2, false);
 #undef SFEM_APPLY
+#undef SFEM_APPLY_GEO
   return hipGetLastError();
 }
 

@@ -10,8 +10,10 @@
 //               r3 = J1 x J2 (degree 2); w |J| J^{-1} J^{-T} = (w / |J|) adj adj^T is applied
 //               as two products with adj;
 //   LineMetric  the metric M = J^T J (degree at most 2) and adj adj^T = adj(M), 12 operations
-//               per point.  It squares the element's aspect ratio into the rounding error, so
-//               it serves the float32 operators only, whose factors are rounded from it.
+//               per point.  adj(M) cancels where two columns of J are nearly parallel: its
+//               entries lose 3e-16 / sin^2 of their angle (LineGeom: 1e-16 / sin).  It serves
+//               the float32 operators, whose factors are rounded from it, on meshes without
+//               such elements (kMetricLimit), and LineGeom those with.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -23,6 +25,11 @@ namespace sfem {
 
 // Stored per element, float64: c1, c2, c3, c12, c13, c23, c123 (3 components each), padded.
 constexpr int kGeoStride = 24;
+
+// Largest 1 / sin^2 of the angle between two columns of J (each of the element's largest length
+// along its direction) at a quadrature point for which the float32 operators form their factors by
+// LineMetric: 3e-10 of error at the limit, against 6e-8 of the rounding to float32.
+constexpr double kMetricLimit = 1048576.0;
 
 // Gauss rule with q points, indexed by the thread.
 template <int Q>
@@ -85,6 +92,17 @@ struct LineGeom {
     }
   }
   __device__ __forceinline__ double det(double x) const { return (d0 + (x * x) * d2) + x * d1; }
+  // s adj adj^T at xi_3 = x as (11, 22, 33, 12, 13, 23), rounded to float32
+  __device__ __forceinline__ void factors(double x, double s, float (&G)[6]) const {
+    double r1[3], r2[3], r3[3];
+    adj(x, r1, r2, r3);
+    G[0] = (float)(s * dot3(r1, r1));
+    G[1] = (float)(s * dot3(r2, r2));
+    G[2] = (float)(s * dot3(r3, r3));
+    G[3] = (float)(s * dot3(r1, r2));
+    G[4] = (float)(s * dot3(r1, r3));
+    G[5] = (float)(s * dot3(r2, r3));
+  }
 };
 
 // Coefficients of the metric M = J^T J and of |J| along a thread's xi_3 line.

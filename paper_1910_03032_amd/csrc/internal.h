@@ -56,6 +56,7 @@ struct ApplyArgs {
   const double *cw;         // w nu / |J| at the points, [nei][q^3], or null (nu = 1)
   int64_t cw_mstride;       // entries of cw between batch members (0 = shared)
   double alpha, beta;       // coefficients of the mass and diffusion terms
+  int thin;                 // some element needs LineGeom's factors in float32 (geom.h)
   int64_t ndof;
   int nbatch;
   int64_t nelem;
@@ -92,13 +93,14 @@ hipError_t launch_apply_cg64(const ApplyArgs &a, const CgIn &g, hipStream_t s);
 hipError_t launch_apply_cg32(const ApplyArgs &a, const CgIn &g, hipStream_t s);
 hipError_t launch_apply_cgz(const ApplyArgs &a, const CgIn &g, hipStream_t s);
 // The float32 kernels that take an element's members in turn (apply_impl.h): the orders whose
-// factors fit the registers, members with one coefficient, and enough workgroups without the
+// factors fit the registers, members with one coefficient, elements whose factors the metric gives
+// (thin: geom.h), and enough workgroups without the
 // members to fill the chip (1024 fit; three members, a solve: 314 groups at 13^3 p = 4 3.95 ms
 // against 3.58 by pairs, 584 at 18^3 p = 3 3.69 against 3.97); in a CG iteration at most as many
 // members as the kernel keeps states of.  groups: workgroups of the elements alone.
 constexpr int kMembersMaxP = 4, kCgMembersMax = 8, kMembersMinGroups = 400;
-inline bool f32_by_members(int p, int op, int nb, bool one_coef, bool cg, int64_t groups) {
-  return p <= kMembersMaxP && nb > 1 && op != SFEM_MASS && one_coef && groups >= kMembersMinGroups &&
+inline bool f32_by_members(int p, int op, int nb, bool one_coef, bool thin, bool cg, int64_t groups) {
+  return p <= kMembersMaxP && nb > 1 && op != SFEM_MASS && one_coef && !thin && groups >= kMembersMinGroups &&
          (!cg || nb <= kCgMembersMax);
 }
 // elements per workgroup of the apply kernel (one partial of p.Ap per workgroup)
@@ -134,7 +136,8 @@ struct DiagArgs {
 };
 hipError_t launch_diag(const DiagArgs &a, hipStream_t s);
 
-// *bad = 1 if |J| is not positive at some quadrature point.
+// bad[0] = 1 if |J| is not positive at some quadrature point, bad[1] = 1 if two columns of J are
+// nearly parallel there (kMetricLimit of geom.h).
 hipError_t launch_check_det(int q, const double *gx, const double *gw, const double *xyz, int64_t nei,
                             int *bad, hipStream_t s);
 // Collocated (GLL-integrated) mass contributions of every element node: sole DoFs into

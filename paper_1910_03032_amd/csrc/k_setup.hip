@@ -90,7 +90,8 @@ __global__ void colloc_mass_kernel(GaussArg g, int p, const double *__restrict__
   }
 }
 
-// |J| > 0 at the quadrature points (else, or not a number, *bad = 1).
+// |J| > 0 at the quadrature points (else, or not a number, bad[0] = 1), and no two columns of J
+// nearly parallel there (else bad[1] = 1; kMetricLimit).
 __global__ void check_det_kernel(GaussArg g, int q, const double *__restrict__ xyz, int64_t nei,
                                  int *__restrict__ bad) {
   const int64_t q3 = (int64_t)q * q * q;
@@ -107,7 +108,27 @@ __global__ void check_det_kernel(GaussArg g, int q, const double *__restrict__ x
   const double A10 = J[1][2] * J[2][0] - J[1][0] * J[2][2];
   const double A20 = J[1][0] * J[2][1] - J[1][1] * J[2][0];
   const double det = J[0][0] * A00 + J[0][1] * A10 + J[0][2] * A20;
-  if (!(det > 0.0)) *bad = 1;
+  if (!(det > 0.0)) bad[0] = 1;
+  // squared lengths: the longest edge along each direction (halved, as the columns of J)
+  const double *X = xyz + e * 24;
+  double len[3] = {0.0, 0.0, 0.0};
+  for (int d = 0; d < 3; ++d)
+    for (int v = 0; v < 8; ++v) {
+      if ((v >> d) & 1) continue;
+      double s = 0.0;
+      for (int r = 0; r < 3; ++r) {
+        const double h = 0.5 * (X[(v + (1 << d)) * 3 + r] - X[v * 3 + r]);
+        s += h * h;
+      }
+      len[d] = s > len[d] ? s : len[d];
+    }
+  for (int i = 0; i < 3; ++i) {
+    const int j = i == 2 ? 0 : i + 1;
+    const double u[3] = {J[0][i], J[1][i], J[2][i]}, v[3] = {J[0][j], J[1][j], J[2][j]};
+    double c[3];
+    cross3(u, v, c);
+    if (len[i] * len[j] > kMetricLimit * dot3(c, c)) bad[1] = 1;
+  }
 }
 
 __global__ void qpoint_coords_kernel(GaussArg g, int q, const double *__restrict__ xyz,
