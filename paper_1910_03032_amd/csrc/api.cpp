@@ -413,11 +413,15 @@ sfem_status check_op_batch(sfem_ctx *c, int op, int nbatch) {
   return SFEM_OK;
 }
 
-// Partials of p.Ap per member that the element kernel of a CG iteration of nb members leaves:
-// one per workgroup (a group of (element, member) pairs).
-int cg_nparts(const sfem_ctx *c, bool f32, int nb) {
-  const int e = f32 ? apply_group_elems_f32(c->p) : apply_group_elems_f64(c->p);
-  return (int)((c->nelem * nb + e - 1) / e);
+// Elements per workgroup of a CG iteration's element kernel, whether it takes the members of an
+// element in turn, and the partials of p.Ap that it leaves per member.
+int cg_group(const sfem_ctx *c, bool f32) { return f32 ? apply_group_elems_f32(c->p) : apply_group_elems_f64(c->p); }
+bool cg_by_members(const sfem_ctx *c, int op, bool f32, int nb) {
+  return f32 && f32_by_members(c->p, op, nb, c->nfield <= 1, c->thin != 0, true,
+                               cg_parts(c->nelem, 1, cg_group(c, f32), false));
+}
+int cg_nparts(const sfem_ctx *c, int op, bool f32, int nb) {
+  return (int)cg_parts(c->nelem, nb, cg_group(c, f32), cg_by_members(c, op, f32, nb));
 }
 
 // Enqueue y = A x on the context stream (no argument checks).  With cg: the first launch of a CG
@@ -448,7 +452,7 @@ sfem_status do_apply(sfem_ctx *c, int op, bool f32, int nbatch, const void *x, v
   a.pos = c->d_pos;
   a.compact = c->compact;
   a.part = part;
-  a.part_mstride = cg ? cg_nparts(c, f32, nbatch) : 0;
+  a.part_mstride = cg ? cg_nparts(c, op, f32, nbatch) : 0;
   a.geo = c->d_geo;
   a.cw = op != SFEM_MASS ? c->d_cw : nullptr;
   a.cw_mstride = c->nfield > 1 ? c->nelem * q3_of(c) : 0;
@@ -516,35 +520,54 @@ template <typename T>
 struct PcgWork {
   T *r, *p, *w;
   double *part;   // vector-kernel partials [nb][5][nblk]
-  double *dpart;  // p^T A p partials of the apply [nb][nparts]
+  double *dpart;  // p^T A p partials of the element kernel [nb][nparts]
+  double *fpart;  // the same folded [nb][nfold] (nfold = 0: not folded)
   PcgScalars *sc;  // [2][nb]: the state after the update, the state after the element kernel
-  int nblk, nparts;
+  int nblk, nparts, nfold;
 };
 
 template <typename T>
-size_t pcg_work_bytes(const sfem_ctx *c, int64_t n, int nb) {
-  const int nblk = vec_nblk(n);
+size_t pcg_work_bytes(const sfem_ctx *c, int op, int64_t n, int nb) {
+  const int nblk = vec_nblk(n), nparts = cg_nparts(c, op, sizeof(T) == 4, nb);
   return 3 * align_up((size_t)n * nb * sizeof(T)) + align_up((size_t)nb * 5 * nblk * sizeof(double)) +
-         align_up((size_t)nb * cg_nparts(c, sizeof(T) == 4, nb) * sizeof(double)) +
-         align_up((size_t)2 * nb * sizeof(PcgScalars));
+         align_up((size_t)nb * nparts * sizeof(double)) +
+         align_up((size_t)nb * cg_fold_nblk(nparts) * sizeof(double)) + align_up((size_t)2 * nb * sizeof(PcgScalars));
 }
 
 template <typename T>
-PcgWork<T> carve_pcg(const sfem_ctx *c, Carver &cv, int64_t n, int nb) {
+PcgWork<T> carve_pcg(const sfem_ctx *c, Carver &cv, int op, int64_t n, int nb) {
   PcgWork<T> w;
   w.nblk = vec_nblk(n);
-  w.nparts = cg_nparts(c, sizeof(T) == 4, nb);
+  w.nparts = cg_nparts(c, op, sizeof(T) == 4, nb);
+  w.nfold = cg_fold_nblk(w.nparts);
   w.r = cv.take<T>(n * nb);
   w.p = cv.take<T>(n * nb);
   w.w = cv.take<T>(n * nb);
   w.part = cv.take<double>((int64_t)nb * 5 * w.nblk);
   w.dpart = cv.take<double>((int64_t)nb * w.nparts);
+  w.fpart = cv.take<double>((int64_t)nb * w.nfold);
   w.sc = cv.take<PcgScalars>(2 * (int64_t)nb);
   return w;
 }
 
-// Jacobi-PCG on the context stream, two launches per iteration (pcg.h).  On return hs[] (pinned
-// host memory) holds the final scalars.
+// The partials of p.Ap that the update sums, [nb][n]: the element kernel's, or those of a long list
+// folded by a launch of its own.
+struct DotParts {
+  const double *p;
+  int n;
+};
+template <typename T>
+hipError_t cg_dot_parts(const PcgWork<T> &w, int nb, hipStream_t s, DotParts &out) {
+  if (!w.nfold) {
+    out = DotParts{w.dpart, w.nparts};
+    return hipSuccess;
+  }
+  out = DotParts{w.fpart, w.nfold};
+  return launch_cg_fold(w.dpart, w.nparts, w.nparts, w.fpart, w.nfold, nb, s);
+}
+
+// Jacobi-PCG on the context stream, two launches per iteration (pcg.h) and one more to fold
+// many partials (cg_plan.h).  On return hs[] (pinned host memory) holds the final scalars.
 template <typename T>
 sfem_status run_pcg(sfem_ctx *c, int op, int nb, const T *b, T *x, bool x0_zero, double rtol,
                     int maxit, int check_every, const T *dinv, int64_t dms, PcgWork<T> &w,
@@ -570,9 +593,7 @@ sfem_status run_pcg(sfem_ctx *c, int op, int nb, const T *b, T *x, bool x0_zero,
     return false;
   };
   if (!any_active()) return SFEM_OK;
-  // (by members a workgroup leaves one partial for each; cg_nparts is enough for both)
-  const bool members = f32 && f32_by_members(c->p, op, nb, c->nfield <= 1, c->thin != 0, true, cg_nparts(c, f32, 1));
-  const int nelem_parts = members ? cg_nparts(c, f32, 1) : cg_nparts(c, f32, nb), unblk = cg_update_nblk(n, nb);
+  const int unblk = cg_update_nblk(n, nb);
   const CgDofs dofs{c->d_doff, c->d_slot};
   CgIn g{};
   g.r = w.r;
@@ -587,8 +608,10 @@ sfem_status run_pcg(sfem_ctx *c, int op, int nb, const T *b, T *x, bool x0_zero,
   g.nullspace = nullspace;
   for (int it = 0; it < maxit; ++it) {
     if ((st = do_apply(c, op, f32, nb, nullptr, w.w, w.dpart, nullptr, false, &g)) != SFEM_OK) return st;
+    DotParts dp;
+    HIPCHK(c, cg_dot_parts(w, nb, s, dp));
     HIPCHK(c, VecOps<T>::update(dofs, (const T *)c->evec.p, c->nentries, w.w, x, w.p, w.r, dinv, dms, w.sc + nb,
-                                w.sc, w.dpart, cg_nparts(c, f32, nb), nelem_parts, w.part, unblk, n, nb, s));
+                                w.sc, dp.p, dp.n, dp.n, w.part, unblk, n, nb, s));
     g.ready = 0;
     if ((it + 1) % check_every == 0 || it + 1 == maxit) {
       HIPCHK(c, launch_cg_finish(w.sc, hs, w.part, unblk, nb, nullspace, n, s));
@@ -680,11 +703,11 @@ hipError_t lor_vcycle(sfem_ctx *c, int op, bool f32, const double *r, double *z)
 // (pcg.h).  The element kernel writes the state it completes to pinned host memory; the host
 // waits for it behind an event with the rest of the iteration already queued, so the GPU never
 // waits for the host.  When the state shows that the solve stopped, that iteration changes
-// nothing (alpha = 0 once inactive).  dpart: the element kernel's partials; part: those of the
-// dots ([5][vec_nblk(n)]).  On return hs holds the final scalars.
+// nothing (alpha = 0 once inactive).  pw: the partials' places (those of the dots are in pw.part).
+// On return hs holds the final scalars.
 template <typename TZ>
 sfem_status run_pcg_lor_z(sfem_ctx *c, int op, const double *b, double *x, bool x0_zero, double rtol, int maxit,
-                          int nullspace, double *dpart, double *part, TZ *z, PcgScalars &hs) {
+                          int nullspace, const PcgWork<double> &pw, TZ *z, PcgScalars &hs) {
   constexpr bool f32 = sizeof(TZ) == 4;
   const int64_t n = c->ndof;
   hipStream_t s = c->stream;
@@ -694,6 +717,7 @@ sfem_status run_pcg_lor_z(sfem_ctx *c, int op, const double *b, double *x, bool 
   PcgScalars *sc = reinterpret_cast<PcgScalars *>(c->lor_scal);  // [2]
   PcgScalars *h = reinterpret_cast<PcgScalars *>(c->h_pinned);   // [2]
   const int unblk = cg_update_nblk(n, 1);
+  double *part = pw.part;
   sfem_status st;
   hs = PcgScalars{};
   const TZ *bz;  // the V-cycle's input
@@ -724,7 +748,6 @@ sfem_status run_pcg_lor_z(sfem_ctx *c, int op, const double *b, double *x, bool 
     (void)hipGetLastError();
     return fail(c, SFEM_E_HIP, "LOR CG: event creation failed");
   }
-  const int nparts = cg_nparts(c, false, 1);
   const CgDofs dofs{c->d_doff, c->d_slot};
   const FirstSweep<TZ> fs = amg_first_sweep<TZ>(amg);
   CgIn g{};
@@ -740,11 +763,13 @@ sfem_status run_pcg_lor_z(sfem_ctx *c, int op, const double *b, double *x, bool 
   auto body = [&]() -> sfem_status {
     for (int it = 0; it < maxit; ++it) {
       g.host = h + (it & 1);
-      if ((st = do_apply(c, op, false, 1, nullptr, w, dpart, nullptr, false, &g)) != SFEM_OK) return st;
+      if ((st = do_apply(c, op, false, 1, nullptr, w, pw.dpart, nullptr, false, &g)) != SFEM_OK) return st;
       HIPCHK(c, hipEventRecord(ev, s));
       g.ready = 0;
+      DotParts dp;
+      HIPCHK(c, cg_dot_parts(pw, 1, s, dp));
       HIPCHK(c, launch_cgz_update<TZ>(dofs, (const double *)c->evec.p, w, x, pv, r, z, r32, fs.t, fs.dinv, fs.omega,
-                                      sc + 1, sc, dpart, nparts, n, s));
+                                      sc + 1, sc, dp.p, dp.n, n, s));
       HIPCHK(c, amg_vcycle<TZ>(amg, bz, z, s, fs.t != nullptr));
       HIPCHK(c, launch_cgz_dots<TZ>(r, z, nullptr, part, unblk, n, s));
       HIPCHK(c, hipEventSynchronize(ev));
@@ -764,12 +789,11 @@ sfem_status run_pcg_lor_z(sfem_ctx *c, int op, const double *b, double *x, bool 
 }
 
 sfem_status run_pcg_lor(sfem_ctx *c, int op, bool f32, const double *b, double *x, bool x0_zero,
-                        double rtol, int maxit, int nullspace, double *dpart, double *part,
+                        double rtol, int maxit, int nullspace, const PcgWork<double> &pw,
                         PcgScalars &hs) {
   if (f32)
-    return run_pcg_lor_z<float>(c, op, b, x, x0_zero, rtol, maxit, nullspace, dpart, part,
-                                c->lor_work32 + c->ndof, hs);
-  return run_pcg_lor_z<double>(c, op, b, x, x0_zero, rtol, maxit, nullspace, dpart, part, c->lor_work + c->ndof, hs);
+    return run_pcg_lor_z<float>(c, op, b, x, x0_zero, rtol, maxit, nullspace, pw, c->lor_work32 + c->ndof, hs);
+  return run_pcg_lor_z<double>(c, op, b, x, x0_zero, rtol, maxit, nullspace, pw, c->lor_work + c->ndof, hs);
 }
 
 sfem_status require_ready(sfem_ctx *c) {
@@ -1235,14 +1259,14 @@ static sfem_status sfem_pcg_body(sfem_ctx *c, int op, int nbatch, const double *
   int outer = 0;
 
   if (opts->mode == 0) {
-    const size_t bytes = pcg_work_bytes<double>(c, n, nb) + align_up((size_t)nb * sizeof(double)) +
+    const size_t bytes = pcg_work_bytes<double>(c, op, n, nb) + align_up((size_t)nb * sizeof(double)) +
                          (ns ? align_up((size_t)n * nb * sizeof(double)) : 0);
     if ((st = ensure_ws(c, bytes)) != SFEM_OK) return st;
     // (the LOR CG keeps two scalar copies in flight)
     if ((st = ensure_pinned(c, std::max(sizeof(PcgScalars), sizeof(double)) * std::max(nb, 2))) != SFEM_OK)
       return st;
     Carver cv{(char *)c->ws.p};
-    PcgWork<double> w = carve_pcg<double>(c, cv, n, nb);
+    PcgWork<double> w = carve_pcg<double>(c, cv, op, n, nb);
     double *d_out = cv.take<double>(nb);
     const double *bs = b;  // the right-hand side actually solved for
     if (ns) {
@@ -1261,8 +1285,7 @@ static sfem_status sfem_pcg_body(sfem_ctx *c, int op, int nbatch, const double *
       // members one after another, each preconditioned by the LOR multigrid V-cycle
       for (int m = 0; m < nb; ++m)
         if ((st = run_pcg_lor(c, op, lor32, bs + (int64_t)m * n, x + (int64_t)m * n,
-                              opts->x0_zero != 0, opts->rtol, opts->maxit, ns, w.dpart, w.part,
-                              fin[m])) != SFEM_OK)
+                              opts->x0_zero != 0, opts->rtol, opts->maxit, ns, w, fin[m])) != SFEM_OK)
           return st;
     } else {
       if ((st = run_pcg<double>(c, op, nb, bs, x, opts->x0_zero != 0, opts->rtol, opts->maxit,
@@ -1293,7 +1316,7 @@ static sfem_status sfem_pcg_body(sfem_ctx *c, int op, int nbatch, const double *
     }
   } else {
     // FP64 iterative refinement around an FP32 Jacobi-PCG
-    const size_t bytes = pcg_work_bytes<float>(c, n, nb) + 2 * align_up((size_t)n * nb * sizeof(double)) +
+    const size_t bytes = pcg_work_bytes<float>(c, op, n, nb) + 2 * align_up((size_t)n * nb * sizeof(double)) +
                          2 * align_up((size_t)n * nb * sizeof(float)) +
                          align_up((size_t)nb * 3 * sizeof(double)) +
                          align_up((size_t)nb * nblk * sizeof(double)) +
@@ -1301,7 +1324,7 @@ static sfem_status sfem_pcg_body(sfem_ctx *c, int op, int nbatch, const double *
     if ((st = ensure_ws(c, bytes)) != SFEM_OK) return st;
     if ((st = ensure_pinned(c, std::max(sizeof(PcgScalars), 3 * sizeof(double)) * nb)) != SFEM_OK) return st;
     Carver cv{(char *)c->ws.p};
-    PcgWork<float> w = carve_pcg<float>(c, cv, n, nb);
+    PcgWork<float> w = carve_pcg<float>(c, cv, op, n, nb);
     double *r64 = cv.take<double>(n * nb);
     double *w64 = cv.take<double>(n * nb);
     float *r32 = cv.take<float>(n * nb);

@@ -881,14 +881,27 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
     if constexpr (C::REFORM) asm volatile("" : "+v"(te));
     emit_e<P, T, LD>(buf, te, active, smap, Ym, ym);
     if constexpr (CG) {
-      // one sum per member; the block's pairs v_lo.. hold members (v_lo + k) mod nbatch,
-      // k < count (a uniform test: members without a pair here get 0 without a sum)
-      for (int mm = 0; mm < nbatch; ++mm) {
-        const bool here = ((mm - (int)r0 + nbatch) % nbatch) < count;
-        double sum = 0.0;
-        if (here)
-          sum = block_sum_d<THREADS>((active && (int)m == mm) ? dot : 0.0, reinterpret_cast<double *>(smem));
-        if (threadIdx.x == 0) part[(int64_t)mm * part_mstride + blockIdx.x] = sum;
+      // one sum per member, or per pair where a workgroup holds a member once at most
+      // (cg_parts); the workgroup's pairs k < count hold the members (r0 + k) mod nbatch
+      double *sh = reinterpret_cast<double *>(smem);
+      if (nbatch == 1) {
+        const double sum = block_sum_d<THREADS>(active ? dot : 0.0, sh);
+        if (threadIdx.x == 0) part[blockIdx.x] = sum;
+      } else {
+        static_assert(E * LD::BUF * sizeof(T) >= THREADS * sizeof(double), "the threads' parts");
+        __syncthreads();
+        sh[threadIdx.x] = active ? dot : 0.0;
+        __syncthreads();
+        constexpr int NWF = THREADS / 64;  // full waves, each takes the next sum
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nsum = cg_sums(nbatch, E, count);
+        for (int i = wave; wave < NWF && i < nsum; i += NWF) {
+          const CgSum c = cg_sum(i, nbatch, E, blockIdx.x, e0, (int)r0);
+          double sum = 0.0;
+          for (int k = c.first; k < count; k += c.step)
+            for (int j = lane; j < TPE; j += 64) sum += sh[k * TPE + j];
+          sum = wave_total(sum);
+          if (lane == 0) part[(int64_t)c.member * part_mstride + c.slot] = sum;
+        }
       }
     }
   }

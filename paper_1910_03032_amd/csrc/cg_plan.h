@@ -1,0 +1,43 @@
+// Sizes and rules of the CG iteration's two launches that need no GPU: the places of the partials
+// of p.Ap, and when a long list of them is folded first.
+#pragma once
+
+#include <stdint.h>
+
+#include "eo.h"
+
+namespace sfem {
+
+// Partials of p.Ap per member that the element kernel leaves, E elements per workgroup: one per
+// workgroup, and where it takes (element, member) pairs of more members than it has pairs, one
+// per element (every other workgroup's partial would be 0).
+SFEM_HD int64_t cg_parts(int64_t nelem, int nb, int E, bool by_members) {
+  if (by_members) return (nelem + E - 1) / E;
+  return nb > E ? nelem : (nelem * nb + E - 1) / E;
+}
+
+// By pairs a workgroup whose first pair is (e0, r0), with count <= E pairs, leaves cg_sums of them:
+// the i-th is the sum of its pairs first, first + step, .. of one member, at slot of that member.
+struct CgSum {
+  int first, step, member;
+  int64_t slot;
+};
+SFEM_HD int cg_sums(int nb, int E, int count) { return nb > E ? count : nb; }
+SFEM_HD CgSum cg_sum(int i, int nb, int E, int64_t block, int64_t e0, int r0) {
+  if (nb > E) return CgSum{i, E, (r0 + i) % nb, e0 + (r0 + i) / nb};
+  return CgSum{(i - r0 + nb) % nb, nb, i, block};
+}
+
+// More than kCgFoldMin partials of a member are summed to cg_fold_nblk(count) before the update, all
+// of whose workgroups read them (0: no fold).  An iteration with and without, float64: 9400 partials
+// (64^3 p = 1) 70 and 71 us, 3.6e4 233 and 233, 7.5e4 (eight members) 531 and 540, 2.1e5 (180^3 p = 1)
+// 1351 and 1401.
+constexpr int64_t kCgFoldMin = 32768;
+constexpr int kCgFoldLen = 1024, kCgFoldMax = 256;
+SFEM_HD int cg_fold_nblk(int64_t count) {
+  if (count <= kCgFoldMin) return 0;
+  const int64_t b = (count + kCgFoldLen - 1) / kCgFoldLen;
+  return (int)(b < kCgFoldMax ? b : kCgFoldMax);
+}
+
+}  // namespace sfem

@@ -7,6 +7,7 @@
 #include <string>
 #include <vector>
 
+#include "cg_plan.h"
 #include "plan.h"
 #include "sfem.h"
 
@@ -67,7 +68,7 @@ struct ApplyArgs {
   const int32_t *pos;       // DoF-ordered E-vector: [nelem][epe] entry of each element
                             // node; null: element-ordered, node r of element e -> e*epe + r
   int compact;              // nodes indexed by surface rank (1, epe = S) or local node (0)
-  double *part;             // CG: one partial of p.Ap per workgroup, [nb][part_mstride]
+  double *part;             // CG: the partials of p.Ap, [nb][part_mstride] (cg_parts)
   int64_t part_mstride;
 };
 // Element phase of the apply over all elements (writes the E-vector).
@@ -103,7 +104,7 @@ inline bool f32_by_members(int p, int op, int nb, bool one_coef, bool thin, bool
   return p <= kMembersMaxP && nb > 1 && op != SFEM_MASS && one_coef && !thin && groups >= kMembersMinGroups &&
          (!cg || nb <= kCgMembersMax);
 }
-// elements per workgroup of the apply kernel (one partial of p.Ap per workgroup)
+// elements per workgroup of the CG iteration's apply kernel
 int apply_group_elems_f64(int p);
 int apply_group_elems_f32(int p);
 // Assembly list on the device (see HostPlan): the assembled DoFs, ascending, the CSR
@@ -117,7 +118,7 @@ struct AsmPlan {
 };
 // Assembly phase over the list: y[g] = sum of g's E-vector entries in element order;
 // essential DoFs get x[g], 1 or 0 per ess_kind.
-constexpr int kMaxParts = 1024;  // cap of the partial-sum count of a reduction
+constexpr int kMaxParts = 1024;  // cap of the partial sums of a dot product by the vector kernels
 template <typename T>
 hipError_t launch_assemble(const AsmPlan &pl, const T *evec, int64_t estride, const T *x, T *y,
                            int64_t n, int nb, int ess_kind, hipStream_t s);
@@ -220,6 +221,9 @@ hipError_t launch_sub_norm(const double *b, const double *w, double *r, double *
 hipError_t launch_pcg_init(const double *part, int nblk, int nb, double rtol, PcgScalars *sc,
                            hipStream_t s, int nullspace = 0, int64_t n = 0);
 int cg_update_nblk(int64_t n, int nb);
+// out[m][b] = sum of the b-th of nblk equal stretches of member m's dcount partials (cg_fold_nblk).
+hipError_t launch_cg_fold(const double *dpart, int64_t dmstride, int dcount, double *out, int nblk, int nb,
+                          hipStream_t s);
 // The same update around a preconditioner applied between the launches (one member, z given in
 // the preconditioner's precision TZ); no partials.  TZ = float: r32 = (float) r, its input.  With
 // t also the preconditioner's first smoothing sweep, t = omega tdinv r.

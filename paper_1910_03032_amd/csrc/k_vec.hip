@@ -246,6 +246,16 @@ cg_update_kernel(CgDofs dofs, const T *__restrict__ Y, int64_t estride, const T 
   }
 }
 
+// out[m][b] = sum of the b-th of nblk equal stretches of member m's dcount partials.
+__global__ void __launch_bounds__(VB)
+cg_fold_kernel(const double *__restrict__ dpart, int64_t dmstride, int dcount, double *__restrict__ out, int nblk) {
+  const int len = (dcount + nblk - 1) / nblk, lo = blockIdx.x * len;
+  const int n = dcount - lo < len ? dcount - lo : len;
+  double v[1] = {0.0};
+  if (n > 0) reduce_parts_m<1, VB>(dpart + (int64_t)blockIdx.y * dmstride + lo, n, 0, v);
+  if (threadIdx.x == 0) out[(int64_t)blockIdx.y * nblk + blockIdx.x] = v[0];
+}
+
 // The state of the next iteration from the update's partials (a block per member), where the
 // host reads it before the next element kernel runs.
 __global__ void __launch_bounds__(256)
@@ -584,6 +594,12 @@ int cg_update_nblk(int64_t n, int nb) {
   if (b < 1) b = 1;
   if (b > most) b = most;
   return (int)b;
+}
+
+hipError_t launch_cg_fold(const double *dpart, int64_t dmstride, int dcount, double *out, int nblk, int nb,
+                          hipStream_t s) {
+  hipLaunchKernelGGL(cg_fold_kernel, dim3(nblk, nb), dim3(VB), 0, s, dpart, dmstride, dcount, out, nblk);
+  return hipGetLastError();
 }
 
 hipError_t launch_cg_finish(PcgScalars *sc, PcgScalars *host, const double *part, int nblk, int nb,
