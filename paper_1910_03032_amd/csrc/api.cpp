@@ -566,8 +566,8 @@ hipError_t cg_dot_parts(const PcgWork<T> &w, int nb, hipStream_t s, DotParts &ou
   return launch_cg_fold(w.dpart, w.nparts, w.nparts, w.fpart, w.nfold, nb, s);
 }
 
-// Jacobi-PCG on the context stream, two launches per iteration (pcg.h) and one more to fold
-// many partials (cg_plan.h).  On return hs[] (pinned host memory) holds the final scalars.
+// Jacobi-PCG on the context stream, two launches per iteration (pcg.h) and on large problems up to
+// two small ones more (cg_plan.h).  On return hs[] (pinned host memory) holds the final scalars.
 template <typename T>
 sfem_status run_pcg(sfem_ctx *c, int op, int nb, const T *b, T *x, bool x0_zero, double rtol,
                     int maxit, int check_every, const T *dinv, int64_t dms, PcgWork<T> &w,
@@ -594,6 +594,7 @@ sfem_status run_pcg(sfem_ctx *c, int op, int nb, const T *b, T *x, bool x0_zero,
   };
   if (!any_active()) return SFEM_OK;
   const int unblk = cg_update_nblk(n, nb);
+  const bool states = cg_states_apart(c->nelem, nb, cg_group(c, f32), cg_by_members(c, op, f32, nb));
   const CgDofs dofs{c->d_doff, c->d_slot};
   CgIn g{};
   g.r = w.r;
@@ -612,10 +613,10 @@ sfem_status run_pcg(sfem_ctx *c, int op, int nb, const T *b, T *x, bool x0_zero,
     HIPCHK(c, cg_dot_parts(w, nb, s, dp));
     HIPCHK(c, VecOps<T>::update(dofs, (const T *)c->evec.p, c->nentries, w.w, x, w.p, w.r, dinv, dms, w.sc + nb,
                                 w.sc, dp.p, dp.n, dp.n, w.part, unblk, n, nb, s));
-    g.ready = 0;
-    if ((it + 1) % check_every == 0 || it + 1 == maxit) {
-      HIPCHK(c, launch_cg_finish(w.sc, hs, w.part, unblk, nb, nullspace, n, s));
-      g.ready = 1;
+    const bool check = (it + 1) % check_every == 0 || it + 1 == maxit;
+    g.ready = check || states;
+    if (g.ready) HIPCHK(c, launch_cg_finish(w.sc, check ? hs : nullptr, w.part, unblk, nb, nullspace, n, s));
+    if (check) {
       HIPCHK(c, hipStreamSynchronize(s));
       if (!any_active()) break;
     }

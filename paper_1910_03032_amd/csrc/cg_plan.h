@@ -1,5 +1,5 @@
 // Sizes and rules of the CG iteration's two launches that need no GPU: the places of the partials
-// of p.Ap, and when a long list of them is folded first.
+// of p.Ap, when a long list of them is folded first, and when the states are formed apart.
 #pragma once
 
 #include <stdint.h>
@@ -38,6 +38,22 @@ SFEM_HD int cg_fold_nblk(int64_t count) {
   if (count <= kCgFoldMin) return 0;
   const int64_t b = (count + kCgFoldLen - 1) / kCgFoldLen;
   return (int)(b < kCgFoldMax ? b : kCgFoldMax);
+}
+
+// Whether a launch of its own forms the states of the next iteration, which otherwise every
+// workgroup of the element kernel forms for its members (up to E of them by pairs, all of them in
+// turn; the first workgroup for the rest too).  That launch takes 1 to 2 us; the sums at the head of
+// a workgroup cost more where many workgroups follow each other on a CU, or one has many members to
+// go through.  An iteration with the launch and without, float64: one member 36^3 p = 1 22.5 and
+// 22.0 us, 28^3 p = 3 42.6 and 42.7, 48^3 p = 4 315 and 325, 100^3 p = 1 228 and 254; three members
+// 20^3 p = 1 19.8 and 19.1, 20^3 p = 2 27.8 and 29.1, 64^3 p = 1 196 and 251; eight 6^3 p = 1 15.9 and
+// 15.7, 4^3 p = 2 15.6 and 16.8, 64^3 p = 1 530 and 980; 32 members 40^3 p = 1 621 and 1950.
+constexpr int64_t kCgStatesApart = 2600;
+constexpr int kCgStatesApartNb = 8;
+SFEM_HD bool cg_states_apart(int64_t nelem, int nb, int E, bool by_members) {
+  const int64_t groups = by_members ? (nelem + E - 1) / E : (nelem * nb + E - 1) / E;
+  const int here = by_members || nb < E ? nb : E;
+  return nb >= kCgStatesApartNb || groups * here >= kCgStatesApart;
 }
 
 }  // namespace sfem

@@ -237,8 +237,8 @@ hipError_t launch_cgz_update(const CgDofs &dofs, const double *evec, const doubl
 template <typename TZ>
 hipError_t launch_cgz_dots(const double *r, const TZ *z, const double *b, double *part, int nblk, int64_t n,
                            hipStream_t s);
-// In place, the state of the next iteration from the update's partials; also written to host
-// (device-visible host memory, [nb]).
+// In place, the state of the next iteration from the update's partials; also written to host, if
+// given (device-visible host memory, [nb]).
 hipError_t launch_cg_finish(PcgScalars *sc, PcgScalars *host, const double *part, int nblk, int nb,
                             int nullspace, int64_t n, hipStream_t s);
 // v[m][i] -= c[m] * scale (member-wise constant shift)

@@ -273,7 +273,7 @@ cg_finish_kernel(PcgScalars *__restrict__ sc, PcgScalars *__restrict__ host, con
   cg_next_from<4>(s, sums, nullspace, n);
   if (threadIdx.x == 0) {
     copy_state(sc[m], s);
-    copy_state(host[m], s);
+    if (host) copy_state(host[m], s);
   }
 }
 
