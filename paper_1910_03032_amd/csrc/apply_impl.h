@@ -599,7 +599,7 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
     constexpr int NW = CG ? THREADS / 64 : 1;
     // CG: the update's partials of the workgroup's first member and the state; also when the
     // state is ready, for loads under a condition are waited for where it ends
-    PartLoads<NW, 2> up;
+    std::conditional_t<CG != 0, PartLoads<NW, 2>, NoCg> up;
     PcgScalars s;
     if constexpr (CG) {
       up.load(cg.upart + (int64_t)r0 * 4 * cg.unblk, cg.unblk);

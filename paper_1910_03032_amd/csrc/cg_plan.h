@@ -8,6 +8,10 @@
 
 namespace sfem {
 
+// Workgroups of the update, and so partials of its sums, at most: every kernel that sums them in one
+// group of loads (PartLoads) is checked against it.
+constexpr int kCgUpdateMax = 512;
+
 // Partials of p.Ap per member that the element kernel leaves, E elements per workgroup: one per
 // workgroup, and where it takes (element, member) pairs of more members than it has pairs, one
 // per element (every other workgroup's partial would be 0).

@@ -128,10 +128,9 @@ __global__ void dot_kernel(const T *__restrict__ a, const T *__restrict__ c, int
 // partials of r.z, r.r, sum z, sum r of the new r.  doff: per DoF the offset of its entries,
 // with the map's flags (the count follows from the next DoF's offset).  Bound by HBM (or the
 // last-level cache): 7 vector streams, the offsets and the entries, in one pass where an
-// assembly, an update and a direction kernel made three.  Blocks of 512 threads, at most 512 of
-// them: few partials for every block of the next launch to sum, and 16 waves per CU in flight.
+// assembly, an update and a direction kernel made three.  Blocks of 512 threads, at most
+// kCgUpdateMax of them: few partials for every block of the next launch to sum, and 16 waves per CU in flight.
 constexpr int CU_NT = 512;
-constexpr int CU_MAXB = 512;  // (at most 4 * 192: PartLoads of the element kernels' 3 full waves)
 
 // With Z (one member) the preconditioned residual z is given instead of dinv r, there are no
 // partials, and what the preconditioner starts from is written too (CgzOut).
@@ -589,7 +588,7 @@ hipError_t launch_pcg_init(const double *part, int nblk, int nb, double rtol, Pc
 // member's p.Ap, which number nb times those of one member, and every workgroup of the element
 // kernel the update's partials of its members)
 int cg_update_nblk(int64_t n, int nb) {
-  const int64_t most = nb < CU_MAXB ? CU_MAXB / nb : 1;
+  const int64_t most = nb < kCgUpdateMax ? kCgUpdateMax / nb : 1;
   int64_t b = (n + CU_NT - 1) / CU_NT;
   if (b < 1) b = 1;
   if (b > most) b = most;

@@ -78,12 +78,13 @@ __device__ __forceinline__ void cg_next(PcgScalars &s, double rz, double rr, dou
   set_beta(s, rz - zs * sr, rr);
 }
 
-// The partials of K quantities (quantity k at p + k nblk, nblk <= 4 * 64 NW) that one thread of
+// The partials of K quantities (quantity k at p + k nblk, nblk <= kCgUpdateMax) that one thread of
 // NW full waves sums: requested early (load), added and combined later (parts).  All loads are
 // in flight together; a loop that waits for each costs microseconds at the head of every
 // workgroup.
 template <int NW, int K>
 struct PartLoads {
+  static_assert(4 * 64 * NW >= kCgUpdateMax, "partials beyond the loads would be dropped");
   double v[K][4];
   __device__ __forceinline__ void load(const double *__restrict__ p, int nblk) {
 #pragma unroll
