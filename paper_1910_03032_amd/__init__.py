@@ -28,8 +28,10 @@ def _ptr(t):
 
 def _stream_handle(index):
     """Handle of PyTorch's current stream on GPU index.  Every call passes it on; the Stream
-    object of torch.cuda.current_stream took 1.9 of a small apply's 12 us."""
-    return torch._C._cuda_getCurrentRawStream(index)
+    object of torch.cuda.current_stream took 1.9 of a small apply's 12 us, so it is asked for
+    only where PyTorch does not have the handle by itself (no part of its public interface)."""
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return raw(index) if raw is not None else torch.cuda.current_stream(index).cuda_stream
 
 
 def check_mesh_shapes(xyz_shape, dofs_shape, ndof, p, ess_shape=None):
