@@ -418,7 +418,7 @@ sfem_status check_op_batch(sfem_ctx *c, int op, int nbatch) {
 int cg_group(const sfem_ctx *c, bool f32) { return f32 ? apply_group_elems_f32(c->p) : apply_group_elems_f64(c->p); }
 bool cg_by_members(const sfem_ctx *c, int op, bool f32, int nb) {
   return f32 && f32_by_members(c->p, op, nb, c->nfield <= 1, c->thin != 0, true,
-                               cg_parts(c->nelem, 1, cg_group(c, f32), false));
+                               cg_parts(c->nelem, 1, cg_group(c, f32), false), cg_group(c, f32) * c->q * c->q);
 }
 int cg_nparts(const sfem_ctx *c, int op, bool f32, int nb) {
   return (int)cg_parts(c->nelem, nb, cg_group(c, f32), cg_by_members(c, op, f32, nb));

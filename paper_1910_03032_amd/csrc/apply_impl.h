@@ -1180,7 +1180,7 @@ hipError_t launch_apply_pt(const ApplyArgs &a, const CgIn &g, hipStream_t s) {
   // 2e5 DoFs at p = 5 to 8, 1.0 at 1.5e6)
   if constexpr (sizeof(T) == 4 && CG <= 1 && P <= kMembersMaxP) {
     if (f32_by_members(P, a.op, a.nbatch, !a.cw || a.cw_mstride == 0, a.thin != 0, CG != 0,
-                       (a.nelem + C::E - 1) / C::E)) {
+                       (a.nelem + C::E - 1) / C::E, C::THREADS)) {
       std::conditional_t<CG != 0, CgIn, NoCg> cg;
       if constexpr (CG != 0) cg = g;
       dim3 eg((unsigned)((a.nelem + C::E - 1) / C::E));

@@ -1,12 +1,29 @@
-// Sizes and rules of the CG iteration's two launches that need no GPU: the places of the partials
-// of p.Ap, when a long list of them is folded first, and when the states are formed apart.
+// Sizes and rules of the applies and of the CG iteration's two launches that need no GPU: where
+// members are taken in turn, the places of the partials of p.Ap, when a long list of them is folded
+// first, and when the states are formed apart.
 #pragma once
 
 #include <stdint.h>
 
 #include "eo.h"
+#include "sfem.h"
 
 namespace sfem {
+
+// The float32 kernels that take an element's members in turn (apply_impl.h): the orders whose
+// factors fit the registers, members with one coefficient, elements whose factors the metric gives
+// (thin: geom.h), and enough waves without the members to fill the chip; in a CG iteration at most
+// as many members as the kernel keeps states of.  groups: workgroups of the elements alone, of
+// threads threads each.  Times by pairs over times in turn, of two, three and eight members: applies
+// of 1250 waves (p = 4) 0.97, 0.90, 0.87, of 1600 to 1750 (p = 2, 3, 4) 1.02 - 1.05, 1.00 - 1.09, 1.03 -
+// 1.10, of 1100 and 880 (p = 3) 0.98, 0.95, 0.94 and 0.94, 0.95, 0.85, and of 1100 to 1500 (p = 1, where
+// a workgroup is one wave) 1.00 - 1.03, 1.03 - 1.05, 1.03; CG iterations of 1600 to 2000 waves (p = 1 to 4)
+// 1.05 - 1.21, 0.94 - 1.17, 0.93 - 1.32, of 1100 to 1250 0.98 - 1.13, 0.89 - 1.04, 0.80 - 0.99.
+constexpr int kMembersMaxP = 4, kCgMembersMax = 8, kMembersMinWaves = 1600;
+inline bool f32_by_members(int p, int op, int nb, bool one_coef, bool thin, bool cg, int64_t groups, int threads) {
+  return p <= kMembersMaxP && nb > 1 && op != SFEM_MASS && one_coef && !thin &&
+         groups * ((threads + 63) / 64) >= kMembersMinWaves && (!cg || nb <= kCgMembersMax);
+}
 
 // Workgroups of the update, and so partials of its sums, at most: every kernel that sums them in one
 // group of loads (PartLoads) is checked against it.

@@ -93,17 +93,6 @@ struct CgIn {
 hipError_t launch_apply_cg64(const ApplyArgs &a, const CgIn &g, hipStream_t s);
 hipError_t launch_apply_cg32(const ApplyArgs &a, const CgIn &g, hipStream_t s);
 hipError_t launch_apply_cgz(const ApplyArgs &a, const CgIn &g, hipStream_t s);
-// The float32 kernels that take an element's members in turn (apply_impl.h): the orders whose
-// factors fit the registers, members with one coefficient, elements whose factors the metric gives
-// (thin: geom.h), and enough workgroups without the
-// members to fill the chip (1024 fit; three members, a solve: 314 groups at 13^3 p = 4 3.95 ms
-// against 3.58 by pairs, 584 at 18^3 p = 3 3.69 against 3.97); in a CG iteration at most as many
-// members as the kernel keeps states of.  groups: workgroups of the elements alone.
-constexpr int kMembersMaxP = 4, kCgMembersMax = 8, kMembersMinGroups = 400;
-inline bool f32_by_members(int p, int op, int nb, bool one_coef, bool thin, bool cg, int64_t groups) {
-  return p <= kMembersMaxP && nb > 1 && op != SFEM_MASS && one_coef && !thin && groups >= kMembersMinGroups &&
-         (!cg || nb <= kCgMembersMax);
-}
 // elements per workgroup of the CG iteration's apply kernel
 int apply_group_elems_f64(int p);
 int apply_group_elems_f32(int p);

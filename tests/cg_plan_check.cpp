@@ -8,7 +8,26 @@
 
 using namespace sfem;
 
+// Where float32 members are taken in turn: elements per workgroup, threads and sizes on both sides of
+// the measured crossover of the applies (E) and of the CG iterations (E of 4 waves each).
+static void check_members() {
+  auto rule = [](int p, bool cg, int E, int n) {
+    return f32_by_members(p, SFEM_HELMHOLTZ, 3, true, false, cg, (n * n * n + E - 1) / E, E * (p + 2) * (p + 2));
+  };
+  const bool ok = !rule(1, false, 7, 18) && rule(1, false, 7, 26) && !rule(2, false, 16, 16) && rule(2, false, 16, 19) &&
+                  !rule(3, false, 5, 14) && rule(3, false, 5, 16) && !rule(4, false, 7, 13) && rule(4, false, 7, 15) &&
+                  !rule(3, true, 10, 14) && rule(3, true, 10, 17) && !rule(4, true, 7, 13) && rule(4, true, 7, 19);
+  if (!ok) std::printf("FAIL members in turn\n");
+  if (f32_by_members(2, SFEM_MASS, 3, true, false, false, 1 << 20, 256) ||
+      f32_by_members(2, SFEM_HELMHOLTZ, 3, false, false, false, 1 << 20, 256) ||
+      f32_by_members(2, SFEM_HELMHOLTZ, 3, true, true, false, 1 << 20, 256) ||
+      f32_by_members(2, SFEM_HELMHOLTZ, 9, true, false, true, 1 << 20, 256) ||
+      f32_by_members(8, SFEM_HELMHOLTZ, 3, true, false, false, 1 << 20, 200))
+    std::printf("FAIL members that go by pairs\n");
+}
+
 int main() {
+  check_members();
   for (int E : {2, 3, 4, 5, 7, 10, 16, 28})
     for (int64_t nelem : {1, 2, 3, 7, 27, 64, 125, 1000})
       for (int nb : {1, 2, 3, 4, 5, 8, 16, 27, 28, 29, 33, 64}) {
