@@ -1081,7 +1081,17 @@ apply_members_kernel(const int32_t *__restrict__ map, const double *__restrict__
         for (int k = 0; k < N; ++k) u[k] = buf[f * LD::YF + k * LD::SP + t];
         return eo::split(u);
       };
-      const eo::Split<N, T> sb = line(0), sg = line(1), sx = line(2);
+      // held in registers, or from p = 5 on read again for every slice pair
+      constexpr bool AGAIN = P >= 5;
+      const eo::Split<N, T> held[3] = {line(0), line(1), line(2)};
+      auto zline = [&](int f) {
+        if constexpr (AGAIN) {
+          asm volatile("" ::: "memory");  // a fresh LDS read, not a reuse of the last one
+          return line(f);
+        } else {
+          return held[f];
+        }
+      };
       eo::Acc<N, T> A1, A2, A3;
       A1.zero();
       A2.zero();
@@ -1096,7 +1106,7 @@ apply_members_kernel(const int32_t *__restrict__ map, const double *__restrict__
         T u0 = 0, u1 = 0, dx0, dx1, dy0, dy1, dz0, dz1, a1, a2, a3, b1, b2, b3;
         // (CG: each energy is summed at once; postponed, its operands would stay live)
         if constexpr (MASS) {
-          line_pair_of<BT>(sb, c, u0, u1);
+          line_pair_of<BT>(zline(0), c, u0, u1);
           const T v0 = wd[c] * u0, v1 = wd[Q - 1 - c] * u1;
           if constexpr (CG) {
             dot = add_energy(add_energy(dot, v0, u0), v1, u1);
@@ -1104,9 +1114,9 @@ apply_members_kernel(const int32_t *__restrict__ map, const double *__restrict__
           }
           A1.template add_pair<BT>(c, v0, v1);
         }
-        line_pair_of<GT>(sb, c, dz0, dz1);
-        line_pair_of<BT>(sg, c, dy0, dy1);
-        line_pair_of<BT>(sx, c, dx0, dx1);
+        line_pair_of<GT>(zline(0), c, dz0, dz1);
+        line_pair_of<BT>(zline(1), c, dy0, dy1);
+        line_pair_of<BT>(zline(2), c, dx0, dx1);
         flux(c, dx0, dy0, dz0, a1, a2, a3);
         if constexpr (CG) {
           dot = add_energy(dot, a1, dx0, a2, dy0, a3, dz0);
@@ -1124,10 +1134,10 @@ apply_members_kernel(const int32_t *__restrict__ map, const double *__restrict__
       if constexpr (Q % 2 == 1) {
         T g1, g2, g3, u = 0;
         if constexpr (MASS) {
-          u = line_mid_of<BT>(sb);
+          u = line_mid_of<BT>(zline(0));
           A1.template add_mid<BT>(wd[Q / 2] * u);
         }
-        const T dx = line_mid_of<BT>(sx), dy = line_mid_of<BT>(sg), dz = line_mid_of<GT>(sb);
+        const T dx = line_mid_of<BT>(zline(2)), dy = line_mid_of<BT>(zline(1)), dz = line_mid_of<GT>(zline(0));
         flux(Q / 2, dx, dy, dz, g1, g2, g3);
         if constexpr (CG) dot = add_energy(add_energy(dot, wd[Q / 2] * u, u), g1, dx, g2, dy, g3, dz);
         A1.template add_mid<GT>(g3);
@@ -1149,7 +1159,9 @@ apply_members_kernel(const int32_t *__restrict__ map, const double *__restrict__
     }
     bwd_y<P, T, true, THREADS>(buf, t);
     bwd_x<P, T, true, THREADS>(buf, t);
-    emit_e<P, T, LD>(buf, t, active, smap, Y + (int64_t)m * estride, y + (int64_t)m * ndof);
+    int te = t;
+    if constexpr (P >= 5) asm volatile("" : "+v"(te));  // addresses formed anew (REFORM of ApplyCfg)
+    emit_e<P, T, LD>(buf, te, active, smap, Y + (int64_t)m * estride, y + (int64_t)m * ndof);
     if constexpr (CG) {
       const double sum = block_sum_d<THREADS>(active ? dot : 0.0, sdot);
       if (threadIdx.x == 0) part[(int64_t)m * part_mstride + blockIdx.x] = sum;
@@ -1175,10 +1187,9 @@ hipError_t launch_apply_pt(const ApplyArgs &a, const CgIn &g, hipStream_t s) {
   using C = ApplyCfg<P, T, CG>;
   dim3 grid((unsigned)((a.nelem * a.nbatch + C::E - 1) / C::E));
   dim3 block(C::THREADS);
-  // (up to p = 4, where the members kernel's registers fit four waves per SIMD: three members
-  // there 1.05 - 1.8 times as fast as by (element, member) pairs; with its spills 0.43 - 0.9 at
-  // 2e5 DoFs at p = 5 to 8, 1.0 at 1.5e6)
-  if constexpr (sizeof(T) == 4 && CG <= 1 && P <= kMembersMaxP) {
+  // (up to p = 6 and, in CG iterations, 4, where the members kernel's registers fit four waves per SIMD:
+  // f32_by_members)
+  if constexpr (sizeof(T) == 4 && CG <= 1 && P <= (CG ? kCgMembersMaxP : kMembersMaxP)) {
     if (f32_by_members(P, a.op, a.nbatch, !a.cw || a.cw_mstride == 0, a.thin != 0, CG != 0,
                        (a.nelem + C::E - 1) / C::E, C::THREADS)) {
       std::conditional_t<CG != 0, CgIn, NoCg> cg;

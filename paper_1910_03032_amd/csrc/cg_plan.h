@@ -19,10 +19,15 @@ namespace sfem {
 // 1.10, of 1100 and 880 (p = 3) 0.98, 0.95, 0.94 and 0.94, 0.95, 0.85, and of 1100 to 1500 (p = 1, where
 // a workgroup is one wave) 1.00 - 1.03, 1.03 - 1.05, 1.03; CG iterations of 1600 to 2000 waves (p = 1 to 4)
 // 1.05 - 1.21, 0.94 - 1.17, 0.93 - 1.32, of 1100 to 1250 0.98 - 1.13, 0.89 - 1.04, 0.80 - 0.99.
-constexpr int kMembersMaxP = 4, kCgMembersMax = 8, kMembersMinWaves = 1600;
+// At p = 5 and 6, where an apply reads its lines again to fit the registers, from twice as many: 2200
+// (p = 5, 6) 0.98 and 0.97, 0.97 and 0.95, 0.97 and 0.98, 3300 1.02 and 1.01, 1.00 and 1.00, 1.07 and 1.08,
+// 4100 to 4700 1.03 - 1.05, 1.04 - 1.08, 1.11 - 1.16; with their factors stored, which three members read
+// from cache, 18^3 p = 5 (4700 waves) had taken 44.7 us, 47.1 now in turn and 49.0 by pairs, 23^3 94.3,
+// 82.0 and 91.2.  At p = 7 the gain was 1.01 - 1.03 from 6500 waves, in CG iterations 1.00 - 1.15.
+constexpr int kMembersMaxP = 6, kCgMembersMaxP = 4, kCgMembersMax = 8, kMembersMinWaves = 1600;
 inline bool f32_by_members(int p, int op, int nb, bool one_coef, bool thin, bool cg, int64_t groups, int threads) {
-  return p <= kMembersMaxP && nb > 1 && op != SFEM_MASS && one_coef && !thin &&
-         groups * ((threads + 63) / 64) >= kMembersMinWaves && (!cg || nb <= kCgMembersMax);
+  return p <= (cg ? kCgMembersMaxP : kMembersMaxP) && nb > 1 && op != SFEM_MASS && one_coef && !thin &&
+         groups * ((threads + 63) / 64) >= (p <= 4 ? 1 : 2) * kMembersMinWaves && (!cg || nb <= kCgMembersMax);
 }
 
 // Workgroups of the update, and so partials of its sums, at most: every kernel that sums them in one

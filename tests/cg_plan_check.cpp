@@ -16,7 +16,8 @@ static void check_members() {
   };
   const bool ok = !rule(1, false, 7, 18) && rule(1, false, 7, 26) && !rule(2, false, 16, 16) && rule(2, false, 16, 19) &&
                   !rule(3, false, 5, 14) && rule(3, false, 5, 16) && !rule(4, false, 7, 13) && rule(4, false, 7, 15) &&
-                  !rule(3, true, 10, 14) && rule(3, true, 10, 17) && !rule(4, true, 7, 13) && rule(4, true, 7, 19);
+                  !rule(5, false, 5, 15) && rule(5, false, 5, 18) && !rule(6, false, 4, 13) && rule(6, false, 4, 16) &&
+                  !rule(7, false, 3, 20) && !rule(5, true, 5, 18) && !rule(3, true, 10, 14) && rule(3, true, 10, 17) && !rule(4, true, 7, 13) && rule(4, true, 7, 19);
   if (!ok) std::printf("FAIL members in turn\n");
   if (f32_by_members(2, SFEM_MASS, 3, true, false, false, 1 << 20, 256) ||
       f32_by_members(2, SFEM_HELMHOLTZ, 3, false, false, false, 1 << 20, 256) ||
