@@ -59,11 +59,13 @@ int build_host_plan(int p, int64_t nelem, const int32_t *dofs_ptr, int64_t ndof,
   // from the E-vector.  Compact position table: indexed by the element's surface nodes
   // only, valid when every element-interior local node is sole or essential.
   const int64_t S = (p == 1) ? 8 : (int64_t)(2 * n * n + (n - 2) * 4 * p);
+  std::vector<int32_t> rank((size_t)n3);  // (the divisions once per order, not once per node)
+  for (int64_t l = 0; l < n3; ++l) rank[(size_t)l] = (int32_t)surface_rank(p, l);
   bool compact = true;
   for (int64_t e = 0; e < nelem && compact; ++e)
     for (int64_t l = 0; l < n3; ++l) {
       const int32_t gd = dofs((size_t)(e * n3 + l));
-      if (surface_rank(p, l) < 0 && !(deg[gd] == 1 || ess[gd])) {
+      if (rank[(size_t)l] < 0 && !(deg[gd] == 1 || ess[gd])) {
         compact = false;
         break;
       }
@@ -109,7 +111,7 @@ int build_host_plan(int p, int64_t nelem, const int32_t *dofs_ptr, int64_t ndof,
       for (int64_t l = 0; l < n3; ++l) {
         const int32_t gd = dofs((size_t)(e * n3 + l));
         if (ess[gd] || deg[gd] == 1) continue;
-        pos[(size_t)(e * epe + (compact ? surface_rank(p, l) : l))] = next[(size_t)apos[gd]]++;
+        pos[(size_t)(e * epe + (compact ? rank[(size_t)l] : l))] = next[(size_t)apos[gd]]++;
       }
   } else {
     out.nentries = nelem * epe;
@@ -119,7 +121,7 @@ int build_host_plan(int p, int64_t nelem, const int32_t *dofs_ptr, int64_t ndof,
       for (int64_t l = 0; l < n3; ++l) {
         const int32_t gd = dofs((size_t)(e * n3 + l));
         if (ess[gd] || deg[gd] == 1) continue;
-        slots[(size_t)next[(size_t)apos[gd]]++] = (int32_t)(e * epe + (compact ? surface_rank(p, l) : l));
+        slots[(size_t)next[(size_t)apos[gd]]++] = (int32_t)(e * epe + (compact ? rank[(size_t)l] : l));
       }
   }
   return 0;
