@@ -256,6 +256,17 @@ struct Nodes {
   }
 };
 
+// The trilinear coefficients of the thread's element into its place in LDS; no barrier.
+template <int P>
+__device__ __forceinline__ void load_geo(double *sg, const double *geo, int64_t e0, uint32_t rel, int t) {
+  constexpr int TPE = Dims<P>::TPE;
+#pragma unroll
+  for (int k = 0; k * TPE < kGeoStride; ++k) {
+    const int i = t + k * TPE < kGeoStride ? t + k * TPE : kGeoStride - 1;
+    sg[i] = ld<double>(geo + e0 * kGeoStride, (rel * kGeoStride + i) * 8u);
+  }
+}
+
 // Gather the element's nodal values (essential DoFs as 0) into the nodal vector of layout
 // Lds<P>.  Ends with a barrier.
 template <int P, typename T>
@@ -763,26 +774,6 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
       A1.zero();
       A2.zero();
       A3.zero();
-      auto row_pair = [](auto tb, const eo::Split<N, T> &x, int c, T &lo, T &hi) {
-        using TT = decltype(tb);
-        T Ev = 0, Od = 0;
-#pragma unroll
-        for (int i = 0; i < N / 2; ++i) {
-          Ev += (T)TT::e(c, i) * x.e[i];
-          Od += (T)TT::o(c, i) * x.o[i];
-        }
-        if constexpr (N % 2 == 1) Ev += (T)TT::t(c, N / 2) * x.e[N / 2];
-        lo = Ev + Od;
-        hi = (TT::S > 0) ? (Ev - Od) : (Od - Ev);
-      };
-      auto row_mid = [](auto tb, const eo::Split<N, T> &x) -> T {
-        using TT = decltype(tb);
-        T M = 0;
-#pragma unroll
-        for (int i = 0; i < N / 2; ++i) M += (T)TT::t(Q / 2, i) * (TT::S > 0 ? x.e[i] : x.o[i]);
-        if constexpr (N % 2 == 1 && TT::S > 0) M += (T)TT::t(Q / 2, N / 2) * x.e[N / 2];
-        return M;
-      };
       // v = alpha w |J| u and g = beta nu w |J| J^-1 J^-T grad_ref u at slice c
       auto qfun = [&](int c, T u, T dx, T dy, T dz, T &v, T &g1, T &g2, T &g3) {
         const double xc = gr.x[c], wc = gr.w[c];
@@ -822,11 +813,11 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
       for (int c = 0; c < Q / 2; ++c) {
         T u0 = 0, u1 = 0, dx0 = 0, dx1 = 0, dy0 = 0, dy1 = 0, dz0 = 0, dz1 = 0;
         const eo::Split<N, T> sbb = zline(0);
-        if constexpr (MASS) row_pair(BT{}, sbb, c, u0, u1);
+        if constexpr (MASS) eo::out_pair<BT>(sbb, c, u0, u1);
         if constexpr (DIFF) {
-          row_pair(GT{}, sbb, c, dz0, dz1);
-          row_pair(BT{}, zline(1), c, dy0, dy1);
-          row_pair(BT{}, zline(2), c, dx0, dx1);
+          eo::out_pair<GT>(sbb, c, dz0, dz1);
+          eo::out_pair<BT>(zline(1), c, dy0, dy1);
+          eo::out_pair<BT>(zline(2), c, dx0, dx1);
         }
         T v0, g10, g20, g30, v1, g11, g21, g31;
         qfun(c, u0, dx0, dy0, dz0, v0, g10, g20, g30);
@@ -841,11 +832,11 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
       if constexpr (Q % 2 == 1) {
         T u = 0, dx = 0, dy = 0, dz = 0;
         const eo::Split<N, T> sbb = zline(0);
-        if constexpr (MASS) u = row_mid(BT{}, sbb);
+        if constexpr (MASS) u = eo::out_mid<BT>(sbb);
         if constexpr (DIFF) {
-          dz = row_mid(GT{}, sbb);
-          dy = row_mid(BT{}, zline(1));
-          dx = row_mid(BT{}, zline(2));
+          dz = eo::out_mid<GT>(sbb);
+          dy = eo::out_mid<BT>(zline(1));
+          dx = eo::out_mid<BT>(zline(2));
         }
         T v, g1, g2, g3;
         qfun(Q / 2, u, dx, dy, dz, v, g1, g2, g3);
@@ -905,29 +896,6 @@ apply_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
       }
     }
   }
-}
-
-// Outputs (c, q-1-c) and, for odd q, the middle output of a 1D contraction from a split line.
-template <typename TB, int N, typename T>
-__device__ __forceinline__ void line_pair_of(const eo::Split<N, T> &x, int c, T &lo, T &hi) {
-  T Ev = 0, Od = 0;
-#pragma unroll
-  for (int i = 0; i < N / 2; ++i) {
-    Ev += (T)TB::e(c, i) * x.e[i];
-    Od += (T)TB::o(c, i) * x.o[i];
-  }
-  if constexpr (N % 2 == 1) Ev += (T)TB::t(c, N / 2) * x.e[N / 2];
-  lo = Ev + Od;
-  hi = (TB::S > 0) ? (Ev - Od) : (Od - Ev);
-}
-template <typename TB, int N, typename T>
-__device__ __forceinline__ T line_mid_of(const eo::Split<N, T> &x) {
-  constexpr int M = (N + 1) / 2;  // q / 2
-  T v = 0;
-#pragma unroll
-  for (int i = 0; i < N / 2; ++i) v += (T)TB::t(M, i) * (TB::S > 0 ? x.e[i] : x.o[i]);
-  if constexpr (N % 2 == 1 && TB::S > 0) v += (T)TB::t(M, N / 2) * x.e[N / 2];
-  return v;
 }
 
 // The float32 apply of several members with one coefficient: a workgroup takes E elements and
@@ -1106,7 +1074,7 @@ apply_members_kernel(const int32_t *__restrict__ map, const double *__restrict__
         T u0 = 0, u1 = 0, dx0, dx1, dy0, dy1, dz0, dz1, a1, a2, a3, b1, b2, b3;
         // (CG: each energy is summed at once; postponed, its operands would stay live)
         if constexpr (MASS) {
-          line_pair_of<BT>(zline(0), c, u0, u1);
+          eo::out_pair<BT>(zline(0), c, u0, u1);
           const T v0 = wd[c] * u0, v1 = wd[Q - 1 - c] * u1;
           if constexpr (CG) {
             dot = add_energy(add_energy(dot, v0, u0), v1, u1);
@@ -1114,9 +1082,9 @@ apply_members_kernel(const int32_t *__restrict__ map, const double *__restrict__
           }
           A1.template add_pair<BT>(c, v0, v1);
         }
-        line_pair_of<GT>(zline(0), c, dz0, dz1);
-        line_pair_of<BT>(zline(1), c, dy0, dy1);
-        line_pair_of<BT>(zline(2), c, dx0, dx1);
+        eo::out_pair<GT>(zline(0), c, dz0, dz1);
+        eo::out_pair<BT>(zline(1), c, dy0, dy1);
+        eo::out_pair<BT>(zline(2), c, dx0, dx1);
         flux(c, dx0, dy0, dz0, a1, a2, a3);
         if constexpr (CG) {
           dot = add_energy(dot, a1, dx0, a2, dy0, a3, dz0);
@@ -1134,10 +1102,10 @@ apply_members_kernel(const int32_t *__restrict__ map, const double *__restrict__
       if constexpr (Q % 2 == 1) {
         T g1, g2, g3, u = 0;
         if constexpr (MASS) {
-          u = line_mid_of<BT>(zline(0));
+          u = eo::out_mid<BT>(zline(0));
           A1.template add_mid<BT>(wd[Q / 2] * u);
         }
-        const T dx = line_mid_of<BT>(zline(2)), dy = line_mid_of<BT>(zline(1)), dz = line_mid_of<GT>(zline(0));
+        const T dx = eo::out_mid<BT>(zline(2)), dy = eo::out_mid<BT>(zline(1)), dz = eo::out_mid<GT>(zline(0));
         flux(Q / 2, dx, dy, dz, g1, g2, g3);
         if constexpr (CG) dot = add_energy(add_energy(dot, wd[Q / 2] * u, u), g1, dx, g2, dy, g3, dz);
         A1.template add_mid<GT>(g3);

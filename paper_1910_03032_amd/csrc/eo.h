@@ -54,29 +54,35 @@ SFEM_HD Split<L, T> split(const T (&v)[L]) {
   return s;
 }
 
+// The outputs (a, q-1-a) of the contraction of a split line, and the middle one of an odd number.
+template <typename TB, typename T>
+SFEM_HD void out_pair(const Split<TB::NI, T> &x, int a, T &lo, T &hi) {
+  T Ev = 0, Od = 0;
+#pragma unroll
+  for (int i = 0; i < TB::NI / 2; ++i) {
+    Ev += (T)TB::e(a, i) * x.e[i];
+    Od += (T)TB::o(a, i) * x.o[i];
+  }
+  if constexpr (TB::NI % 2 == 1) Ev += (T)TB::t(a, TB::NI / 2) * x.e[TB::NI / 2];
+  lo = Ev + Od;
+  hi = (TB::S > 0) ? (Ev - Od) : (Od - Ev);
+}
+template <typename TB, typename T>
+SFEM_HD T out_mid(const Split<TB::NI, T> &x) {
+  constexpr int M = TB::NO / 2;
+  T v = 0;
+#pragma unroll
+  for (int i = 0; i < TB::NI / 2; ++i) v += (T)TB::t(M, i) * (TB::S > 0 ? x.e[i] : x.o[i]);
+  if constexpr (TB::NI % 2 == 1 && TB::S > 0) v += (T)TB::t(M, TB::NI / 2) * x.e[TB::NI / 2];
+  return v;
+}
+
 // out[a] = sum_i T(a, i) v[i] for the table TB (NO x NI), from the split of v.
 template <typename TB, typename T, int NO = TB::NO, int NI = TB::NI>
 SFEM_HD void apply(const Split<NI, T> &x, T (&out)[NO]) {
-  constexpr int HI = NI / 2, HO = NO / 2;
 #pragma unroll
-  for (int a = 0; a < HO; ++a) {
-    T E = 0, O = 0;
-#pragma unroll
-    for (int i = 0; i < HI; ++i) {
-      E += (T)TB::e(a, i) * x.e[i];
-      O += (T)TB::o(a, i) * x.o[i];
-    }
-    if constexpr (NI % 2 == 1) E += (T)TB::t(a, HI) * x.e[HI];
-    out[a] = E + O;
-    out[NO - 1 - a] = (TB::S > 0) ? (E - O) : (O - E);
-  }
-  if constexpr (NO % 2 == 1) {
-    T M = 0;
-#pragma unroll
-    for (int i = 0; i < HI; ++i) M += (T)TB::t(HO, i) * (TB::S > 0 ? x.e[i] : x.o[i]);
-    if constexpr (NI % 2 == 1 && TB::S > 0) M += (T)TB::t(HO, HI) * x.e[HI];
-    out[HO] = M;
-  }
+  for (int a = 0; a < NO / 2; ++a) out_pair<TB>(x, a, out[a], out[NO - 1 - a]);
+  if constexpr (NO % 2 == 1) out[NO / 2] = out_mid<TB>(x);
 }
 
 // Transposed contraction out[i] = sum_a T(a, i) in[a] (NI outputs), accumulated one input

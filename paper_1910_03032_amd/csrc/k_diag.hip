@@ -59,11 +59,7 @@ diag_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo,
     Nodes<P> nd;
     nd.load_map(z, t, rel);
     nd.load_rank(z, t);
-#pragma unroll
-    for (int k = 0; k * TPE < kGeoStride; ++k) {
-      const int i = t + k * TPE < kGeoStride ? t + k * TPE : kGeoStride - 1;
-      sg[i] = ld<double>(geo + e0 * kGeoStride, (rel * kGeoStride + i) * 8u);
-    }
+    load_geo<P>(sg, geo, e0, rel, t);
     nd.template load_dest<POS>(z, rel);
     nd.keep(smap, t);
   }

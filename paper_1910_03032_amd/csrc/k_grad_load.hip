@@ -21,31 +21,6 @@
 namespace sfem {
 namespace {
 
-// Outputs (c, q-1-c), or the middle one, of a 1D contraction from the even-odd split of its
-// input line.
-template <typename TB>
-__device__ __forceinline__ void line_pair(const eo::Split<TB::NI, double> &x, int c, double &lo,
-                                          double &hi) {
-  double Ev = 0.0, Od = 0.0;
-#pragma unroll
-  for (int i = 0; i < TB::NI / 2; ++i) {
-    Ev += TB::e(c, i) * x.e[i];
-    Od += TB::o(c, i) * x.o[i];
-  }
-  if constexpr (TB::NI % 2 == 1) Ev += TB::t(c, TB::NI / 2) * x.e[TB::NI / 2];
-  lo = Ev + Od;
-  hi = (TB::S > 0) ? (Ev - Od) : (Od - Ev);
-}
-template <typename TB>
-__device__ __forceinline__ double line_mid(const eo::Split<TB::NI, double> &x) {
-  constexpr int M = TB::NO / 2;
-  double v = 0.0;
-#pragma unroll
-  for (int i = 0; i < TB::NI / 2; ++i) v += TB::t(M, i) * (TB::S > 0 ? x.e[i] : x.o[i]);
-  if constexpr (TB::NI % 2 == 1 && TB::S > 0) v += TB::t(M, TB::NI / 2) * x.e[TB::NI / 2];
-  return v;
-}
-
 // xi_3 lines of a field's three xi_1/xi_2-contracted forms, even-odd split.
 template <int P>
 struct Lines {
@@ -59,26 +34,16 @@ struct Lines {
   }
   // reference gradient at slices c and q-1-c, and at the middle slice
   __device__ __forceinline__ void grad_pair(int c, double (&lo)[3], double (&hi)[3]) const {
-    line_pair<eo::Tab1<P, 0>>(bg, c, lo[0], hi[0]);
-    line_pair<eo::Tab1<P, 0>>(gb, c, lo[1], hi[1]);
-    line_pair<eo::Tab1<P, 1>>(bb, c, lo[2], hi[2]);
+    eo::out_pair<eo::Tab1<P, 0>>(bg, c, lo[0], hi[0]);
+    eo::out_pair<eo::Tab1<P, 0>>(gb, c, lo[1], hi[1]);
+    eo::out_pair<eo::Tab1<P, 1>>(bb, c, lo[2], hi[2]);
   }
   __device__ __forceinline__ void grad_mid(double (&m)[3]) const {
-    m[0] = line_mid<eo::Tab1<P, 0>>(bg);
-    m[1] = line_mid<eo::Tab1<P, 0>>(gb);
-    m[2] = line_mid<eo::Tab1<P, 1>>(bb);
+    m[0] = eo::out_mid<eo::Tab1<P, 0>>(bg);
+    m[1] = eo::out_mid<eo::Tab1<P, 0>>(gb);
+    m[2] = eo::out_mid<eo::Tab1<P, 1>>(bb);
   }
 };
-
-template <int P>
-__device__ __forceinline__ void put_geo(double *sg, const double *geo, int64_t e0, uint32_t rel, int t) {
-  constexpr int TPE = Dims<P>::TPE;
-#pragma unroll
-  for (int k = 0; k * TPE < kGeoStride; ++k) {
-    const int i = t + k * TPE < kGeoStride ? t + k * TPE : kGeoStride - 1;
-    sg[i] = ld<double>(geo + e0 * kGeoStride, (rel * kGeoStride + i) * 8u);
-  }
-}
 
 template <int P>
 __global__ void __launch_bounds__(Dims<P>::THREADS, 2)
@@ -98,7 +63,7 @@ grad_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo, dou
   double *buf = smem + le * Lds<P>::BUF;
   Nodes<P> nd;
   nd.load_map(elem_tab<P>(map, nullptr, 1, e0), t, rel);
-  put_geo<P>(sgeo + le * kGeoStride, geo, e0, rel, t);
+  load_geo<P>(sgeo + le * kGeoStride, geo, e0, rel, t);
   for (int m = 0; m < nbatch; ++m) {
     double uv[Nodes<P>::NL];  // both fields' nodal values in flight together
     nd.load_values(u + (int64_t)m * ndof, uv);
@@ -176,7 +141,7 @@ load_kernel(const int32_t *__restrict__ map, const double *__restrict__ geo, int
     nd.load_map(z, t, rel);
     nd.load_rank(z, t);
     load_f(0);
-    put_geo<P>(sgeo + le * kGeoStride, geo, e0, rel, t);
+    load_geo<P>(sgeo + le * kGeoStride, geo, e0, rel, t);
     nd.template load_dest<POS>(z, rel);
     nd.keep(smap, t);
   }

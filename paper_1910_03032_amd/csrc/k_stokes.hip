@@ -42,31 +42,6 @@ struct TabEO {
   static constexpr double o(int a, int i) { return 0.5 * (t(a, i) - t(a, NI - 1 - i)); }
 };
 
-// Outputs (a, q-1-a) of a 1D contraction from the even-odd split x of its input line.
-template <typename TB>
-__device__ __forceinline__ void row_pair(const eo::Split<TB::NI, double> &x, int a, double &lo,
-                                         double &hi) {
-  double Ev = 0.0, Od = 0.0;
-#pragma unroll
-  for (int i = 0; i < TB::NI / 2; ++i) {
-    Ev += TB::e(a, i) * x.e[i];
-    Od += TB::o(a, i) * x.o[i];
-  }
-  if constexpr (TB::NI % 2 == 1) Ev += TB::t(a, TB::NI / 2) * x.e[TB::NI / 2];
-  lo = Ev + Od;
-  hi = (TB::S > 0) ? (Ev - Od) : (Od - Ev);
-}
-// The middle output (a = q/2) of an odd q.
-template <typename TB>
-__device__ __forceinline__ double row_mid(const eo::Split<TB::NI, double> &x) {
-  constexpr int M = TB::NO / 2;
-  double v = 0.0;
-#pragma unroll
-  for (int i = 0; i < TB::NI / 2; ++i) v += TB::t(M, i) * (TB::S > 0 ? x.e[i] : x.o[i]);
-  if constexpr (TB::NI % 2 == 1 && TB::S > 0) v += TB::t(M, TB::NI / 2) * x.e[TB::NI / 2];
-  return v;
-}
-
 // Where the stages keep a field of order PO in an element's buffer: [k][j][i] at NOD, then
 // [k][j][a] (line stride LQ, plane SK, field XF), then [k][b][a] (plane SP, field YF).  Dense
 // serves any (order, q); Padded the velocity, with the strides of Lds<P> and the nodal vector
@@ -317,17 +292,6 @@ __device__ __forceinline__ void emit_add_vel(const double *buf, int t, bool acti
   }
 }
 
-// The elements' trilinear coefficients into LDS (sg: [E][kGeoStride]); no barrier.
-template <int P>
-__device__ __forceinline__ void load_geo(double *sg, const double *geo, int64_t e0, uint32_t rel, int t) {
-  constexpr int TPE = Dims<P>::TPE;
-#pragma unroll
-  for (int k = 0; k * TPE < kGeoStride; ++k) {
-    const int i = t + k * TPE < kGeoStride ? t + k * TPE : kGeoStride - 1;
-    sg[i] = ld<double>(geo + e0 * kGeoStride, (rel * kGeoStride + i) * 8u);
-  }
-}
-
 // Nodal values held in registers (Nodes::load_values) into buf[k][j][i], essential DoFs as 0
 // unless ESS; no barrier.
 template <int P, bool ESS>
@@ -438,18 +402,18 @@ coupling_kernel(const int32_t *__restrict__ vmap, const int32_t *__restrict__ vp
 #pragma unroll
     for (int c = 0; c < Q / 2; ++c) {
       double uz0, uz1, uy0, uy1, ux0, ux1, pz0, pz1, py0, py1, px0, px1;
-      row_pair<VG>(ubb, c, uz0, uz1);
-      row_pair<VB>(ugb, c, uy0, uy1);
-      row_pair<VB>(ubg, c, ux0, ux1);
-      row_pair<PG>(pbb, c, pz0, pz1);
-      row_pair<PB>(pgb, c, py0, py1);
-      row_pair<PB>(pbg, c, px0, px1);
+      eo::out_pair<VG>(ubb, c, uz0, uz1);
+      eo::out_pair<VB>(ugb, c, uy0, uy1);
+      eo::out_pair<VB>(ubg, c, ux0, ux1);
+      eo::out_pair<PG>(pbb, c, pz0, pz1);
+      eo::out_pair<PB>(pgb, c, py0, py1);
+      eo::out_pair<PB>(pbg, c, px0, px1);
       point(c, ux0, uy0, uz0, px0, py0, pz0);
       point(Q - 1 - c, ux1, uy1, uz1, px1, py1, pz1);
     }
     if constexpr (Q % 2 == 1)
-      point(Q / 2, row_mid<VB>(ubg), row_mid<VB>(ugb), row_mid<VG>(ubb), row_mid<PB>(pbg),
-            row_mid<PB>(pgb), row_mid<PG>(pbb));
+      point(Q / 2, eo::out_mid<VB>(ubg), eo::out_mid<VB>(ugb), eo::out_mid<VG>(ubb), eo::out_mid<PB>(pbg),
+            eo::out_mid<PB>(pgb), eo::out_mid<PG>(pbb));
     // G p, component r: added into yv / the velocity E-vector
     bwd_mass<P, Q, 1, VelLay<P>>(buf, t, n);
     emit_add_vel<P, POS>(buf + VelLay<P>::NOD, t, active, smap, Yv + r * vestride, yv + r * nv);
@@ -551,11 +515,11 @@ __device__ __forceinline__ void contravariant(double *buf, int t, const double *
 #pragma unroll
     for (int c = 0; c < Q / 2; ++c) {
       double v0, v1;
-      row_pair<VB>(sv, c, v0, v1);
+      eo::out_pair<VB>(sv, c, v0, v1);
       point(c, v0);
       point(Q - 1 - c, v1);
     }
-    if constexpr (Q % 2 == 1) point(Q / 2, row_mid<VB>(sv));
+    if constexpr (Q % 2 == 1) point(Q / 2, eo::out_mid<VB>(sv));
   }
 }
 
@@ -649,16 +613,16 @@ convection_kernel(const int32_t *__restrict__ vmap, const int32_t *__restrict__ 
 #pragma unroll
       for (int c = 0; c < Q / 2; ++c) {
         double x0, x1, y0, y1, z0, z1;
-        row_pair<VB>(bg, c, x0, x1);
-        row_pair<VB>(gb, c, y0, y1);
-        row_pair<VG>(bb, c, z0, z1);
+        eo::out_pair<VB>(bg, c, x0, x1);
+        eo::out_pair<VB>(gb, c, y0, y1);
+        eo::out_pair<VG>(bb, c, z0, z1);
         A.template add_pair<VB>(c, h[0][c] * x0 + h[1][c] * y0 + h[2][c] * z0,
                                 h[0][Q - 1 - c] * x1 + h[1][Q - 1 - c] * y1 + h[2][Q - 1 - c] * z1);
       }
       if constexpr (Q % 2 == 1) {
         constexpr int M = Q / 2;
-        A.template add_mid<VB>(h[0][M] * row_mid<VB>(bg) + h[1][M] * row_mid<VB>(gb) +
-                               h[2][M] * row_mid<VG>(bb));
+        A.template add_mid<VB>(h[0][M] * eo::out_mid<VB>(bg) + h[1][M] * eo::out_mid<VB>(gb) +
+                               h[2][M] * eo::out_mid<VG>(bb));
       }
       A.finish(p[0]);
     }
@@ -740,13 +704,13 @@ weak_phi_kernel(const int32_t *__restrict__ vmap, const int32_t *__restrict__ vp
 #pragma unroll
     for (int c = 0; c < Q / 2; ++c) {
       double x0, x1c, y0, y1, z0, z1;
-      row_pair<VB>(bg, c, x0, x1c);
-      row_pair<VB>(gb, c, y0, y1);
-      row_pair<VG>(bb, c, z0, z1);
+      eo::out_pair<VB>(bg, c, x0, x1c);
+      eo::out_pair<VB>(gb, c, y0, y1);
+      eo::out_pair<VG>(bb, c, z0, z1);
       point(c, x0, y0, z0);
       point(Q - 1 - c, x1c, y1, z1);
     }
-    if constexpr (Q % 2 == 1) point(Q / 2, row_mid<VB>(bg), row_mid<VB>(gb), row_mid<VG>(bb));
+    if constexpr (Q % 2 == 1) point(Q / 2, eo::out_mid<VB>(bg), eo::out_mid<VB>(gb), eo::out_mid<VG>(bb));
     if constexpr (CURL) {
 #pragma unroll
       for (int c = 0; c < Q; ++c) {
