@@ -202,11 +202,11 @@ __device__ __forceinline__ void bwd_mass(double *buf, int t, const double (&v)[N
   bwd_mass_xy<PO, Q, NF, L>(buf, t, r);
 }
 
-// Gather of a pressure-space element (order P - 1, no essential DoFs) into buf and its
-// map entries into smap, for the q^2 threads of the element (TPE = (P + 2)^2).
+// Gather of a pressure-space element (order P - 1, no essential DoFs) into buf, for the q^2
+// threads of the element (TPE = (P + 2)^2).
 template <int P>
 __device__ __forceinline__ void gather_pres(double *buf, int t, bool active, const int32_t *emap,
-                                            const double *__restrict__ x, int32_t *smap) {
+                                            const double *__restrict__ x) {
   constexpr int NP3 = P * P * P, TPE = (P + 2) * (P + 2);
   constexpr int NL = (NP3 + TPE - 1) / TPE;
   int32_t c[NL];
@@ -221,10 +221,7 @@ __device__ __forceinline__ void gather_pres(double *buf, int t, bool active, con
 #pragma unroll
   for (int k = 0; k < NL; ++k) {
     const int l = t + k * TPE;
-    if (l < NP3) {
-      buf[l] = active ? v[k] : 0.0;
-      smap[l] = c[k];
-    }
+    if (l < NP3) buf[l] = active ? v[k] : 0.0;
   }
   __syncthreads();
 }
@@ -357,7 +354,7 @@ coupling_kernel(const int32_t *__restrict__ vmap, const int32_t *__restrict__ vp
   nd.load_rank(z, t);
   load_geo<P>(sgeo + le * kGeoStride, geo, e0, rel, t);
   // pressure element: the xi_3 lines of its reference gradient
-  gather_pres<P>(buf, t, active, pmap + (int64_t)es * NP3, pres, smap);
+  gather_pres<P>(buf, t, active, pmap + (int64_t)es * NP3, pres);
   nd.template load_dest<POS>(z, rel);
   double v[Nodes<P>::NL];  // the next component's nodal values
   nd.load_values(u, v);
