@@ -500,7 +500,7 @@ __device__ __forceinline__ int xcd_block() {
 //   ZLDS   the xi_3 stage's input lines are read from LDS again for every slice pair, one at
 //          a time, instead of being held in registers for the whole stage: where that decides
 //          the waves per SIMD.  Float64 p = 7 has two either way and holds them (243 registers
-//          of 256, LDS half busy: three members at 24^3 377 -> 350 us);
+//          of 256, LDS busy a third: three members at 24^3 377 -> 350 us);
 //   OCC    minimum waves per SIMD the kernel is compiled for (launch bound): three float64
 //          ones at p = 5 and 6 as well (29^3 p = 5 115 -> 100 us, 24^3 p = 6 101 -> 82 us,
 //          Helmholtz with nu).  Four at p = 3 and 4, and three at p = 7, would spill 44 to

@@ -330,7 +330,6 @@ coupling_kernel(const int32_t *__restrict__ vmap, const int32_t *__restrict__ vp
                 int64_t nv, double *__restrict__ Yv, int64_t vestride, double *__restrict__ yv,
                 double *__restrict__ Yp, double *__restrict__ yp) {
   using S = SDims<P>;
-  using D = Dims<P>;
   constexpr int N = S::N, NP = S::NP, Q = S::Q, TPE = S::TPE, E = S::E;
   constexpr int N3 = N * N * N, NP3 = NP * NP * NP;
   constexpr rules::GaussRule<Q> gr = rules::gauss<Q>();
@@ -570,7 +569,6 @@ convection_kernel(const int32_t *__restrict__ vmap, const int32_t *__restrict__ 
                   const double *__restrict__ u, int64_t nv, double *__restrict__ Yv,
                   int64_t vestride, double *__restrict__ yv) {
   using S = SDims<P>;
-  using D = Dims<P>;
   constexpr int N = S::N, Q = S::Q, TPE = S::TPE, E = S::E, N3 = N * N * N;
   using VB = TabEO<P, Q, 0>;
   using VG = TabEO<P, Q, 1>;
@@ -642,7 +640,6 @@ weak_phi_kernel(const int32_t *__restrict__ vmap, const int32_t *__restrict__ vp
                 const double *__restrict__ u, int64_t nv, double *__restrict__ Yv,
                 int64_t vestride, double *__restrict__ yv) {
   using S = SDims<P>;
-  using D = Dims<P>;
   constexpr int N = S::N, Q = S::Q, TPE = S::TPE, E = S::E, N3 = N * N * N;
   constexpr int NIN = CURL ? 3 : 1;
   constexpr rules::GaussRule<Q> gr = rules::gauss<Q>();

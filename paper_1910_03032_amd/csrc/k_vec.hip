@@ -1,11 +1,12 @@
 // Vector kernels of the Jacobi-preconditioned CG (Section 5, Section 5.3) and of the
 // FP64 iterative refinement around an FP32 inner CG.
 //
-// All dot products accumulate in float64, also for float32 vectors.  Reductions are
-// two-level and in a fixed order (per-block partial sums, then one block per batch
-// member), so every result is bitwise reproducible for a given size.  The CG scalars
-// (rho, alpha, beta, ...) stay on the device; the host only reads them at its
-// convergence checks.
+// All dot products form and add their terms in float64, also for float32 vectors (p.Ap: energy.h).
+// Reductions go by per-block partial sums in a fixed order, so every result is bitwise
+// reproducible for a given size; in a CG iteration the partials are summed by every workgroup that
+// needs them, a long list first and many members' by launches of their own (cg_plan.h).  The CG
+// scalars (rho, alpha, beta, ...) stay on the device; the host only reads them at its convergence
+// checks.
 #include <hip/hip_runtime.h>
 
 #include <cmath>

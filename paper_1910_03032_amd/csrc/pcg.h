@@ -5,7 +5,8 @@
 // sums of p.Ap taken at the quadrature points (so they need no assembled vector); the update
 // kernel assembles w = A p DoF by DoF, forms the same p again and writes p, x += alpha p,
 // r -= alpha w with the partial sums of the new r.z and r.r.  Every block that needs a scalar
-// sums the partials itself in a fixed order.  The states alternate between two arrays, so
+// sums the partials itself in a fixed order, on large problems what cg_fold_kernel and
+// cg_finish_kernel have left of them (cg_plan.h).  The states alternate between two arrays, so
 // that no block reads a value another block of the same launch writes: the element kernel
 // reads the state the update left, adds beta (cg_next) and writes the other array; the
 // update adds alpha (set_alpha).
