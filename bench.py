@@ -65,8 +65,8 @@ def log(*a):
 # assembly dispatch), from rocprofv3 FETCH_SIZE / WRITE_SIZE runs scaled by a plain
 # copy's readings; valid only for the kernel sources they were taken with (keyed by
 # the hash of those sources), otherwise the roofline reports traffic = null.
-KERNEL_SOURCES = ["apply_impl.h", "eo.h", "energy.h", "geom.h", "pcg.h", "cg_plan.h", "wave.h", "rules.h", "internal.h", "plan.h",
-                  "k_apply_f64.hip", "k_vec.hip"]
+KERNEL_SOURCES = ["apply_impl.h", "eo.h", "energy.h", "geom.h", "pcg.h", "cg_plan.h", "wave.h", "rules.h",
+                  "internal.h", "plan.h", "k_apply_f64.hip", "k_vec.hip"]
 MEASURED_TRAFFIC = {
     # profiles/helmholtz_apply_p4_32e_hbm_bytes.md (FP64 apply, both dispatches)
     ("8425a74bd5e4e1e3", "helmholtz_p4_32e"): 213254730,
