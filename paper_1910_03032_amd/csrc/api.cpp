@@ -708,7 +708,10 @@ hipError_t lor_vcycle(sfem_ctx *c, int op, bool f32, const double *r, double *z)
 // On return hs holds the final scalars.
 template <typename TZ>
 sfem_status run_pcg_lor_z(sfem_ctx *c, int op, const double *b, double *x, bool x0_zero, double rtol, int maxit,
-                          int nullspace, const PcgWork<double> &pw, TZ *z, PcgScalars &hs) {
+                          int nullspace, PcgWork<double> pw, TZ *z, PcgScalars &hs) {
+  // (the workspace is that of all members; the partials here are one member's)
+  pw.nparts = cg_nparts(c, op, false, 1);
+  pw.nfold = cg_fold_nblk(pw.nparts);
   constexpr bool f32 = sizeof(TZ) == 4;
   const int64_t n = c->ndof;
   hipStream_t s = c->stream;
